@@ -73,8 +73,8 @@ enum { SPD_STAGE_PREFIX = 1, SPD_STAGE_SUFFIX = 2, SPD_STAGE_MERGE = 4 };
  *
  * Supported: dtype bf16 or f32, head_dim a multiple of 8 up to 256, page_size 0
  * (contiguous KV) or 16.  bf16 with head_dim 128 and at most 16 query heads per
- * KV head runs on the MFMA kernels; everything else on the plain kernels (fp32
- * arithmetic, one lane per token).
+ * KV head runs on the tiled MFMA kernels; everything else on a general kernel (fp32
+ * inputs stay fp32 throughout; bf16 inputs keep fp32 probabilities).
  */
 typedef struct spd_attn_desc {
     int32_t dtype;                  /* spd_dtype of Q, K, V and the output */

@@ -63,6 +63,11 @@ inline int part_tokens(long long len, int min_tokens, int max_parts, int quantum
     return (int)t;
 }
 
+// Query rows per wavefront of the general kernel (fp32, other head dimensions): 32 use every loaded K and
+// V register twice; 16 when there are no more rows than that, or when two blocks' queries and
+// accumulators would not leave room for two wavefronts per SIMD (more than 64 channels).
+inline int rows_per_block(int head_dim, long long rows) { return rows > 16 && head_dim <= 64 ? 32 : 16; }
+
 // Tokens per split of a prefix level with `groups` groups of at most `spp` samples and lengths up to
 // `max_prefix`, at most `max_splits` splits.
 inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long long max_prefix, int max_splits)
@@ -79,7 +84,12 @@ inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long l
         if (t < 128) t = 128;  // at least two tiles per split: a one-tile workgroup is all start-up
         return (int)t;
     }
-    return part_tokens(max_prefix, 256, max_splits, 64);
+    // general kernel: enough splits for a workgroup per CU, a tile or more per wavefront
+    const long long rows = (long long)spp * (d->num_q_heads / d->num_kv_heads);
+    const int block = rows_per_block(d->head_dim, rows);
+    const long long base = (long long)groups * d->num_kv_heads * ((rows + block - 1) / block);
+    const long long want = (256 + base - 1) / base;
+    return part_tokens(max_prefix, d->dtype == SPD_BF16 ? 128 : 64, (int)(want > max_splits ? max_splits : want), 64);
 }
 
 // Tokens per suffix chunk: enough (sample, KV head, chunk) items to keep every CU busy, chunks of

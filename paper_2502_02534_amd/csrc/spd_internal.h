@@ -161,7 +161,7 @@ __device__ __forceinline__ long long kv_row_offset(int t, int j, int Hkv, int D,
     return ((pg * Hkv + j) * page_size + (t % page_size)) * (long long)D;
 }
 
-hipError_t launch_attn_plain(const AttnParams& p, bool prefix, bool suffix, hipStream_t s);
+hipError_t launch_attn_rows(const AttnParams& p, bool prefix, bool suffix, hipStream_t s);
 bool prefix_mfma_supported(const AttnParams& p);
 int prefix_mfma_block_rows(int rows);
 hipError_t launch_attn_prefix_mfma(const AttnParams& p, hipStream_t s);

@@ -373,7 +373,7 @@ int run_attention(const spd_attn_desc* desc, const void* q, int num_levels, cons
         const bool want_suffix = last && (stages & SPD_STAGE_SUFFIX) != 0;
         const bool suffix_tiled = spd::suffix_mfma_supported(p);
         const bool prefix_tiled = spd::prefix_mfma_supported(p);
-        e = spd::launch_attn_plain(p, want_prefix && !prefix_tiled, want_suffix && !suffix_tiled, s);
+        e = spd::launch_attn_rows(p, want_prefix && !prefix_tiled, want_suffix && !suffix_tiled, s);
         if (e != hipSuccess)
             return SPD_ELAUNCH;
         const bool fused = want_prefix && want_suffix && spd::attn_fused_supported(p);

@@ -1,0 +1,79 @@
+"""The general attention kernel (fp32, head dimensions other than 128, more than 16 query heads per KV
+head) at the sizes where its tiling can go wrong: padded head dimensions, row counts either side
+of its 16- and 32-row blocks, ranges either side of its 16- and 32-token tiles, items shared by a
+workgroup's wavefronts and items of one wavefront."""
+import numpy as np
+import pytest
+
+from gpu_checks import check_attention
+from paper_2502_02534_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+CASES = [
+    # padded head dimensions (registers for 64, 128 or 256 channels), both types, contiguous and paged
+    dict(dtype="f32", num_q_heads=2, num_kv_heads=1, head_dim=8, prefix_len=(17, 17), suffix_len=(0, 16)),
+    dict(dtype="f32", num_q_heads=6, num_kv_heads=2, head_dim=72, prefix_len=(1, 130), suffix_len=(0, 65), page_size=16),
+    dict(dtype="f32", num_q_heads=4, num_kv_heads=2, head_dim=200, prefix_len=(15, 90), suffix_len=(1, 33)),
+    dict(dtype="f32", num_q_heads=4, num_kv_heads=2, head_dim=256, prefix_len=(63, 200), suffix_len=(0, 64), page_size=16),
+    dict(dtype="bf16", num_q_heads=4, num_kv_heads=2, head_dim=40, prefix_len=(31, 140), suffix_len=(0, 33), page_size=16),
+    dict(dtype="bf16", num_q_heads=6, num_kv_heads=2, head_dim=96, prefix_len=(1, 300), suffix_len=(0, 97)),
+    dict(dtype="bf16", num_q_heads=4, num_kv_heads=2, head_dim=136, prefix_len=(65, 300), suffix_len=(1, 31)),
+    dict(dtype="bf16", num_q_heads=8, num_kv_heads=2, head_dim=256, prefix_len=(1, 200), suffix_len=(0, 70), page_size=16),
+    # one row, exactly one block, one more than a block, one more than two
+    dict(dtype="f32", num_q_heads=1, num_kv_heads=1, head_dim=64, samples_per_prompt=1, prefix_len=(64, 64), suffix_len=(1, 1)),
+    dict(dtype="f32", num_q_heads=4, num_kv_heads=1, head_dim=128, samples_per_prompt=4, prefix_len=(65, 65), suffix_len=(0, 3)),
+    dict(dtype="bf16", num_q_heads=2, num_kv_heads=2, head_dim=64, samples_per_prompt=17, prefix_len=(129, 129), suffix_len=(0, 129)),
+    dict(dtype="bf16", num_q_heads=3, num_kv_heads=1, head_dim=64, samples_per_prompt=11, prefix_len=(127, 127), suffix_len=(0, 33)),
+    # more than 16 heads per KV head: suffix rows in several blocks (with head_dim 128 the prefix stays on its own kernel)
+    dict(dtype="bf16", num_q_heads=24, num_kv_heads=1, head_dim=128, samples_per_prompt=5, prefix_len=(1, 300), suffix_len=(0, 200)),
+    dict(dtype="bf16", num_q_heads=66, num_kv_heads=2, head_dim=64, samples_per_prompt=3, prefix_len=(1, 90), suffix_len=(0, 70), page_size=16),
+    # more than 1024 prefix items and suffix items: one wavefront each, and an odd number of them
+    dict(dtype="f32", num_q_heads=8, num_kv_heads=4, head_dim=64, num_prompts=3, samples_per_prompt=333, prefix_len=(30, 70), suffix_len=(0, 20)),
+    dict(dtype="bf16", num_q_heads=32, num_kv_heads=16, head_dim=64, num_prompts=9, samples_per_prompt=131, prefix_len=(0, 150), suffix_len=(0, 17),
+         page_size=16),
+]
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2502_02534_amd import binding, device
+    binding.load()
+    return device
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_general_kernel_shapes(dev, oracle, i):
+    spec = dict(num_prompts=2, samples_per_prompt=3)
+    spec.update(CASES[i])
+    print(f"general kernel case {i}: {spec}", flush=True)
+    check_attention(dev, oracle, W.make_attn_inputs(0, spec=W.small_spec(**spec), seed=900 + i, poison_padding=True))
+
+
+@pytest.mark.parametrize("shared", [True, False], ids=["shared", "single"])
+def test_tokens_with_minus_infinity_scores_add_nothing(dev, shared):
+    """Keys whose score is -inf for every row, whole tiles of them at the start and in the middle: the
+    result is attention over the others (fp32: nothing but the order of the sums differs, 1e-5)."""
+    spec = W.small_spec(dtype="f32", num_q_heads=4, num_kv_heads=4, head_dim=64, samples_per_prompt=400 if not shared else 5,
+                        prefix_len=(200, 200), suffix_len=(40, 40))
+    inp = W.make_attn_inputs(0, spec=spec, seed=950)
+    inp.q[..., 0] = 1.0
+    inp.k_prefix[:70, :, 0] = -np.inf
+    inp.k_prefix[100:140, :, 0] = -np.inf
+    inp.k_suffix[:, 3, :, 0] = -np.inf
+    d = dev.upload_attn(inp)
+    d.run()
+    torch.cuda.synchronize()
+    kept = np.r_[70:100, 140:200]
+    k = np.concatenate([np.broadcast_to(inp.k_prefix[kept][None], (spec.num_samples,) + inp.k_prefix[kept].shape),
+                        np.delete(inp.k_suffix, 3, axis=1)], axis=1).astype(np.float64)
+    v = np.concatenate([np.broadcast_to(inp.v_prefix[kept][None], (spec.num_samples,) + inp.v_prefix[kept].shape),
+                        np.delete(inp.v_suffix, 3, axis=1)], axis=1).astype(np.float64)
+    s = np.einsum("nhd,nthd->nht", inp.q.astype(np.float64), k) / 8.0
+    w = np.exp(s - s.max(-1, keepdims=True))
+    ref = np.einsum("nht,nthd->nhd", w / w.sum(-1, keepdims=True), v)
+    got = d.out.cpu().numpy()
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6)
