@@ -3,7 +3,7 @@
 // Two paths.  The sliced path (below: two stream-ordered kernels) reads a row from HBM once, leaves
 // what the row-level step needs in the workspace, and finds the exact nucleus threshold without
 // sorting.  The whole-row routine (one workgroup per row, every pass from memory) covers what the
-// sliced path does not take: unaligned rows, vocabularies beyond 16 slices, the rare row whose
+// sliced path does not take: vocabularies beyond 16 slices (or of a few logits), the rare row whose
 // candidate set overflows, and rows whose min-p or top-k filter reaches further down than the
 // sliced path's windows.
 //
@@ -145,8 +145,8 @@ struct RowLds {
 };
 
 // Whole-row routine for one workgroup of kBlock threads: every pass reads the row from
-// global memory.  Used when the sliced kernel cannot take a row (unaligned rows, very
-// large vocabularies, candidate overflow).
+// global memory.  Used when the sliced kernel cannot take a row (very large vocabularies,
+// candidate overflow).
 __device__ void sample_row_from_memory(const SamplerParams& sp, long long r, RowLds& L)
 {
     double* hist = L.hist;
@@ -524,43 +524,56 @@ __device__ __forceinline__ double bin_unit(int bin)
     return root * __hiloint2double((1023 - 15 - (bin >> 4)) << 20, 0);
 }
 
-// Loads the slice [e0, e1) of a row into 32 registers per thread (whole float4s only; lanes
-// past the end hold -inf).  The last one to three logits of a row whose length is not a
-// multiple of 4 (the "tail") are not loaded here: thread 0 handles them straight from memory.
+// A row that does not start on a 16-byte boundary (a vocabulary that is not a multiple of 4) is
+// handled in positions counted from the boundary before it: position i holds logit i - lead, and
+// positions below `lead` hold none.  Everything up to the token (pairs, segments, the walk) is in
+// positions.
+__device__ __forceinline__ int row_lead(const float* x) { return (int)(((uintptr_t)x >> 2) & 3); }
+
+// Slice [e0, e1) of a row's positions; [v0, v4end) are its whole float4s.
 struct SliceRange {
-    int e0, e1, v4end, ntail;
+    int e0, e1, v0, v4end, lead;
 };
 
-__device__ __forceinline__ SliceRange slice_range(int slice, int slice_elems, int V)
+__device__ __forceinline__ SliceRange slice_range(int slice, int slice_elems, int V, int lead)
 {
     SliceRange g;
     g.e0 = slice * slice_elems;
-    g.e1 = min(V, g.e0 + slice_elems);
+    g.e1 = min(V + lead, g.e0 + slice_elems);
+    g.v0 = slice == 0 && lead > 0 ? 4 : g.e0;
     g.v4end = g.e1 & ~3;
-    g.ntail = (g.e1 == V && g.e0 < V) ? (V & 3) : 0;
+    g.lead = lead;
     return g;
 }
 
-// Every load is unconditional (lanes past the end re-read the slice's last float4), so that the
-// hardware's in-order load counter stays exact for the compiler and later loads need not wait
-// for these.  SPD_MASK_SLICE, applied where the values are first needed, replaces what lies
-// past the end by -inf.  Every slice holds at least one whole float4 (the host sends rows
-// shorter than that to the whole-row kernel, and slices are never shorter than about 2000).
-#define SPD_LOAD_SLICE(xv, x, g, tid)                                                   \
+// Loads a slice into 32 registers per thread; `xa` points at position 0.  Every load is unconditional
+// (lanes outside the whole float4s re-read the nearest one), so that the hardware's in-order load
+// counter stays exact for the compiler and later loads need not wait for these.  SPD_MASK_SLICE,
+// applied where the values are first needed, replaces what lies outside the row by -inf and fetches
+// the one to three logits of a float4 that the row only partly fills.  Every slice holds at least one
+// whole float4 (the host sends rows shorter than that to the whole-row kernel, and slices are never
+// shorter than about 2000).
+#define SPD_LOAD_SLICE(xv, xa, g, tid)                                                  \
     _Pragma("unroll") for (int j = 0; j < 8; ++j)                                       \
     {                                                                                   \
-        const int i_ = (g).e0 + j * kIter + (tid) * 4;                                  \
-        const float4 v_ = *reinterpret_cast<const float4*>((x) + min(i_, (g).v4end - 4)); \
+        const int i_ = min((g).e0 + j * kIter + (tid) * 4, (g).v4end - 4);              \
+        const float4 v_ = *reinterpret_cast<const float4*>((xa) + (j == 0 ? max(i_, (g).v0) : i_)); \
         (xv)[4 * j] = v_.x;                                                             \
         (xv)[4 * j + 1] = v_.y;                                                         \
         (xv)[4 * j + 2] = v_.z;                                                         \
         (xv)[4 * j + 3] = v_.w;                                                         \
     }
-#define SPD_MASK_SLICE(xv, g, tid)                                                      \
+#define SPD_MASK_SLICE(xv, xa, g, tid)                                                  \
     _Pragma("unroll") for (int j = 0; j < 8; ++j)                                       \
     {                                                                                   \
-        if (!((g).e0 + j * kIter + (tid) * 4 < (g).v4end)) {                            \
-            (xv)[4 * j] = (xv)[4 * j + 1] = (xv)[4 * j + 2] = (xv)[4 * j + 3] = -INFINITY; \
+        const int i_ = (g).e0 + j * kIter + (tid) * 4;                                  \
+        if (i_ < (g).v0 || i_ >= (g).v4end) {                                           \
+            _Pragma("unroll") for (int k_ = 0; k_ < 4; ++k_)                            \
+            {                                                                           \
+                (xv)[4 * j + k_] = -INFINITY;                                           \
+                if (i_ + k_ >= (g).lead && i_ + k_ < (g).e1)                            \
+                    (xv)[4 * j + k_] = (xa)[i_ + k_];                                   \
+            }                                                                           \
         }                                                                               \
     }
 
@@ -663,8 +676,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long r = blockIdx.x / slices;
     const int slice = blockIdx.x % slices;
-    const float* __restrict__ x = sp.logits + r * sp.stride;
-    const SliceRange g = slice_range(slice, slice_elems, (int)sp.vocab);
+    const float* __restrict__ row_x = sp.logits + r * sp.stride;
+    const int lead = row_lead(row_x);
+    const float* __restrict__ x = row_x - lead;  // position 0
+    const SliceRange g = slice_range(slice, slice_elems, (int)sp.vocab, lead);
     const RowWs W = row_ws(ws, r, slices);
     const float T = sp.temperature[r];
     const bool greedy = (T == 0.f);
@@ -675,11 +690,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
     float xv[32];
     SPD_LOAD_SLICE(xv, x, g, tid)
-    float tail[3] = {-INFINITY, -INFINITY, -INFINITY};  // the row's last one to three logits (thread 0 of the last slice)
-    if (tid == 0)
-        for (int k = 0; k < 3; ++k)
-            if (k < g.ntail)
-                tail[k] = x[g.v4end + k];
     for (int b = tid; b < kPubBins + 64; b += kBlock)
         L.hist[b] = 0u;
     if (tid == 0) {
@@ -689,12 +699,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         L.overflow = 0;
         L.rest = 0.0;
     }
-    // wavefronts whose 32 x 64 x 4 logits all lie inside the slice skip the end-of-slice masking
-    const bool whole = g.e0 + 7 * kIter + (tid | 63) * 4 + 4 <= g.v4end;
+    // wavefronts whose 32 x 64 x 4 logits all lie inside the row skip the masking of its ends
+    const bool whole = g.e0 + 7 * kIter + (tid | 63) * 4 + 4 <= g.v4end && g.e0 + (tid & ~63) * 4 >= g.v0;
     if (!whole) {
-        SPD_MASK_SLICE(xv, g, tid)
+        SPD_MASK_SLICE(xv, x, g, tid)
     }
-    float mx = fmaxf(fmaxf(tail[0], tail[1]), tail[2]);
+    float mx = -INFINITY;
 #pragma unroll
     for (int q = 0; q < 32; ++q)
         mx = fmaxf(mx, xv[q]);
@@ -713,9 +723,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int q = 31; q >= 0; --q)
             if (xv[q] == mx)
                 mi = g.e0 + (q >> 2) * kIter + tid * 4 + (q & 3);
-        for (int k = 2; k >= 0; --k)
-            if (tail[k] == mx)  // (-inf where there is no tail logit, and a slice maximum is finite)
-                mi = min(mi, g.v4end + k);
         for (int o = 32; o > 0; o >>= 1)
             mi = min(mi, __shfl_xor(mi, o));
         if (lane == 0)
@@ -741,8 +748,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     double* seg_out = W.seg + (size_t)slice * kSegPerSlice;
 
     if (!cut) {
-        // ---- nothing is cut: the mass of every 256-element segment, relative to the slice maximum; the
-        // row's tail logits travel as pairs ----
+        // ---- nothing is cut: the mass of every 256-element segment, relative to the slice maximum ----
         float s_seg[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -757,17 +763,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         if ((lane & 7) == 0)
             seg_out[(lane >> 3) * kWaves + wave] = (double)a1;
         if (tid == 0) {
-            int n = 0;
-            for (int k = 0; k < 3; ++k)
-                if (tail[k] != -INFINITY)
-                    out[n++] = (unsigned long long)__float_as_uint(tail[k]) | ((unsigned long long)(unsigned)(g.v4end + k) << 32);
             SliceStat* st = stat_at(W, slice);
             st->max_x = mx;
             st->argmax = 0;
             st->rest = 0.0;
             st->win_lo = 0;
             st->win_hi = -1;
-            st->count = n;
+            st->count = 0;
         }
         return;
     }
@@ -789,9 +791,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
     for (int q = 0; q < 32; ++q)
         bin_one(xv[q]);
-    for (int k = 0; k < 3; ++k)
-        if (tail[k] != -INFINITY)
-            bin_one(tail[k]);
     lds_barrier();  // histogram complete
     // what the lanes collected past the last bin belongs to the last bin (every wavefront adds the
     // places up for itself; only the owner of the last bin uses the sum)
@@ -844,7 +843,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // ---- which bins to write out.  Element counts come from the fixed-point sums: every element adds
     // between 32768 and 34219 units, so (units >> 15) never undercounts.  Every thread tests two
     // places of the search range; the largest that fits wins. ----
-    const int cap = kEmitCap - 3;  // room for the row's tail logits
+    const int cap = kEmitCap - 3;
     const int Lb = L.cut_bin;
     auto units = [&](int a, int z) { return L.cumq[z] - (a > 0 ? L.cumq[a - 1] : 0u); };
     auto fits = [&](int a, int z) { return (int)(units(a, z) >> 15) <= cap; };
@@ -920,10 +919,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 gather(__builtin_amdgcn_ballot_w64(in) & __builtin_amdgcn_ballot_w64(below), in && below, xv[q],
                        g.e0 + (q >> 2) * kIter + tid * 4 + (q & 3));
             }
-        }
-        for (int k = 0; k < 3; ++k) {
-            const bool in = tail[k] * rc.c16 >= t_emit;  // (-inf where there is no tail logit)
-            gather(__builtin_amdgcn_ballot_w64(in), in, tail[k], g.v4end + k);
         }
     }
     int base = 0;
@@ -1065,26 +1060,23 @@ struct FinishLds {
     uint32_t kmin[kWaves], kmax[kWaves];
 };
 
-// FILTERED = false takes the rows without a min-p / top-k filter, FILTERED = true the rows with one
-// (a launch with filter arrays runs both; each leaves the other's rows alone).
-// Three workgroups of the unfiltered kind share a CU (80 registers per lane, 50 KB of LDS each): the
-// step is bound by the latency of its phases, so the third one is nearly free (1024 rows: 78 -> 67 us).
+// One row without (FILTERED = false) or with (true) a min-p / top-k filter, by one workgroup.  False: the
+// row has to go to the whole-row routine.
 template <bool FILTERED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED ? 4 : 6))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
+__device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, int slices, int slice_elems, FinishLds& L)
 {
-    __shared__ FinishLds L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const long long r = blockIdx.x;
     const RowWs W = row_ws(ws, r, slices);
-    const float* __restrict__ x = sp.logits + r * sp.stride;
+    const float* __restrict__ row_x = sp.logits + r * sp.stride;
+    const int lead = row_lead(row_x);
+    const float* __restrict__ x = row_x - lead;  // position 0
     const int V = (int)sp.vocab;
     const float T = sp.temperature[r];
     const float top_p = sp.top_p[r];
     const bool greedy = (T == 0.f);
-    const int top_k = sp.top_k ? sp.top_k[r] : 0;
-    const float min_p = sp.min_p ? sp.min_p[r] : 0.f;
-    if (((top_k > 0 || min_p > 0.f) && !greedy) != FILTERED)
-        return;
+    const int top_k = FILTERED && sp.top_k ? sp.top_k[r] : 0;
+    const float min_p = FILTERED && sp.min_p ? sp.min_p[r] : 0.f;
     const bool cut = !greedy && top_p < 1.f;
     const int nseg = slices * kSegPerSlice;
     double* seg_mass = L.row.seg_mass;
@@ -1113,8 +1105,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
     }
     if (greedy) {
         if (tid == 0)
-            sp.tokens[r] = arg == 0x7fffffff ? 0 : arg;
-        return;
+            sp.tokens[r] = arg == 0x7fffffff ? 0 : max(arg - lead, 0);
+        return true;
     }
     const RowConst rc = row_const(T);
     RowScale rs;
@@ -1366,16 +1358,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
     for (int s = 0; s < (FILTERED ? 0 : slices); ++s) {
         if (L.covered[s])
             continue;
-        const SliceRange g = slice_range(s, slice_elems, V);
+        const SliceRange g = slice_range(s, slice_elems, V, lead);
         float xv[32];
         SPD_LOAD_SLICE(xv, x, g, tid)
+        SPD_MASK_SLICE(xv, x, g, tid)
 #pragma unroll
         for (int q = 0; q < 32; ++q) {
             const int i = g.e0 + (q >> 2) * kIter + tid * 4 + (q & 3);
-            take(i < g.v4end, xv[q], i, s);
+            take(i >= lead && i < g.e1, xv[q], i, s);
         }
-        for (int k = 0; k < 3; ++k)
-            take(tid == 0 && k < g.ntail, tid == 0 && k < g.ntail ? x[g.v4end + k] : 0.f, g.v4end + k, s);
         s_part += (double)f_part;
         f_part = 0.f;
     }
@@ -1417,8 +1408,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
         for (int s = 0; s < slices; ++s)
             ok = ok && L.covered[s];
         if (!ok) {
-            sample_row_from_memory(sp, r, L.row);
-            return;
+            return false;
         }
         unsigned long long ev[8][4];
         int cnt[8];
@@ -1457,8 +1447,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
             if (!bad)
                 key_k = radix_select((int)listed, true, 0.0, rank, bad, reached);
             if (bad) {
-                sample_row_from_memory(sp, r, L.row);
-                return;
+                return false;
             }
             __syncthreads();
             if (tid == 0)
@@ -1509,8 +1498,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
     }
     if (bad) {
         // candidate overflow or an estimate that missed the cut: redo the row the slow way
-        sample_row_from_memory(sp, r, L.row);
-        return;
+        return false;
     }
 
     // kept candidates join their segments (vocabulary order)
@@ -1577,7 +1565,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
         if (seg >= 0) {
             const int s = seg / kSegPerSlice;
             const int base = s * slice_elems + (seg % kSegPerSlice) * kSeg + lane * 4;
-            const int end = min(V, (s + 1) * slice_elems);
+            const int end = min(V + lead, (s + 1) * slice_elems);
             float pk[4];
             bool keep[4];
             float s4 = 0.f;
@@ -1586,7 +1574,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
                 const int i = base + k;
                 pk[k] = 0.f;
                 keep[k] = false;
-                if (i < end) {
+                if (i >= lead && i < end) {
                     const float xi = x[i];
                     const int b = bin_below(kf_row, bin_coord(xi, rc.c16));
                     if (b < lo || (b <= hi && order_key(xi) >= key_tau)) {
@@ -1619,7 +1607,30 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(FILTERED
             token = (first != 0x7fffffff && !take_last) ? first : lastk;
         }
         if (lane == 0)
-            sp.tokens[r] = token >= 0 ? token : 0;
+            sp.tokens[r] = token >= 0 ? token - lead : 0;
+    }
+    return true;
+}
+
+// ANY = false: no row has a filter; three workgroups share a CU (80 registers per lane, 50 KB of LDS
+// each): the step is bound by the latency of its phases, so the third one is nearly free (1024 rows:
+// 78 -> 67 us).  ANY = true (filter arrays are given): every row takes the routine it needs in one
+// launch, so that the two kinds run side by side.  (192 rows of 50257 unaligned logits, a third of them
+// each with top-k, min-p and no filter, some greedy: whole call 55 us; 249 in the whole-row routine,
+// which unaligned rows used to take.)
+template <bool ANY>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(ANY ? 4 : 6))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
+{
+    __shared__ FinishLds L;
+    const long long r = blockIdx.x;
+    bool done;
+    if (ANY && sp.temperature[r] != 0.f && ((sp.top_k && sp.top_k[r] > 0) || (sp.min_p && sp.min_p[r] > 0.f)))
+        done = finish_row<true>(sp, ws, slices, slice_elems, L);
+    else
+        done = finish_row<false>(sp, ws, slices, slice_elems, L);
+    if (!done) {
+        __syncthreads();
+        sample_row_from_memory(sp, r, L.row);
     }
 }
 
@@ -1656,19 +1667,23 @@ size_t sampler_workspace_bytes(long long rows, long long vocab)
 hipError_t launch_sampler(const SamplerParams& p, void* ws, hipStream_t s)
 {
     const int slices = sampler_slices(p.rows, p.vocab);
+    // Rows that do not all start on a 16-byte boundary are cut in positions counted from the boundary
+    // before each (up to three more than the vocabulary).
     const bool aligned = (p.stride % 4 == 0) && ((uintptr_t)p.logits % 16 == 0);
-    if (slices == 0 || !aligned || p.vocab < 4) {
+    const long long span = aligned ? p.vocab : p.vocab + 3;
+    if (slices == 0 || span > (long long)slices * kSliceMax || p.vocab < (aligned ? 4 : 8)) {
         hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p);
         return hipGetLastError();
     }
-    int slice_elems = (int)((p.vocab + slices - 1) / slices);
+    int slice_elems = (int)((span + slices - 1) / slices);
     slice_elems = (slice_elems + 3) / 4 * 4;
     hipLaunchKernelGGL(sampler_scan_kernel, dim3((unsigned)(p.rows * slices)), dim3(kBlock), 0, s, p, (char*)ws, slices,
                        slice_elems);
-    hipLaunchKernelGGL(sampler_finish_kernel<false>, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p, (char*)ws, slices,
-                       slice_elems);
-    if (p.top_k || p.min_p)  // rows with a filter
+    if (p.top_k || p.min_p)
         hipLaunchKernelGGL(sampler_finish_kernel<true>, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p, (char*)ws,
+                           slices, slice_elems);
+    else
+        hipLaunchKernelGGL(sampler_finish_kernel<false>, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p, (char*)ws,
                            slices, slice_elems);
     return hipGetLastError();
 }

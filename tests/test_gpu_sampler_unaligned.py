@@ -1,0 +1,64 @@
+"""Rows that do not start on a 16-byte boundary (a vocabulary or a row stride that is no multiple of 4, a
+logits pointer that is only 4-byte aligned) run through the sliced sampler kernels: every distance of
+a row's start from a boundary, vocabularies either side of a slice's and a float4's end, all kinds
+of rows, and what surrounds a row in memory is never taken for a logit."""
+import numpy as np
+import pytest
+
+from gpu_checks import compare_tokens
+from paper_2502_02534_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2502_02534_amd import binding, device
+    binding.load()
+    return device
+
+
+# (vocabulary, row stride, floats by which the first row is off a 16-byte boundary)
+SHAPES = [(8, 9, 1), (9, 9, 2), (4097, 4101, 0), (4099, 4099, 3), (12289, 12290, 1), (16381, 16381, 1), (16384, 16385, 0),
+          (32003, 32003, 2), (50257, 50257, 0), (65534, 65535, 3), (128256, 128256, 2), (131071, 131071, 0), (200003, 200003, 1)]
+
+
+@pytest.mark.parametrize("vocab,stride,off", SHAPES)
+def test_unaligned_rows(dev, oracle, vocab, stride, off):
+    from paper_2502_02534_amd import binding as B
+    rows = 13 if vocab > 100000 else 37
+    print(f"unaligned rows: vocab {vocab}, stride {stride}, offset {off}", flush=True)
+    rng = np.random.default_rng(vocab + stride + off)
+    x = (rng.standard_normal((rows, vocab)) * 3.0).astype(np.float32)
+    x[1::4] = W.bf16_bits_to_f32(W.f32_to_bf16_bits(x[1::4]))  # many exact ties
+    x[2::5, : vocab // 2] -= 40.0                              # slices far below the row's maximum: not covered
+    x[3, :] = np.sort(x[3])                                    # one wavefront holds a slice's whole window
+    x[5, 0] = x[5].max() + 1.0                                 # the first and the last logit of a row stand out
+    x[6, -1] = x[6].max() + 1.0
+    t = rng.choice(np.array([0.4, 0.7, 1.0], np.float32), rows)
+    t[4::6] = 0.0
+    top_p = np.full(rows, 0.95, np.float32)
+    top_p[3::7] = 1.0
+    u = rng.random(rows, dtype=np.float32)
+    u[7], u[8] = 0.0, np.float32(1.0) - np.float32(2.0 ** -24)
+    buf = torch.full((off + rows * stride + 8,), 1e30, dtype=torch.float32, device="cuda")
+    view = buf[off:off + rows * stride].view(rows, stride)
+    view[:, :vocab] = torch.from_numpy(x).cuda()
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ws = torch.full((max(256, B.sample_tokens_workspace_size(rows, vocab)),), 255, dtype=torch.uint8, device="cuda")
+    tokens = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+    td, pd, ud = to(t), to(top_p), to(u)
+    B.sample_tokens(view, B.SPD_F32, rows, vocab, stride, td, pd, ud, tokens, ws)
+    torch.cuda.synchronize()
+    compare_tokens(tokens.cpu().numpy(), oracle.sample_tokens(x, t, top_p, u), u, vocab, label="plain ")
+    top_k = rng.choice(np.array([0, 1, 50, 700], np.int32), rows)
+    min_p = rng.choice(np.array([0.0, 0.02, 0.3], np.float32), rows)
+    kd, md = to(np.minimum(top_k, vocab).astype(np.int32)), to(min_p)
+    tokens.fill_(-7)
+    B.sample_tokens_filtered(view, B.SPD_F32, rows, vocab, stride, td, pd, kd, md, ud, tokens, ws)
+    torch.cuda.synchronize()
+    o = oracle.sample_tokens_filtered(x, t, top_p, u, np.minimum(top_k, vocab).astype(np.int32), min_p)
+    compare_tokens(tokens.cpu().numpy(), o, u, vocab, label="filtered ")
