@@ -10,8 +10,6 @@
 
 #include <hip/hip_fp16.h>
 
-#include <type_traits>
-
 namespace spd {
 namespace {
 
@@ -24,161 +22,181 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
     return (uint16_t)(u >> 16);
 }
 
-constexpr int kMergeThreads = 256;
-constexpr int kMaxSlots = 128;   // prefix splits + suffix chunks (each at most 64)
+constexpr int kMergeWaves = 4;   // wavefronts per workgroup
 
-// One workgroup merges kMergeThreads / (D/4) rows; a thread owns 4 channels of one row.
-// The threads of a row share out the (m, l) pairs, find the row's m and l with shuffles and
-// leave the weights l_i 2^(m_i - m) (0 for empty partials) in LDS; then every thread combines
-// the partial outputs, whose loads (up to 32 independent loads per thread) were issued first.
-// HALF: the partial outputs are fp16 (8 bytes per thread and partial) instead of fp32 (16).
-template <bool HALF> struct PartVec;
-template <> struct PartVec<false> {
-    typedef float4 type;
-    static __device__ __forceinline__ float4 zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-    static __device__ __forceinline__ float4 widen(float4 v) { return v; }
-};
-template <> struct PartVec<true> {
-    typedef uint2 type;
-    static __device__ __forceinline__ uint2 zero() { return make_uint2(0u, 0u); }
-    static __device__ __forceinline__ float4 widen(uint2 v)
+// 16 bytes of a partial output: 8 channels of fp16 or 4 of fp32.
+template <bool HALF> struct PartVec {
+    static constexpr int kChannels = HALF ? 8 : 4;
+    static __device__ __forceinline__ void widen(const uint4& v, float (&f)[kChannels])
     {
-        const float2 a = __half22float2(*reinterpret_cast<const __half2*>(&v.x));
-        const float2 b = __half22float2(*reinterpret_cast<const __half2*>(&v.y));
-        return make_float4(a.x, a.y, b.x, b.y);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (HALF) {
+                const float2 a = __half22float2(*reinterpret_cast<const __half2*>(&w[i]));
+                f[2 * i] = a.x;
+                f[2 * i + 1] = a.y;
+            } else {
+                f[i] = __uint_as_float(w[i]);
+            }
+        }
     }
 };
 
-// BATCH: output parts a thread loads at a time (8 when the row has at most 8 slots, else 32).
-// PERLANE: (m, l) pairs a thread may have to take (kMaxSlots / tpr, rounded up).  Both only size
-// register arrays: the smaller the arrays, the more workgroups a CU holds.
-template <bool HALF, int BATCH, int PERLANE>
-__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p, int tpr /* threads per row */)
+// CL lanes own the 16-byte pieces of a row (a power of two that covers them); GROUPS such groups of
+// lanes share the row's slots (group g takes slots g, g + GROUPS, ...) and add their sums with shuffles; a
+// wavefront takes 64 / (CL GROUPS) rows.  The lanes of a row also take its (m, l) pairs, and hand
+// their weights round with shuffles, so there is no LDS and no barrier.  BATCH is the number of parts a
+// lane requests at a time.
+//   few rows: all 64 lanes on one row (up to 128 slots, two pairs per lane).  Bound: latency, i.e. one round
+//     trip for everything (the pairs and the first BATCH parts of every lane are requested together,
+//     from clamped places rather than under branches) and the launch.
+//   many rows of at most eight slots: one group per row.  Bound: HBM (partial states).
+// Measured in replayed graphs (before: 32 threads per row, up to 32 guarded loads each, weights through
+// LDS): 512 rows x 20 slots 6.1 -> 3.6 us, 2048 x 22 6.6 -> 4.7, 13312 x 26 18.0 -> 10.1,
+// 16 x 5 (fp32) 3.7 -> 2.5; 32768 x 8 14.4 -> 14.2 (16.2 with all 64 lanes on one row).
+template <bool HALF, int CL, int GROUPS, int BATCH>
+__global__ __launch_bounds__(kMergeWaves * 64) void attn_merge_kernel(AttnParams p)
 {
-    typedef typename PartVec<HALF>::type vec_t;
-    typedef typename std::conditional<HALF, __half, float>::type elem_t;
-    __shared__ float wgt[kMergeThreads / 8][kMaxSlots];  // at most 32 rows per block (D = 32)
-
-    const int rows_per_block = kMergeThreads / tpr;
-    const int r_in = threadIdx.x / tpr;
-    const int c = threadIdx.x % tpr;  // channel group
-    const long long total = (long long)p.N * p.Hq;
-    const long long row = (long long)blockIdx.x * rows_per_block + r_in;
-    const bool row_ok = row < total;
-
+    constexpr int kLanes = CL * GROUPS, kRows = 64 / kLanes, kCh = PartVec<HALF>::kChannels;
+    constexpr int kPairs = kLanes == 64 ? 2 : 1;   // (m, l) pairs per lane
+    const int lane = threadIdx.x & 63, mine = lane % kLanes, c = lane % CL, g = mine / CL;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = ((int)blockIdx.x * kMergeWaves + wave) * kRows + lane / kLanes;
+    const bool row_ok = row < p.N * p.Hq;
     // Every slot of the row holds an (m, l) pair: the pass that owns a slot stores l = 0 when its
     // token range is empty (a prefix split past the group's length, a suffix chunk past the
     // sample's), and leaves the slot's output part unwritten.  The row therefore needs no lengths
     // here; a slot with l = 0 gets weight 0 and its output part, though loaded, is not used.
-    const int S = row_ok ? p.num_slots : 0;
-    const bool ch_ok = row_ok && 4 * c < p.D;
-    const elem_t* base = (const elem_t*)p.part_acc + part_index(p, row_ok ? row : 0, 0) * p.D + 4 * c;
-    // The first batch of output-part loads does not need the weights: it is issued together
-    // with the (m, l) loads so that both round trips overlap.
-    constexpr int kBatch = BATCH;
-    vec_t v[kBatch];
+    const int S = p.num_slots;
+    const long long base = part_index(p, row_ok ? row : 0, 0);
+    const bool ch_ok = kCh * c < p.D;
+    const char* parts = (const char*)p.part_acc + (base * p.D + (ch_ok ? kCh * c : 0)) * (HALF ? 2 : 4);
+    const unsigned part_bytes = (unsigned)p.D * (HALF ? 2u : 4u);
+    uint4 v[BATCH];
+    auto request = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-        v[u] = PartVec<HALF>::zero();
-        if (ch_ok && u < S)
-            v[u] = *reinterpret_cast<const vec_t*>(base + (long long)u * p.D);
-    }
-    // Weights: the tpr threads of a row (a power of two <= 64, aligned inside a wavefront) each
-    // take every tpr-th slot; maximum and sum go round the group with shuffles.
-    constexpr int kPerLane = PERLANE;
-    float2 mine[kPerLane];
+        for (int u = 0; u < BATCH; ++u)
+            v[u] = *reinterpret_cast<const uint4*>(parts + (size_t)((unsigned)min(s0 + u * GROUPS + g, S - 1) * part_bytes));
+    };
+    float2 ml[kPairs];
     float m = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < kPerLane; ++k) {
-        const int i = c + k * tpr;
-        mine[k] = make_float2(-INFINITY, 0.f);
-        if (i < S)
-            mine[k] = p.part_ml[part_index(p, row, i)];
-        if (mine[k].y > 0.f)
-            m = fmaxf(m, mine[k].x);
+    for (int k = 0; k < kPairs; ++k) {
+        ml[k] = make_float2(-INFINITY, 0.f);
+        if (mine + kLanes * k < S)
+            ml[k] = p.part_ml[base + mine + kLanes * k];
     }
-    for (int o = tpr >> 1; o > 0; o >>= 1)
+    if (S > 0)
+        request(0);
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k)
+        m = ml[k].y > 0.f ? fmaxf(m, ml[k].x) : m;
+#pragma unroll
+    for (int o = kLanes >> 1; o > 0; o >>= 1)
         m = fmaxf(m, __shfl_xor(m, o));
-    float l = 0.f;
+    float w[kPairs], l = 0.f;
 #pragma unroll
-    for (int k = 0; k < kPerLane; ++k) {
-        const int i = c + k * tpr;
-        const float w = mine[k].y > 0.f ? mine[k].y * __builtin_amdgcn_exp2f(mine[k].x - m) : 0.f;
-        if (i < S)
-            wgt[r_in][i] = w;
-        l += w;
+    for (int k = 0; k < kPairs; ++k) {
+        w[k] = ml[k].y > 0.f ? ml[k].y * __builtin_amdgcn_exp2f(ml[k].x - m) : 0.f;
+        l += w[k];
     }
-    for (int o = tpr >> 1; o > 0; o >>= 1)
+#pragma unroll
+    for (int o = kLanes >> 1; o > 0; o >>= 1)
         l += __shfl_xor(l, o);
-    __syncthreads();
-    if (!ch_ok)
-        return;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i0 = 0; i0 < S; i0 += kBatch) {
-        if (i0 > 0) {
+    float acc[kCh];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                v[u] = PartVec<HALF>::zero();
-                if (i0 + u < S)
-                    v[u] = *reinterpret_cast<const vec_t*>(base + (long long)(i0 + u) * p.D);
-            }
-        }
+    for (int e = 0; e < kCh; ++e)
+        acc[e] = 0.f;
+    for (int s0 = 0; s0 < S; s0 += BATCH * GROUPS) {
+        if (s0 > 0)
+            request(s0);
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const float w = i0 + u < S ? wgt[r_in][i0 + u] : 0.f;
-            if (w != 0.f) {
-                const float4 f = PartVec<HALF>::widen(v[u]);
-                acc.x = fmaf(f.x, w, acc.x);
-                acc.y = fmaf(f.y, w, acc.y);
-                acc.z = fmaf(f.z, w, acc.z);
-                acc.w = fmaf(f.w, w, acc.w);
+        for (int u = 0; u < BATCH; ++u) {
+            const int s = s0 + u * GROUPS + g;
+            float ws = __shfl(w[0], (lane & ~(kLanes - 1)) + (s & (kLanes - 1)));
+            if (kPairs == 2 && S > kLanes)
+                ws = s < kLanes ? ws : __shfl(w[1], s & (kLanes - 1));
+            float f[kCh];
+            PartVec<HALF>::widen(v[u], f);
+            if (ws != 0.f && s < S) {
+#pragma unroll
+                for (int e = 0; e < kCh; ++e)
+                    acc[e] = fmaf(f[e], ws, acc[e]);
             }
         }
     }
+#pragma unroll
+    for (int o = CL; o < kLanes; o <<= 1)
+#pragma unroll
+        for (int e = 0; e < kCh; ++e)
+            acc[e] += __shfl_xor(acc[e], o);
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    acc.x *= inv;
-    acc.y *= inv;
-    acc.z *= inv;
-    acc.w *= inv;
-    if (p.dtype == 0) {
-        *reinterpret_cast<float4*>((float*)p.out + row * p.D + 4 * c) = acc;
-    } else {
-        uint2 o;
-        o.x = (uint32_t)f32_to_bf16_rne(acc.x) | ((uint32_t)f32_to_bf16_rne(acc.y) << 16);
-        o.y = (uint32_t)f32_to_bf16_rne(acc.z) | ((uint32_t)f32_to_bf16_rne(acc.w) << 16);
-        *reinterpret_cast<uint2*>((uint16_t*)p.out + row * p.D + 4 * c) = o;
+#pragma unroll
+    for (int e = 0; e < kCh; ++e)
+        acc[e] *= inv;
+    if (g == 0 && ch_ok && row_ok) {
+        const long long at = (long long)row * p.D + kCh * c;
+        if constexpr (HALF) {
+            uint4 o;
+            o.x = (uint32_t)f32_to_bf16_rne(acc[0]) | ((uint32_t)f32_to_bf16_rne(acc[1]) << 16);
+            o.y = (uint32_t)f32_to_bf16_rne(acc[2]) | ((uint32_t)f32_to_bf16_rne(acc[3]) << 16);
+            o.z = (uint32_t)f32_to_bf16_rne(acc[4]) | ((uint32_t)f32_to_bf16_rne(acc[5]) << 16);
+            o.w = (uint32_t)f32_to_bf16_rne(acc[6]) | ((uint32_t)f32_to_bf16_rne(acc[7]) << 16);
+            *reinterpret_cast<uint4*>((uint16_t*)p.out + at) = o;
+        } else {
+            *reinterpret_cast<float4*>((float*)p.out + at) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        }
     }
-    if (p.lse && c == 0)
+    if (p.lse && mine == 0 && row_ok)
         p.lse[row] = l > 0.f ? (m + __log2f(l)) * kLn2 : -INFINITY;
+}
+
+template <bool HALF, int CL, int GROUPS, int BATCH>
+void launch_merge_kernel(const AttnParams& p, hipStream_t s)
+{
+    constexpr int kRowsPerBlock = kMergeWaves * 64 / (CL * GROUPS);
+    const dim3 grid((unsigned)(((long long)p.N * p.Hq + kRowsPerBlock - 1) / kRowsPerBlock));
+    hipLaunchKernelGGL((attn_merge_kernel<HALF, CL, GROUPS, BATCH>), grid, dim3(kMergeWaves * 64), 0, s, p);
+}
+
+template <bool HALF, int CL>
+void launch_merge_cl(const AttnParams& p, hipStream_t s)
+{
+    // From 8192 rows on (two wavefronts per SIMD with four rows each) there are loads enough in flight without
+    // sharing a row's slots out (32768 rows x 8 slots: 14.2 us against 16.2).
+    if (CL < 64 && p.num_slots <= 8 && (long long)p.N * p.Hq >= 8192) {
+        if (p.num_slots <= 4)
+            launch_merge_kernel<HALF, CL, 1, 4>(p, s);
+        else
+            launch_merge_kernel<HALF, CL, 1, 8>(p, s);
+        return;
+    }
+    const int per_lane = (p.num_slots + 64 / CL - 1) / (64 / CL);
+    if (per_lane <= 2)
+        launch_merge_kernel<HALF, CL, 64 / CL, 2>(p, s);
+    else if (per_lane <= 4)
+        launch_merge_kernel<HALF, CL, 64 / CL, 4>(p, s);
+    else
+        launch_merge_kernel<HALF, CL, 64 / CL, 8>(p, s);
 }
 
 }  // namespace
 
+// Partial outputs are fp16 exactly when the result is bf16 (p.part_half).
 hipError_t launch_attn_merge(const AttnParams& p, hipStream_t s)
 {
-    // threads per row: the power of two >= max(8, D/4); lanes past D/4 idle
-    int use = 8;
-    while (use * 4 < p.D)
-        use <<= 1;
-    const int rows_per_block = kMergeThreads / use;
-    const long long total = (long long)p.N * p.Hq;
-    const dim3 grid((unsigned)((total + rows_per_block - 1) / rows_per_block));
-    const bool few = p.num_slots <= 8, wide = use >= 32;
-    const dim3 block(kMergeThreads);
-#define SPD_MERGE(HALF, BATCH, PERLANE) \
-    hipLaunchKernelGGL((attn_merge_kernel<HALF, BATCH, PERLANE>), grid, block, 0, s, p, use)
+    const int pieces = p.D * (p.part_half ? 2 : 4) / 16;
     if (p.part_half) {
-        if (few && wide) SPD_MERGE(true, 8, kMaxSlots / 32);
-        else if (wide) SPD_MERGE(true, 32, kMaxSlots / 32);
-        else if (few) SPD_MERGE(true, 8, kMaxSlots / 8);
-        else SPD_MERGE(true, 32, kMaxSlots / 8);
+        if (pieces <= 8) launch_merge_cl<true, 8>(p, s);
+        else if (pieces <= 16) launch_merge_cl<true, 16>(p, s);
+        else launch_merge_cl<true, 32>(p, s);
     } else {
-        if (few && wide) SPD_MERGE(false, 8, kMaxSlots / 32);
-        else if (wide) SPD_MERGE(false, 32, kMaxSlots / 32);
-        else if (few) SPD_MERGE(false, 8, kMaxSlots / 8);
-        else SPD_MERGE(false, 32, kMaxSlots / 8);
+        if (pieces <= 8) launch_merge_cl<false, 8>(p, s);
+        else if (pieces <= 16) launch_merge_cl<false, 16>(p, s);
+        else if (pieces <= 32) launch_merge_cl<false, 32>(p, s);
+        else launch_merge_cl<false, 64>(p, s);
     }
-#undef SPD_MERGE
     return hipGetLastError();
 }
 
