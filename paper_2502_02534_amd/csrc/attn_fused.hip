@@ -3,8 +3,7 @@
 // The prefix pass is bound by the matrix pipe and the vector ALU, the suffix pass by HBM, and
 // neither needs the other's result before the merge.  One grid of 256-thread workgroups with
 // 80 KB of LDS carries both, two workgroups per CU: the first workgroups run the prefix body
-// (four wavefronts, 128 rows, K ring of 2 and V ring of 3 tiles, copies one tile ahead), the
-// rest run the suffix body (four wavefront items; it uses no LDS).  Workgroups start in index order; the prefix workgroups come first (or, when there are
+// (four wavefronts, 128 rows, rings of five 32-token tiles), the rest run the suffix body (four wavefront items; it uses no LDS).  Workgroups start in index order; the prefix workgroups come first (or, when there are
 // more of them than CUs, evenly spread through the grid), so that a CU holds one prefix workgroup
 // and, beside it, suffix workgroups: each SIMD has one wavefront that multiplies and one that
 // streams, HBM is busy during the prefix pass, and there is no launch (with its ramp and tail)
@@ -23,7 +22,7 @@ namespace spd {
 namespace {
 
 constexpr int kFusedWaves = 4;
-constexpr int kFusedLds = prefix_impl::prefix_lds_bytes(2, 3);
+constexpr int kFusedLds = prefix_impl::kPrefixLds;
 
 template <bool PAGED>
 __global__ __launch_bounds__(kFusedWaves * 64) __attribute__((amdgpu_waves_per_eu(2))) void attn_fused_kernel(
@@ -56,7 +55,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) __attribute__((amdgpu_waves_per_e
         const PrefixLevelParams& lv = fl.level[l];
         const prefix_impl::PrefixItem it =
             prefix_impl::prefix_item(pidx - fl.first_block[l], lv.num_splits, lv.rowtiles, lv.groups * p.Hkv);
-        prefix_impl::prefix_body<kFusedWaves, PAGED, 2, 3, 1>(p, lv, lds, it.split, it.rowtile, it.z);
+        prefix_impl::prefix_body<kFusedWaves, PAGED>(p, lv, lds, it.split, it.rowtile, it.z);
     } else {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const long long item = sidx * kFusedWaves + wave;

@@ -7,10 +7,9 @@
 // A query row is (sample, head in group); each wavefront owns 32 rows (one 32-wide column
 // block of the transposed products).
 //
-// Data movement.  K and V tiles of 64 tokens go from global memory straight into LDS
-// (global_load_lds_dwordx4, no registers in between), into a ring of K slots and a ring of V
-// slots, one or two tiles ahead of the tile in use (K of a tile is needed one iteration before
-// its V).  Both tiles are row-major [token][256 bytes] without
+// Data movement.  K and V tiles of 32 tokens go from global memory straight into LDS
+// (global_load_lds_dwordx4, no registers in between), into a ring of five K slots and a ring of five V
+// slots, four tiles ahead of their use.  Both tiles are row-major [token][256 bytes] without
 // padding; bank conflicts are avoided by an XOR swizzle of the 16-byte pieces of a row,
 // applied on the global side of the copy (lane L of a copy instruction always lands at
 // LDS offset 16 L, but it may fetch any piece).
@@ -26,6 +25,18 @@
 // Every lane owns one query row in both products, so the online-softmax statistics and the
 // accumulator rescale are lane-local.  The running state is the deferred-division form of the
 // paper's online-softmax recurrence (App., attn task 2).
+//
+// Bound: the matrix pipe (16 products a tile and wavefront at about 25 ns each under load, i.e. near the
+// 1.2 PFLOP/s that a large matrix product reaches on this card) and about 9 us of launch, first copies and the
+// partial states.  Three tiles are in work at once, the scores of one, the softmax of the one before
+// and P V of the one before that, interleaved instruction by instruction, because a wavefront is alone
+// on its SIMD here (or beside a streaming one).  Measured against 64-token tiles with copies one tile
+// ahead and the softmax between two MFMA regions: own launch, 8 prompts x 128 samples (longest split 208
+// old tiles) 385 -> 296 us, 32 samples x 8 heads of a 16k prompt 28.7 -> 27.7; with the suffix pass in the
+// launch, whole call, the latter 48.7 -> 44.5, 64 samples of an 8k prompt 58.2 -> 57.0, 16 samples of a
+// 2k prompt unchanged.  Tried without gain: the two halves of a workgroup in opposite phases
+// (products / softmax, own launch 28.7 -> 30.3), 64 KB of copies under way instead of 32 alone, five or
+// seven LDS fragments ahead instead of four, tile orders rotated from split to split.
 #pragma once
 
 #include "spd_internal.h"
@@ -46,7 +57,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kD = 128;
-constexpr int kTileN = 64;               // tokens per tile
+constexpr int kTileN = 32;               // tokens per tile
 constexpr int kTileBytes = kTileN * 256;  // one K or V tile
 constexpr int kRowU4 = kD * 2 / 16;
 constexpr int kAhead = 4;                // LDS fragments in flight ahead of the MFMAs
@@ -75,17 +86,16 @@ template <int N> __device__ __forceinline__ void wait_vmcnt()
 }
 
 // One LDS fragment: a K fragment is one ds_read_b128, a V fragment two transposing reads.
-// QK: a = channel step (0..7), b = token block (0..1).  PV: a = token step (0..3), b = channel
-// block (0..3).  When a region holds both products they alternate.
+// QK: a = channel step (0..7).  PV: a = token step (0..1), b = channel block (0..3).  When a region
+// holds both products they alternate.
 template <bool QK, bool PV, int K> struct Frag {
     static constexpr bool both = QK && PV;
     static constexpr int idx = both ? (K >> 1) : K;
     static constexpr bool is_pv = both ? ((K & 1) != 0) : PV;
-    static constexpr int a = is_pv ? (idx >> 2) : (idx >> 1);
-    static constexpr int b = is_pv ? (idx & 3) : (idx & 1);
-    static constexpr int ops = is_pv ? 2 : 1;
+    static constexpr int a = is_pv ? (idx >> 2) : idx;
+    static constexpr int b = is_pv ? (idx & 3) : 0;
 };
-template <bool QK, bool PV> constexpr int frag_count() { return (QK ? 16 : 0) + (PV ? 16 : 0); }
+template <bool QK, bool PV> constexpr int frag_count() { return (QK ? 8 : 0) + (PV ? 8 : 0); }
 // LDS instructions issued after fragment K while K is the oldest outstanding one
 template <bool QK, bool PV, int K> constexpr int ops_after()
 {
@@ -151,22 +161,20 @@ __device__ __forceinline__ PrefixItem prefix_item(int local, int num_splits, int
     return it;
 }
 
-// LDS of a workgroup: KS slots for K tiles followed by VS slots for V tiles.
-constexpr int prefix_lds_bytes(int KS, int VS) { return (KS + VS) * kTileBytes; }
+// Copies of a tile start kCopyAhead tiles before its use; a ring holds the tile in use and those under way.
+constexpr int kCopyAhead = 4;
+constexpr int kRing = kCopyAhead + 1;
+// LDS of a workgroup: the K ring followed by the V ring.
+constexpr int kPrefixLds = 2 * kRing * kTileBytes;
 
 // Body of one workgroup of WAVES wavefronts for prefix level `lv`: (split, rowtile,
 // z = group * Hkv + KV head).  `lds` is
-// prefix_lds_bytes(KS, VS) of LDS; every wavefront of the workgroup must call it (it uses
-// workgroup barriers).  Copies run AHEAD tiles ahead of the tile in use.  K of tile t is read
-// in iteration t and V of tile t in iteration t + 1, and the copies of tile t + AHEAD start at
-// the top of iteration t, so the rings need KS >= AHEAD + 1 and VS >= AHEAD + 2 slots.
-template <int WAVES, bool PAGED, int KS = 4, int VS = 4, int AHEAD = 2>
+// kPrefixLds bytes of LDS; every wavefront of the workgroup must call it (it uses workgroup barriers).
+template <int WAVES, bool PAGED>
 __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLevelParams& lv, uint4* lds, int split,
                                             int rowtile, int z)
 {
-    static_assert(AHEAD == 1 || AHEAD == 2, "copy distance");
-    static_assert(KS >= AHEAD + 1 && VS >= AHEAD + 2, "rings too short for the copy distance");
-    constexpr int kIPW = 32 / WAVES;  // copy instructions per wave per tile
+    constexpr int kIPW = 16 / WAVES;  // copy instructions per wave per step
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -218,88 +226,55 @@ __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLev
     }
 
     // ---- global -> LDS copies -------------------------------------------------------------------
-    // A tile takes 32 copy instructions (16 for K, 16 for V), each covering 4 token rows; wave w
-    // issues instructions w kIPW .. w kIPW + kIPW - 1.  Lane (r, c) of instruction q fetches piece
-    // c ^ swz(row) of row 4 (q & 15) + r.  Rows past the end of the split are clamped to its last
-    // token (their scores are masked later).  The four rows of an instruction lie in one page, so
-    // the page number is uniform over the wavefront.
+    // A tile takes 16 copy instructions (8 for K, 8 for V), each covering 4 token rows.  The first half of
+    // the wavefronts copies K, the other half V: wavefront w of its half issues instructions
+    // w kIPW .. w kIPW + kIPW - 1.  Lane (r, c) of instruction q fetches piece c ^ swz(row) of row 4 q + r.
+    // Rows past the end of the split are clamped to its last token (their scores are masked later).
+    // A wavefront's rows of a tile lie in one page, so the page number is uniform over it.
     const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds;
     const int lane_row = lane >> 4;
-    unsigned lane_off[kIPW];  // byte offset of this lane's piece for a full tile, relative to the group's first row
+    const bool copies_v = wave >= WAVES / 2;
+    const int row_first = 4 * kIPW * (copies_v ? wave - WAVES / 2 : wave);  // of this wavefront's rows within a tile
+    unsigned lane_off[kIPW];  // byte offset of this lane's piece for a full tile, relative to the tile's first row
 #pragma unroll
     for (int i = 0; i < kIPW; ++i) {
-        const int tl = 4 * ((wave * kIPW + i) & 15) + lane_row;
-        lane_off[i] = (unsigned)(lane_row * (unsigned)tok_stride + (((lane & 15) ^ swz(tl)) << 4));
+        const int tl = row_first + 4 * i + lane_row;
+        lane_off[i] = (unsigned)((4 * i + lane_row) * (unsigned)tok_stride + (((lane & 15) ^ swz(tl)) << 4));
     }
-    // page numbers of the next tile to be copied, fetched one tile ahead of their use
-    int next_page[kIPW];
-    auto fetch_pages = [&](int tile) __attribute__((always_inline)) {
-        if (PAGED) {
-#pragma unroll
-            for (int i = 0; i < kIPW; ++i) {
-                const int tg = min(t0 + tile * kTileN + 4 * ((wave * kIPW + i) & 15), t1 - 1);
-                next_page[i] = pages[tg >> 4];
-            }
-        }
+    const char* const tensor = copies_v ? vg : kg;
+    const char* const first_row = tensor + head_base + (long long)row_first * tok_stride;  // contiguous KV: + tile's first token
+    uint4* const ring_lds = lds + ((copies_v ? kRing * kTileBytes : 0) + row_first * 256) / 16;
+    // page number of the next tile to be copied, fetched one tile ahead of its use
+    int next_page = 0;
+    auto fetch_page = [&](int tile) __attribute__((always_inline)) {
+        if (PAGED)
+            next_page = pages[min(t0 + tile * kTileN + row_first, t1 - 1) >> 4];
     };
-    fetch_pages(0);
-    // Contiguous KV, whole tiles: the source of copy i is a fixed pointer (tensor, KV head, first row
-    // of the group) plus a per-tile offset shared by all copies, so a copy costs one 64-bit add.
-    const char* group_ptr[kIPW];
-#pragma unroll
-    for (int i = 0; i < kIPW; ++i) {
-        const int q = wave * kIPW + i;
-        group_ptr[i] = (q < 16 ? kg : vg) + head_base + (long long)(4 * (q & 15)) * tok_stride;
-    }
+    fetch_page(0);
     auto issue_tile = [&](int tile) __attribute__((always_inline)) {
         const int tb = t0 + tile * kTileN;
-        const int kslot_bytes = (tile % KS) * kTileBytes, vslot_bytes = (KS + tile % VS) * kTileBytes;
+        uint4* const dst = ring_lds + (tile % kRing) * (kTileBytes / 16);
         const bool full = tb + kTileN <= t1;
-        if (!PAGED && full) {
-            const long long tile_off = (long long)tb * tok_stride;
-#pragma unroll
-            for (int i = 0; i < kIPW; ++i) {
-                const int q = wave * kIPW + i;
-                const char* src = group_ptr[i] + tile_off + lane_off[i];
-                uint4* dst = lds + ((q < 16 ? kslot_bytes : vslot_bytes) + (q & 15) * 1024) / 16;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                                 (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-            }
-            return;
-        }
+        const int tg = min(tb + row_first, t1 - 1);  // this wavefront's first row, clamped
+        const char* const src = PAGED ? tensor + (long long)next_page * page_stride + head_base + (tg & 15) * 256
+                                      : first_row + (long long)(full ? tb : tg - row_first) * tok_stride;
 #pragma unroll
         for (int i = 0; i < kIPW; ++i) {
-            const int q = wave * kIPW + i;
-            const int g = 4 * (q & 15);  // first row of the group within the tile
-            const int tg = min(tb + g, t1 - 1);
-            long long base;              // uniform: byte offset of row tg
-            if (PAGED)
-                base = (long long)next_page[i] * page_stride + head_base + (tg & 15) * 256;
-            else
-                base = head_base + (long long)tg * tok_stride;
             unsigned off = lane_off[i];
             if (!full) {
-                const int rr = min(tg + lane_row, t1 - 1) - tg;  // clamped row within the group
-                off = (unsigned)(rr * (unsigned)tok_stride + (((lane & 15) ^ swz(g + lane_row)) << 4));
+                const int row = min(tg + 4 * i + lane_row, t1 - 1) - tg;  // clamped row, relative to the first
+                off = (unsigned)(row * (unsigned)tok_stride + (((lane & 15) ^ swz(row_first + 4 * i + lane_row)) << 4));
             }
-            const char* src = (q < 16 ? kg : vg) + base + off;
-            uint4* dst = lds + ((q < 16 ? kslot_bytes : vslot_bytes) + (q & 15) * 1024) / 16;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + off),
+                                             (__attribute__((address_space(3))) void*)(dst + i * 64), 16, 0, 0);
         }
-        fetch_pages(tile + 1);
+        fetch_page(tile + 1);
     };
 
     // ---- per-lane LDS addresses of the MFMA operand fragments (relative to a tile) ---------------
-    // K fragment (st, mb): row tl = 32 mb + col, piece (2 st + h) ^ swz(tl).  2 st has no bit 0 and
-    // h is bit 0 only, so the piece is 2 st ^ (h ^ swz(tl)) and its byte offset 32 st ^ k_xor[mb].
-    unsigned k_row[2], k_xor[2];
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-        const int tl = 32 * mb + col;
-        k_row[mb] = (unsigned)(tl * 256);
-        k_xor[mb] = (unsigned)((h ^ swz(tl)) << 4);
-    }
+    // K fragment st: row col, piece (2 st + h) ^ swz(col).  2 st has no bit 0 and h is bit 0 only, so the
+    // piece is 2 st ^ (h ^ swz(col)) and its byte offset 32 st ^ k_xor.
+    const unsigned k_row = (unsigned)(col * 256), k_xor = (unsigned)((h ^ swz(col)) << 4);
     // V fragment (ks, db), half `part`: source lane (r, q4) of a 16-lane group points at token
     // 16 ks + 8 part + 4 h + r, channels 32 db + 16 g16 + 4 q4 .. + 3; the transposing read then
     // hands lane i of the group the four tokens of channel 32 db + 16 g16 + i.  The token step
@@ -324,13 +299,15 @@ __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLev
 #pragma unroll
         for (int i = 0; i < 16; ++i)
             o[db][i] = 0.f;
-    floatx16 sacc[2];
-    bf16x8 pf[4];  // P of the previous tile, B-operand layout
 
-    // One MFMA region: the scores of the tile in stage `ks` (16 MFMAs) and, alternating with
-    // them, O^T += V^T P^T for the previous tile in stage `vs` (16 more).  The two products are
-    // independent, so their accumulator chains hide each other's latency.  Fragments are read
-    // kAhead ahead of their MFMA.
+    // One MFMA region: the scores of the tile in K slot `kstage` into `sn` (8 MFMAs), alternating
+    // with O^T += V^T P^T for the tile in V slot `vstage` and probabilities `pp` (8 more), and between the
+    // MFMAs the probabilities `pn` of the scores `so` of the tile before (their sum over the lane is
+    // returned).  The three work on different tiles and do not depend on each other, so the
+    // accumulator chains hide each other's latency and the vector instructions issue in the MFMAs'
+    // shadow: a wavefront alone on its SIMD otherwise leaves the matrix cores idle during the
+    // softmax and the vector ALU idle during the products.  Fragments are read kAhead ahead of
+    // their MFMA.
     // Ring of fragment registers: kAhead + 1 reads in flight, and one more slot so that a new
     // read never targets the registers of the MFMA issued just before it.
     // A K fragment is one 128-bit read into `ring`; a V fragment is two 64-bit reads into
@@ -341,24 +318,25 @@ __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLev
     // body use no scratch memory, and a host-side test of the build keeps it that way.
     u32x4 ring[kAhead + 2];
     u32x2 ring_lo[kAhead + 2], ring_hi[kAhead + 2];
-    auto region = [&](auto qk_tag, auto pv_tag, int kstage, int vstage) __attribute__((always_inline)) {
-        constexpr bool QK = decltype(qk_tag)::value, PV = decltype(pv_tag)::value;
+    auto region = [&](auto qk_tag, auto sm_tag, auto pv_tag, int kstage, int vstage, floatx16& sn, const floatx16& so,
+                      bf16x8 (&pn)[2], const bf16x8 (&pp)[2]) __attribute__((always_inline)) -> float {
+        constexpr bool QK = decltype(qk_tag)::value, SM = decltype(sm_tag)::value, PV = decltype(pv_tag)::value;
         constexpr int NF = frag_count<QK, PV>();
-        const unsigned kbase = lds_base + (unsigned)kstage * kTileBytes;
-        const unsigned vbase = lds_base + (unsigned)(KS + vstage) * kTileBytes;
+        // (opaque to the optimiser, which would otherwise keep a running address per fragment)
+        unsigned kbase = lds_base + (unsigned)kstage * kTileBytes;
+        unsigned vbase = lds_base + (unsigned)(kRing + vstage) * kTileBytes;
+        asm("" : "+s"(kbase), "+s"(vbase));
         if (QK) {
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    sacc[mb][i] = 0.f;
+            for (int i = 0; i < 16; ++i)
+                sn[i] = 0.f;
         }
         auto issue = [&](auto kc) __attribute__((always_inline)) {
             constexpr int K = decltype(kc)::value;
             if constexpr (K < NF) {
                 using F = Frag<QK, PV, K>;
                 if constexpr (!F::is_pv) {
-                    const unsigned addr = kbase + k_row[F::b] + ((32u * F::a) ^ k_xor[F::b]);
+                    const unsigned addr = kbase + k_row + ((32u * F::a) ^ k_xor);
                     u32x4& dst = ring[K % (kAhead + 2)];
                     asm volatile("ds_read_b128 %0, %1" : "=v"(dst) : "v"(addr));
                 } else {
@@ -377,129 +355,221 @@ __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLev
             if constexpr (!F::is_pv) {
                 u32x4& f = ring[K % (kAhead + 2)];
                 asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(f) : "n"(ops_after<QK, PV, K>()));
-                sacc[F::b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f), qf[F::a], sacc[F::b], 0, 0, 0);
+                sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f), qf[F::a], sn, 0, 0, 0);
             } else {
                 u32x2& lo = ring_lo[K % (kAhead + 2)];
                 u32x2& hi = ring_hi[K % (kAhead + 2)];
                 asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(lo), "+v"(hi) : "n"(ops_after<QK, PV, K>()));
                 const u32x4 f = {lo[0], lo[1], hi[0], hi[1]};
-                o[F::b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f), pf[F::a], o[F::b], 0, 0, 0);
+                o[F::b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f), pp[F::a], o[F::b], 0, 0, 0);
+            }
+        };
+        // Slot e of the softmax: the exponent of score e, the exponential of score e - 1, the sum of score
+        // e - 2 (three short chains side by side, none waiting for the one before it).
+        float psum = 0.f, x[16], pv[16];
+        uint32_t w[8];
+        auto soft = [&](auto ec) __attribute__((always_inline)) {
+            constexpr int e = decltype(ec)::value;
+            if constexpr (SM && e >= 0 && e < 18) {
+                if constexpr (e < 16)
+                    x[e] = __builtin_fmaf(so[e], p.scale_log2, -m_run);
+                if constexpr (e >= 1 && e < 17)
+                    pv[e - 1] = __builtin_amdgcn_exp2f(x[e - 1]);
+                if constexpr (e >= 2) {
+                    psum += pv[e - 2];
+                    if constexpr ((e & 1) != 0)
+                        w[(e - 2) >> 1] = pack_bf16_rne(pv[e - 3], pv[e - 2]);
+                }
+            }
+        };
+        for_each_index(issue, std::make_integer_sequence<int, kAhead + 1>{});
+        // the first slots pass while the first fragments are under way
+        constexpr int kLead = 18 - NF > 0 ? 18 - NF : 0;
+        if constexpr (SM) {
+            for_each_index(soft, std::make_integer_sequence<int, kLead>{});
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        for_each_index(
+            [&](auto kc) __attribute__((always_inline)) {
+                consume(kc);
+                issue(std::integral_constant<int, decltype(kc)::value + kAhead + 1>{});
+                if constexpr (SM) {
+                    soft(std::integral_constant<int, decltype(kc)::value + kLead>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            },
+            std::make_integer_sequence<int, NF>{});
+        if constexpr (SM) {
+            static_assert(kLead + NF >= 18, "every score gets its slot");
+            const uint4 p0 = make_uint4(w[0], w[1], w[2], w[3]), p1 = make_uint4(w[4], w[5], w[6], w[7]);
+            pn[0] = as_bf16x8(p0);
+            pn[1] = as_bf16x8(p1);
+        }
+        return psum;
+    };
+
+    // The scores of tiles 0 and 1 together (two independent accumulator chains).
+    auto first_scores = [&](floatx16& s0, floatx16& s1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            s0[i] = s1[i] = 0.f;
+        auto issue = [&](auto kc) __attribute__((always_inline)) {
+            constexpr int K = decltype(kc)::value;
+            if constexpr (K < 16) {
+                const unsigned addr = lds_base + (K & 1) * kTileBytes + k_row + ((32u * (K >> 1)) ^ k_xor);
+                u32x4& dst = ring[K % (kAhead + 2)];
+                asm volatile("ds_read_b128 %0, %1" : "=v"(dst) : "v"(addr));
             }
         };
         for_each_index(issue, std::make_integer_sequence<int, kAhead + 1>{});
         for_each_index(
             [&](auto kc) __attribute__((always_inline)) {
-                consume(kc);
-                issue(std::integral_constant<int, decltype(kc)::value + kAhead + 1>{});
+                constexpr int K = decltype(kc)::value, kAfter = K + kAhead < 16 ? kAhead : 15 - K;
+                u32x4& f = ring[K % (kAhead + 2)];
+                asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(f) : "n"(kAfter));
+                floatx16& sc = (K & 1) ? s1 : s0;
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f), qf[K >> 1], sc, 0, 0, 0);
+                issue(std::integral_constant<int, K + kAhead + 1>{});
             },
-            std::make_integer_sequence<int, NF>{});
+            std::make_integer_sequence<int, 16>{});
     };
 
-    // Online softmax of the scores in `sacc` (lane-local per row): updates (m, l), rescales O
-    // (which already holds every earlier tile) and leaves P in `pf`.  Scores stay unscaled in
-    // the accumulator; the scale is folded into the exponent: p = 2^(s * scale - m).
-    auto softmax_tile = [&](int tb) __attribute__((always_inline)) {
-        const bool full = tb + kTileN <= t1;  // only the last tile of a split can be ragged
-        if (!full) {
+    // Online softmax: (m, l) of the row and the probabilities of a tile.  Scores stay unscaled in the
+    // accumulator; the scale is folded into the exponent: p = 2^(s * scale - m).
+    auto mask_tile = [&](int tb, floatx16& sc) __attribute__((always_inline)) {
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    // accumulator register i of lane-half h is token 32 mb + 8 (i/4) + 4 h + i%4
-                    const int t = tb + 32 * mb + 8 * (i >> 2) + 4 * h + (i & 3);
-                    if (t >= t1)
-                        sacc[mb][i] = -INFINITY;
-                }
+        for (int i = 0; i < 16; ++i) {
+            // accumulator register i of lane-half h is token 8 (i/4) + 4 h + i%4
+            const int t = tb + 8 * (i >> 2) + 4 * h + (i & 3);
+            if (t >= t1)
+                sc[i] = -INFINITY;
         }
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                tmax = fmaxf(tmax, sacc[mb][i]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32)) * p.scale_log2;
-        // The reference maximum m only has to bound the exponents, so it is raised only when some
-        // row of this wavefront exceeds it by more than kSlack (p <= 2^kSlack otherwise, exact in
-        // fp32 and bf16 alike); the accumulators then need no rescale on most tiles.
-        constexpr float kSlack = 8.f;
-        const bool raise = __ballot(tmax > m_run + kSlack) != 0;
-        float corr = 1.f;
-        if (raise) {
-            const float m_up = fmaxf(m_run, tmax);
-            corr = __builtin_amdgcn_exp2f(m_run - m_up);
-            m_run = m_up;
-        }
-        const float m_new = m_run;
+    };
+    auto probabilities = [&](const floatx16& sc, bf16x8 (&pn)[2]) __attribute__((always_inline)) -> float {
         float psum = 0.f;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int u = 0; u < 2; ++u) {
+            float pv[8];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                float pv[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    pv[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[mb][8 * u + e], p.scale_log2, -m_new));
-                    psum += pv[e];
-                }
-                uint4 pu;
-                pu.x = pack_bf16_rne(pv[0], pv[1]);
-                pu.y = pack_bf16_rne(pv[2], pv[3]);
-                pu.z = pack_bf16_rne(pv[4], pv[5]);
-                pu.w = pack_bf16_rne(pv[6], pv[7]);
-                pf[2 * mb + u] = as_bf16x8(pu);
+            for (int e = 0; e < 8; ++e) {
+                pv[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[8 * u + e], p.scale_log2, -m_run));
+                psum += pv[e];
             }
-        l_run = l_run * corr + psum;
-        if (raise) {
+            uint4 pu;
+            pu.x = pack_bf16_rne(pv[0], pv[1]);
+            pu.y = pack_bf16_rne(pv[2], pv[3]);
+            pu.z = pack_bf16_rne(pv[4], pv[5]);
+            pu.w = pack_bf16_rne(pv[6], pv[7]);
+            pn[u] = as_bf16x8(pu);
+        }
+        return psum;
+    };
+    // The reference maximum m only has to bound the exponents.  After the first tile it is looked at
+    // again only when a lane's 16 probabilities add up to more than kRaise (none of them is above
+    // that otherwise: exact in fp32 and bf16 alike), so that most tiles find no maximum, exchange
+    // nothing between lanes and rescale nothing.
+    constexpr float kRaise = 1024.f;
+    auto raise_maximum = [&](const floatx16& sc) __attribute__((always_inline)) -> float {
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            tmax = fmaxf(tmax, sc[i]);
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32)) * p.scale_log2;
+        const float m_up = fmaxf(m_run, tmax);
+        const float corr = __builtin_amdgcn_exp2f(m_run - m_up);
+        m_run = m_up;
+        return corr;
+    };
+    // Takes in a tile's sum of probabilities; raises the maximum, and does the tile's probabilities again,
+    // if it has to.  O holds every earlier tile by then.
+    auto take_sum = [&](float psum, const floatx16& sc, bf16x8 (&pn)[2]) __attribute__((always_inline)) {
+        if (__ballot(!(psum <= kRaise)) != 0) {
+            const float corr = raise_maximum(sc);
+            psum = probabilities(sc, pn);
+            l_run *= corr;
 #pragma unroll
             for (int db = 0; db < 4; ++db)
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     o[db][i] *= corr;
         }
+        l_run += psum;
     };
 
     // ---- pipeline over tiles ----------------------------------------------------------------------
-    // Iteration `it` starts the copies of tile it+AHEAD, runs one MFMA region (scores of tile `it`
-    // together with P V of tile it-1), waits until its own copies of tile it+1 have landed, meets
-    // the other wavefronts at a barrier, then runs the softmax of tile `it`.
+    // Step t computes the scores of tile t, the probabilities of tile t-1 and P V of tile t-2 in one MFMA
+    // region.  It starts the copies of K of tile t + A and V of tile t + A - 2 (A = kCopyAhead; both are
+    // A steps ahead of their use, 64 KB per workgroup under way), then runs the region, waits until its
+    // own copies of K of tile t+1 and V of tile t-1 have landed, and meets the other wavefronts at a
+    // barrier.  A copy into a ring slot is issued only after a barrier that every wavefront reaches
+    // after its last read of that slot, and a tile is read only after a barrier that every
+    // wavefront reaches after its copies of that tile landed.
     const int ntiles = (t1 - t0 + kTileN - 1) / kTileN;
     const std::true_type yes{};
     const std::false_type no{};
-    issue_tile(0);
-    if (AHEAD == 2 && ntiles > 1)
-        issue_tile(1);
-    if (AHEAD == 2 && ntiles > 1)
-        wait_vmcnt<kIPW>();
-    else
-        wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    // One barrier per tile, after the MFMA region (own copies of the next tile have landed by
-    // then).  A copy into a ring slot is issued only after a barrier that every wavefront reaches
-    // after its last read of that slot, and a tile is read only after a barrier that every
-    // wavefront reaches after its copies of that tile landed.
-    auto end_of_region = [&](int it) __attribute__((always_inline)) {
-        if (it + 1 < ntiles) {
-            if (AHEAD == 2 && it + 2 < ntiles)
-                wait_vmcnt<kIPW>();
-            else
-                wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();
-        }
+    auto start_copies = [&](int t) __attribute__((always_inline)) {
+        const int tile = copies_v ? t + kCopyAhead - 2 : t + kCopyAhead;
+        if (tile >= 0 && tile < ntiles)
+            issue_tile(tile);
     };
-    // first tile: scores only (kept out of the loop so that the loop body is one straight path)
-    if (ntiles > AHEAD)
-        issue_tile(AHEAD);
-    region(yes, no, 0, 0);
-    end_of_region(0);
-    softmax_tile(t0);
-    for (int it = 1; it < ntiles; ++it) {
-        if (it + AHEAD < ntiles)
-            issue_tile(it + AHEAD);
-        region(yes, yes, it % KS, (it - 1) % VS);
-        end_of_region(it);
-        softmax_tile(t0 + it * kTileN);
+    // Waits until at most `tiles` later tiles of this wavefront's copies are under way; everybody has then.
+    auto wait_copies = [&](int tiles) __attribute__((always_inline)) {
+        if (tiles >= kCopyAhead - 1)
+            wait_vmcnt<(kCopyAhead - 1) * kIPW>();
+        else if (tiles == 2)
+            wait_vmcnt<2 * kIPW>();
+        else if (tiles == 1)
+            wait_vmcnt<kIPW>();
+        else
+            wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+    };
+    static_assert(kCopyAhead == 4, "wait_copies lists the counts below kCopyAhead - 1");
+    // At the end of step t the copies of up to A - 1 later tiles may be under way (fewer near the end; the
+    // count is that of the K copies, V has more; after the last step everything has landed).
+    auto end_of_step = [&](int t) __attribute__((always_inline)) { wait_copies(ntiles - 2 - t); };
+    floatx16 sa, sb;      // scores of tiles with an even / odd number
+    bf16x8 pa[2], pb[2];  // their probabilities, B-operand layout
+#pragma unroll
+    for (int t = -kCopyAhead; t <= 0; ++t)  // K of tiles 0 .. A, V of tiles 0 .. A-2
+        start_copies(t);
+    end_of_step(0);
+    if (ntiles > 1) {
+        // steps 0 and 1 in one; the copies of step 1 wait until the slots of K of tiles 0 and 1 are free
+        first_scores(sa, sb);
+        raise_maximum(sa);  // (the first tile of several is whole)
+        l_run = probabilities(sa, pa);
+        wait_copies(min(ntiles - 3, kCopyAhead - 2));
+        start_copies(1);
+        // two steps a round, so that scores and probabilities change roles instead of registers
+        int t = 2;
+        for (; t + 1 < ntiles; t += 2) {
+            start_copies(t);
+            take_sum(region(yes, yes, yes, t % kRing, (t - 2) % kRing, sa, sb, pb, pa), sb, pb);
+            end_of_step(t);
+            start_copies(t + 1);
+            take_sum(region(yes, yes, yes, (t + 1) % kRing, (t - 1) % kRing, sb, sa, pa, pb), sa, pa);
+            end_of_step(t + 1);
+        }
+        if (t < ntiles) {
+            start_copies(t);
+            take_sum(region(yes, yes, yes, t % kRing, (t - 2) % kRing, sa, sb, pb, pa), sb, pb);
+            end_of_step(t);
+            sb = sa;  // the last tile's scores
+            pa[0] = pb[0];  // and the probabilities of the one before
+            pa[1] = pb[1];
+        }
+        // the last tile; only it can be ragged
+        if (t0 + ntiles * kTileN > t1)
+            mask_tile(t0 + (ntiles - 1) * kTileN, sb);
+        take_sum(region(no, yes, yes, 0, (ntiles - 2) % kRing, sa, sb, pb, pa), sb, pb);
+    } else {
+        region(yes, no, no, 0, 0, sa, sa, pa, pa);
+        mask_tile(t0, sa);
+        raise_maximum(sa);
+        l_run = probabilities(sa, pb);
     }
-    region(no, yes, 0, (ntiles - 1) % VS);
+    region(no, no, yes, 0, (ntiles - 1) % kRing, sa, sa, pa, pb);
 
     // ---- write the partial state ------------------------------------------------------------------
     const float l = l_run + __shfl_xor(l_run, 32);

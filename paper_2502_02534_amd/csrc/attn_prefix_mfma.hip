@@ -6,16 +6,13 @@ namespace {
 
 using namespace prefix_impl;
 
-// 128-row workgroups (4 wavefronts) take the short rings (80 KB) so that two of them share a CU;
-// 256-row workgroups (8 wavefronts) keep the long rings, copies two tiles ahead.
 template <int WAVES, bool PAGED>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : 1, 2))) void
 attn_prefix_mfma_kernel(AttnParams p, int rowtiles)
 {
-    constexpr int KS = WAVES == 4 ? 2 : 4, VS = WAVES == 4 ? 3 : 4, AHEAD = WAVES == 4 ? 1 : 2;
-    __shared__ uint4 lds[prefix_lds_bytes(KS, VS) / 16];
+    __shared__ uint4 lds[kPrefixLds / 16];
     const PrefixItem it = prefix_item((int)blockIdx.x, p.num_prefix_splits, rowtiles, p.B * p.Hkv);
-    prefix_body<WAVES, PAGED, KS, VS, AHEAD>(p, level_of(p, rowtiles), lds, it.split, it.rowtile, it.z);
+    prefix_body<WAVES, PAGED>(p, level_of(p, rowtiles), lds, it.split, it.rowtile, it.z);
 }
 
 template <int WAVES>
@@ -57,7 +54,7 @@ hipError_t launch_attn_prefix_mfma(const AttnParams& p, hipStream_t s)
     if (p.num_prefix_splits <= 0)
         return hipSuccess;
     // On its own (no suffix workgroups to share a CU with) a matrix-bound pass does better with
-    // 256-row workgroups and the long rings, provided that still gives most CUs a workgroup;
+    // 256-row workgroups, provided that still gives most CUs a workgroup;
     // the split plan does not depend on the row tile.
     const long long wide_blocks = (long long)p.num_prefix_splits * ((p.max_spp * p.G + 255) / 256) * p.B * p.Hkv;
     if (p.max_spp * p.G > 128 && wide_blocks >= 192)
