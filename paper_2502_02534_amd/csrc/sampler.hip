@@ -44,6 +44,74 @@ __device__ __forceinline__ double wave_sum_f64(double v)
     return v;
 }
 
+// ---- scans and reductions across a wavefront without LDS traffic (data-parallel primitives: shifts inside
+// rows of 16 lanes, then the last lane of a row broadcast into the rows after it).  All 64 lanes
+// must be active.  A lane that receives nothing keeps `none`.
+template <int CTRL, int ROWS> __device__ __forceinline__ unsigned dpp_u32(unsigned none, unsigned v)
+{
+    return (unsigned)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_f64(double v)  // 0.0 where nothing arrives
+{
+    const unsigned lo = dpp_u32<CTRL, ROWS>(0u, (unsigned)__double2loint(v)), hi = dpp_u32<CTRL, ROWS>(0u, (unsigned)__double2hiint(v));
+    return __hiloint2double((int)hi, (int)lo);
+}
+constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118, kBcast15 = 0x142, kBcast31 = 0x143;
+
+// A value that is the same in every lane, moved to a scalar register.
+__device__ __forceinline__ float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
+// Inclusive scan over the lanes.
+__device__ __forceinline__ double wave_scan_f64(double v)
+{
+    v += dpp_f64<kShr1, 0xf>(v);
+    v += dpp_f64<kShr2, 0xf>(v);
+    v += dpp_f64<kShr4, 0xf>(v);
+    v += dpp_f64<kShr8, 0xf>(v);
+    v += dpp_f64<kBcast15, 0xa>(v);
+    v += dpp_f64<kBcast31, 0xc>(v);
+    return v;
+}
+__device__ __forceinline__ unsigned wave_scan_u32(unsigned v)
+{
+    v += dpp_u32<kShr1, 0xf>(0u, v);
+    v += dpp_u32<kShr2, 0xf>(0u, v);
+    v += dpp_u32<kShr4, 0xf>(0u, v);
+    v += dpp_u32<kShr8, 0xf>(0u, v);
+    v += dpp_u32<kBcast15, 0xa>(0u, v);
+    v += dpp_u32<kBcast31, 0xc>(0u, v);
+    return v;
+}
+__device__ __forceinline__ double lane63_f64(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+// Reductions: the same value in every lane.
+template <typename F> __device__ __forceinline__ unsigned wave_reduce_u32(unsigned v, unsigned none, F f)
+{
+    v = f(v, dpp_u32<kShr1, 0xf>(none, v));
+    v = f(v, dpp_u32<kShr2, 0xf>(none, v));
+    v = f(v, dpp_u32<kShr4, 0xf>(none, v));
+    v = f(v, dpp_u32<kShr8, 0xf>(none, v));
+    v = f(v, dpp_u32<kBcast15, 0xa>(none, v));
+    v = f(v, dpp_u32<kBcast31, 0xc>(none, v));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ float wave_max_f32(float v)
+{
+    return __uint_as_float(wave_reduce_u32(__float_as_uint(v), 0xff800000u /* -inf */, [](unsigned a, unsigned b) {
+        return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+    }));
+}
+__device__ __forceinline__ unsigned wave_min_u32(unsigned v)
+{
+    return wave_reduce_u32(v, 0xffffffffu, [](unsigned a, unsigned b) { return min(a, b); });
+}
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v)
+{
+    return wave_reduce_u32(v, 0u, [](unsigned a, unsigned b) { return max(a, b); });
+}
+
 // Block-wide sum in fp64 with a fixed reduction tree (deterministic).
 __device__ double block_sum_f64(double v, double* scratch /* kWaves */)
 {
@@ -501,6 +569,15 @@ __device__ __forceinline__ int bin_below(float kf_max, float kf)
     return (int)fminf(fmaxf(kf_max - kf, 0.f), (float)(kBins - 1));
 }
 
+// A slice's histogram is kept in the workspace as a ring over the bin coordinate itself (bin b of a slice
+// whose maximum has coordinate kf goes to place (kf - b) mod kPubBins), so that the row-level kernel can
+// request the same place of every slice before it knows any of the maxima.
+__device__ __forceinline__ int ring_base(float kf)
+{
+    // (floats beyond 2^62 are multiples of kPubBins; a slice of -inf holds no units)
+    return fabsf(kf) < 4.0e18f ? (int)((long long)kf & (kPubBins - 1)) : 0;
+}
+
 struct RowConst {
     float c_hi, c_lo, c16;
     double cd;
@@ -632,13 +709,6 @@ __device__ __forceinline__ unsigned bin_units(float f)
     return (unsigned)__builtin_fmaf(__builtin_fmaf(b2, f, b1), f, b0);
 }
 
-__device__ __forceinline__ int wave_max_i32(int v)
-{
-    for (int o = 32; o > 0; o >>= 1)
-        v = max(v, __shfl_xor(v, o));
-    return v;
-}
-
 // Folds eight per-lane partial sums (one per 256-element segment j of the wavefront's pass) across the
 // wavefront: after the exchange across 32 lanes each half keeps four segments, then two, then one,
 // so that lane 8 s ends up with the sum of segment s (10 exchanges instead of 48).
@@ -708,8 +778,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
     for (int q = 0; q < 32; ++q)
         mx = fmaxf(mx, xv[q]);
-    for (int o = 32; o > 0; o >>= 1)
-        mx = fmaxf(mx, __shfl_xor(mx, o));
+    mx = wave_max_f32(mx);
     if (lane == 0)
         L.red_f[wave] = mx;
     lds_barrier();
@@ -795,24 +864,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // what the lanes collected past the last bin belongs to the last bin (every wavefront adds the
     // places up for itself; only the owner of the last bin uses the sum)
     static_assert(kPubBins == 2 * kBlock, "thread t owns bins 2t and 2t+1; the last thread owns the last bin");
-    unsigned far_units = L.hist[kPubBins + lane];
-    for (int o = 32; o > 0; o >>= 1)
-        far_units += __shfl_xor(far_units, o);
+    const unsigned far_units = wave_reduce_u32(L.hist[kPubBins + lane], 0u, [](unsigned a, unsigned b) { return a + b; });
 
     // ---- running sums over the bins (thread t owns bins 2t, 2t+1): fixed-point units for the element
     // counts, estimated mass for the slice's own cut bin ----
     const unsigned q0 = L.hist[2 * tid], q1 = L.hist[2 * tid + 1] + (tid == kBlock - 1 ? far_units : 0u);
     const double m0 = (double)q0 * bin_unit(2 * tid), m1 = (double)q1 * bin_unit(2 * tid + 1);
-    unsigned qi = q0 + q1;
-    double mi = m0 + m1;
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned uq = __shfl_up(qi, o);
-        const double um = __shfl_up(mi, o);
-        if (lane >= o) {
-            qi += uq;
-            mi += um;
-        }
-    }
+    unsigned qi = wave_scan_u32(q0 + q1);
+    double mi = wave_scan_f64(m0 + m1);
     if (lane == 63) {
         L.wave_q[wave] = qi;
         L.wave_mass[wave] = mi;
@@ -867,7 +926,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 mine = w;
         }
     }
-    mine = wave_max_i32(mine);
+    mine = (int)wave_max_u32((unsigned)(mine + 1)) - 1;
     if (lane == 0 && mine >= 0)
         atomicMax(&L.best, mine);
     lds_barrier();
@@ -946,7 +1005,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int i = lane; i < min(have, kWaveStage); i += 64)
             if (base + i < kEmitCap)
                 out[base + i] = L.stage[wave][i];
-    *reinterpret_cast<uint2*>(&W.hist[(size_t)slice * kPubBins + 2 * tid]) = make_uint2(q0, q1);
+    {
+        unsigned* ring = W.hist + (size_t)slice * kPubBins;
+        const int place = ring_base(kf_loc) - 2 * tid;
+        ring[place & (kPubBins - 1)] = q0;
+        ring[(place - 1) & (kPubBins - 1)] = q1;
+    }
     // ---- segment sums: what lies above the window (nothing when the window starts at the top) ----
     float a1 = 0.f;
     if (win_hi >= 0 && win_lo > 0) {
@@ -964,12 +1028,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         seg_out[(lane >> 3) * kWaves + wave] = (double)a1;
 }
 
-// ---- bin selection by one wavefront ----------------------------------------------------------------
-// A histogram of kBins doubles in "rank order" (bin 0 = most probable) is kept transposed in
-// LDS, bin b in slot (b & 31) * 64 + (b >> 5), so that lane l owns the 32 consecutive bins
-// 32 l .. 32 l + 31 and the 64 lanes read consecutive slots.
-__device__ __forceinline__ int rank_slot(int b) { return (b & 31) * 64 + (b >> 5); }
-
+// ---- bin selection by the workgroup ------------------------------------------------------------------
 struct BinPick {
     int bin;        // first non-empty bin whose cumulative mass reaches `need`
     double above;   // mass strictly above it (including `above0`)
@@ -977,62 +1036,96 @@ struct BinPick {
     double total;   // sum of the histogram
 };
 
-// Every lane of the calling wavefront returns the same result; no workgroup barrier is used, so
-// all wavefronts of a workgroup may call it redundantly on a finished histogram.  With
-// `relative`, `need` is a fraction of the histogram's total.  If rounding leaves even the total
-// short of `need`, the last non-empty bin is taken (everything is kept).
-__device__ __forceinline__ BinPick wave_pick(const double* H, double above0, double need, bool relative)
+// What the wavefronts tell each other.
+struct PickLds {
+    double sum[kWaves];
+    double above[2][kWaves], in_bin[2][kWaves];  // [0] the first bin that reaches `need`, [1] the last non-empty bin
+    int bin[2][kWaves];                          // (-1: none)
+};
+
+// H: kBins masses, bin 0 = most probable, in LDS and complete (a barrier behind the last addition); thread
+// t owns bins 4 t .. 4 t + 3.  Every thread returns the same result.  With `relative`, `need` is a
+// fraction of the histogram's total.  If rounding leaves even the total short of `need`, the last
+// non-empty bin is taken (everything is kept).  Two barriers; H may be overwritten and `P` used again once
+// every thread has passed another one.
+__device__ __forceinline__ BinPick block_pick(const double* H, double above0, double need, bool relative, PickLds& P)
 {
-    const int lane = threadIdx.x & 63;
-    double own = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k)
-        own += H[k * 64 + lane];
-    double incl = own;
-    for (int o = 1; o < 64; o <<= 1) {
-        const double up = __shfl_up(incl, o);
-        if (lane >= o)
-            incl += up;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(kBinsPerThread == 4, "two 16-byte reads per thread");
+    double h[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        h[k] = H[4 * tid + k];
+    const double own = (h[0] + h[1]) + (h[2] + h[3]);
+    const double incl = wave_scan_f64(own);
+    if (lane == 63)
+        P.sum[wave] = incl;
+    lds_barrier();
+    double before = above0 + (incl - own), total = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        total += P.sum[w];
+        before += w < wave ? P.sum[w] : 0.0;
+    }
+    if (relative)
+        need *= total;
+    // this thread's first bin that reaches `need`, and its last non-empty one
+    int bin[2] = {-1, -1};
+    double above[2] = {0.0, 0.0}, in_bin[2] = {0.0, 0.0}, cum = before;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double next = cum + h[k];
+        if (h[k] > 0.0) {
+            if (bin[0] < 0 && next >= need) {
+                bin[0] = 4 * tid + k;
+                above[0] = cum;
+                in_bin[0] = h[k];
+            }
+            bin[1] = 4 * tid + k;
+            above[1] = cum;
+            in_bin[1] = h[k];
+        }
+        cum = next;
+    }
+    const unsigned long long hit = __ballot(bin[0] >= 0), some = __ballot(bin[1] >= 0);
+    const int first = hit ? __ffsll((long long)hit) - 1 : -1, last = some ? 63 - __clzll((long long)some) : -1;
+    if (lane == (first < 0 ? 0 : first)) {
+        P.bin[0][wave] = bin[0];
+        P.above[0][wave] = above[0];
+        P.in_bin[0][wave] = in_bin[0];
+    }
+    if (lane == (last < 0 ? 0 : last)) {
+        P.bin[1][wave] = bin[1];
+        P.above[1][wave] = above[1];
+        P.in_bin[1][wave] = in_bin[1];
+    }
+    lds_barrier();
+    // the first wavefront with a hit, else the last one with anything
+    int from = -1, kind = 0;
+#pragma unroll
+    for (int w = kWaves - 1; w >= 0; --w)
+        from = P.bin[0][w] >= 0 ? w : from;
+    if (from < 0) {
+        kind = 1;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+            from = P.bin[1][w] >= 0 ? w : from;
     }
     BinPick r;
-    r.total = __shfl(incl, 63);
-    if (relative)
-        need *= r.total;
-    const double before_lane = above0 + (incl - own);
-    const unsigned long long nonempty = __ballot(own > 0.0);
-    const unsigned long long hit = __ballot(own > 0.0 && before_lane + own >= need);
-    r.bin = 0;
-    r.above = above0;
-    r.in_bin = 0.0;
-    if (!nonempty)
-        return r;
-    const int hl = hit ? __ffsll((long long)hit) - 1 : 63 - __clzll((long long)nonempty);
-    // the 32 bins of lane hl, one per lane (both halves of the wavefront hold the same), scanned
-    const double h = H[(lane & 31) * 64 + hl];
-    double cum = h;
-    for (int o = 1; o < 32; o <<= 1) {
-        const double up = __shfl_up(cum, o);
-        if ((lane & 31) >= o)
-            cum += up;
-    }
-    cum += __shfl(before_lane, hl);
-    const unsigned ne32 = (unsigned)__ballot(h > 0.0);
-    const unsigned hit32 = hit ? (unsigned)__ballot(h > 0.0 && cum >= need) : 0u;
-    // first bin that reaches `need`; else (rounding, or nothing reaches it) the last non-empty one
-    const int k = hit32 ? __ffs((int)hit32) - 1 : 31 - __clz((int)ne32);
-    r.bin = 32 * hl + k;
-    r.in_bin = __shfl(h, k);
-    r.above = __shfl(cum, k) - r.in_bin;
+    r.total = total;
+    r.bin = from < 0 ? 0 : P.bin[kind][from];
+    r.above = from < 0 ? above0 : P.above[kind][from];
+    r.in_bin = from < 0 ? 0.0 : P.in_bin[kind][from];
     return r;
 }
 
 // Two block-wide fp64 sums at once (fixed reduction tree).
 __device__ void block_sum2_f64(double& a, double& b, double* scratch /* 2 kWaves */)
 {
-    a = wave_sum_f64(a);
-    b = wave_sum_f64(b);
+    a = wave_scan_f64(a);
+    b = wave_scan_f64(b);
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 63) {
         scratch[threadIdx.x >> 6] = a;
         scratch[kWaves + (threadIdx.x >> 6)] = b;
     }
@@ -1049,13 +1142,9 @@ __device__ void block_sum2_f64(double& a, double& b, double* scratch /* 2 kWaves
 struct FinishLds {
     RowLds row;                           // hist / scratch / seg_mass of the row routines
     unsigned long long cand[kCandCap];    // candidates: logit bits | index << 32
-    double srest[kMaxSlices];             // estimated mass past the slice's window, relative to the row maximum
-    double sfac[kMaxSlices];              // 2^((slice max - row max) c)
-    float smax[kMaxSlices];
-    int sarg[kMaxSlices];
-    int shift[kMaxSlices];
-    int swin_lo[kMaxSlices], swin_hi[kMaxSlices], scount[kMaxSlices];
-    int covered[kMaxSlices];
+    PickLds pick;
+    double seg_sum[kWaves], seg_before[kWaves];  // the wavefronts' shares of the segment scan
+    int seg_hit[kWaves], seg_last[kWaves];
     unsigned cand_total;
     uint32_t kmin[kWaves], kmax[kWaves];
 };
@@ -1081,128 +1170,124 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     const int nseg = slices * kSegPerSlice;
     double* seg_mass = L.row.seg_mass;
 
-    if (tid < slices) {
-        const SliceStat* st = stat_at(W, tid);
-        L.smax[tid] = st->max_x;
-        L.sarg[tid] = st->argmax;
-        if (!greedy) {
-            L.srest[tid] = st->rest;
-            L.swin_lo[tid] = st->win_lo;
-            L.swin_hi[tid] = st->win_hi;
-            L.scount[tid] = st->count;
-        }
-    }
+    // Lane s of every wavefront holds slice s's statistics (lanes past the last slice repeat it); what all
+    // lanes need of a slice is read out of its lane.
+    const SliceStat st = *stat_at(W, min(lane, slices - 1));
+    const double seg0 = W.seg[min(tid, nseg - 1)];
     if (tid == 0)
         L.cand_total = 0u;
-    __syncthreads();
-    float M = -INFINITY;
-    int arg = 0x7fffffff;
-    for (int s = 0; s < slices; ++s) {
-        if (L.smax[s] > M || (L.smax[s] == M && L.sarg[s] < arg)) {
-            M = L.smax[s];
-            arg = L.sarg[s];
-        }
-    }
+    // Units of the slices' histograms: places 2 tid and 2 tid + 1 of every ring, requested before any
+    // maximum is known, eight slices at a time.
+    auto request_units = [&](int s0, uint2 (&hv)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            hv[u] = *reinterpret_cast<const uint2*>(W.hist + (size_t)min(s0 + u, slices - 1) * kPubBins + 2 * tid);
+    };
+    const bool units = FILTERED ? top_k > 0 : cut;
+    uint2 hv[8];
+    if (units)
+        request_units(0, hv);
+    const float M = wave_max_f32(st.max_x);
     if (greedy) {
+        const unsigned arg = wave_min_u32(st.max_x == M ? (unsigned)st.argmax : 0xffffffffu);
         if (tid == 0)
-            sp.tokens[r] = arg == 0x7fffffff ? 0 : max(arg - lead, 0);
+            sp.tokens[r] = arg >= 0x7fffffffu ? 0 : max((int)arg - lead, 0);
         return true;
     }
-    const RowConst rc = row_const(T);
+    RowConst rc = row_const(T);
+    rc.c_hi = uniform(rc.c_hi);  // (in scalar registers: every vector register counts here)
+    rc.c_lo = uniform(rc.c_lo);
+    rc.c16 = uniform(rc.c16);
     RowScale rs;
     rs.max_x = M;
     rs.c_hi = rc.c_hi;
     rs.c_lo = rc.c_lo;
-    const float kf_row = bin_coord(M, rc.c16);
-    if (tid < slices) {
-        const bool empty = L.smax[tid] == -INFINITY;
-        L.shift[tid] = empty ? kBins : (int)fminf(fmaxf(kf_row - bin_coord(L.smax[tid], rc.c16), 0.f), (float)kBins);
-        L.sfac[tid] = empty ? 0.0 : exp2(((double)L.smax[tid] - (double)M) * rc.cd);
-        // the slice's histogram units refer to 2^(bin_coord(slice max) / 16); the row maximum is 2^(M c16 / 16)
-        L.srest[tid] = empty ? 0.0
-                             : L.srest[tid] * exp2(((double)bin_coord(L.smax[tid], rc.c16) - (double)M * (double)rc.c16) * 0.0625);
-    }
-    __syncthreads();
-
-    int lo = kBins, hi = kBins;  // candidate bins, counted down from the maximum's bin; kBins = no cut
-    // Units of the slices' histograms per row bin: bin b of slice s is bin b + shift[s] of the row;
-    // thread t gathers row bins 4 t .. 4 t + 3 (all loads of four slices are requested before any
-    // is used; loads are unconditional from clamped positions, what lies outside a slice's bins is
-    // masked afterwards).
-    const int rb0 = kBinsPerThread * tid;
-    auto gather_units = [&](unsigned long long (&qsum)[kBinsPerThread]) __attribute__((always_inline)) {
+    const float kf_row = bin_coord(M, rc.c16), kf_slice = bin_coord(st.max_x, rc.c16);
+    const bool empty = st.max_x == -INFINITY;
+    // bin b of the slice is bin b + shift of the row
+    const int shift = empty ? kBins : (int)fminf(fmaxf(kf_row - kf_slice, 0.f), (float)kBins);
+    const int base_slice = ring_base(kf_slice), base_row = ring_base(kf_row);
+    auto of_slice = [&](int v, int s) __attribute__((always_inline)) -> int { return __builtin_amdgcn_readlane(v, s); };
+    // Row histogram in LDS from the rings: place q of slice s is its bin (base_s - q) mod kPubBins, and
+    // the row's bin for that place is (base_row - q) mod kPubBins or that plus kPubBins.
+    auto row_histogram = [&](bool as_mass) __attribute__((always_inline)) {
+        unsigned long long near[2] = {0ull, 0ull}, far[2] = {0ull, 0ull};
+        int rb[2];
 #pragma unroll
-        for (int k = 0; k < kBinsPerThread; ++k)
-            qsum[k] = 0ull;
-        for (int s0 = 0; s0 < slices; s0 += 4) {
-            unsigned qv[4][kBinsPerThread];
-            int sh[4];
+        for (int k = 0; k < 2; ++k)
+            rb[k] = (base_row - 2 * tid - k) & (kPubBins - 1);
+        for (int s0 = 0; s0 < slices; s0 += 8) {
+            if (s0 > 0)
+                request_units(s0, hv);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int sl = min(s0 + u, slices - 1);
-                sh[u] = s0 + u < slices ? L.shift[sl] : kBins;
+            for (int u = 0; u < 8; ++u) {
+                if (s0 + u >= slices)
+                    break;
+                const int sh = of_slice(shift, s0 + u), bs = of_slice(base_slice, s0 + u);
 #pragma unroll
-                for (int k = 0; k < kBinsPerThread; ++k) {
-                    const int b = min(max(rb0 + k - sh[u], 0), kPubBins - 1);
-                    qv[u][k] = W.hist[(size_t)sl * kPubBins + b];
+                for (int k = 0; k < 2; ++k) {
+                    const int b = ((bs - 2 * tid - k) & (kPubBins - 1)) + sh;
+                    const unsigned v = k ? hv[u].y : hv[u].x;
+                    near[k] += b == rb[k] ? v : 0u;
+                    far[k] += b == rb[k] + kPubBins ? v : 0u;
                 }
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int k = 0; k < kBinsPerThread; ++k) {
-                    const int b = rb0 + k - sh[u];
-                    qsum[k] += (b >= 0 && b < kPubBins) ? qv[u][k] : 0u;
-                }
         }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            L.row.hist[rb[k]] = (double)near[k] * (as_mass ? bin_unit(rb[k]) : 1.0);
+            L.row.hist[rb[k] + kPubBins] = (double)far[k] * (as_mass ? bin_unit(rb[k] + kPubBins) : 1.0);
+        }
+        __syncthreads();
     };
+    static_assert(kPubBins == 2 * kBlock && kBins == 2 * kPubBins, "two places of every ring per thread");
+
+    int lo = kBins, hi = kBins;  // candidate bins, counted down from the maximum's bin; kBins = no cut
     if (cut && !FILTERED) {
         // Estimate of the nucleus cut from the slices' histograms.
-        unsigned long long qsum[kBinsPerThread];
-        gather_units(qsum);
-#pragma unroll
-        for (int k = 0; k < kBinsPerThread; ++k)
-            L.row.hist[rank_slot(rb0 + k)] = (double)qsum[k] * bin_unit(rb0 + k);
-        __syncthreads();
-        const BinPick est = wave_pick(L.row.hist, 0.0, (double)top_p, true);
+        row_histogram(true);
+        const BinPick est = block_pick(L.row.hist, 0.0, (double)top_p, true, L.pick);
         // the estimate is good to about 1e-5 of the total; be generous
         const double need_est = (double)top_p * est.total, tol = 1e-3 * est.total;
-        lo = hi = est.bin;
+        lo = hi = __builtin_amdgcn_readfirstlane(est.bin);
         if (need_est - est.above <= tol && lo > 0)
             --lo;
         if (est.above + est.in_bin - need_est <= tol && hi < kBins - 1)
             ++hi;
-        __syncthreads();  // the histogram array is reused below
     }
     // A slice is covered when its emitted bins contain the row's cut bins and everything it summed
-    // as above its window is above `lo` (bin b of the slice is bin b + shift of the row).
-    if (tid < slices) {
-        bool ok = !FILTERED;  // (a row with a filter is finished from its pairs further down)
-        if (cut && !FILTERED) {
-            const int a = L.swin_lo[tid], z = L.swin_hi[tid], sh = L.shift[tid];
-            ok = L.scount[tid] >= 0 && z >= 0 && (a == 0 || a + sh <= lo) && (z >= kPubBins - 1 || hi <= z + sh);
-        }
-        L.covered[tid] = ok ? 1 : 0;
-    }
-    __syncthreads();
+    // as above its window is above `lo`.  (A row with a filter is finished from its pairs further down.)
+    bool cov = !FILTERED;
+    if (cut && !FILTERED)
+        cov = st.count >= 0 && st.win_hi >= 0 && (st.win_lo == 0 || st.win_lo + shift <= lo) &&
+              (st.win_hi >= kPubBins - 1 || hi <= st.win_hi + shift);
+    const unsigned covered = (unsigned)__ballot(cov) & ((1u << slices) - 1u);  // bit s: slice s
     // Bin tests without forming the bin (see the scan kernel): lo == kBins keeps everything,
     // hi == kBins - 1 makes every remaining element a candidate.
-    const float t_above = lo >= kBins ? -INFINITY : kf_row - (float)lo + 1.f;
-    const float t_cand = hi >= kBins - 1 ? -INFINITY : kf_row - (float)hi;
+    const float t_above = uniform(lo >= kBins ? -INFINITY : kf_row - (float)lo + 1.f);
+    const float t_cand = uniform(hi >= kBins - 1 ? -INFINITY : kf_row - (float)hi);
 
     // ---- mass kept for certain, per 256-element segment in vocabulary order; candidates ----------------
     // The row mass S is put together on the way: exact for every element this kernel sees (the pairs
     // of the covered slices, every logit of the others) and for what the covered slices summed above
     // their windows, estimated from the histograms for the bins past the windows.
     double s_part = 0.0;
-    for (int sidx = tid; sidx < nseg; sidx += kBlock) {
-        const int s = sidx / kSegPerSlice;
-        const double v = L.covered[s] ? W.seg[sidx] * L.sfac[s] : 0.0;
+    auto take_segment = [&](int sidx, double v) __attribute__((always_inline)) {  // (a wavefront's 64 segments are one slice's)
+        if (sidx >= nseg)
+            return;
+        const int s = __builtin_amdgcn_readfirstlane(sidx / kSegPerSlice);
+        const float top = __int_as_float(of_slice(__float_as_int(st.max_x), s));
+        v = ((covered >> s) & 1u) && top != -INFINITY ? v * exp2(((double)top - (double)M) * rc.cd) : 0.0;
         seg_mass[sidx] = v;
         s_part += v;
-    }
-    if (cut && tid < slices && L.covered[tid])
-        s_part += L.srest[tid];
+    };
+    static_assert(kSegPerSlice == 64, "a wavefront's segments belong to one slice");
+    take_segment(tid, seg0);
+    if (nseg > kBlock)
+        take_segment(tid + kBlock, W.seg[min(tid + kBlock, nseg - 1)]);
+    if (cut && tid < slices && ((covered >> tid) & 1u) && !empty)
+        // the slice's histogram units refer to 2^(bin_coord(slice max) / 16); the row maximum is 2^(M c16 / 16)
+        s_part += st.rest * exp2(((double)kf_slice - (double)M * (double)rc.c16) * 0.0625);
     __syncthreads();
     // One element: kept for certain -> its segment; inside the cut bins -> the candidate list (the
     // lanes of a wavefront take consecutive places reserved with one counter update); else dropped.
@@ -1252,10 +1337,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             kmin = min(kmin, key);
             kmax = max(kmax, key);
         }
-        for (int o = 32; o > 0; o >>= 1) {
-            kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-            kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-        }
+        kmin = wave_min_u32(kmin);
+        kmax = wave_max_u32(kmax);
         __syncthreads();  // an earlier call's readers of kmin / kmax are through
         if (lane == 0) {
             L.kmin[wave] = kmin;
@@ -1274,23 +1357,23 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         uint32_t prefix = 0u;
         double abv = above0;
         bad = !(above0 < need);
-        for (int shift = 11 * ((nbits - 1) / 11); shift >= 0 && !bad; shift -= 11) {
+        for (int bit = 11 * ((nbits - 1) / 11); bit >= 0 && !bad; bit -= 11) {
             for (int i = tid; i < C; i += kBlock) {
                 const float xc = __uint_as_float((unsigned)L.cand[i]);
                 const uint32_t rel = kmax - order_key(xc);
-                if ((uint64_t)rel >> (shift + 11) == prefix)
-                    atomicAdd(&H[rank_slot((rel >> shift) & 0x7ffu)], by_count ? 1.0 : (double)prob(xc, rs));
+                if ((uint64_t)rel >> (bit + 11) == prefix)
+                    atomicAdd(&H[(rel >> bit) & 0x7ffu], by_count ? 1.0 : (double)prob(xc, rs));
             }
             __syncthreads();
-            const BinPick pk = wave_pick(H, abv, need, false);
+            const BinPick pk = block_pick(H, abv, need, false, L.pick);
             // the threshold must fall among the candidates
-            if (shift == 11 * ((nbits - 1) / 11) && !(above0 + pk.total >= need))
+            if (bit == 11 * ((nbits - 1) / 11) && !(above0 + pk.total >= need))
                 bad = true;
             prefix = (prefix << 11) | (uint32_t)pk.bin;
             abv = pk.above;
             reached = pk.above + pk.in_bin;
             __syncthreads();
-            if (shift > 0) {
+            if (bit > 0) {
                 for (int b = tid; b < kBins; b += kBlock)
                     H[b] = 0.0;
                 __syncthreads();
@@ -1311,7 +1394,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int s = min(s0 + u, slices - 1);
-            cnt[u] = (s0 + u < slices && L.covered[s]) ? min(L.scount[s], kEmitCap) : 0;
+            cnt[u] = (s0 + u < slices && ((covered >> s) & 1u)) ? min(of_slice(st.count, s), kEmitCap) : 0;
             const ulonglong2* e = reinterpret_cast<const ulonglong2*>(W.emit + (size_t)s * kEmitCap) + 2 * tid;
             const ulonglong2 a = e[0], b = e[1];
             ev[u][0] = a.x;
@@ -1356,7 +1439,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     }
     // slices that are not covered: a second look at their logits
     for (int s = 0; s < (FILTERED ? 0 : slices); ++s) {
-        if (L.covered[s])
+        if ((covered >> s) & 1u)
             continue;
         const SliceRange g = slice_range(s, slice_elems, V, lead);
         float xv[32];
@@ -1382,14 +1465,10 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         // later than the k-th element's bin and 34219 k no earlier
         int b1 = 0, b2 = 0;
         if (top_k > 0) {
-            unsigned long long qsum[kBinsPerThread];
-            gather_units(qsum);
-#pragma unroll
-            for (int k = 0; k < kBinsPerThread; ++k)
-                L.row.hist[rank_slot(rb0 + k)] = (double)qsum[k];
+            row_histogram(false);
+            const BinPick p1 = block_pick(L.row.hist, 0.0, 32768.0 * (double)top_k, false, L.pick);
             __syncthreads();
-            const BinPick p1 = wave_pick(L.row.hist, 0.0, 32768.0 * (double)top_k, false);
-            const BinPick p2 = wave_pick(L.row.hist, 0.0, 34219.0 * (double)top_k, false);
+            const BinPick p2 = block_pick(L.row.hist, 0.0, 34219.0 * (double)top_k, false, L.pick);
             b1 = p1.bin;
             b2 = p2.bin;
             // fewer than k elements inside the histogram's range: not a case for this path
@@ -1399,14 +1478,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         // row bin that every slice's window has to reach: the k-th element's, else the last one that
         // can hold p >= min_p (bins are 1/16 octave; two bins of slack for the rounding of p)
         const int reach = top_k > 0 ? b2 : min(kBins - 1, (int)(-__log2f(min_p) * 16.f) + 2);
-        if (tid < slices) {
-            const int z = L.swin_hi[tid], sh = L.shift[tid];
-            L.covered[tid] = sh >= kBins ||
-                             (L.scount[tid] >= 0 && z >= 0 && L.swin_lo[tid] == 0 && (z >= kPubBins - 1 || z + sh >= reach));
-        }
-        __syncthreads();
-        for (int s = 0; s < slices; ++s)
-            ok = ok && L.covered[s];
+        const bool reaches = shift >= kBins || (st.count >= 0 && st.win_hi >= 0 && st.win_lo == 0 &&
+                                                (st.win_hi >= kPubBins - 1 || st.win_hi + shift >= reach));
+        ok = ok && __ballot(reaches) == ~0ull;  // (lanes past the last slice repeat it)
         if (!ok) {
             return false;
         }
@@ -1415,7 +1489,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int s = min(u, slices - 1);
-            cnt[u] = (u < slices && L.shift[s] < kBins) ? min(L.scount[s], kEmitCap) : 0;
+            cnt[u] = (u < slices && of_slice(shift, s) < kBins) ? min(of_slice(st.count, s), kEmitCap) : 0;
             const unsigned long long* e = W.emit + (size_t)s * kEmitCap;
 #pragma unroll
             for (int k = 0; k < 4; ++k)
@@ -1469,8 +1543,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 append(keep, ev[u][k]);
             }
         s_part += (double)f_part;
-        for (int o = 32; o > 0; o >>= 1)
-            kfl = min(kfl, (uint32_t)__shfl_xor((int)kfl, o));
+        kfl = wave_min_u32(kfl);
         if (lane == 0)
             L.kmin[wave] = kfl;
         __syncthreads();
@@ -1513,52 +1586,44 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     __syncthreads();
     const double target = (double)sp.uniforms[r] * Z;
 
+    // The segment that takes the running mass past the target: thread t owns `per` consecutive segments.
+    {
+        const int per = nseg > kBlock ? 2 : 1;
+        const int g0 = per * tid;
+        const double a = g0 < nseg ? seg_mass[g0] : 0.0, b = per == 2 && g0 + 1 < nseg ? seg_mass[g0 + 1] : 0.0;
+        const double inc = wave_scan_f64(a + b);
+        if (lane == 63)
+            L.seg_sum[wave] = inc;
+        lds_barrier();
+        double before = inc - (a + b);
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+            before += w < wave ? L.seg_sum[w] : 0.0;
+        const bool in_a = before + a > target, in_b = per == 2 && before + a + b > target;
+        const unsigned long long hit = __ballot(in_a || in_b), some = __ballot(a > 0.0 || b > 0.0);
+        if (lane == (hit ? __ffsll((long long)hit) - 1 : 0)) {
+            L.seg_hit[wave] = hit ? (in_a ? g0 : g0 + 1) : -1;
+            L.seg_before[wave] = in_a ? before : before + a;
+        }
+        if (lane == (some ? 63 - __clzll((long long)some) : 0))
+            L.seg_last[wave] = some ? (b > 0.0 ? g0 + 1 : g0) : -1;
+        lds_barrier();
+    }
     if (wave == 0) {
-        const int per = (nseg + 63) / 64;
-        double mine = 0.0;
-        for (int k = 0; k < per; ++k) {
-            const int sidx = lane * per + k;
-            if (sidx < nseg)
-                mine += seg_mass[sidx];
-        }
-        double inc = mine;
-        for (int o = 1; o < 64; o <<= 1) {
-            const double up = __shfl_up(inc, o);
-            if (lane >= o)
-                inc += up;
-        }
-        const double before_lane = inc - mine;
-        const unsigned long long hit = __ballot(inc > target);
-        int seg = -1;
+        int seg = -1, from = -1;
         double before = 0.0;
+#pragma unroll
+        for (int w = kWaves - 1; w >= 0; --w)
+            from = L.seg_hit[w] >= 0 ? w : from;
         bool take_last = false;
-        if (hit) {
-            const int hl = __ffsll((long long)hit) - 1;
-            double run = __shfl(before_lane, hl);
-            for (int k = 0; k < per; ++k) {
-                const int sidx = hl * per + k;
-                if (sidx >= nseg)
-                    break;
-                const double sm = seg_mass[sidx];
-                if (run + sm > target) {
-                    seg = sidx;
-                    before = run;
-                    break;
-                }
-                run += sm;
-            }
-        }
-        if (seg < 0) {
+        if (from >= 0) {
+            seg = L.seg_hit[from];
+            before = L.seg_before[from];
+        } else {
             // rounding: the target is not below the total; take the last segment with mass
-            int last = -1;
-            for (int k = 0; k < per; ++k) {
-                const int sidx = lane * per + k;
-                if (sidx < nseg && seg_mass[sidx] > 0.0)
-                    last = sidx;
-            }
-            for (int o = 32; o > 0; o >>= 1)
-                last = max(last, __shfl_xor(last, o));
-            seg = last;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+                seg = L.seg_last[w] >= 0 ? L.seg_last[w] : seg;
             take_last = true;
         }
         int token = -1;
@@ -1584,12 +1649,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     }
                 }
             }
-            double inc2 = (double)s4;
-            for (int o = 1; o < 64; o <<= 1) {
-                const double up = __shfl_up(inc2, o);
-                if (lane >= o)
-                    inc2 += up;
-            }
+            const double inc2 = wave_scan_f64((double)s4);
             double run = before + inc2 - (double)s4;
             int first = 0x7fffffff, lastk = -1;
 #pragma unroll
@@ -1600,10 +1660,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     if (run > target && first == 0x7fffffff)
                         first = base + k;
                 }
-            for (int o = 32; o > 0; o >>= 1) {
-                first = min(first, __shfl_xor(first, o));
-                lastk = max(lastk, __shfl_xor(lastk, o));
-            }
+            first = (int)wave_min_u32((unsigned)first);
+            lastk = (int)wave_max_u32((unsigned)(lastk + 1)) - 1;
             token = (first != 0x7fffffff && !take_last) ? first : lastk;
         }
         if (lane == 0)
@@ -1612,14 +1670,19 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     return true;
 }
 
-// ANY = false: no row has a filter; three workgroups share a CU (80 registers per lane, 50 KB of LDS
-// each): the step is bound by the latency of its phases, so the third one is nearly free (1024 rows:
-// 78 -> 67 us).  ANY = true (filter arrays are given): every row takes the routine it needs in one
-// launch, so that the two kinds run side by side.  (192 rows of 50257 unaligned logits, a third of them
-// each with top-k, min-p and no filter, some greedy: whole call 55 us; 249 in the whole-row routine,
-// which unaligned rows used to take.)
+// The row-level step is a chain of short dependent phases (a global round trip or an LDS exchange each),
+// so what counts is how many there are and how long one takes: scans and reductions stay in registers
+// (DPP), a bin is picked by the whole workgroup (8 reads per lane and two barriers instead of 32 reads
+// and eleven dependent shuffles in every wavefront), the slices' histograms are requested together with
+// their statistics, and the segment scan takes one segment per thread.  64 rows x 128256: 27.0 -> 21.2 us,
+// 1024 rows: 73 -> 63.5.  Two workgroups share a CU (128 registers); a third one (80 registers) costs spills
+// and gains nothing any more (64 rows 22.8, 1024 rows 62.8 us and a slower average).
+// ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
+// needs in one launch, so that the two kinds run side by side.  (192 rows of 50257 unaligned logits, a third
+// of them each with top-k, min-p and no filter, some greedy: whole call 48 us; 249 in the whole-row
+// routine, which unaligned rows used to take.)
 template <bool ANY>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(ANY ? 4 : 6))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
 {
     __shared__ FinishLds L;
     const long long r = blockIdx.x;
