@@ -97,14 +97,21 @@ def status_string(status: int) -> str:
     return load().spd_status_string(status).decode()
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+# What a call passes is plain integers (the prototypes turn them into pointers): a ctypes object per
+# argument, and a stream object per call, cost more host time than the smallest calls take on the GPU.
+def _ptr(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _bytes(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.numel() * t.element_size()
+
+
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        torch.cuda.init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def make_desc(*, dtype: int, num_q_heads: int, num_kv_heads: int, head_dim: int, num_prompts: int,
@@ -136,7 +143,7 @@ def shared_prefix_decode_attn(desc: AttnDesc, q, k_prefix, v_prefix, prefix_lens
         _ptr(prefix_indptr), _ptr(prefix_page_indices), _ptr(sample_indptr), _ptr(k_suffix),
         _ptr(v_suffix), _ptr(suffix_lens), _ptr(suffix_page_indptr), _ptr(suffix_page_indices),
         int(max_prefix_len), int(max_suffix_len), _ptr(out), _ptr(lse_out), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream))
+        _bytes(workspace), _stream(stream))
     if rc != SPD_OK:
         raise SpdError(rc, "shared_prefix_decode_attn")
 
@@ -150,7 +157,7 @@ def sample_tokens(logits, logits_dtype: int, rows: int, vocab: int, row_stride: 
     rc = load().sample_tokens(
         _ptr(logits), logits_dtype, int(rows), int(vocab), int(row_stride), _ptr(temperature),
         _ptr(top_p), _ptr(uniforms), _ptr(tokens_out), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream))
+        _bytes(workspace), _stream(stream))
     if rc != SPD_OK:
         raise SpdError(rc, "sample_tokens")
 
@@ -231,7 +238,7 @@ def shared_prefix_decode_attn_levels(desc: AttnDesc, q, levels, k_suffix, v_suff
     rc = load().shared_prefix_decode_attn_levels(
         ctypes.byref(desc), _ptr(q), len(levels), levels, _ptr(k_suffix), _ptr(v_suffix), _ptr(suffix_lens),
         _ptr(suffix_page_indptr), _ptr(suffix_page_indices), int(max_suffix_len), _ptr(out), _ptr(lse_out),
-        _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size(),
+        _ptr(workspace), _bytes(workspace),
         _stream(stream))
     if rc != SPD_OK:
         raise SpdError(rc, "shared_prefix_decode_attn_levels")
@@ -242,6 +249,6 @@ def sample_tokens_filtered(logits, logits_dtype: int, rows: int, vocab: int, row
     rc = load().sample_tokens_filtered(
         _ptr(logits), logits_dtype, int(rows), int(vocab), int(row_stride), _ptr(temperature), _ptr(top_p),
         _ptr(top_k), _ptr(min_p), _ptr(uniforms), _ptr(tokens_out), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream))
+        _bytes(workspace), _stream(stream))
     if rc != SPD_OK:
         raise SpdError(rc, "sample_tokens_filtered")
