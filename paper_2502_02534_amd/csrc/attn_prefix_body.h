@@ -537,7 +537,10 @@ __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLev
     if (ntiles > 1) {
         // steps 0 and 1 in one; the copies of step 1 wait until the slots of K of tiles 0 and 1 are free
         first_scores(sa, sb);
-        raise_maximum(sa);  // (the first tile of several is whole)
+        // the first reference is the maximum of 64 tokens (tile 0 is whole; where tile 1 is not, the rows
+        // past its end repeat its last token)
+        raise_maximum(sa);
+        raise_maximum(sb);
         l_run = probabilities(sa, pa);
         wait_copies(min(ntiles - 3, kCopyAhead - 2));
         start_copies(1);
