@@ -299,36 +299,52 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
             load_k(tb + tstep, base);
             next_base = tile_base(min(tb + 2 * tstep, tlast));
         }
-        // ---- online softmax, base 2 (a tile whose scores are all -inf adds nothing)
+        // ---- online softmax, base 2.  The reference maximum only has to bound the exponents: after the first
+        // tile it is looked at again only when a lane's probabilities add up to more than kRaise
+        // (none of them is above that otherwise), or while a query has met no score but -inf (such tiles
+        // add nothing); most tiles then exchange nothing between lanes and rescale nothing.
+        constexpr float kRaise = 1024.f;
         float pv[QB][kVTok];
 #pragma unroll
         for (int b = 0; b < QB; ++b) {
+            float sc[kVTok];
 #pragma unroll
             for (int t = 0; t < kVTok; ++t)
-                pv[b][t] = sacc[b][t >> 2][t & 3];
+                sc[t] = sacc[b][t >> 2][t & 3];
             if (tb + kTile > it.t1) {  // only the last tile of a range can be ragged
 #pragma unroll
                 for (int t = 0; t < kVTok; ++t)
                     if (tb + 16 * (t >> 2) + 4 * r + (t & 3) >= it.t1)
-                        pv[b][t] = -INFINITY;
+                        sc[t] = -INFINITY;
             }
-            float tmax = pv[b][0];
+            auto probabilities = [&](float ref) __attribute__((always_inline)) -> float {
+                float psum = 0.f;
 #pragma unroll
-            for (int t = 1; t < kVTok; ++t)
-                tmax = fmaxf(tmax, pv[b][t]);
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-            const float m_new = fmaxf(m_run[b], tmax * p.scale_log2);
-            const float ref = m_new == -INFINITY ? 0.f : m_new;
-            const float corr = __builtin_amdgcn_exp2f(m_run[b] - ref);
+                for (int t = 0; t < kVTok; ++t) {
+                    pv[b][t] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[t], p.scale_log2, -ref));
+                    psum += pv[b][t];
+                }
+                return psum;
+            };
             float psum = 0.f;
-#pragma unroll
-            for (int t = 0; t < kVTok; ++t) {
-                pv[b][t] = __builtin_amdgcn_exp2f(__builtin_fmaf(pv[b][t], p.scale_log2, -ref));
-                psum += pv[b][t];
+            bool raise = true;
+            if (__ballot(m_run[b] == -INFINITY) == 0ull) {
+                psum = probabilities(m_run[b]);
+                raise = __ballot(!(psum <= kRaise)) != 0ull;
             }
-            l_run[b] = l_run[b] * corr + psum;
-            if (__ballot(m_new != m_run[b])) {
+            if (raise) {
+                float tmax = sc[0];
+#pragma unroll
+                for (int t = 1; t < kVTok; ++t)
+                    tmax = fmaxf(tmax, sc[t]);
+                tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+                tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+                const float m_new = fmaxf(m_run[b], tmax * p.scale_log2);
+                const float ref = m_new == -INFINITY ? 0.f : m_new;
+                const float corr = __builtin_amdgcn_exp2f(m_run[b] - ref);
+                psum = probabilities(ref);
+                l_run[b] *= corr;
+                m_run[b] = m_new;
                 // accumulator register i of lane-row r belongs to query 4 r + i
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -338,7 +354,7 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
                         o[b][k][i] *= f;
                 }
             }
-            m_run[b] = m_new;
+            l_run[b] += psum;
         }
         // ---- O += P V: column c of product k is channel kVPiece (16 (k / kVPiece) + c) + k % kVPiece
         if constexpr (F32) {
