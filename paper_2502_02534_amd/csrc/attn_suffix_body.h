@@ -66,6 +66,18 @@ __device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi)
     return *reinterpret_cast<const uint32_t*>(&r);
 }
 
+// Maximum over the four lanes that share a column (one in each row of 16 lanes), by swaps of lane rows: the
+// exchange stays in the vector ALU (an LDS shuffle is a round trip of more than 100 clocks, two of them in
+// every tile's chain).
+__device__ __forceinline__ float max_over_lane_rows(float v)
+{
+    const unsigned u = __float_as_uint(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned w = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+    const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // Body of one wavefront: work item `item`.  No LDS, no workgroup barriers.
 template <bool PAGED>
 __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long long item)
@@ -225,8 +237,7 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             tmax = fmaxf(tmax, sv[i]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+        tmax = max_over_lane_rows(tmax);
         const float m_new = fmaxf(m_run, tmax * p.scale_log2);  // finite: the tile holds a valid token
         const float corr = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first tile
         float psum = 0.f;
