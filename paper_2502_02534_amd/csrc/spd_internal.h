@@ -135,32 +135,6 @@ __device__ __forceinline__ long long part_index(const AttnParams& p, long long r
     return row * p.num_slots + slot;
 }
 
-// Prompt that owns sample n (sample_indptr is sorted, B >= 1).
-__device__ __forceinline__ int prompt_of_sample(const int* __restrict__ indptr, int B, int n)
-{
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (indptr[mid] <= n)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
-// Element offset of (token t, KV head j, channel 0) inside a KV tensor.
-//   contiguous: [token][Hkv][D], sequence starts at token `start`
-//   paged:      [page][Hkv][page_size][D], `pages` lists the sequence's pages
-__device__ __forceinline__ long long kv_row_offset(int t, int j, int Hkv, int D, int page_size,
-                                                   long long start, const int* __restrict__ pages)
-{
-    if (page_size == 0)
-        return ((start + t) * Hkv + j) * (long long)D;
-    const long long pg = pages[t / page_size];
-    return ((pg * Hkv + j) * page_size + (t % page_size)) * (long long)D;
-}
-
 hipError_t launch_attn_rows(const AttnParams& p, bool prefix, bool suffix, hipStream_t s);
 bool prefix_mfma_supported(const AttnParams& p);
 int prefix_mfma_block_rows(int rows);
