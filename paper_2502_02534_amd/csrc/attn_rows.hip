@@ -18,9 +18,10 @@
 //
 //   fp32: v_mfma_f32_16x16x4_f32, tiles of 16 tokens; nothing leaves fp32.
 //   bf16: v_mfma_f32_16x16x32_bf16, tiles of 32 tokens.  K and Q enter as they are (their products are
-//         exact in fp32); the probabilities are fp32 and enter as the sum of two bf16 numbers, i.e.
-//         two products per V fragment (what the pair leaves out is below 2^-17 of a probability, far
-//         under the roundings of the stored state and of the result).
+//         exact in fp32); the probabilities are fp32 and enter as the sum of three bf16 numbers of
+//         eight bits each, which together are the fp32 number, i.e. three products per V fragment
+//         (two leave out up to 2^-17 of a probability, which shows where values cancel; the third costs 3 %
+//         of the last call below, 28.6 -> 29.6 us).
 //
 // Bound: HBM for the suffix chunks; for prefixes with many rows the fp32 product (32 clocks of a
 // SIMD per 16x16x4 step), for a few rows latency, hence splits down to one tile per wavefront.  A
@@ -30,7 +31,7 @@
 //   fp32, 4/1 heads of 64 channels, 4 samples, prompt 256, suffix 32           93 ->  9.4 us
 //   fp32, 32/8 heads of 128 channels, 16 samples, prompt 2048, suffixes up to 256  582 ->  23 us
 //   bf16, 32/8 heads of 64 channels, 3 prompts of up to 4001 tokens x 21 samples,
-//   suffixes up to 501, paged                                                 840..1060 -> 28 us
+//   suffixes up to 501, paged                                                 840..1060 -> 29 us
 // Where the last two go: launch and first loads 5 us, the tiles (1 to 2 us each with one or two
 // wavefronts per SIMD: dependent products, softmax, a load round trip) 15, the merge 3 (the first is bound
 // by the host).
@@ -367,19 +368,22 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
                     for (int b = 0; b < QB; ++b)
                         o[b][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[b][i], __uint_as_float(vv[i][k]), o[b][k], 0, 0, 0);
         } else {
-            uint4 hi[QB], lo[QB];
+            uint4 term[3][QB];  // the probabilities, most significant bits first
 #pragma unroll
-            for (int b = 0; b < QB; ++b) {
-                uint32_t h[4], l[4];
+            for (int b = 0; b < QB; ++b)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    h[t] = pack_bf16(pv[b][2 * t], pv[b][2 * t + 1]);
-                    l[t] = pack_bf16(pv[b][2 * t] - __uint_as_float(h[t] << 16),
-                                     pv[b][2 * t + 1] - __uint_as_float(h[t] & 0xffff0000u));
+                for (int e = 0; e < 3; ++e) {
+                    uint32_t w[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        w[t] = pack_bf16(pv[b][2 * t], pv[b][2 * t + 1]);
+                        if (e < 2) {  // what is left (exact)
+                            pv[b][2 * t] -= __uint_as_float(w[t] << 16);
+                            pv[b][2 * t + 1] -= __uint_as_float(w[t] & 0xffff0000u);
+                        }
+                    }
+                    term[e][b] = make_uint4(w[0], w[1], w[2], w[3]);
                 }
-                hi[b] = make_uint4(h[0], h[1], h[2], h[3]);
-                lo[b] = make_uint4(l[0], l[1], l[2], l[3]);
-            }
 #pragma unroll
             for (int k = 0; k < kCols; ++k) {
                 const uint32_t sel = (k & 1) ? 0x07060302u : 0x05040100u;
@@ -389,10 +393,10 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
                 f.z = __builtin_amdgcn_perm(vv[5][k >> 1], vv[4][k >> 1], sel);
                 f.w = __builtin_amdgcn_perm(vv[7][k >> 1], vv[6][k >> 1], sel);
 #pragma unroll
-                for (int b = 0; b < QB; ++b) {
-                    o[b][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(lo[b]), as_bf16x8(f), o[b][k], 0, 0, 0);
-                    o[b][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(hi[b]), as_bf16x8(f), o[b][k], 0, 0, 0);
-                }
+                for (int e = 2; e >= 0; --e)
+#pragma unroll
+                    for (int b = 0; b < QB; ++b)
+                        o[b][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(term[e][b]), as_bf16x8(f), o[b][k], 0, 0, 0);
             }
         }
         if (more)

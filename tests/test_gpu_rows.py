@@ -77,3 +77,45 @@ def test_tokens_with_minus_infinity_scores_add_nothing(dev, shared):
     ref = np.einsum("nht,nthd->nhd", w / w.sum(-1, keepdims=True), v)
     got = d.out.cpu().numpy()
     assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-6)
+
+
+@pytest.mark.parametrize("side", ["prefix", "suffix"])
+@pytest.mark.parametrize("d", [64, 96, 256])
+def test_bf16_inputs_keep_fp32_probabilities(dev, d, side):
+    """Three values per channel that cancel to 2^-18 of their size: what is left shows the probabilities'
+    own error.  Bound: fp32 probabilities are good to 2^-21 (the exponent, below 4 in magnitude, is
+    rounded a few times at 2^-24, the exponential once at 2^-23) and the products are added in fp32, so
+    2^-20 of sum p |v| / sum p covers them; beside it the result's roundings to fp16 and bf16, 2^-8 of the
+    result and 2^-24 (fp16's smallest step)."""
+    n, g = 5, 7
+    rng = np.random.default_rng(d)
+    spec = W.small_spec(dtype="bf16", num_q_heads=g, num_kv_heads=1, head_dim=d, num_prompts=1, samples_per_prompt=n,
+                        prefix_len=(3, 3) if side == "prefix" else (0, 0), suffix_len=(0, 0) if side == "prefix" else (3, 3))
+    inp = W.make_attn_inputs(0, spec=spec, seed=77)
+    as_f64 = lambda bits: W.bf16_bits_to_f32(bits).astype(np.float64)
+    inp.q[:] = W.f32_to_bf16_bits(rng.standard_normal(d).astype(np.float32))      # one query for all rows
+    k = inp.k_prefix if side == "prefix" else inp.k_suffix.reshape(n * 3, 1, d)
+    v = inp.v_prefix if side == "prefix" else inp.v_suffix.reshape(n * 3, 1, d)
+    ref, mass = np.empty((n, d)), np.empty((n, d))
+    for a in range(0, k.shape[0], 3):
+        s = as_f64(k[a:a + 3, 0]) @ as_f64(inp.q[0, 0]) / np.sqrt(d)
+        p = np.exp(s - s.max())
+        left = np.zeros(d)
+        for t in range(3):
+            if t == 0:
+                want = rng.uniform(100.0, 200.0, d).astype(np.float32)
+            else:
+                want = (-left / p[t]).astype(np.float32)
+            v[a + t, 0] = W.f32_to_bf16_bits(want)
+            left = left + p[t] * as_f64(v[a + t, 0])
+        out, size = left / p.sum(), (p[:, None] * np.abs(as_f64(v[a:a + 3, 0]))).sum(0) / p.sum()
+        sample = slice(None) if side == "prefix" else a // 3
+        ref[sample], mass[sample] = out, size
+    x = dev.upload_attn(inp)
+    x.run()
+    torch.cuda.synchronize()
+    err = np.abs(x.out.float().cpu().numpy().astype(np.float64) - ref[:, None, :])
+    assert np.abs(ref).max() < 2.0 ** -15 * mass.max()        # the values do cancel
+    bound = 2.0 ** -20 * mass + 2.0 ** -8 * np.abs(ref) + 2.0 ** -24
+    print(f"{side} {d}: error / bound at most {(err / bound[:, None, :]).max():.3f}", flush=True)
+    assert np.all(err <= bound[:, None, :])
