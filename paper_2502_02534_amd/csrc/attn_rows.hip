@@ -360,6 +360,16 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
         }
         // ---- O += P V: column c of product k is channel kVPiece (16 (k / kVPiece) + c) + k % kVPiece
         if constexpr (F32) {
+            // Past the end of the range the last token's values were loaded: zeros in their place, since
+            // a probability of zero does not take an infinite value out.
+            if (tb + kTile > it.t1) {
+#pragma unroll
+                for (int t = 0; t < kVTok; ++t)
+                    if (tb + 4 * r + t >= it.t1)
+#pragma unroll
+                        for (int k = 0; k < kCols; ++k)
+                            vv[t][k] = 0u;
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll

@@ -119,3 +119,34 @@ def test_bf16_inputs_keep_fp32_probabilities(dev, d, side):
     bound = 2.0 ** -20 * mass + 2.0 ** -8 * np.abs(ref) + 2.0 ** -24
     print(f"{side} {d}: error / bound at most {(err / bound[:, None, :]).max():.3f}", flush=True)
     assert np.all(err <= bound[:, None, :])
+
+
+@pytest.mark.parametrize("d,page", [(64, 0), (64, 16), (128, 0), (200, 16)])
+def test_an_infinite_value_stays_in_its_channel(dev, d, page):
+    """fp32 values have no range limit: an infinite value in the last token of a range that ends inside a
+    tile gives an infinite output in its own channel and leaves the other channels alone (1e-5: the
+    order of the sums)."""
+    spec = W.small_spec(dtype="f32", num_q_heads=4, num_kv_heads=2, head_dim=d, samples_per_prompt=5, prefix_len=(21, 21),
+                        suffix_len=(7, 7), page_size=page)
+    inp = W.make_attn_inputs(0, spec=spec, seed=960)
+    plain = dev.upload_attn(inp)
+    plain.run()
+
+    def row(v, side, seq, t):   # [2 heads, d] view of token t
+        if not page:
+            return v[t] if side == "prefix" else v[seq, t]
+        indptr = inp.prefix_indptr if side == "prefix" else inp.suffix_page_indptr
+        pages = inp.prefix_page_indices if side == "prefix" else inp.suffix_page_indices
+        return v[pages[indptr[seq] + t // page], :, t % page]
+
+    row(inp.v_prefix, "prefix", 0, 20)[0, 3] = np.inf
+    for n in range(5):
+        row(inp.v_suffix, "suffix", n, 6)[1, d - 1] = -np.inf
+    x = dev.upload_attn(inp)
+    x.run()
+    torch.cuda.synchronize()
+    got, ref = x.out.cpu().numpy(), plain.out.cpu().numpy().copy()
+    ref[:, :2, 3], ref[:, 2:, d - 1] = np.inf, -np.inf
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-5 * np.abs(ref[fin]) + 1e-6)
