@@ -89,7 +89,11 @@ typedef struct spd_attn_desc {
     uint32_t stages;                /* 0 = whole call; else OR of SPD_STAGE_* */
 } spd_attn_desc;
 
-/* Bytes of workspace the attention call needs for these bounds (0 on invalid desc). */
+/* Bytes of workspace the attention call needs for these bounds (0 on invalid desc).
+ * On the general kernel (fp32, or a head_dim other than 128) a workspace of this size does for every
+ * call of no more samples, however grouped into prompts, and no longer bounds.  On the bf16 / head_dim
+ * 128 kernels the size is that of this one call, and a smaller batch may need more (it is cut into more
+ * splits): allocate the largest of the sizes in use. */
 SPD_API size_t shared_prefix_decode_attn_workspace_size(const spd_attn_desc *desc,
                                                 int64_t max_prefix_len,
                                                 int64_t max_suffix_len);
@@ -160,7 +164,8 @@ typedef struct spd_prefix_level {
 #define SPD_MAX_PREFIX_LEVELS 4
 
 /* Bytes of workspace the multi-level call needs (0 on invalid arguments).  `levels` is host
- * memory; only num_groups, max_samples_per_group and max_len are read. */
+ * memory; only num_groups, max_samples_per_group and max_len are read.  Smaller calls with as many
+ * levels: as above. */
 SPD_API size_t shared_prefix_decode_attn_levels_workspace_size(const spd_attn_desc *desc,
                                                        int32_t num_levels,
                                                        const spd_prefix_level *levels,

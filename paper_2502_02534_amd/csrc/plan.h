@@ -68,6 +68,9 @@ inline int part_tokens(long long len, int min_tokens, int max_parts, int quantum
 // accumulators would not leave room for two wavefronts per SIMD (more than 64 channels).
 inline int rows_per_block(int head_dim, long long rows) { return rows > 16 && head_dim <= 64 ? 32 : 16; }
 
+// Fewest tokens per split in the general kernel: a tile or more for each of four wavefronts.
+inline int min_split_tokens(const spd_attn_desc* d) { return d->dtype == SPD_BF16 ? 128 : 64; }
+
 // Tokens per split of a prefix level with `groups` groups of at most `spp` samples and lengths up to
 // `max_prefix`, at most `max_splits` splits.
 inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long long max_prefix, int max_splits)
@@ -89,7 +92,7 @@ inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long l
     const int block = rows_per_block(d->head_dim, rows);
     const long long base = (long long)groups * d->num_kv_heads * ((rows + block - 1) / block);
     const long long want = (256 + base - 1) / base;
-    return part_tokens(max_prefix, d->dtype == SPD_BF16 ? 128 : 64, (int)(want > max_splits ? max_splits : want), 64);
+    return part_tokens(max_prefix, min_split_tokens(d), (int)(want > max_splits ? max_splits : want), 64);
 }
 
 // Tokens per suffix chunk: enough (sample, KV head, chunk) items to keep every CU busy, chunks of
@@ -109,6 +112,81 @@ inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
     if (t == 128 || t == 256) t = t / 4 * 3;
     if (max_suffix > t * kMaxSplits) t = part_tokens(max_suffix, 64, kMaxSplits, 64);
     return (int)t;
+}
+
+// ---- workspace sizes -----------------------------------------------------------------------------------
+// A program allocates once, for its largest batch and its longest lengths.  Split counts fall in steps as
+// rows are added, so a call's own need is not monotone; what the size functions report is the most
+// that any call of no more samples, however grouped, and no longer lengths can need.  (On the bf16 /
+// head_dim 128 path they report the call's own need.)
+
+// Most suffix chunks that `samples` samples with suffixes of up to `max_suffix` tokens are cut into: the count
+// is largest at `max_suffix`, where a chunk size stops being used, or where it reaches kMaxSplits chunks.
+inline int most_suffix_chunks(const spd_attn_desc* d, long long samples, long long max_suffix)
+{
+    spd_attn_desc t = *d;
+    t.num_samples = (int)samples;
+    const long long pairs = samples * d->num_kv_heads, want = (2048 + pairs - 1) / pairs;
+    long long most = 0;
+    auto at = [&](long long len) {
+        len = len < max_suffix ? len : max_suffix;
+        const int chunk = plan_suffix_chunk(&t, len);
+        const long long n = (len + chunk - 1) / chunk;
+        most = n > most ? n : most;
+    };
+    at(max_suffix);
+    for (int k = 1; k <= 5; ++k) {
+        at(64 * k * want);
+        at(64ll * k * kMaxSplits);
+    }
+    at(96ll * kMaxSplits);
+    return (int)most;
+}
+
+// Most splits of a prefix level of up to `max_len` tokens that `samples` samples share.  One group takes the
+// fewest row blocks, so it is cut into the most splits.
+inline int most_prefix_splits(const spd_attn_desc* d, long long samples, long long max_len, int max_splits)
+{
+    const long long rows = samples * (d->num_q_heads / d->num_kv_heads);
+    const int block = rows_per_block(d->head_dim, kPrefixBlockRows);  // the larger of the two blocks
+    const long long base = (long long)d->num_kv_heads * ((rows + block - 1) / block);
+    long long want = (256 + base - 1) / base;
+    want = want > max_splits ? max_splits : want;
+    const int least = min_split_tokens(d);
+    const long long splits = (max_len + least - 1) / least;
+    return (int)(splits < want ? splits : want);
+}
+
+// Bytes to report for a call of d->num_samples samples with prefix levels of up to max_len[] tokens; `own` is
+// what the call itself needs.
+inline size_t workspace_bytes(const spd_attn_desc* d, int num_levels, const long long* max_len, long long max_suffix,
+                              size_t own)
+{
+    if (d->dtype == SPD_BF16 && d->head_dim == 128)
+        return own;
+    auto slots = [&](long long samples) {
+        long long n = most_suffix_chunks(d, samples, max_suffix);
+        for (int l = 0; l < num_levels; ++l)
+            n += most_prefix_splits(d, samples, max_len[l], kMaxSplits / num_levels);
+        return n;
+    };
+    // the largest samples * slots(samples) of all batches up to this one; slots() only falls, so the
+    // batches that count are the last ones before it falls
+    const long long top = slots(1);
+    long long most = 0;
+    for (long long n = d->num_samples; n > 0 && n * top > most;) {
+        const long long s = slots(n);
+        most = n * s > most ? n * s : most;
+        long long more = 0, same = n;  // slots(more) > s (or more == 0), slots(same) == s
+        while (same - more > 1) {
+            const long long mid = (more + same) / 2;
+            (slots(mid) > s ? more : same) = mid;
+        }
+        n = more;
+    }
+    const size_t acc = align_up((size_t)most * d->num_q_heads * d->head_dim * sizeof(float), 256);
+    const size_t ml = align_up((size_t)most * d->num_q_heads * 2 * sizeof(float), 256);
+    return acc + ml > own ? acc + ml : own;
 }
 
 inline int make_plan(const spd_attn_desc* d, long long max_prefix, long long max_suffix, Plan* pl)

@@ -241,7 +241,8 @@ size_t shared_prefix_decode_attn_workspace_size(const spd_attn_desc* desc, int64
     Plan pl;
     if (make_plan(desc, max_prefix_len, max_suffix_len, &pl) != SPD_OK)
         return 0;
-    return pl.acc_bytes + pl.ml_bytes + 256;
+    const long long len = max_prefix_len;
+    return workspace_bytes(desc, 1, &len, max_suffix_len, pl.acc_bytes + pl.ml_bytes) + 256;
 }
 
 }  // extern "C"
@@ -449,7 +450,10 @@ size_t shared_prefix_decode_attn_levels_workspace_size(const spd_attn_desc* desc
     LevelPlan lp;
     if (!desc || make_level_plan(desc, num_levels, levels, max_suffix_len, &lp) != SPD_OK)
         return 0;
-    return lp.acc_bytes + lp.ml_bytes + 256;
+    long long len[SPD_MAX_PREFIX_LEVELS];
+    for (int l = 0; l < num_levels; ++l)
+        len[l] = levels[l].max_len;
+    return workspace_bytes(desc, num_levels, len, max_suffix_len, lp.acc_bytes + lp.ml_bytes) + 256;
 }
 
 int shared_prefix_decode_attn_levels(const spd_attn_desc* desc, const void* q, int32_t num_levels,

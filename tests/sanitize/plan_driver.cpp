@@ -52,6 +52,8 @@ int main()
                                         pl.ml_bytes < slots * N * d.num_q_heads * 8 || pl.ml_bytes % 256)
                                         return fail("workspace too small or misaligned", (long long)pl.acc_bytes,
                                                     (long long)pl.ml_bytes);
+                                    if (workspace_bytes(&d, 1, &lp, ls, pl.acc_bytes + pl.ml_bytes) < pl.acc_bytes + pl.ml_bytes)
+                                        return fail("reported size below the call's own need", lp, ls);
                                     // the same problem as a tree of one to four levels
                                     for (int levels = 1; levels <= SPD_MAX_PREFIX_LEVELS; ++levels) {
                                         spd_prefix_level lv[SPD_MAX_PREFIX_LEVELS] = {};
