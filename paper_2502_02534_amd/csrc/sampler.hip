@@ -215,7 +215,7 @@ struct RowLds {
 // Whole-row routine for one workgroup of kBlock threads: every pass reads the row from
 // global memory.  Used when the sliced kernel cannot take a row (very large vocabularies,
 // candidate overflow).
-__device__ void sample_row_from_memory(const SamplerParams& sp, long long r, RowLds& L)
+__device__ __forceinline__ void sample_row_from_memory(const SamplerParams& sp, long long r, RowLds& L)
 {
     double* hist = L.hist;
     double* scratch = L.scratch;
@@ -1459,7 +1459,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         // kernel wrote such a row's slices out from the top, so everything that survives is among the
         // pairs, provided every slice's window reaches as far down as the filters do; otherwise the
         // row goes to the whole-row routine.  Survivors become the candidate list. ----
-        bool ok = slices <= 8;  // the pairs of a row stay in registers (four per thread and slice)
+        bool ok = slices <= 8;  // (the pairs of a row are requested together, four per thread and slice)
         // top-k: the k-th largest logit lies in row bins b1 .. b2, by the element-count bounds of the
         // histogram units (an element adds 32768 to 34219 units): the running units reach 32768 k no
         // later than the k-th element's bin and 34219 k no earlier
@@ -1484,17 +1484,25 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         if (!ok) {
             return false;
         }
-        unsigned long long ev[8][4];
-        int cnt[8];
+        // All pairs of the row, four per thread and slice, requested together; `f(live, pair)` for each.  With
+        // top-k they are read twice (the second time from L2): held across the selection between the two they
+        // would take 64 registers that it does not have.
+        auto for_pairs = [&](auto f) __attribute__((always_inline)) {
+            unsigned long long ev[8][4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int s = min(u, slices - 1);
-            cnt[u] = (u < slices && of_slice(shift, s) < kBins) ? min(of_slice(st.count, s), kEmitCap) : 0;
-            const unsigned long long* e = W.emit + (size_t)s * kEmitCap;
+            for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                ev[u][k] = e[tid + k * kBlock];
-        }
+                for (int k = 0; k < 4; ++k)
+                    ev[u][k] = W.emit[(size_t)min(u, slices - 1) * kEmitCap + tid + k * kBlock];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int s = min(u, slices - 1);
+                const int cnt = (u < slices && of_slice(shift, s) < kBins) ? min(of_slice(st.count, s), kEmitCap) : 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    f(tid + k * kBlock < cnt, ev[u][k]);
+            }
+        };
         uint32_t key_k = 0u;
         if (top_k > 0) {
             // elements above bin b1 are counted, those in b1 .. b2 listed; the k-th largest is found
@@ -1502,16 +1510,12 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             const float t_b1 = b1 <= 0 ? INFINITY : kf_row - (float)b1 + 1.f;
             const float t_b2 = kf_row - (float)b2;
             int n_above = 0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool live = tid + k * kBlock < cnt[u];
-                    const float t = __uint_as_float((unsigned)ev[u][k]) * rc.c16;
-                    const bool above = live && t >= t_b1;
-                    n_above += above ? 1 : 0;
-                    append(live && !above && t >= t_b2, ev[u][k]);
-                }
+            for_pairs([&](bool live, unsigned long long pair) __attribute__((always_inline)) {
+                const float t = __uint_as_float((unsigned)pair) * rc.c16;
+                const bool above = live && t >= t_b1;
+                n_above += above ? 1 : 0;
+                append(live && !above && t >= t_b2, pair);
+            });
             double da = (double)n_above, db = 0.0;
             block_sum2_f64(da, db, L.row.scratch);  // (its barriers also complete the list)
             const unsigned listed = L.cand_total;
@@ -1530,18 +1534,15 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         }
         // survivors: at least as large as the k-th largest logit, and p >= min_p
         uint32_t kfl = 0xffffffffu;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float xq = __uint_as_float((unsigned)ev[u][k]);
-                const uint32_t key = order_key(xq);
-                const float pq = prob(xq, rs);
-                const bool keep = tid + k * kBlock < cnt[u] && key >= key_k && pq >= min_p;
-                f_part += keep ? pq : 0.f;
-                kfl = keep ? min(kfl, key) : kfl;
-                append(keep, ev[u][k]);
-            }
+        for_pairs([&](bool live, unsigned long long pair) __attribute__((always_inline)) {
+            const float xq = __uint_as_float((unsigned)pair);
+            const uint32_t key = order_key(xq);
+            const float pq = prob(xq, rs);
+            const bool keep = live && key >= key_k && pq >= min_p;
+            f_part += keep ? pq : 0.f;
+            kfl = keep ? min(kfl, key) : kfl;
+            append(keep, pair);
+        });
         s_part += (double)f_part;
         kfl = wave_min_u32(kfl);
         if (lane == 0)
@@ -1678,9 +1679,11 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // 1024 rows: 73 -> 63.5.  Two workgroups share a CU (128 registers); a third one (80 registers) costs spills
 // and gains nothing any more (64 rows 22.8, 1024 rows 62.8 us and a slower average).
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
-// needs in one launch, so that the two kinds run side by side.  (192 rows of 50257 unaligned logits, a third
-// of them each with top-k, min-p and no filter, some greedy: whole call 48 us; 249 in the whole-row
-// routine, which unaligned rows used to take.)
+// needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory: the
+// filtered routine reads its pairs twice instead of holding them across the selection, and the whole-row
+// routine is inlined (a call would have the arguments copied to memory, which every phase then reads).
+// (192 rows of 50257 unaligned logits, a third of them each with top-k, min-p and no filter, some greedy:
+// whole call 45.8 us, 48.5 with the spills; 249 in the whole-row routine.)
 template <bool ANY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
 {
