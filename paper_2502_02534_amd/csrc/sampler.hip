@@ -626,8 +626,10 @@ __device__ __forceinline__ SliceRange slice_range(int slice, int slice_elems, in
 // Loads a slice into 32 registers per thread; `xa` points at position 0.  Every load is unconditional
 // (lanes outside the whole float4s re-read the nearest one), so that the hardware's in-order load
 // counter stays exact for the compiler and later loads need not wait for these.  SPD_MASK_SLICE,
-// applied where the values are first needed, replaces what lies outside the row by -inf and fetches
-// the one to three logits of a float4 that the row only partly fills.  Every slice holds at least one
+// applied where the values are first needed, replaces what lies outside the row by -inf and, in a slice that
+// begins or ends inside a float4, fetches the logits there.  (Fetched under a branch per float4 they cost
+// every slice that is not full about a microsecond, 1024 greedy rows of 1000 logits 11.9 us against 9.6, and
+// the row-level kernel some 20 registers.)  Every slice holds at least one
 // whole float4 (the host sends rows shorter than that to the whole-row kernel, and slices are never
 // shorter than about 2000).
 #define SPD_LOAD_SLICE(xv, xa, g, tid)                                                  \
@@ -644,15 +646,37 @@ __device__ __forceinline__ SliceRange slice_range(int slice, int slice_elems, in
     _Pragma("unroll") for (int j = 0; j < 8; ++j)                                       \
     {                                                                                   \
         const int i_ = (g).e0 + j * kIter + (tid) * 4;                                  \
-        if (i_ < (g).v0 || i_ >= (g).v4end) {                                           \
-            _Pragma("unroll") for (int k_ = 0; k_ < 4; ++k_)                            \
-            {                                                                           \
-                (xv)[4 * j + k_] = -INFINITY;                                           \
-                if (i_ + k_ >= (g).lead && i_ + k_ < (g).e1)                            \
-                    (xv)[4 * j + k_] = (xa)[i_ + k_];                                   \
-            }                                                                           \
-        }                                                                               \
+        if (i_ < (g).v0 || i_ >= (g).v4end)                                             \
+            (xv)[4 * j] = (xv)[4 * j + 1] = (xv)[4 * j + 2] = (xv)[4 * j + 3] = -INFINITY; \
+    }                                                                                   \
+    if ((g).v0 > (g).e0 || (g).e1 > (g).v4end)                                          \
+        load_slice_ends(xv, xa, g, tid);
+
+// The logits of the float4s that a slice only partly fills: up to three before its first whole one (thread
+// 0), up to three behind its last.
+__device__ __forceinline__ void load_slice_ends(float (&xv)[32], const float* __restrict__ xa, const SliceRange& g, int tid)
+{
+    if (g.v0 > g.e0 && tid == 0) {
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+            if (k >= g.lead)
+                xv[k] = xa[k];
     }
+    const int behind = g.v4end - g.e0 - 4 * tid;  // of this thread's first float4
+    if (g.e1 > g.v4end && behind >= 0 && behind % kIter == 0) {
+        float end[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            end[k] = g.v4end + k < g.e1 ? xa[g.v4end + k] : -INFINITY;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (behind == j * kIter) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    xv[4 * j + k] = end[k];
+            }
+    }
+}
 
 // Largest b in [lo_b, hi_b] with pred(b), where pred is true on a prefix of the range; lo_b - 1
 // if it is false everywhere.
@@ -1676,8 +1700,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // (DPP), a bin is picked by the whole workgroup (8 reads per lane and two barriers instead of 32 reads
 // and eleven dependent shuffles in every wavefront), the slices' histograms are requested together with
 // their statistics, and the segment scan takes one segment per thread.  64 rows x 128256: 27.0 -> 21.2 us,
-// 1024 rows: 73 -> 63.5.  Two workgroups share a CU (128 registers); a third one (80 registers) costs spills
-// and gains nothing any more (64 rows 22.8, 1024 rows 62.8 us and a slower average).
+// 1024 rows: 73 -> 63.5.  Three workgroups share a CU (79 registers, 50 KB of LDS each).
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
 // needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory: the
 // filtered routine reads its pairs twice instead of holding them across the selection, and the whole-row

@@ -88,8 +88,9 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode != 0 and "one GPU" in r.stderr
 
 
-def _scratch_sizes(src):
-    """(kernel, bytes of scratch memory per lane) of every kernel in a source file, with the build's flags."""
+def _kernel_resources(src):
+    """(kernel, bytes of scratch memory per lane, wavefronts per SIMD) of every kernel in a source file, with the
+    build's flags."""
     import re
     import shutil
     import subprocess
@@ -106,8 +107,9 @@ def _scratch_sizes(src):
             capture_output=True, text=True, check=True).stderr
     names = re.findall(r"Function Name: (\S+)", out)
     scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", out)]
-    assert names and len(names) == len(scratch), out[-2000:]
-    return list(zip(names, scratch))
+    occupancy = [int(v) for v in re.findall(r"Occupancy \[waves/SIMD\]: (\d+)", out)]
+    assert names and len(names) == len(scratch) == len(occupancy), out[-2000:]
+    return list(zip(names, scratch, occupancy))
 
 
 def test_hand_scheduled_attention_kernels_do_not_spill():
@@ -117,13 +119,17 @@ def test_hand_scheduled_attention_kernels_do_not_spill():
     do so, so the build must keep these kernels free of scratch memory."""
     import concurrent.futures
     with concurrent.futures.ThreadPoolExecutor(2) as pool:
-        for kernels in pool.map(_scratch_sizes, ["attn_prefix_mfma.hip", "attn_fused.hip"]):
-            for name, scratch in kernels:
+        for kernels in pool.map(_kernel_resources, ["attn_prefix_mfma.hip", "attn_fused.hip"]):
+            for name, scratch, _ in kernels:
                 assert scratch == 0, (name, scratch)
 
 
-def test_sampler_kernels_use_no_scratch_memory():
+def test_sampler_kernels_use_no_scratch_memory_and_leave_room_for_each_other():
     """Every register of the sampler's kernels is counted; a spill, or arguments copied to memory for a call
-    that was not inlined, would sit in each of their short phases."""
-    for name, scratch in _scratch_sizes("sampler.hip"):
+    that was not inlined, would sit in each of their short phases.  The row-level kernel (eight wavefronts
+    per workgroup) runs three workgroups per CU, i.e. six wavefronts per SIMD, when there are no filters."""
+    kernels = _kernel_resources("sampler.hip")
+    for name, scratch, occupancy in kernels:
         assert scratch == 0, (name, scratch)
+        assert occupancy >= (6 if "finish_kernelILb0E" in name else 4), (name, occupancy)
+    assert any("finish_kernelILb0E" in name for name, _, _ in kernels)
