@@ -3,9 +3,11 @@
 // Two paths.  The sliced path (below: two stream-ordered kernels) reads a row from HBM once, leaves
 // what the row-level step needs in the workspace, and finds the exact nucleus threshold without
 // sorting.  The whole-row routine (one workgroup per row, every pass from memory) covers what the
-// sliced path does not take: vocabularies beyond 16 slices (or of a few logits), the rare row whose
-// candidate set overflows, and rows whose min-p or top-k filter reaches further down than the
-// sliced path's windows.
+// sliced path does not take: vocabularies of fewer than 4 logits, the rare row whose candidate set
+// overflows, rows whose min-p or top-k filter reaches further down than the sliced path's windows, and,
+// among rows that do not start on a 16-byte boundary, short ones and those whose positions (up to three
+// more than logits) overrun the slices that the vocabulary is cut into (16382 to 16384 logits in one slice,
+// 131070 to 131072 in eight, 262142 to 262144 in sixteen).
 //
 // Probabilities are evaluated by one shared routine, p_i = 2^((x_i - max) c) with
 // c = log2(e)/T carried as hi + lo floats, so every pass sees the same bits; every sum that
@@ -1760,7 +1762,14 @@ hipError_t launch_sampler(const SamplerParams& p, void* ws, hipStream_t s)
     // before each (up to three more than the vocabulary).
     const bool aligned = (p.stride % 4 == 0) && ((uintptr_t)p.logits % 16 == 0);
     const long long span = aligned ? p.vocab : p.vocab + 3;
-    if (slices == 0 || span > (long long)slices * kSliceMax || p.vocab < (aligned ? 4 : 8)) {
+    // Short rows that are not aligned take the whole-row kernel, one launch whose passes all hit the L2.  The
+    // two sides at 64 rows: 2001 logits 17.7 us against 19.2 in the sliced kernels, 4001 20.8 / 19.8, 5001
+    // 22.7 / 19.2; without a cut 4001 9.5 / 10.1, 5001 10.7 / 9.9; with filters 5001 31.9 / 33.0, 7001 38.5 / 33.0;
+    // the lines lie within 1000 logits of these from 1 to 2048 rows, except near 768.  (Greedy rows alone
+    // would cross at 11000, 4.6 / 5.9 us at 5001: they are not known here.)
+    const bool filters = p.top_k || p.min_p;
+    const long long least = aligned ? 4 : filters ? 6144 : 4096;
+    if (slices == 0 || span > (long long)slices * kSliceMax || p.vocab < least) {
         hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p);
         return hipGetLastError();
     }
@@ -1768,7 +1777,7 @@ hipError_t launch_sampler(const SamplerParams& p, void* ws, hipStream_t s)
     slice_elems = (slice_elems + 3) / 4 * 4;
     hipLaunchKernelGGL(sampler_scan_kernel, dim3((unsigned)(p.rows * slices)), dim3(kBlock), 0, s, p, (char*)ws, slices,
                        slice_elems);
-    if (p.top_k || p.min_p)
+    if (filters)
         hipLaunchKernelGGL(sampler_finish_kernel<true>, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p, (char*)ws,
                            slices, slice_elems);
     else

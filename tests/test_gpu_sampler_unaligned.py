@@ -1,7 +1,8 @@
 """Rows that do not start on a 16-byte boundary (a vocabulary or a row stride that is no multiple of 4, a
-logits pointer that is only 4-byte aligned) run through the sliced sampler kernels: every distance of
-a row's start from a boundary, vocabularies either side of a slice's and a float4's end, all kinds
-of rows, and what surrounds a row in memory is never taken for a logit."""
+logits pointer that is only 4-byte aligned) run through the sliced sampler kernels from 4096 logits on (6144
+with filters) and through the whole-row kernel below that: every distance of a row's start from a
+boundary, vocabularies either side of a slice's and a float4's end, all kinds of rows, and what
+surrounds a row in memory is never taken for a logit."""
 import numpy as np
 import pytest
 
@@ -62,3 +63,29 @@ def test_unaligned_rows(dev, oracle, vocab, stride, off):
     torch.cuda.synchronize()
     o = oracle.sample_tokens_filtered(x, t, top_p, u, np.minimum(top_k, vocab).astype(np.int32), min_p)
     compare_tokens(tokens.cpu().numpy(), o, u, vocab, label="filtered ")
+
+
+@pytest.mark.parametrize("vocab,filters,one_launch", [(1001, False, True), (4095, False, True), (4097, False, False),
+                                                      (4097, True, True), (6143, True, True), (6145, True, False)])
+def test_short_unaligned_rows_take_the_one_launch_kernel(dev, oracle, vocab, filters, one_launch):
+    """Below 4096 logits (6144 with filter arrays) the two launches of the sliced kernels cost more than the
+    whole-row kernel's passes over a row that stays in the L2.  That kernel leaves the workspace alone,
+    which tells the two apart."""
+    from paper_2502_02534_amd import binding as B
+    rows = 21
+    rng = np.random.default_rng(vocab)
+    x = (rng.standard_normal((rows, vocab)) * 3.0).astype(np.float32)
+    t = rng.choice(np.array([0.0, 0.4, 1.0], np.float32), rows)
+    top_p = rng.choice(np.array([0.8, 1.0], np.float32), rows)
+    u = rng.random(rows, dtype=np.float32)
+    top_k = rng.choice(np.array([0, 7, 300], np.int32), rows) if filters else None
+    min_p = rng.choice(np.array([0.0, 0.05], np.float32), rows) if filters else None
+    to = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ws = torch.full((max(256, B.sample_tokens_workspace_size(rows, vocab)),), 93, dtype=torch.uint8, device="cuda")
+    tokens = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+    xd, td, pd, ud, kd, md = to(x), to(t), to(top_p), to(u), to(top_k), to(min_p)
+    B.sample_tokens_filtered(xd, B.SPD_F32, rows, vocab, vocab, td, pd, kd, md, ud, tokens, ws)
+    torch.cuda.synchronize()
+    o = oracle.sample_tokens_filtered(x, t, top_p, u, top_k, min_p) if filters else oracle.sample_tokens(x, t, top_p, u)
+    compare_tokens(tokens.cpu().numpy(), o, u, vocab)
+    assert bool((ws == 93).all()) == one_launch
