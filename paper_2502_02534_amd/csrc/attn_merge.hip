@@ -51,7 +51,8 @@ template <bool HALF> struct PartVec {
 //   few rows: all 64 lanes on one row (up to 128 slots, two pairs per lane).  Bound: latency, i.e. one round
 //     trip for everything (the pairs and the first BATCH parts of every lane are requested together,
 //     from clamped places rather than under branches) and the launch.
-//   many rows of at most eight slots: one group per row.  Bound: HBM (partial states).
+//   many rows of at most eight slots: one group per row.  Bound: HBM (partial states) from some 16384 rows
+//     on, latency below.
 // Measured in replayed graphs (before: 32 threads per row, up to 32 guarded loads each, weights through
 // LDS): 512 rows x 20 slots 6.1 -> 3.6 us, 2048 x 22 6.6 -> 4.7, 13312 x 26 18.0 -> 10.1,
 // 16 x 5 (fp32) 3.7 -> 2.5; 32768 x 8 14.4 -> 14.2 (16.2 with all 64 lanes on one row).
@@ -163,9 +164,11 @@ void launch_merge_kernel(const AttnParams& p, hipStream_t s)
 template <bool HALF, int CL>
 void launch_merge_cl(const AttnParams& p, hipStream_t s)
 {
-    // From 8192 rows on (two wavefronts per SIMD with four rows each) there are loads enough in flight without
-    // sharing a row's slots out (32768 rows x 8 slots: 14.2 us against 16.2).
-    if (CL < 64 && p.num_slots <= 8 && (long long)p.N * p.Hq >= 8192) {
+    // With up to eight slots a lane requests a row's whole column at once, so sharing the slots out only adds
+    // wavefronts, which pays while there are few rows.  Shared / not shared, bf16, 128 channels: 1024 rows
+    // x 2 slots 3.8 / 3.6 us, x 5 3.8 / 3.9, 2048 x 5 4.0 / 4.0, 4096 x 2 4.6 / 3.7, x 8 4.6 / 4.1,
+    // 6144 x 5 5.3 / 4.3, 16384 x 8 9.1 / 7.0, 32768 x 8 16.2 / 14.2 (fp32 and other widths cross there too).
+    if (CL < 64 && p.num_slots <= 8 && (long long)p.N * p.Hq >= (p.num_slots <= 4 ? 1024 : 2048)) {
         if (p.num_slots <= 4)
             launch_merge_kernel<HALF, CL, 1, 4>(p, s);
         else

@@ -6,7 +6,7 @@
 // sliced path does not take: vocabularies of fewer than 4 logits, the rare row whose candidate set
 // overflows, rows whose min-p or top-k filter reaches further down than the sliced path's windows, and,
 // among rows that do not start on a 16-byte boundary, short ones and those whose positions (up to three
-// more than logits) overrun the slices that the vocabulary is cut into (16382 to 16384 logits in one slice,
+// more than logits) overrun the slices that the vocabulary is cut into (so 16382 to 16384 logits in one slice,
 // 131070 to 131072 in eight, 262142 to 262144 in sixteen).
 //
 // Probabilities are evaluated by one shared routine, p_i = 2^((x_i - max) c) with

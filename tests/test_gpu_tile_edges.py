@@ -67,3 +67,15 @@ def test_merges_of_every_kind(dev, oracle, i):
     n = spec.num_samples * spec.num_q_heads
     rows = None if n <= 64 else np.sort(np.random.default_rng(i).choice(n, 160, replace=False))
     check_attention(dev, oracle, W.make_attn_inputs(0, spec=spec, seed=1400 + i, poison_padding=True), rows=rows)
+
+
+@pytest.mark.parametrize("samples,prefix,suffix,slots", [(127, 70, 60, 2), (128, 70, 60, 2), (255, 300, 330, 5), (256, 300, 330, 5)])
+def test_merges_either_side_of_sharing_a_rows_slots(dev, oracle, samples, prefix, suffix, slots):
+    """From 1024 rows of up to four slots, and from 2048 of up to eight, a row's slots are no longer shared out."""
+    spec = W.small_spec(num_q_heads=8, num_kv_heads=4, samples_per_prompt=samples, prefix_len=(prefix, prefix), suffix_len=(0, suffix))
+    inp = W.make_attn_inputs(0, spec=spec, seed=1500 + samples, poison_padding=True)
+    from paper_2502_02534_amd import binding as B
+    plan = B.spd_attn_plan(dev.upload_attn(inp).desc, prefix, suffix)
+    assert plan[1] + plan[3] == slots
+    rows = np.sort(np.random.default_rng(samples).choice(spec.num_samples * 8, 160, replace=False))
+    check_attention(dev, oracle, inp, rows=rows)
