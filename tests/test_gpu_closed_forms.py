@@ -214,8 +214,8 @@ def test_tree_of_prefixes_peaked_and_constant_value(dev, oracle, i):
 
 
 # A prefix pass on a launch of its own with more than 128 query rows per KV head and at least 192 wide
-# workgroups takes the 256-row workgroups with the long K/V rings (copies two tiles ahead): a call
-# without suffixes over many prompts reaches it.
+# workgroups takes the 256-row workgroups (eight wavefronts on the same five-slot rings): a call without
+# suffixes over many prompts reaches it.
 @pytest.mark.parametrize("page", [0, 16])
 def test_wide_prefix_workgroups_on_their_own_launch(dev, oracle, page):
     print(f"256-row prefix workgroups, page_size {page}", flush=True)
