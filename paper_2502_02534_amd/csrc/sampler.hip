@@ -15,7 +15,6 @@
 // patterns, so all ties with the threshold are kept by construction.
 #include "spd_internal.h"
 
-#include <cstdlib>
 #include <type_traits>
 
 namespace spd {
@@ -83,10 +82,6 @@ __device__ __forceinline__ unsigned wave_scan_u32(unsigned v)
     v += dpp_u32<kBcast15, 0xa>(0u, v);
     v += dpp_u32<kBcast31, 0xc>(0u, v);
     return v;
-}
-__device__ __forceinline__ double lane63_f64(double v)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 // Reductions: the same value in every lane.
 template <typename F> __device__ __forceinline__ unsigned wave_reduce_u32(unsigned v, unsigned none, F f)
@@ -680,21 +675,6 @@ __device__ __forceinline__ void load_slice_ends(float (&xv)[32], const float* __
     }
 }
 
-// Largest b in [lo_b, hi_b] with pred(b), where pred is true on a prefix of the range; lo_b - 1
-// if it is false everywhere.
-template <typename F> __device__ __forceinline__ int last_true(int lo_b, int hi_b, F pred)
-{
-    int lo = lo_b - 1, hi = hi_b;  // invariant: pred(lo) (or lo == lo_b - 1), answer <= hi
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (pred(mid))
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
 // ---- kernel 1: the pass over the logits --------------------------------------------------------------
 constexpr int kWaveStage = kEmitCap / kWaves * 2;  // pairs one wavefront may gather (twice its even share)
 
@@ -928,10 +908,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     // ---- which bins to write out.  Element counts come from the fixed-point sums: every element adds
     // between 32768 and 34219 units, so (units >> 15) never undercounts.  Every thread tests two
     // places of the search range; the largest that fits wins. ----
-    const int cap = kEmitCap - 3;
     const int Lb = L.cut_bin;
     auto units = [&](int a, int z) { return L.cumq[z] - (a > 0 ? L.cumq[a - 1] : 0u); };
-    auto fits = [&](int a, int z) { return (int)(units(a, z) >> 15) <= cap; };
+    auto fits = [&](int a, int z) { return (int)(units(a, z) >> 15) <= kEmitCap; };
     // (a row with a filter: always from the top, as many bins as fit; its filters decide later how
     // far down they reach)
     const bool from_top = filtered || fits(0, min(Lb + kTopProbe, kPubBins - 1));
@@ -939,9 +918,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     if (from_top) {
         // bins 0 .. z, z as large as fits, at most L + kTopMargin
         const int zmax = filtered ? kPubBins - 1 : min(Lb + kTopMargin, kPubBins - 1);
-        if (2 * tid + 1 <= zmax && (int)(qi >> 15) <= cap)
+        if (2 * tid + 1 <= zmax && (int)(qi >> 15) <= kEmitCap)
             mine = 2 * tid + 1;
-        else if (2 * tid <= zmax && (int)((qi - q1) >> 15) <= cap)
+        else if (2 * tid <= zmax && (int)((qi - q1) >> 15) <= kEmitCap)
             mine = 2 * tid;
     } else if (fits(Lb, Lb)) {
         // bins L - w .. L + w, w as large as fits
