@@ -35,7 +35,9 @@ __device__ __forceinline__ float prob(float x, const RowScale& r)
 {
     const float d = x - r.max_x;
     const float y = __builtin_fmaf(d, r.c_hi, d * r.c_lo);
-    return __builtin_amdgcn_exp2f(y);
+    // (a logit of -inf: where c_lo is negative, as at temperatures 0.4 and 0.7, the two terms are infinities of
+    // opposite sign; the maximum takes the zero)
+    return fmaxf(__builtin_amdgcn_exp2f(y), 0.f);
 }
 
 __device__ __forceinline__ double wave_sum_f64(double v)
