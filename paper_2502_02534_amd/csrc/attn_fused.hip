@@ -3,7 +3,8 @@
 // The prefix pass is bound by the matrix pipe and the vector ALU, the suffix pass by HBM, and
 // neither needs the other's result before the merge.  One grid of 256-thread workgroups with
 // 80 KB of LDS carries both, two workgroups per CU: the first workgroups run the prefix body
-// (four wavefronts, 128 rows, rings of five 32-token tiles), the rest run the suffix body (four wavefront items; it uses no LDS).  Workgroups start in index order; the prefix workgroups come first (or, when there are
+// (four wavefronts, 128 rows, rings of five 32-token tiles), the rest run the suffix body (four wavefront
+// items; it uses no LDS).  Workgroups start in index order; the prefix workgroups come first (or, when there are
 // more of them than CUs, evenly spread through the grid), so that a CU holds one prefix workgroup
 // and, beside it, suffix workgroups: each SIMD has one wavefront that multiplies and one that
 // streams, HBM is busy during the prefix pass, and there is no launch (with its ramp and tail)

@@ -31,12 +31,12 @@
 // partial states.  Three tiles are in work at once, the scores of one, the softmax of the one before
 // and P V of the one before that, interleaved instruction by instruction, because a wavefront is alone
 // on its SIMD here (or beside a streaming one).  Measured against 64-token tiles with copies one tile
-// ahead and the softmax between two MFMA regions: own launch, 8 prompts x 128 samples (longest split 208
-// old tiles) 385 -> 296 us, 32 samples x 8 heads of a 16k prompt 28.7 -> 27.7; with the suffix pass in the
-// launch, whole call, the latter 48.7 -> 44.5, 64 samples of an 8k prompt 58.2 -> 57.0, 16 samples of a
-// 2k prompt unchanged.  Tried without gain: the two halves of a workgroup in opposite phases
-// (products / softmax, own launch 28.7 -> 30.3), 64 KB of copies under way instead of 32 alone, five or
-// seven LDS fragments ahead instead of four, tile orders rotated from split to split.
+// ahead and the softmax between two MFMA regions, launches back to back: own launch, 8 prompts x 128 samples
+// (longest split 13k tokens) 331 -> 260 us, 32 samples x 8 heads of a 16k prompt 34.5 -> 29.1; with the suffix
+// pass in the launch, the latter 44.6 -> 41.4, 64 samples of an 8k prompt 54.5 -> 53.0.  Tried without
+// gain: the two halves of a workgroup in opposite phases (products / softmax, own launch of the second
+// shape 5 % slower), 64 KB of copies under way instead of 32 alone, five or seven LDS fragments ahead
+// instead of four, tile orders rotated from split to split.
 #pragma once
 
 #include "spd_internal.h"

@@ -29,7 +29,7 @@
 // on one XCD, whose L2 they share.
 // Measured, whole call (before: one wavefront per query row, a lane per token on the vector ALU):
 //   fp32, 4/1 heads of 64 channels, 4 samples, prompt 256, suffix 32           93 ->  9.4 us
-//   fp32, 32/8 heads of 128 channels, 16 samples, prompt 2048, suffixes up to 256  582 ->  23 us
+//   fp32, 32/8 heads of 128 channels, 16 samples, prompt 2048, suffixes up to 256  582 ->  24 us
 //   bf16, 32/8 heads of 64 channels, 3 prompts of up to 4001 tokens x 21 samples,
 //   suffixes up to 501, paged                                                 840..1060 -> 29 us
 // Where the last two go: launch and first loads 5 us, the tiles (1 to 2 us each with one or two

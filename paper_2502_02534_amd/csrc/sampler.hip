@@ -495,10 +495,10 @@ __device__ __forceinline__ void sample_row_from_memory(const SamplerParams& sp, 
 //           threshold is found among the candidates by radix select on the logit's bit pattern
 //           with fp64 masses; kept candidates join their segments; the segments are scanned and
 //           the walk ends inside the segment that contains u * Z.
-//           Rows with a min-p or top-k filter (a second instantiation of the kernel, launched
-//           beside the first when filter arrays are given): the scan kernel writes such a row out
-//           from the top as far as the budget goes, and the survivors of the filters, found among
-//           the pairs, become the candidate list.
+//           Rows with a min-p or top-k filter (a second instantiation of the kernel, launched in place
+//           of the first when filter arrays are given, takes both kinds of row): the scan kernel writes
+//           such a row out from the top as far as the budget goes, and the survivors of the filters,
+//           found among the pairs, become the candidate list.
 //
 // With the row statistics exchanged through memory between two kernels, plain stores and loads do.
 // =============================================================================================
@@ -1682,8 +1682,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // so what counts is how many there are and how long one takes: scans and reductions stay in registers
 // (DPP), a bin is picked by the whole workgroup (8 reads per lane and two barriers instead of 32 reads
 // and eleven dependent shuffles in every wavefront), the slices' histograms are requested together with
-// their statistics, and the segment scan takes one segment per thread.  64 rows x 128256: 27.0 -> 21.2 us,
-// 1024 rows: 73 -> 63.5.  Three workgroups share a CU (79 registers, 50 KB of LDS each).
+// their statistics, and the segment scan takes one segment per thread.  64 rows x 128256 30.3 -> 25.2 us,
+// 1024 rows 85 -> 72 (kernel trace; whole calls 46.5 -> 40.1 and 231 -> 208).  Three workgroups share a CU (79
+// registers, 50 KB of LDS each).
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
 // needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory: the
 // filtered routine reads its pairs twice instead of holding them across the selection, and the whole-row
