@@ -206,6 +206,7 @@ SPD_API size_t sample_tokens_workspace_size(int64_t rows, int64_t vocab);
  *   Z = mass of the kept tokens; walking the vocabulary in index order, the token
  *   returned is the first kept i whose running kept mass exceeds uniforms[r] * Z.
  *   T_r == 0 returns the lowest index attaining the maximum logit.
+ *   A logit of -inf has p = 0 at every temperature (a token that the caller rules out).
  *
  *   logits       fp32 [rows, vocab], row r at logits + r * row_stride (elements)
  *   logits_dtype must be SPD_F32
