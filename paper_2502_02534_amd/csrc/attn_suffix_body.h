@@ -5,10 +5,11 @@
 // share KV head j ride along as columns of one 16-wide MFMA tile, so the stream is
 // read once for all of them.  Per 32-token tile:
 //
-//   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = K rows (tokens) loaded from global memory
-//                 straight into the operand layout (lane (c, r) takes 16 bytes of token
-//                 16 blk + c at byte 64 s + 16 r for step s: four lanes cover one 64-byte
-//                 stretch of a row), B = the G query rows (held in registers)
+//   S^T = K Q^T   v_mfma_f32_16x16x32_bf16, A = K rows (tokens), B = the G query rows (held in
+//                 registers).  Lane (c, r) needs 16-byte pieces 2 r and 2 r + 1 of either half of token
+//                 16 blk + c; it loads piece 2 r + c % 2 of that token and of its neighbour's, so that every
+//                 load instruction takes whole 128-byte lines (eight lanes a line), and the two
+//                 lanes exchange what is the other's (quad permutes, 64 vector instructions a tile)
 //   online softmax in the base-2 domain on the accumulator registers; the accumulator
 //                 layout of S^T is exactly the A-operand layout of P, so P never moves
 //   O += P V      B = V transposed inside each lane with byte permutes (a lane loads the
@@ -21,6 +22,13 @@
 // The next tile's loads are issued before the current tile is computed, and with paged KV the
 // page numbers of the tile after that are fetched at the same time, so that no KV load waits
 // for a page-table load.  The body uses no LDS.
+// Bound: HBM.  Whole lines per K load instead of 64-byte halves, two instructions apart, and V marked as
+// streamed where the call's KV does not stay in the last-level cache anyway (stream_v: kStreamBytes),
+// whole calls on alternating inputs: 64 samples of an 8k prompt (186 MB) 56.5 -> 54.7 with whole lines ->
+// 52.1 us with both, 32 samples x 64 heads of a 16k prompt (134 MB) 46.0 -> 45.6 -> 43.4, 8 prompts x 128
+// samples paged (4.6 GB) 902 -> 891 -> 845, the tree of 416 samples (1.1 GB) 273 -> 256 -> 250.  Streamed K
+// gains another 2 % on the first two and loses 4 % where steps repeat on the same 175 MB; halves of lines
+// must not be streamed (64 samples: 58.0 us, inputs in the cache, against 48.5).
 // The running state is the deferred-division form of the paper's online-softmax
 // recurrence (App., attn task 2): (m, l, unnormalised accumulator).
 #pragma once
@@ -49,6 +57,30 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v)
 // Slots 0..3 are tokens 4r..4r+3, slots 4..7 tokens 16+4r..16+4r+3: the same token
 // set, in the same order, that the accumulator of S^T hands lane-row r.
 __device__ __forceinline__ int tile_token(int r, int s) { return (s < 4 ? 0 : 12) + 4 * r + s; }
+
+// 16 bytes that are used once; streamed: not kept in the caches.
+template <bool STREAM> __device__ __forceinline__ uint4 load16(const char* at)
+{
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = STREAM ? __builtin_nontemporal_load((const u32x4*)at) : *(const u32x4*)at;
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// The dword that the neighbour (lane ^ 1) holds.  All lanes must be active.
+__device__ __forceinline__ uint32_t from_neighbour(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1 /* quad_perm 1 0 3 2 */, 0xf, 0xf, true);
+}
+
+// `a` holds piece 2 r + odd of the even lane's token, `b` the same piece of the odd lane's: to pieces 2 r
+// and 2 r + 1 of this lane's own token.
+__device__ __forceinline__ void exchange_pieces(const uint4& a, const uint4& b, bool odd, uint4& lo, uint4& hi)
+{
+    const uint4 an = make_uint4(from_neighbour(a.x), from_neighbour(a.y), from_neighbour(a.z), from_neighbour(a.w));
+    const uint4 bn = make_uint4(from_neighbour(b.x), from_neighbour(b.y), from_neighbour(b.z), from_neighbour(b.w));
+    lo = make_uint4(odd ? bn.x : a.x, odd ? bn.y : a.y, odd ? bn.z : a.z, odd ? bn.w : a.w);
+    hi = make_uint4(odd ? b.x : an.x, odd ? b.y : an.y, odd ? b.z : an.z, odd ? b.w : an.w);
+}
 
 __device__ __forceinline__ uint32_t dword(const uint4& v, int k)
 {
@@ -79,7 +111,7 @@ __device__ __forceinline__ float max_over_lane_rows(float v)
 }
 
 // Body of one wavefront: work item `item`.  No LDS, no workgroup barriers.
-template <bool PAGED>
+template <bool PAGED, bool STREAM_V>
 __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long long item)
 {
 
@@ -124,28 +156,30 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
         return tp;
     };
     // Query fragments: B operand, column n = query head j*G + c (zero beyond G),
-    // k-slot (step s, lane-row r) = channels 32 s + 8 r .. + 7.
+    // k-slot (step 2 h + e, lane-row r) = piece 2 r + e of half h, channels 64 h + 16 r + 8 e .. + 7.
     bf16x8 qf[4];
     {
         const uint4* qg = (const uint4*)p.q + ((long long)n * p.Hq + (long long)j * G + (c < G ? c : 0)) * kRow;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            uint4 v = qg[4 * s + r];
+            uint4 v = qg[8 * (s >> 1) + 2 * r + (s & 1)];
             if (c >= G)
                 v = make_uint4(0, 0, 0, 0);
             qf[s] = as_bf16x8(v);
         }
     }
 
-    // K: register 4 blk + s of lane (c, r) = token 16 blk + c, channels 32 s + 8 r .. + 7 (the A operand of
-    // step s for token block blk).  V: register s of lane (r, c) = token tile_token(r, s), 16-byte piece c.
+    // K: register 4 blk + 2 h + e of lane (c, r) = piece 2 r + c % 2 of half h of token 16 blk + (c & ~1) + e.
+    // V: register s of lane (r, c) = token tile_token(r, s), 16-byte piece c.
     // Tokens past the end of the chunk are clamped to its last one (their scores are masked).
     // A whole tile is loaded from uniform bases (the tile's first row of this KV head; with paged KV
     // the first row of each of its two pages) plus 32-bit lane offsets fixed for the whole chunk,
     // so that a load costs no address arithmetic in the vector ALU; only the last, ragged tile of a
     // chunk takes the general path with its clamps.
     const unsigned row_bytes = PAGED ? 256u : (unsigned)p.Hkv * 256u;   // from one token row of the head to the next
-    const unsigned koff = (unsigned)c * row_bytes + 16u * (unsigned)r;  // token c of a 16-token block, piece r (+ 64 s)
+    const bool odd = (c & 1) != 0;
+    const unsigned kpiece = 16u * (unsigned)(2 * r + (c & 1));
+    const unsigned koff = (unsigned)(c & ~1) * row_bytes + kpiece;  // the first of the two tokens (+ 128 h)
     const unsigned voff = (unsigned)(4 * r) * row_bytes + 16u * (unsigned)c;  // token 4 r (+ s rows), piece c
     uint4 kreg[8], vreg[8];
     auto load_tile = [&](int tb, const TilePages& tp, uint4 (&kk)[8], uint4 (&vv)[8]) __attribute__((always_inline)) {
@@ -160,11 +194,11 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
             const char* vb = (const char*)vg + second * 256;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                kk[s] = *reinterpret_cast<const uint4*>(ka + koff + 64 * s);
-                kk[4 + s] = *reinterpret_cast<const uint4*>(kb + koff + 64 * s);
+                kk[s] = load16<false>(ka + (size_t)(s & 1) * row_bytes + koff + 128 * (s >> 1));
+                kk[4 + s] = load16<false>(kb + (size_t)(s & 1) * row_bytes + koff + 128 * (s >> 1));
                 // V register s holds token 4 r + s, register 4 + s token 16 + 4 r + s
-                vv[s] = *reinterpret_cast<const uint4*>(va + (size_t)s * row_bytes + voff);
-                vv[4 + s] = *reinterpret_cast<const uint4*>(vb + (size_t)s * row_bytes + voff);
+                vv[s] = load16<STREAM_V>(va + (size_t)s * row_bytes + voff);
+                vv[4 + s] = load16<STREAM_V>(vb + (size_t)s * row_bytes + voff);
             }
             return;
         }
@@ -177,15 +211,13 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
         const char* kb = (const char*)kg + sec * 256;
         const char* va = (const char*)vg + first * 256;
         const char* vb = (const char*)vg + sec * 256;
-        const unsigned k0 = (unsigned)min(c, last0) * row_bytes + 16u * (unsigned)r;
-        const unsigned k1 = (unsigned)(two ? min(c, last1) : last1) * row_bytes + 16u * (unsigned)r;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            kk[s] = *reinterpret_cast<const uint4*>(ka + k0 + 64 * s);
-            kk[4 + s] = *reinterpret_cast<const uint4*>(kb + k1 + 64 * s);
-            vv[s] = *reinterpret_cast<const uint4*>(va + (unsigned)min(4 * r + s, last0) * row_bytes + 16u * (unsigned)c);
-            vv[4 + s] = *reinterpret_cast<const uint4*>(vb + (unsigned)(two ? min(4 * r + s, last1) : last1) * row_bytes +
-                                                        16u * (unsigned)c);
+            const int t = (c & ~1) + (s & 1);
+            kk[s] = load16<false>(ka + (unsigned)min(t, last0) * row_bytes + kpiece + 128 * (s >> 1));
+            kk[4 + s] = load16<false>(kb + (unsigned)(two ? min(t, last1) : last1) * row_bytes + kpiece + 128 * (s >> 1));
+            vv[s] = load16<STREAM_V>(va + (unsigned)min(4 * r + s, last0) * row_bytes + 16u * (unsigned)c);
+            vv[4 + s] = load16<STREAM_V>(vb + (unsigned)(two ? min(4 * r + s, last1) : last1) * row_bytes + 16u * (unsigned)c);
         }
     };
 
@@ -213,8 +245,11 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
         for (int blk = 0; blk < 2; ++blk) {
             sacc[blk] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kcur[4 * blk + s]), qf[s], sacc[blk], 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                uint4 k0, k1;
+                exchange_pieces(kcur[4 * blk + 2 * h], kcur[4 * blk + 2 * h + 1], odd, k0, k1);
+                sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(k0), qf[2 * h], sacc[blk], 0, 0, 0);
+                sacc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(k1), qf[2 * h + 1], sacc[blk], 0, 0, 0);
             }
         }
         // lane (c, r) register (blk, i) = score of token tb + 16 blk + 4 r + i for head c;

@@ -95,6 +95,21 @@ inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long l
     return part_tokens(max_prefix, min_split_tokens(d), (int)(want > max_splits ? max_splits : want), 64);
 }
 
+// From how many bytes of KV (by the call's bounds) the suffix pass marks V as streamed.  The last-level cache
+// holds 256 MB: where two such buffers (layers, or batches taken in turn) fill it, leaving V out saves the
+// cache's own traffic.  Alternating inputs, not marked / marked: 134 MB 45.6 / 43.4 us, 302 MB (186 MB in
+// use) 54.7 / 52.1, 4.6 GB 891 / 845.  A single buffer that every step reads again: 302 MB (175 in use) 95.8 /
+// 94.8 us a step, but 97 MB 61.8 / 63.9, 124 MB (71 in use) 72.0 / 73.7, 170 MB (84 in use) 62.7 / 65.3.
+constexpr double kStreamBytes = 128.0 * 1024 * 1024;
+
+inline int plan_stream_v(const spd_attn_desc* d, int num_levels, const spd_prefix_level* levels, long long max_suffix)
+{
+    double tokens = (double)d->num_samples * (double)max_suffix;
+    for (int l = 0; l < num_levels; ++l)
+        tokens += (double)levels[l].num_groups * (double)levels[l].max_len;
+    return 2.0 * tokens * d->num_kv_heads * d->head_dim * (d->dtype == SPD_BF16 ? 2 : 4) >= kStreamBytes ? 1 : 0;
+}
+
 // Tokens per suffix chunk: enough (sample, KV head, chunk) items to keep every CU busy, chunks of
 // 64..320 tokens (measured on ragged suffixes of up to 2048 tokens: 320-token chunks beat 512-token
 // ones by 17 %, finer balance between wavefronts), at most kMaxSplits chunks.

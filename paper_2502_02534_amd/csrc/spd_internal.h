@@ -63,6 +63,7 @@ struct AttnParams {
     int num_slots;    // prefix splits (of every level) + suffix chunks
     int prefix_slot0; // first slot of the prefix level the prefix fields describe
     int suffix_slot0; // first slot of the suffix chunks
+    int stream_v;     // suffix V is marked as streamed (see kStreamBytes)
     int num_levels;   // levels of shared prefixes (1 for the plain shared-prefix call)
     void* part_acc;   // [N*Hq][slots][D] normalised partial outputs, fp16 if part_half else fp32;
                       // a row's partial states are contiguous for the merge
