@@ -572,8 +572,8 @@ __global__ __launch_bounds__(kWaves * 64) void attn_rows_kernel(AttnParams p, Ro
         }
         it.j = (int)(rest % (unsigned)p.Hkv);
         rest /= (unsigned)p.Hkv;
-        const int chunk = (int)(rest % (unsigned)p.num_suffix_chunks);
-        const int n = (int)(rest / (unsigned)p.num_suffix_chunks);
+        const SuffixPlace at = suffix_place(p, rest);
+        const int chunk = at.chunk, n = at.n;
         it.s0 = n;
         it.rows = p.G;
         it.t0 = chunk * p.suffix_chunk_tokens;

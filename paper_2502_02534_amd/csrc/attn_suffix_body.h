@@ -117,15 +117,14 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
 
     const int lane = threadIdx.x & 63;
     const int r = lane >> 4, c = lane & 15;
-    const int nc = p.num_suffix_chunks;
-    const long long total = (long long)p.N * p.Hkv * nc;
+    const long long total = (long long)p.N * p.Hkv * p.num_suffix_chunks;
     if (item >= total)
         return;
     // KV head fastest: the waves of a workgroup (and neighbouring workgroups) read the heads of
     // the same tokens at the same time, i.e. one contiguous stretch of the [token][head][D] cache
     const int j = (int)(item % p.Hkv);
-    const int chunk = (int)((item / p.Hkv) % nc);
-    const int n = (int)(item / ((long long)nc * p.Hkv));
+    const SuffixPlace at = suffix_place(p, (unsigned)(item / p.Hkv));
+    const int chunk = at.chunk, n = at.n;
     const int Ls = p.suffix_lens[n];
     const int t0 = chunk * p.suffix_chunk_tokens;
     const int t1 = min(Ls, t0 + p.suffix_chunk_tokens);

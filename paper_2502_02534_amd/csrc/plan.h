@@ -110,10 +110,13 @@ inline int plan_stream_v(const spd_attn_desc* d, int num_levels, const spd_prefi
     return 2.0 * tokens * d->num_kv_heads * d->head_dim * (d->dtype == SPD_BF16 ? 2 : 4) >= kStreamBytes ? 1 : 0;
 }
 
-// Tokens per suffix chunk: enough (sample, KV head, chunk) items to keep every CU busy, chunks of
-// 64..320 tokens (measured on ragged suffixes of up to 2048 tokens: 320-token chunks beat 512-token
-// ones by 17 %, finer balance between wavefronts), at most kMaxSplits chunks.
-inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
+// From how many (sample, KV head) pairs the chunks alone fill the chip's 2048 wavefront places.
+constexpr long long kManyPairs = 2048;
+
+inline bool many_suffixes(const spd_attn_desc* d) { return (long long)d->num_samples * d->num_kv_heads >= kManyPairs; }
+
+// Tokens per chunk for about a place per (pair, chunk) item: 64 to 320, neither 128 nor 256 (see below).
+inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 {
     const long long pairs = (long long)d->num_samples * d->num_kv_heads;
     const long long want_chunks = (2048 + pairs - 1) / pairs;
@@ -121,10 +124,32 @@ inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
     t = (t + 63) / 64 * 64;
     if (t < 64) t = 64;
     if (t > 320) t = 320;
-    // Chunks of 128 or 256 tokens start every wavefront of the launch at addresses that agree in
-    // many low bits (the rows of a sample are 2 KB apart), which costs 5 to 20 % of the HBM rate;
-    // three quarters of the size spreads them.
-    if (t == 128 || t == 256) t = t / 4 * 3;
+    return t == 128 || t == 256 ? t / 4 * 3 : t;
+}
+
+// Tokens per suffix chunk, at most kMaxSplits chunks.
+//   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 96 to 320 tokens (16 samples
+//   x 8 heads x 256 tokens: 64-token chunks 13.8 us, 96 13.3, 128 13.7, 192 15.9; 32 x 8 x 512: 42.5, 41.7,
+//   41.0, 41.3).  The workgroups of such a call go through one sample after another, and to the eight XCDs
+//   in turn: where a sample has 8 or 16 of them, an XCD gets the same chunks of every sample, and with ragged
+//   lengths the late ones are mostly empty.  Chunks of 128 or 256 tokens (three quarters are taken
+//   instead) and of 288 do that to the usual lengths: 8 prompts x 128 samples, up to 2048 tokens, 256 tokens 1083 us,
+//   288 1136, 224 840..920, 320 848; with the chunks dealt out evenly 256 872, 288 869, 320 853.
+//   More: the launch takes chunk after chunk of all samples (even over the XCDs, and the chunks that are
+//   mostly empty come last), in as few equal parts as chunks of up to 768 tokens allow: a chunk pays some 4 us
+//   before its first tile is there and leaves a partial state.  The batch above (same order) 320 tokens
+//   861 us, 416 840, 512 825, 640 817, 768 801, 1024 807; 416 samples x 8 heads, up to 1024 tokens, beside a
+//   tree of prefixes: 320 264, 512 257, 640 257, 768 266, 1024 279.
+inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
+{
+    long long t;
+    if (many_suffixes(d)) {
+        const long long parts = max_suffix > 768 ? (max_suffix + 767) / 768 : 1;
+        t = ((max_suffix + parts - 1) / parts + 31) / 32 * 32;
+    } else {
+        t = short_chunk(d, max_suffix);
+    }
+    if (t < 96) t = 96;
     if (max_suffix > t * kMaxSplits) t = part_tokens(max_suffix, 64, kMaxSplits, 64);
     return (int)t;
 }
@@ -133,7 +158,13 @@ inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
 // A program allocates once, for its largest batch and its longest lengths.  Split counts fall in steps as
 // rows are added, so a call's own need is not monotone; what the size functions report is the most
 // that any call of no more samples, however grouped, and no longer lengths can need.  (On the bf16 /
-// head_dim 128 path they report the call's own need.)
+// head_dim 128 path they report the call's own need.)  Suffixes are counted in the chunks of short_chunk, of
+// which plan_suffix_chunk never makes more: the longer chunks of many pairs are no help to smaller batches.
+inline int sized_suffix_chunks(const spd_attn_desc* d, long long max_suffix)
+{
+    const long long t = short_chunk(d, max_suffix), n = (max_suffix + t - 1) / t;
+    return (int)(n < kMaxSplits ? n : kMaxSplits);
+}
 
 // Most suffix chunks that `samples` samples with suffixes of up to `max_suffix` tokens are cut into: the count
 // is largest at `max_suffix`, where a chunk size stops being used, or where it reaches kMaxSplits chunks.
@@ -145,8 +176,7 @@ inline int most_suffix_chunks(const spd_attn_desc* d, long long samples, long lo
     long long most = 0;
     auto at = [&](long long len) {
         len = len < max_suffix ? len : max_suffix;
-        const int chunk = plan_suffix_chunk(&t, len);
-        const long long n = (len + chunk - 1) / chunk;
+        const long long n = sized_suffix_chunks(&t, len);
         most = n > most ? n : most;
     };
     at(max_suffix);
@@ -172,8 +202,15 @@ inline int most_prefix_splits(const spd_attn_desc* d, long long samples, long lo
     return (int)(splits < want ? splits : want);
 }
 
+// Bytes of `slots` partial states for every output row.
+inline size_t state_bytes(const spd_attn_desc* d, long long slots)
+{
+    const size_t rows = (size_t)d->num_samples * d->num_q_heads * (size_t)slots;
+    return align_up(rows * d->head_dim * sizeof(float), 256) + align_up(rows * 2 * sizeof(float), 256);
+}
+
 // Bytes to report for a call of d->num_samples samples with prefix levels of up to max_len[] tokens; `own` is
-// what the call itself needs.
+// what the call itself needs (with sized_suffix_chunks).
 inline size_t workspace_bytes(const spd_attn_desc* d, int num_levels, const long long* max_len, long long max_suffix,
                               size_t own)
 {

@@ -242,7 +242,8 @@ size_t shared_prefix_decode_attn_workspace_size(const spd_attn_desc* desc, int64
     if (make_plan(desc, max_prefix_len, max_suffix_len, &pl) != SPD_OK)
         return 0;
     const long long len = max_prefix_len;
-    return workspace_bytes(desc, 1, &len, max_suffix_len, pl.acc_bytes + pl.ml_bytes) + 256;
+    const int chunks = sized_suffix_chunks(desc, max_suffix_len);
+    return workspace_bytes(desc, 1, &len, max_suffix_len, state_bytes(desc, pl.num_prefix_splits + chunks)) + 256;
 }
 
 }  // extern "C"
@@ -300,6 +301,7 @@ int run_attention(const spd_attn_desc* desc, const void* q, int num_levels, cons
     p.num_slots = lp.num_slots;
     p.suffix_slot0 = lp.num_slots - lp.num_suffix_chunks;
     p.num_levels = num_levels;
+    p.chunks_first = many_suffixes(desc) ? 1 : 0;
     p.stream_v = plan_stream_v(desc, num_levels, levels, max_suffix_len);
     p.part_acc = workspace;
     p.part_half = desc->dtype == SPD_BF16 ? 1 : 0;
@@ -454,7 +456,9 @@ size_t shared_prefix_decode_attn_levels_workspace_size(const spd_attn_desc* desc
     long long len[SPD_MAX_PREFIX_LEVELS];
     for (int l = 0; l < num_levels; ++l)
         len[l] = levels[l].max_len;
-    return workspace_bytes(desc, num_levels, len, max_suffix_len, lp.acc_bytes + lp.ml_bytes) + 256;
+    const int chunks = sized_suffix_chunks(desc, max_suffix_len);
+    return workspace_bytes(desc, num_levels, len, max_suffix_len,
+                           state_bytes(desc, lp.num_slots - lp.num_suffix_chunks + chunks)) + 256;
 }
 
 int shared_prefix_decode_attn_levels(const spd_attn_desc* desc, const void* q, int32_t num_levels,
