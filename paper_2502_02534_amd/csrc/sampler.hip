@@ -1150,9 +1150,10 @@ struct FinishLds {
     RowLds row;                           // hist / scratch / seg_mass of the row routines
     unsigned long long cand[kCandCap];    // candidates: logit bits | index << 32
     PickLds pick;
-    double seg_sum[kWaves], seg_before[kWaves];  // the wavefronts' shares of the segment scan
-    int seg_hit[kWaves], seg_last[kWaves];
+    double slice_mass[kMaxSlices];               // kept mass of every slice
+    double above[kMaxSlices / kWaves][kWaves];   // what each wavefront found kept for certain among its pairs
     unsigned cand_total;
+    unsigned members;                            // candidates in the bin that a select has come down to
     uint32_t kmin[kWaves], kmax[kWaves];
 };
 
@@ -1351,6 +1352,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             L.kmin[wave] = kmin;
             L.kmax[wave] = kmax;
         }
+        if (tid == 0)
+            L.members = 0u;
         double* H = L.row.hist;
         for (int b = tid; b < kBins; b += kBlock)
             H[b] = 0.0;
@@ -1364,7 +1367,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         uint32_t prefix = 0u;
         double abv = above0;
         bad = !(above0 < need);
-        for (int bit = 11 * ((nbits - 1) / 11); bit >= 0 && !bad; bit -= 11) {
+        const int top_bit = 11 * ((nbits - 1) / 11);
+        for (int bit = top_bit; bit >= 0 && !bad; bit -= 11) {
             for (int i = tid; i < C; i += kBlock) {
                 const float xc = __uint_as_float((unsigned)L.cand[i]);
                 const uint32_t rel = kmax - order_key(xc);
@@ -1374,75 +1378,130 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             __syncthreads();
             const BinPick pk = block_pick(H, abv, need, false, L.pick);
             // the threshold must fall among the candidates
-            if (bit == 11 * ((nbits - 1) / 11) && !(above0 + pk.total >= need))
+            if (bit == top_bit && !(above0 + pk.total >= need))
                 bad = true;
             prefix = (prefix << 11) | (uint32_t)pk.bin;
             abv = pk.above;
             reached = pk.above + pk.in_bin;
-            __syncthreads();
-            if (bit > 0) {
-                for (int b = tid; b < kBins; b += kBlock)
-                    H[b] = 0.0;
-                __syncthreads();
+            if (bit == 0 || bad)
+                break;
+            // The bin usually holds one to three different candidates: up to 64 are told apart directly (every
+            // wavefront does it for itself: lane i sums what is not below its own), more take another level.
+            unsigned long long* const member = reinterpret_cast<unsigned long long*>(H);
+            for (int i = tid; i < C; i += kBlock) {
+                const float xc = __uint_as_float((unsigned)L.cand[i]);
+                const uint32_t rel = kmax - order_key(xc);
+                if (rel >> bit == prefix) {
+                    const unsigned at = atomicAdd(&L.members, 1u);
+                    if (at < 64u)
+                        member[at] = ((unsigned long long)rel << 32) | __float_as_uint(by_count ? 1.f : prob(xc, rs));
+                }
             }
+            __syncthreads();
+            const int members = (int)L.members;
+            if (members <= 64) {
+                const unsigned long long own = member[max(min(lane, members - 1), 0)];
+                const uint32_t rel = (uint32_t)(own >> 32);
+                double upper = abv;
+                for (int j = 0; j < members; ++j) {
+                    const uint32_t rel_j = (uint32_t)__builtin_amdgcn_readlane((int)rel, j);
+                    const float p_j = __int_as_float(__builtin_amdgcn_readlane((int)(uint32_t)own, j));
+                    upper += rel_j <= rel ? (double)p_j : 0.0;
+                }
+                // the most probable that reaches `need`; where rounding leaves all of them short, the least
+                const uint32_t first = wave_min_u32(upper >= need ? rel : 0xffffffffu);
+                prefix = first != 0xffffffffu ? first : wave_max_u32(rel);
+                const int at = __ffsll((long long)__ballot(rel == prefix)) - 1;
+                reached = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(upper), at),
+                                           __builtin_amdgcn_readlane(__double2loint(upper), at));
+                __syncthreads();  // (callers and later calls use H again)
+                break;
+            }
+            __syncthreads();
+            if (tid == 0)
+                L.members = 0u;
+            for (int b = tid; b < kBins; b += kBlock)
+                H[b] = 0.0;
+            __syncthreads();
         }
         return kmax - prefix;
     };
-    // pairs written out by the covered slices: four consecutive ones per thread and slice, four slices
-    // at a time, all requested before any is used (unconditional loads; what lies past a slice's count
-    // is masked).  A wavefront of the scan kernel lists its pairs segment by segment, so a thread's
-    // four pairs mostly belong to one 256-element segment: their kept mass is added up in the thread
-    // and goes to the segment's sum with one LDS addition per run of equal segments (one addition
-    // per pair would have most of a wavefront's lanes meet at one LDS address).
-    static_assert(kEmitCap == 4 * kBlock, "four pairs per thread and slice");
-    for (int s0 = 0; s0 < (FILTERED ? 0 : slices); s0 += 4) {
-        unsigned long long ev[4][4];
-        int cnt[4];
+    // pairs written out by the covered slices.  A slice belongs to one wavefront (or to 2, 4, 8 where there are
+    // no more than 4, 2, 1 slices), which needs no more of it here than its mass kept for certain, one sum in
+    // registers; where in the slice that mass lies is asked of the one slice that the walk ends in.  Two
+    // pairs per lane and load, four loads requested ahead (what lies past a slice's count is masked).
+    // Candidates are gathered in the wavefront's share of the histogram's place (free until the select) and
+    // join the list in one piece: one reservation per step and its round trip took 3 of the 6 us of this
+    // phase (64 rows, some 500 candidates each).
+    const int wps = slices > 4 ? 1 : slices > 2 ? 2 : slices == 2 ? 4 : 8;  // wavefronts per slice
+    constexpr int kStage = kBins / kWaves;
+    static_assert(sizeof(L.row.hist[0]) == sizeof(L.cand[0]) && kStage >= 64, "a wavefront's step fits its share");
+    unsigned long long* const stage = reinterpret_cast<unsigned long long*>(L.row.hist) + wave * kStage;
+    int have = 0;  // (uniform)
+    auto flush = [&]() __attribute__((always_inline)) {
+        unsigned base = 0u;
+        if (lane == 0)
+            base = atomicAdd(&L.cand_total, (unsigned)have);
+        base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+        for (int i = lane; i < have; i += 64)
+            if (base + (unsigned)i < (unsigned)kCandCap)
+                L.cand[base + (unsigned)i] = stage[i];
+        have = 0;
+    };
+    for (int round = 0; round < (FILTERED ? 0 : (slices + kWaves - 1) / kWaves); ++round) {
+        const int s = round * kWaves + wave / wps, part = wave & (wps - 1);
+        double above_mass = 0.0;
+        if (s < slices && ((covered >> s) & 1u)) {
+            const int cnt = min(of_slice(st.count, s), kEmitCap);
+            const ulonglong2* e = reinterpret_cast<const ulonglong2*>(W.emit + (size_t)s * kEmitCap) + 64 * part + lane;
+            const int step = 64 * wps, steps = (cnt + 2 * step - 1) / (2 * step);  // (never past the slice's list)
+            constexpr int kBatch = 4;
+            ulonglong2 now[kBatch], next[kBatch];
+            auto request = [&](int i0, ulonglong2 (&v)[kBatch]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int s = min(s0 + u, slices - 1);
-            cnt[u] = (s0 + u < slices && ((covered >> s) & 1u)) ? min(of_slice(st.count, s), kEmitCap) : 0;
-            const ulonglong2* e = reinterpret_cast<const ulonglong2*>(W.emit + (size_t)s * kEmitCap) + 2 * tid;
-            const ulonglong2 a = e[0], b = e[1];
-            ev[u][0] = a.x;
-            ev[u][1] = a.y;
-            ev[u][2] = b.x;
-            ev[u][3] = b.y;
-        }
+                for (int u = 0; u < kBatch; ++u)
+                    v[u] = e[(size_t)min(i0 + u, kEmitCap / (2 * step) - 1) * step];
+            };
+            request(0, now);
+            for (int i0 = 0; i0 < steps; i0 += kBatch) {
+                request(i0 + kBatch, next);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int s = min(s0 + u, slices - 1);
-            const int mine = min(max(cnt[u] - 4 * tid, 0), 4);  // how many of the four places hold a pair
-            if (__builtin_amdgcn_ballot_w64(mine > 0) == 0ull)
-                continue;  // nothing in this wavefront's 256 places
-            double run = 0.0;   // kept mass of the present run of pairs of one segment
-            int run_seg = -1;
+                for (int u = 0; u < kBatch; ++u) {
+                    const int first = 2 * ((i0 + u) * step + 64 * part + lane);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool live = k < mine;
-                const float xq = __uint_as_float((unsigned)ev[u][k]);
-                const int idx = (int)(ev[u][k] >> 32);
-                const float t = xq * rc.c16;
-                const bool above = live && t >= t_above;
-                const bool candq = live && !above && t >= t_cand;
-                const float pq = live ? prob(xq, rs) : 0.f;
-                f_part += pq;
-                const int seg = s * kSegPerSlice + (int)((unsigned)(idx - s * slice_elems) / (unsigned)kSeg);
-                if (above && seg != run_seg && run_seg >= 0) {
-                    atomicAdd(&seg_mass[run_seg], run);
-                    run = 0.0;
+                    for (int k = 0; k < 2; ++k) {
+                        const unsigned long long pair = k ? now[u].y : now[u].x;
+                        const bool live = first + k < cnt;
+                        const float xq = __uint_as_float((unsigned)pair);
+                        const float t = xq * rc.c16;
+                        const bool above = live && t >= t_above, candq = live && !above && t >= t_cand;
+                        const float pq = live ? prob(xq, rs) : 0.f;
+                        above_mass += (double)(above ? pq : 0.f);
+                        f_part += above ? 0.f : pq;
+                        const unsigned long long mask = __builtin_amdgcn_ballot_w64(candq);
+                        if (mask != 0ull) {
+                            if (have + __popcll(mask) > kStage)
+                                flush();
+                            if (candq)
+                                stage[__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((unsigned)mask, (unsigned)have))] = pair;
+                            have += __popcll(mask);
+                        }
+                    }
                 }
-                if (above) {
-                    run_seg = seg;
-                    run += (double)pq;
-                }
-                append_masked(__builtin_amdgcn_ballot_w64(candq), candq, ev[u][k]);
+#pragma unroll
+                for (int u = 0; u < kBatch; ++u)
+                    now[u] = next[u];
+                s_part += (double)f_part;
+                f_part = 0.f;
             }
-            if (run_seg >= 0)
-                atomicAdd(&seg_mass[run_seg], run);
         }
-        s_part += (double)f_part;
-        f_part = 0.f;
+        if (have > 0)
+            flush();
+        s_part += above_mass;
+        above_mass = wave_scan_f64(above_mass);
+        if (lane == 63)
+            L.above[round][wave] = above_mass;
     }
     // slices that are not covered: a second look at their logits
     for (int s = 0; s < (FILTERED ? 0 : slices); ++s) {
@@ -1564,10 +1623,27 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     __syncthreads();
     const unsigned cand_total = L.cand_total;
     const int C = (int)min(cand_total, (unsigned)kCandCap);
+    // mass kept for certain, slice by slice: the segments that hold some already (what the scan kernel summed
+    // above its window, or all of a slice that was read again) and the pairs
+    for (int s = wave; s < slices; s += kWaves) {
+        double v = wave_scan_f64(seg_mass[s * kSegPerSlice + lane]);
+        if (!FILTERED)
+            for (int k = 0; k < wps; ++k)
+                v += L.above[s / kWaves][s % kWaves * wps + k];
+        if (lane == 63)
+            L.slice_mass[s] = v;
+    }
+    s_part = wave_scan_f64(s_part);
+    if (lane == 63)
+        L.row.scratch[wave] = s_part;
+    __syncthreads();
     double above_total = 0.0;
-    for (int sidx = tid; sidx < nseg; sidx += kBlock)
-        above_total += seg_mass[sidx];
-    block_sum2_f64(above_total, s_part, L.row.scratch);
+    for (int s = 0; s < slices; ++s)
+        above_total += L.slice_mass[s];
+    s_part = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w)
+        s_part += L.row.scratch[w];
     const double need = (double)top_p * s_part;  // s_part: the row mass S (of what the filters left)
 
     uint32_t key_tau = key_floor;
@@ -1588,51 +1664,81 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         if (order_key(xc) >= key_tau) {
             const int idx = (int)(L.cand[i] >> 32);
             const int s = idx / slice_elems;
-            atomicAdd(&seg_mass[s * kSegPerSlice + (idx - s * slice_elems) / kSeg], (double)prob(xc, rs));
+            const double pc = (double)prob(xc, rs);
+            atomicAdd(&seg_mass[s * kSegPerSlice + (idx - s * slice_elems) / kSeg], pc);
+            atomicAdd(&L.slice_mass[s], pc);
         }
     }
     __syncthreads();
     const double target = (double)sp.uniforms[r] * Z;
 
-    // The segment that takes the running mass past the target: thread t owns `per` consecutive segments.
+    // The slice that takes the running mass past the target (rounding may leave the target at the total: then
+    // the last one with mass, and its last kept token), and the mass before it.
+    int hit = -1;
+    double before = 0.0;
+    bool take_last = false;
     {
-        const int per = nseg > kBlock ? 2 : 1;
-        const int g0 = per * tid;
-        const double a = g0 < nseg ? seg_mass[g0] : 0.0, b = per == 2 && g0 + 1 < nseg ? seg_mass[g0 + 1] : 0.0;
-        const double inc = wave_scan_f64(a + b);
-        if (lane == 63)
-            L.seg_sum[wave] = inc;
-        lds_barrier();
-        double before = inc - (a + b);
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w)
-            before += w < wave ? L.seg_sum[w] : 0.0;
-        const bool in_a = before + a > target, in_b = per == 2 && before + a + b > target;
-        const unsigned long long hit = __ballot(in_a || in_b), some = __ballot(a > 0.0 || b > 0.0);
-        if (lane == (hit ? __ffsll((long long)hit) - 1 : 0)) {
-            L.seg_hit[wave] = hit ? (in_a ? g0 : g0 + 1) : -1;
-            L.seg_before[wave] = in_a ? before : before + a;
+        int last = -1;
+        double run = 0.0, before_last = 0.0;
+        for (int s = 0; s < slices; ++s) {
+            const double m = L.slice_mass[s];
+            if (hit < 0 && run + m > target) {
+                hit = s;
+                before = run;
+            }
+            if (m > 0.0) {
+                last = s;
+                before_last = run;
+            }
+            run += m;
         }
-        if (lane == (some ? 63 - __clzll((long long)some) : 0))
-            L.seg_last[wave] = some ? (b > 0.0 ? g0 + 1 : g0) : -1;
-        lds_barrier();
-    }
-    if (wave == 0) {
-        int seg = -1, from = -1;
-        double before = 0.0;
-#pragma unroll
-        for (int w = kWaves - 1; w >= 0; --w)
-            from = L.seg_hit[w] >= 0 ? w : from;
-        bool take_last = false;
-        if (from >= 0) {
-            seg = L.seg_hit[from];
-            before = L.seg_before[from];
-        } else {
-            // rounding: the target is not below the total; take the last segment with mass
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w)
-                seg = L.seg_last[w] >= 0 ? L.seg_last[w] : seg;
+        if (hit < 0) {
+            hit = last;
+            before = before_last;
             take_last = true;
+        }
+        hit = __builtin_amdgcn_readfirstlane(hit);
+    }
+    // Its segments, in vocabulary order: the pairs kept for certain join them.  A wavefront of the scan kernel
+    // lists its pairs segment by segment, so a thread's four pairs mostly belong to one segment and go to its
+    // sum with one LDS addition per run of equal segments.
+    static_assert(kEmitCap == 4 * kBlock, "four pairs per thread");
+    if (!FILTERED && hit >= 0 && ((covered >> hit) & 1u)) {
+        const int mine = min(max(min(of_slice(st.count, hit), kEmitCap) - 4 * tid, 0), 4);  // of the four places
+        if (mine > 0) {
+            const ulonglong2* e = reinterpret_cast<const ulonglong2*>(W.emit + (size_t)hit * kEmitCap) + 2 * tid;
+            const ulonglong2 lo2 = e[0], hi2 = e[1];
+            const unsigned long long ev[4] = {lo2.x, lo2.y, hi2.x, hi2.y};
+            double run = 0.0;
+            int run_seg = -1;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float xq = __uint_as_float((unsigned)ev[k]);
+                const int seg = (int)((unsigned)((int)(ev[k] >> 32) - hit * slice_elems) / (unsigned)kSeg);
+                if (k < mine && xq * rc.c16 >= t_above) {
+                    if (seg != run_seg && run_seg >= 0) {
+                        atomicAdd(&seg_mass[hit * kSegPerSlice + run_seg], run);
+                        run = 0.0;
+                    }
+                    run_seg = seg;
+                    run += (double)prob(xq, rs);
+                }
+            }
+            if (run_seg >= 0)
+                atomicAdd(&seg_mass[hit * kSegPerSlice + run_seg], run);
+        }
+    }
+    lds_barrier();
+    if (wave == 0) {
+        int seg = -1;
+        if (hit >= 0) {
+            const double m = seg_mass[hit * kSegPerSlice + lane], inc = before + wave_scan_f64(m);
+            const unsigned long long reach = __ballot(inc > target), some = __ballot(m > 0.0);
+            take_last = take_last || reach == 0ull;
+            const int at = take_last ? (some ? 63 - __clzll((long long)some) : -1) : __ffsll((long long)reach) - 1;
+            seg = at < 0 ? -1 : hit * kSegPerSlice + at;
+            before = at < 0 ? 0.0 : __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(inc - m), at),
+                                                     __builtin_amdgcn_readlane(__double2loint(inc - m), at));
         }
         int token = -1;
         if (seg >= 0) {
@@ -1682,15 +1788,18 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // so what counts is how many there are and how long one takes: scans and reductions stay in registers
 // (DPP), a bin is picked by the whole workgroup (8 reads per lane and two barriers instead of 32 reads
 // and eleven dependent shuffles in every wavefront), the slices' histograms are requested together with
-// their statistics, and the segment scan takes one segment per thread.  64 rows x 128256 30.3 -> 25.2 us,
-// 1024 rows 85 -> 72 (kernel trace; whole calls 46.5 -> 40.1 and 231 -> 208).  Three workgroups share a CU (79
-// registers, 50 KB of LDS each).
+// their statistics.  Phases of a row of 64 x 128256 (clock stamps, us; before: four pairs of every slice per
+// thread, kept mass to its segment, a list reservation per step, every select of two levels): statistics and
+// histograms 3.4, pick 1.8, pairs 7.6 -> 4.7, sums 1.9 -> 2.2, select 3.7 -> 3.0, the slice and segment of the
+// token 1.0 -> 2.0, walk 1.4.  Whole calls: 64 rows 37.8 -> 36.0 us, 1 row 27.7 -> 25.0, 39 x 167649 39.0 -> 37.3,
+// 300 x 32000 32.9 -> 31.8, 1024 x 128256 204.6 -> 202.3.  Three workgroups share a CU (79 registers, 50 KB
+// of LDS each).
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
 // needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory: the
 // filtered routine reads its pairs twice instead of holding them across the selection, and the whole-row
 // routine is inlined (a call would have the arguments copied to memory, which every phase then reads).
 // (192 rows of 50257 unaligned logits, a third of them each with top-k, min-p and no filter, some greedy:
-// whole call 45.8 us, 48.5 with the spills; 249 in the whole-row routine.)
+// whole call 43.8 us, 3 more with the spills; 249 in the whole-row routine.)
 template <bool ANY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
 {
