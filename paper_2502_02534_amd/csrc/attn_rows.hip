@@ -31,7 +31,7 @@
 //   fp32, 4/1 heads of 64 channels, 4 samples, prompt 256, suffix 32           93 ->  9.4 us
 //   fp32, 32/8 heads of 128 channels, 16 samples, prompt 2048, suffixes up to 256  582 ->  24 us
 //   bf16, 32/8 heads of 64 channels, 3 prompts of up to 4001 tokens x 21 samples,
-//   suffixes up to 501, paged                                                 840..1060 -> 29 us
+//   suffixes up to 501, paged                                                 840..1060 -> 25 us
 // Where the last two go: launch and first loads 5 us, the tiles (1 to 2 us each with one or two
 // wavefronts per SIMD: dependent products, softmax, a load round trip) 15, the merge 3 (the first is bound
 // by the host).
@@ -75,11 +75,62 @@ struct RowsItem {
     unsigned g_inv;     // min(floor(2^32 / G), 2^32 - 1)
 };
 
-// States of the wavefronts of a workgroup where several share an item.
-template <int DT, int QB> struct SharedState {
-    float o[kWaves][16 * QB][DT];
-    float2 ml[kWaves][16 * QB];
+// How K and V reach the products.
+//   RING (bf16, 64 channels): tiles go from global memory straight into LDS (global_load_lds_dwordx4), into two K
+//     and two V slots of the wavefront's own, two tiles ahead of their use, so that a wavefront nearly alone on
+//     its SIMD does not wait for a round trip in every tile; no barrier is needed.  3 prompts of up to 4001
+//     tokens x 21 samples 28.5 -> 24.9 us, 64 samples of an 8k prompt 38.3 -> 35.7, 4 x 100 samples, suffixes up to
+//     1000 tokens, 131.6 -> 111.0.
+//   otherwise: registers, reloaded in place.  (With a ring fp32 loses: 128 channels 22.3 -> 28.7 us, 128 KB of LDS
+//     leave one wavefront per SIMD; 64 channels 23.7 -> 25.6, its products already hide the loads.)
+constexpr int kDepth = 2;
+constexpr int kRingRow = 128;              // bytes of a token row
+constexpr int kRingTile = 32 * kRingRow;   // of a K or V tile
+constexpr int kRingCopies = kRingTile / 1024;  // copy instructions per tile, eight rows each
+// 16-byte piece p of token row `tok` lies at piece p ^ swz(tok): two rows share the 256-byte bank window, and
+// the sixteen rows of a K operand get sixteen different places in it.
+__device__ __forceinline__ int swz(int tok) { return (tok >> 1) & 7; }
+
+// LDS of a wavefront: its ring, then, where several wavefronts share an item, its state.
+template <int DT, int QB, bool RING> union WaveLds {
+    uint4 ring[RING ? 2 * kDepth * kRingTile / 16 : 1];
+    struct {
+        float o[16 * QB][DT];
+        float2 ml[16 * QB];
+    } state;
 };
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// LDS reads that the copies under way do not hold up: the compiler would wait for every copy before any
+// read of its own.  Complete when they return.
+// K of a tile: two places of a row (channels 0 .. 31, 32 .. 63), in the first and in the second 16 tokens.
+__device__ __forceinline__ void ring_read_k(unsigned a0, unsigned a1, u32x4 (&v)[4])
+{
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %4 offset:%6\n\t"
+                 "ds_read_b128 %3, %5 offset:%6\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+                 : "v"(a0), "v"(a1), "n"(16 * kRingRow)
+                 : "memory");
+}
+// V of a tile: eight bytes of rows 4 i and 16 + 4 i from a[i] on.
+__device__ __forceinline__ void ring_read_v(const unsigned (&a)[4], u32x2 (&v)[8])
+{
+    constexpr int S = 4 * kRingRow, B = 16 * kRingRow;
+    asm volatile("ds_read_b64 %0, %8\n\tds_read_b64 %1, %9 offset:%12\n\t"
+                 "ds_read_b64 %2, %10 offset:%13\n\tds_read_b64 %3, %11 offset:%14\n\t"
+                 "ds_read_b64 %4, %8 offset:%15\n\tds_read_b64 %5, %9 offset:%16\n\t"
+                 "ds_read_b64 %6, %10 offset:%17\n\tds_read_b64 %7, %11 offset:%18\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(S), "n"(2 * S), "n"(3 * S), "n"(B), "n"(B + S),
+                   "n"(B + 2 * S), "n"(B + 3 * S)
+                 : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_copies()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
 // Output row (sample, query head) of query row rr of an item.
 __device__ __forceinline__ long long item_out_row(const AttnParams& p, const RowsItem& it, int rr)
@@ -115,8 +166,8 @@ __device__ __forceinline__ void store_part(const AttnParams& p, long long at, co
 
 // T: float or uint16_t (bf16 bits).  DT: head_dim rounded up to 64, 128 or 256; channels from p.D on are
 // zero.  QB: 16-row blocks per wavefront.
-template <typename T, int DT, int QB, bool PAGED>
-__device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& it, SharedState<DT, QB>& lds)
+template <typename T, int DT, int QB, bool PAGED, bool RING, typename Lds>
+__device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& it, Lds* lds)
 {
     constexpr bool F32 = std::is_same<T, float>::value;
     constexpr int kTile = F32 ? 16 : 32;          // tokens per tile
@@ -133,7 +184,10 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
     const int lane = threadIdx.x & 63;
     const int r = lane >> 4, c = lane & 15;
     const int D = p.D;
-    const bool padded = D != DT;
+    const bool padded = !RING && D != DT;
+    // Token of a 16-token block that row m of the scores stands for.  (From LDS: lane-rows 0 and 1 read V rows
+    // of different parity, which lie in different halves of the bank window.)
+    auto token_of = [](int m) { return RING ? 4 * (m & 3) + (m >> 2) : m; };
 
     // ---- query rows: contraction slot r of step s holds, fp32, channels 16 s + 4 r + e (e = one product
     // each), bf16, channels 32 s + 8 r .. + 7
@@ -157,16 +211,18 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
     // ---- tiles ----
     const unsigned row_elems = PAGED ? (unsigned)D : (unsigned)(p.Hkv * D);  // from one token of the head to the next
     const int last_page = PAGED ? (it.t1 - 1) >> 4 : 0;
+    typedef const __attribute__((address_space(4))) int* const_int_ptr;
+    const const_int_ptr pages = (const_int_ptr)it.pages;  // (uniform places: scalar loads)
     struct Base {
         long long a, b;  // element offset of the tile's first row in each of its 16-token blocks
     };
     auto tile_base = [&](int tb) -> Base {
         Base x = {0, 0};
         if (PAGED) {
-            const long long pa = it.pages[min(tb >> 4, last_page)];
+            const long long pa = pages[min(tb >> 4, last_page)];
             x.a = (pa * p.Hkv + it.j) * 16 * D;
             if (kBlk == 2) {
-                const long long pb = it.pages[min((tb >> 4) + 1, last_page)];
+                const long long pb = pages[min((tb >> 4) + 1, last_page)];
                 x.b = (pb * p.Hkv + it.j) * 16 * D;
             }
         } else {
@@ -209,6 +265,54 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
                 const uint2 x = *reinterpret_cast<const uint2*>(src);
                 dst[0] = x.x;
                 dst[1] = x.y;
+            }
+        }
+    };
+    // ---- ring: copies, and reads into the same registers ----
+    static_assert(!RING || (!F32 && DT == 64), "the ring's layout is that of 128-byte rows and 32-token tiles");
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint4* const ring = lds[wave].ring;
+    const unsigned ring_at = (unsigned)(size_t)(__attribute__((address_space(3))) void*)ring;
+    // Copy i brings rows 8 i .. 8 i + 7, lane L the place L % 8 of row 8 i + L / 8.  K in slots 0 .. kDepth - 1, V
+    // behind them.
+    auto copy_tile = [&](bool is_v, int slot, int tb, const Base& base) __attribute__((always_inline)) {
+        const T* const src = (const T*)(is_v ? it.v : it.k);
+        uint4* const dst = ring + ((is_v ? kDepth : 0) + slot) * (kRingTile / 16);
+        const int last = it.t1 - 1 - tb;  // the tile's last valid token
+#pragma unroll
+        for (int i = 0; i < kRingCopies; ++i) {
+            const int row = 8 * i + (lane >> 3), valid = min(row, last);  // tokens past the end are clamped to the last
+            const T* at = src + (valid < 16 ? base.a : base.b) + (unsigned)(valid & 15) * row_elems + ((lane & 7) ^ swz(row)) * 8;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)at,
+                                             (__attribute__((address_space(3))) void*)(dst + i * 64), 16, 0, 0);
+        }
+    };
+    const unsigned k_at = ring_at + (unsigned)(token_of(c) * kRingRow), k_xor = (unsigned)((r ^ swz(token_of(c))) << 4);
+    // (V row 4 i + r of a block: its swizzle is that of row r with the bits of 2 i flipped)
+    const unsigned v_at = ring_at + (unsigned)(kDepth * kRingTile + r * kRingRow + 8 * (c & 1));
+    const unsigned v_xor = (unsigned)(((c >> 1) ^ swz(r)) << 4);
+    auto read_k = [&](int slot) __attribute__((always_inline)) {
+        if constexpr (RING) {
+            const unsigned at = k_at + (unsigned)(slot * kRingTile);
+            u32x4 v[4];
+            ring_read_k(at + k_xor, at + (k_xor ^ 64u), v);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                kk[i >> 1][i & 1] = make_uint4(v[i][0], v[i][1], v[i][2], v[i][3]);
+        }
+    };
+    auto read_v = [&](int slot) __attribute__((always_inline)) {
+        if constexpr (RING) {
+            unsigned a[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                a[i] = v_at + (unsigned)(slot * kRingTile) + (v_xor ^ (32u * (unsigned)i));
+            u32x2 v[8];
+            ring_read_v(a, v);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                vv[t][0] = v[t][0];
+                vv[t][1] = v[t][1];
             }
         }
     };
@@ -255,18 +359,40 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
     // K is reloaded in place as soon as the scores have read it, V after P V: one set of registers
     // leaves room for two or more wavefronts per SIMD up to 128 channels, whose phases cover each other's
     // loads (for one with more).
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tfirst = it.t0 + it.part * kTile, tstep = it.share * kTile;
     const int tlast = (it.t1 - 1) & ~(kTile - 1);  // the range's last tile
+    constexpr int kAhead = RING ? kDepth : 1;  // tiles between a load and its use
     if (tfirst < it.t1) {
         const Base base = tile_base(tfirst);
-        load_k(tfirst, base);
-        load_v(tfirst, base);
+        if constexpr (RING) {
+            copy_tile(false, 0, tfirst, base);
+            copy_tile(true, 0, tfirst, base);
+            if (tfirst + tstep < it.t1) {
+                const Base second = tile_base(tfirst + tstep);
+                copy_tile(false, 1, tfirst + tstep, second);
+                copy_tile(true, 1, tfirst + tstep, second);
+            }
+        } else {
+            load_k(tfirst, base);
+            load_v(tfirst, base);
+        }
     }
-    Base next_base = tile_base(min(tfirst + tstep, tlast));
+    static_assert(kDepth == 2, "two tiles are copied ahead of the loop, and the waits count on it");
+    Base next_base = tile_base(min(tfirst + kAhead * tstep, tlast));
+    int slot = 0;
     for (int tb = tfirst; tb < it.t1; tb += tstep) {
-        const bool more = tb + tstep < it.t1;
-        const Base base = next_base;  // of the next tile
+        const bool more = tb + kAhead * tstep < it.t1;
+        const Base base = next_base;  // of the tile kAhead tiles on
+        if constexpr (RING) {
+            // copies after K of this tile: V of it, K and V of the next (the last tile: its V)
+            if (tb + tstep < it.t1)
+                wait_copies<3 * kRingCopies>();
+            else
+                wait_copies<kRingCopies>();
+            read_k(slot);
+            if (more)
+                copy_tile(false, slot, tb + kAhead * tstep, base);
+        }
         if (padded) {  // channels past the head dimension
 #pragma unroll
             for (int blk = 0; blk < kBlk; ++blk)
@@ -299,8 +425,9 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
                     }
                 }
         if (more) {
-            load_k(tb + tstep, base);
-            next_base = tile_base(min(tb + 2 * tstep, tlast));
+            if constexpr (!RING)
+                load_k(tb + tstep, base);
+            next_base = tile_base(min(tb + (kAhead + 1) * tstep, tlast));
         }
         // ---- online softmax, base 2.  The reference maximum only has to bound the exponents: after the first
         // tile it is looked at again only when a lane's probabilities add up to more than kRaise
@@ -317,7 +444,7 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
             if (tb + kTile > it.t1) {  // only the last tile of a range can be ragged
 #pragma unroll
                 for (int t = 0; t < kVTok; ++t)
-                    if (tb + 16 * (t >> 2) + 4 * r + (t & 3) >= it.t1)
+                    if (tb + 16 * (t >> 2) + token_of(4 * r + (t & 3)) >= it.t1)
                         sc[t] = -INFINITY;
             }
             auto probabilities = [&](float ref) __attribute__((always_inline)) -> float {
@@ -359,6 +486,19 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
             }
             l_run[b] += psum;
         }
+        if constexpr (RING) {
+            // copies after V of this tile: K and V of the next, K of the one after
+            if (more)
+                wait_copies<3 * kRingCopies>();
+            else if (tb + tstep < it.t1)
+                wait_copies<2 * kRingCopies>();
+            else
+                wait_copies<0>();
+            read_v(slot);
+            if (more)
+                copy_tile(true, slot, tb + kAhead * tstep, base);
+            slot ^= 1;
+        }
         // ---- O += P V: column c of product k is channel kVPiece (16 (k / kVPiece) + c) + k % kVPiece
         if constexpr (F32) {
             // Past the end of the range the last token's values were loaded: zeros in their place, since
@@ -366,7 +506,7 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
             if (tb + kTile > it.t1) {
 #pragma unroll
                 for (int t = 0; t < kVTok; ++t)
-                    if (tb + 4 * r + t >= it.t1)
+                    if (tb + token_of(4 * r + t) >= it.t1)
 #pragma unroll
                         for (int k = 0; k < kCols; ++k)
                             vv[t][k] = 0u;
@@ -410,7 +550,7 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
                         o[b][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(term[e][b]), as_bf16x8(f), o[b][k], 0, 0, 0);
             }
         }
-        if (more)
+        if (!RING && more)
             load_v(tb + tstep, base);
     }
 
@@ -424,7 +564,7 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
         const int rr = it.row0 + 16 * b + c;
         if (r == 0) {
             if (shared)
-                lds.ml[wave][16 * b + c] = make_float2(m_run[b], l);
+                lds[wave].state.ml[16 * b + c] = make_float2(m_run[b], l);
             else if (rr < it.rows)
                 p.part_ml[part_index(p, out_row(rr), it.slot)] = make_float2(m_run[b], l);
         }
@@ -443,7 +583,7 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
                 if (shared) {
 #pragma unroll
                     for (int e = 0; e < kVPiece; e += 4)
-                        *reinterpret_cast<float4*>(&lds.o[wave][row][ch + e]) = make_float4(y[e], y[e + 1], y[e + 2], y[e + 3]);
+                        *reinterpret_cast<float4*>(&lds[wave].state.o[row][ch + e]) = make_float4(y[e], y[e + 1], y[e + 2], y[e + 3]);
                 } else if (it.row0 + row < it.rows && !(padded && ch >= D)) {
 #pragma unroll
                     for (int e = 0; e < kVPiece; ++e)
@@ -457,8 +597,8 @@ __device__ __forceinline__ void rows_body(const AttnParams& p, const RowsItem& i
 
 // The states that the wavefronts of an item left in LDS, put together by those wavefronts (after a
 // workgroup barrier) and stored.
-template <typename T, int DT, int QB>
-__device__ __forceinline__ void combine_shared(const AttnParams& p, const RowsItem& it, const SharedState<DT, QB>& lds)
+template <typename T, int DT, int QB, typename Lds>
+__device__ __forceinline__ void combine_shared(const AttnParams& p, const RowsItem& it, const Lds* lds)
 {
     constexpr int kThreadsPerRow = DT / 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w0 = wave - it.part;
@@ -467,13 +607,13 @@ __device__ __forceinline__ void combine_shared(const AttnParams& p, const RowsIt
         const int row = x / kThreadsPerRow, ch = x % kThreadsPerRow * 4;
         float m = -INFINITY, l = 0.f;
         for (int w = 0; w < it.share; ++w)
-            m = fmaxf(m, lds.ml[w0 + w][row].x);
+            m = fmaxf(m, lds[w0 + w].state.ml[row].x);
         const float ref = m == -INFINITY ? 0.f : m;
         float y[4] = {0.f, 0.f, 0.f, 0.f};
         for (int w = 0; w < it.share; ++w) {
-            const float2 ml = lds.ml[w0 + w][row];
+            const float2 ml = lds[w0 + w].state.ml[row];
             const float f = __builtin_amdgcn_exp2f(ml.x - ref);
-            const float4 a = *reinterpret_cast<const float4*>(&lds.o[w0 + w][row][ch]);
+            const float4 a = *reinterpret_cast<const float4*>(&lds[w0 + w].state.o[row][ch]);
             l = __builtin_fmaf(ml.y, f, l);
             y[0] = __builtin_fmaf(a.x, f, y[0]);
             y[1] = __builtin_fmaf(a.y, f, y[1]);
@@ -505,12 +645,12 @@ __device__ __forceinline__ void mark_empty(const AttnParams& p, const RowsItem& 
 
 // One item (or, with nothing to do, `live` = false): every wavefront of the workgroup calls this with
 // the same `share`.
-template <typename T, int DT, int QB, bool PAGED>
-__device__ __forceinline__ void run_item(const AttnParams& p, const RowsItem& it, bool live, SharedState<DT, QB>& lds)
+template <typename T, int DT, int QB, bool PAGED, bool RING, typename Lds>
+__device__ __forceinline__ void run_item(const AttnParams& p, const RowsItem& it, bool live, Lds* lds)
 {
     const bool some = live && it.t0 < it.t1;
     if (some)
-        rows_body<T, DT, QB, PAGED>(p, it, lds);
+        rows_body<T, DT, QB, PAGED, RING>(p, it, lds);
     else if (live)
         mark_empty(p, it, 16 * QB);
     if (it.share > 1) {
@@ -529,13 +669,10 @@ struct RowsLaunch {
 // Prefix and suffix items in one launch: workgroups below prefix_blocks take prefix items (the row
 // blocks of one split, prompt and KV head on one XCD), the others suffix items (row block fastest, then
 // KV head, chunk, sample, so that neighbours read one contiguous stretch).
-template <typename T, int DT, int QB, bool PAGED>
+template <typename T, int DT, int QB, bool PAGED, bool RING>
 __global__ __launch_bounds__(kWaves * 64) void attn_rows_kernel(AttnParams p, RowsLaunch a)
 {
-    __shared__ union {
-        SharedState<DT, QB> prefix;
-        SharedState<DT, 1> suffix;
-    } lds;
+    __shared__ WaveLds<DT, QB, RING> lds[kWaves];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     RowsItem it;
     it.g_inv = a.g_inv;
@@ -557,7 +694,7 @@ __global__ __launch_bounds__(kWaves * 64) void attn_rows_kernel(AttnParams p, Ro
         it.v = p.v_prefix;
         it.start = PAGED ? 0 : p.prefix_indptr[b];
         it.pages = PAGED ? p.prefix_pages + p.prefix_indptr[b] : nullptr;
-        run_item<T, DT, QB, PAGED>(p, it, it.row0 < it.rows, lds.prefix);
+        run_item<T, DT, QB, PAGED, RING>(p, it, it.row0 < it.rows, lds);
     } else {
         it.share = a.suffix_share;
         it.part = wave & (it.share - 1);
@@ -583,28 +720,31 @@ __global__ __launch_bounds__(kWaves * 64) void attn_rows_kernel(AttnParams p, Ro
         it.v = p.v_suffix;
         it.start = (long long)n * p.max_suffix_len;
         it.pages = PAGED ? p.suffix_pages + p.suffix_page_indptr[n] : nullptr;
-        run_item<T, DT, 1, PAGED>(p, it, live, lds.suffix);
+        run_item<T, DT, 1, PAGED, RING>(p, it, live, lds);
     }
 }
 
-template <typename T, int DT, int QB>
+template <typename T, int DT, int QB, bool RING>
 void launch_rows(const AttnParams& p, unsigned grid, const RowsLaunch& a, hipStream_t s)
 {
     if (p.page_size)
-        hipLaunchKernelGGL((attn_rows_kernel<T, DT, QB, true>), dim3(grid), dim3(kWaves * 64), 0, s, p, a);
+        hipLaunchKernelGGL((attn_rows_kernel<T, DT, QB, true, RING>), dim3(grid), dim3(kWaves * 64), 0, s, p, a);
     else
-        hipLaunchKernelGGL((attn_rows_kernel<T, DT, QB, false>), dim3(grid), dim3(kWaves * 64), 0, s, p, a);
+        hipLaunchKernelGGL((attn_rows_kernel<T, DT, QB, false, RING>), dim3(grid), dim3(kWaves * 64), 0, s, p, a);
 }
 
 template <typename T>
 void launch_rows_dim(const AttnParams& p, int qb, unsigned grid, const RowsLaunch& a, hipStream_t s)
 {
-    if (p.D <= 64)
-        qb == 1 ? launch_rows<T, 64, 1>(p, grid, a, s) : launch_rows<T, 64, 2>(p, grid, a, s);
+    constexpr bool kRing = std::is_same<T, uint16_t>::value;
+    if (kRing && p.D == 64)
+        qb == 1 ? launch_rows<T, 64, 1, kRing>(p, grid, a, s) : launch_rows<T, 64, 2, kRing>(p, grid, a, s);
+    else if (p.D <= 64)
+        qb == 1 ? launch_rows<T, 64, 1, false>(p, grid, a, s) : launch_rows<T, 64, 2, false>(p, grid, a, s);
     else if (p.D <= 128)  // (one row block: rows_per_block)
-        launch_rows<T, 128, 1>(p, grid, a, s);
+        launch_rows<T, 128, 1, false>(p, grid, a, s);
     else
-        launch_rows<T, 256, 1>(p, grid, a, s);
+        launch_rows<T, 256, 1, false>(p, grid, a, s);
 }
 
 // Wavefronts per item: as many as fit the chip's registers at once, no more than the item has tiles.  Two per

@@ -71,6 +71,16 @@ inline int rows_per_block(int head_dim, long long rows) { return rows > 16 && he
 // Fewest tokens per split in the general kernel: a tile or more for each of four wavefronts.
 inline int min_split_tokens(const spd_attn_desc* d) { return d->dtype == SPD_BF16 ? 128 : 64; }
 
+// Workgroups that the splits of a prefix level should give in the general kernel: one per CU, or, from LDS (bf16, 64
+// channels) with several prompts, whose lengths differ, half as many again: the splits past the end of the
+// shorter ones are empty.  One per CU / 1.5 / 2: 3 prompts x 21 samples 24.7 / 23.5 / 27.2 us, 2 x 128 87.9 / 78.4 /
+// 78.4, 4 x 20 on one KV head 19.2 / 16.9 / 16.0; one prompt of 8k tokens 35.5 / 37.8 / 39.7, fp32 3 x 100
+// 74.8 / 78.0 / 76.4.
+inline int split_workgroups(const spd_attn_desc* d, int groups)
+{
+    return d->dtype == SPD_BF16 && d->head_dim == 64 && groups > 1 ? 384 : 256;
+}
+
 // Tokens per split of a prefix level with `groups` groups of at most `spp` samples and lengths up to
 // `max_prefix`, at most `max_splits` splits.
 inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long long max_prefix, int max_splits)
@@ -91,7 +101,7 @@ inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long l
     const long long rows = (long long)spp * (d->num_q_heads / d->num_kv_heads);
     const int block = rows_per_block(d->head_dim, rows);
     const long long base = (long long)groups * d->num_kv_heads * ((rows + block - 1) / block);
-    const long long want = (256 + base - 1) / base;
+    const long long want = (split_workgroups(d, groups) + base - 1) / base;
     return part_tokens(max_prefix, min_split_tokens(d), (int)(want > max_splits ? max_splits : want), 64);
 }
 
@@ -128,9 +138,10 @@ inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 }
 
 // Tokens per suffix chunk, at most kMaxSplits chunks.
-//   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 96 to 320 tokens (16 samples
-//   x 8 heads x 256 tokens: 64-token chunks 13.8 us, 96 13.3, 128 13.7, 192 15.9; 32 x 8 x 512: 42.5, 41.7,
-//   41.0, 41.3).  The workgroups of such a call go through one sample after another, and to the eight XCDs
+//   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 64 to 320 tokens, on the
+//   tiled path 96 at least (16 samples x 8 heads x 256 tokens: 64-token chunks 13.8 us, 96 13.3, 128 13.7, 192
+//   15.9; 32 x 8 x 512: 42.5, 41.7, 41.0, 41.3; 90 x 2 x 700 loses, 22.3 / 23.0; in the general kernel fp32 20 x
+//   8 x 100 loses, 24.7 / 26.5, bf16 9 x 4 x 400 with 64 channels too, 10.8 / 11.7).  The workgroups of such a call go through one sample after another, and to the eight XCDs
 //   in turn: where a sample has 8 or 16 of them, an XCD gets the same chunks of every sample, and with ragged
 //   lengths the late ones are mostly empty.  Chunks of 128 or 256 tokens (three quarters are taken
 //   instead) and of 288 do that to the usual lengths: 8 prompts x 128 samples, up to 2048 tokens, 256 tokens 1083 us,
@@ -146,10 +157,11 @@ inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
     if (many_suffixes(d)) {
         const long long parts = max_suffix > 768 ? (max_suffix + 767) / 768 : 1;
         t = ((max_suffix + parts - 1) / parts + 31) / 32 * 32;
+        if (t < 64) t = 64;
     } else {
         t = short_chunk(d, max_suffix);
     }
-    if (t < 96) t = 96;
+    if (t < 96 && d->dtype == SPD_BF16 && d->head_dim == 128) t = 96;
     if (max_suffix > t * kMaxSplits) t = part_tokens(max_suffix, 64, kMaxSplits, 64);
     return (int)t;
 }
@@ -189,13 +201,19 @@ inline int most_suffix_chunks(const spd_attn_desc* d, long long samples, long lo
 }
 
 // Most splits of a prefix level of up to `max_len` tokens that `samples` samples share.  One group takes the
-// fewest row blocks, so it is cut into the most splits.
+// fewest row blocks, so it is cut into the most splits (two of half the samples into more where they are planned
+// for more workgroups).
 inline int most_prefix_splits(const spd_attn_desc* d, long long samples, long long max_len, int max_splits)
 {
     const long long rows = samples * (d->num_q_heads / d->num_kv_heads);
     const int block = rows_per_block(d->head_dim, kPrefixBlockRows);  // the larger of the two blocks
     const long long base = (long long)d->num_kv_heads * ((rows + block - 1) / block);
-    long long want = (256 + base - 1) / base;
+    const long long base2 = base > 2 * d->num_kv_heads ? base : 2 * d->num_kv_heads;  // of two groups
+    long long want = (split_workgroups(d, 1) + base - 1) / base;
+    if (samples > 1) {
+        const long long two = (split_workgroups(d, 2) + base2 - 1) / base2;
+        want = two > want ? two : want;
+    }
     want = want > max_splits ? max_splits : want;
     const int least = min_split_tokens(d);
     const long long splits = (max_len + least - 1) / least;
