@@ -751,9 +751,12 @@ void launch_rows_dim(const AttnParams& p, int qb, unsigned grid, const RowsLaunc
 // SIMD up to 128 channels, one with more (256 registers and up to 208 accumulation registers each): shared out
 // for two, a second round of workgroups started behind the first (256 channels, 32/8 heads, 3 prompts of
 // 700 tokens x 40 samples: fp32 91 -> 74 us, bf16 53 -> 40; of 58 shapes three fp32 ones lost 9 %).
-int share_of(long long items, int tiles, int head_dim)
+// Suffix items find half of the prefix items' places taken (fp32, 16 samples of a 2k prompt, suffixes of up to 256:
+// four wavefronts a 64-token chunk 23.3 us, two 21.5; 20 samples x 8 heads x 100 tokens keep four, 25.5 / 26.4;
+// 32 samples x 8 heads with 64 channels lose a little, 23.9 / 24.2).
+int share_of(long long items, int tiles, int head_dim, long long prefix_waves = 0)
 {
-    const long long places = head_dim > 128 ? 1024 : 2048;
+    const long long places = head_dim > 128 ? 1024 : 2048 - prefix_waves / 2;
     int share = 1;
     while (2 * share <= kWaves && 2 * share <= tiles && items * share * 2 <= places)
         share *= 2;
@@ -776,7 +779,8 @@ hipError_t launch_attn_rows(const AttnParams& p, bool prefix, bool suffix, hipSt
     const long long suffix_items = suffix ? (long long)((p.G + 15) / 16) * p.Hkv * p.num_suffix_chunks * p.N : 0;
     RowsLaunch a;
     a.prefix_share = share_of(rowblocks * units, p.prefix_split_tokens / tile, p.D);
-    a.suffix_share = share_of(suffix_items, p.suffix_chunk_tokens / tile, p.D);
+    const long long prefix_waves = rowblocks * units * a.prefix_share;
+    a.suffix_share = share_of(suffix_items, p.suffix_chunk_tokens / tile, p.D, prefix_waves < 2048 ? prefix_waves : 2048);
     const int per_p = kWaves / a.prefix_share, per_s = kWaves / a.suffix_share;
     const long long prefix_blocks = units * ((rowblocks + per_p - 1) / per_p);
     const long long blocks = prefix_blocks + (suffix_items + per_s - 1) / per_s;
