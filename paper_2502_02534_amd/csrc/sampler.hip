@@ -1255,8 +1255,11 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         // Estimate of the nucleus cut from the slices' histograms.
         row_histogram(true);
         const BinPick est = block_pick(L.row.hist, 0.0, (double)top_p, true, L.pick);
-        // the estimate is good to about 1e-5 of the total; be generous
-        const double need_est = (double)top_p * est.total, tol = 1e-3 * est.total;
+        // The estimate is good to 3e-5 of the total (a unit is a 32768th of an element at least; a miss is
+        // noticed below).  A wider margin takes neighbouring bins in too often: in flat rows, whose bins hold a
+        // thousandth of the mass each, three bins did not fit the list (1e-3: 643 rows x 127843 at sigma 1.9,
+        // top-p 0.98 752 us, most of them in the whole-row routine).
+        const double need_est = (double)top_p * est.total, tol = 1e-4 * est.total;
         lo = hi = __builtin_amdgcn_readfirstlane(est.bin);
         if (need_est - est.above <= tol && lo > 0)
             --lo;
@@ -1525,7 +1528,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         // kernel wrote such a row's slices out from the top, so everything that survives is among the
         // pairs, provided every slice's window reaches as far down as the filters do; otherwise the
         // row goes to the whole-row routine.  Survivors become the candidate list. ----
-        bool ok = slices <= 8;  // (the pairs of a row are requested together, four per thread and slice)
+        bool ok = true;
         // top-k: the k-th largest logit lies in row bins b1 .. b2, by the element-count bounds of the
         // histogram units (an element adds 32768 to 34219 units): the running units reach 32768 k no
         // later than the k-th element's bin and 34219 k no earlier
@@ -1550,23 +1553,25 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         if (!ok) {
             return false;
         }
-        // All pairs of the row, four per thread and slice, requested together; `f(live, pair)` for each.  With
-        // top-k they are read twice (the second time from L2): held across the selection between the two they
-        // would take 64 registers that it does not have.
+        // All pairs of the row, four per thread and slice, those of eight slices requested together; `f(live, pair)` for
+        // each.  With top-k they are read twice (the second time from L2): held across the selection between the
+        // two they would take 64 registers that it does not have.
         auto for_pairs = [&](auto f) __attribute__((always_inline)) {
-            unsigned long long ev[8][4];
+            for (int s0 = 0; s0 < slices; s0 += 8) {
+                unsigned long long ev[8][4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+                for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    ev[u][k] = W.emit[(size_t)min(u, slices - 1) * kEmitCap + tid + k * kBlock];
+                    for (int k = 0; k < 4; ++k)
+                        ev[u][k] = W.emit[(size_t)min(s0 + u, slices - 1) * kEmitCap + tid + k * kBlock];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int s = min(u, slices - 1);
-                const int cnt = (u < slices && of_slice(shift, s) < kBins) ? min(of_slice(st.count, s), kEmitCap) : 0;
+                for (int u = 0; u < 8; ++u) {
+                    const int s = min(s0 + u, slices - 1);
+                    const int cnt = (s0 + u < slices && of_slice(shift, s) < kBins) ? min(of_slice(st.count, s), kEmitCap) : 0;
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    f(tid + k * kBlock < cnt, ev[u][k]);
+                    for (int k = 0; k < 4; ++k)
+                        f(tid + k * kBlock < cnt, ev[u][k]);
+                }
             }
         };
         uint32_t key_k = 0u;
