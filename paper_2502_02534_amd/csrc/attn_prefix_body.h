@@ -142,6 +142,19 @@ __host__ __device__ inline PrefixLevelParams level_of(const AttnParams& p, int r
 struct PrefixItem {
     int split, rowtile, z;
 };
+// The split that a unit of index u (u % num_splits counted around) takes: where num_splits shares a factor with
+// the eight XCDs, u % num_splits alone would give an XCD the same splits of every prompt, and those past the
+// end of the shorter prompts are empty (fp32, 3 prompts of 3003 .. 10880 tokens x 79 samples, four splits: 345 us
+// against 269 with two).
+__device__ __forceinline__ int turned_split(int u, int num_splits)
+{
+    if (num_splits & 1)
+        return u % num_splits;
+    // (constant over the splits of a unit's prompt in either case, so that every split is taken once)
+    const int turn = num_splits == 2 || num_splits == 4 ? u >> 3 : u / num_splits;
+    return (int)((unsigned)(u + turn) % (unsigned)num_splits);
+}
+
 __device__ __forceinline__ PrefixItem prefix_item(int local, int num_splits, int rowtiles, int zs)
 {
     PrefixItem it;
@@ -150,10 +163,10 @@ __device__ __forceinline__ PrefixItem prefix_item(int local, int num_splits, int
         const int slot = local >> 3;
         const int u = (local & 7) + 8 * (slot / rowtiles);
         it.rowtile = slot % rowtiles;
-        it.split = u % num_splits;
+        it.split = turned_split(u, num_splits);
         it.z = u / num_splits;
     } else {
-        it.split = local % num_splits;
+        it.split = turned_split(local, num_splits);
         const int rest = local / num_splits;
         it.rowtile = rest % rowtiles;
         it.z = rest / rowtiles;
