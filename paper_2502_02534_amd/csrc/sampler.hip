@@ -631,11 +631,19 @@ __device__ __forceinline__ SliceRange slice_range(int slice, int slice_elems, in
 // the row-level kernel some 20 registers.)  Every slice holds at least one
 // whole float4 (the host sends rows shorter than that to the whole-row kernel, and slices are never
 // shorter than about 2000).
-#define SPD_LOAD_SLICE(xv, xa, g, tid)                                                  \
+// STREAM: not kept in the caches (the pass of launch_sampler over logits that do not fit them).
+template <bool STREAM> __device__ __forceinline__ float4 load4(const float* at)
+{
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const f32x4 v = STREAM ? __builtin_nontemporal_load((const f32x4*)at) : *(const f32x4*)at;
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+
+#define SPD_LOAD_SLICE(STREAM, xv, xa, g, tid)                                          \
     _Pragma("unroll") for (int j = 0; j < 8; ++j)                                       \
     {                                                                                   \
         const int i_ = min((g).e0 + j * kIter + (tid) * 4, (g).v4end - 4);              \
-        const float4 v_ = *reinterpret_cast<const float4*>((xa) + (j == 0 ? max(i_, (g).v0) : i_)); \
+        const float4 v_ = load4<STREAM>((xa) + (j == 0 ? max(i_, (g).v0) : i_));        \
         (xv)[4 * j] = v_.x;                                                             \
         (xv)[4 * j + 1] = v_.y;                                                         \
         (xv)[4 * j + 2] = v_.z;                                                         \
@@ -748,6 +756,7 @@ __device__ __forceinline__ float fold_segments(const float (&s_seg)[8])
     return a1;  // lanes 8 s .. 8 s + 7 hold segment j = 4 (lane/32) + 2 (lane/16 % 2) + lane/8 % 2 = lane >> 3
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sampler_scan_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
 {
     __shared__ ScanLds L;
@@ -767,7 +776,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const bool cut = !greedy && (top_p < 1.f || filtered);
 
     float xv[32];
-    SPD_LOAD_SLICE(xv, x, g, tid)
+    SPD_LOAD_SLICE(STREAM, xv, x, g, tid)
     for (int b = tid; b < kPubBins + 64; b += kBlock)
         L.hist[b] = 0u;
     if (tid == 0) {
@@ -1512,7 +1521,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             continue;
         const SliceRange g = slice_range(s, slice_elems, V, lead);
         float xv[32];
-        SPD_LOAD_SLICE(xv, x, g, tid)
+        SPD_LOAD_SLICE(false, xv, x, g, tid)
         SPD_MASK_SLICE(xv, x, g, tid)
 #pragma unroll
         for (int q = 0; q < 32; ++q) {
@@ -1871,7 +1880,10 @@ hipError_t launch_sampler(const SamplerParams& p, void* ws, hipStream_t s)
     }
     int slice_elems = (int)((span + slices - 1) / slices);
     slice_elems = (slice_elems + 3) / 4 * 4;
-    hipLaunchKernelGGL(sampler_scan_kernel, dim3((unsigned)(p.rows * slices)), dim3(kBlock), 0, s, p, (char*)ws, slices,
+    // Logits that the last-level cache (256 MB) cannot hold are read past it: 1024 x 128256 (525 MB) 207 -> 202 us;
+    // 64 x 128256 (33 MB, where the LM head has just left them) would lose, 38.9 / 39.9.
+    const bool stream = 4.0 * (double)p.rows * (double)p.vocab >= 256e6;
+    hipLaunchKernelGGL(stream ? sampler_scan_kernel<true> : sampler_scan_kernel<false>, dim3((unsigned)(p.rows * slices)), dim3(kBlock), 0, s, p, (char*)ws, slices,
                        slice_elems);
     if (filters)
         hipLaunchKernelGGL(sampler_finish_kernel<true>, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p, (char*)ws,
