@@ -17,13 +17,14 @@ namespace plan {
 struct Plan {
     int prefix_split_tokens, num_prefix_splits;
     int suffix_chunk_tokens, num_suffix_chunks;
+    int chunks_first;  // order of the suffix items: chunk after chunk of all samples, else sample after sample
     size_t acc_bytes, ml_bytes;
 };
 
 // Plan of a multi-level call: split size and count per level, slot offsets, suffix chunks.
 struct LevelPlan {
     int split_tokens[SPD_MAX_PREFIX_LEVELS], num_splits[SPD_MAX_PREFIX_LEVELS], slot0[SPD_MAX_PREFIX_LEVELS];
-    int suffix_chunk_tokens, num_suffix_chunks, num_slots;
+    int suffix_chunk_tokens, num_suffix_chunks, chunks_first, num_slots;
     size_t acc_bytes, ml_bytes;
 };
 
@@ -81,16 +82,47 @@ inline int split_workgroups(const spd_attn_desc* d, int groups)
     return d->dtype == SPD_BF16 && d->head_dim == 64 && groups > 1 ? 384 : 256;
 }
 
+inline bool tiled(const spd_attn_desc* d) { return d->dtype == SPD_BF16 && d->head_dim == 128; }
+
+// Workgroups of 128 rows, independent of the splits, that a prefix level of the tiled path has.
+inline long long prefix_units(const spd_attn_desc* d, int groups, int spp)
+{
+    const long long rows = (long long)spp * (d->num_q_heads / d->num_kv_heads);
+    return (long long)groups * d->num_kv_heads * ((rows + kPrefixBlockRows - 1) / kPrefixBlockRows);
+}
+
+// Workgroups that the prefix pass of a plain call should have on the tiled path: one per CU, or half or a quarter as
+// many where the suffix stream (by the call's bounds, 5.5 TB/s) lasts longer than those take (0.9 us a
+// 32-token tile beside the stream, 5 us before the first): every workgroup less is a place for four wavefronts that
+// stream, and a partial state less per row.  256 / 128 / 64 workgroups (with the chunks that go with them): 32
+// samples of an 8k prompt, suffixes up to 1024 tokens 33.6 / 27.3 / 34.0 us, 64 samples 51.6 / 47.1 / 60.4, of a 3k
+// prompt 41.5 / 39.5 / 35.8, 96 samples 68.3 / 58.6; 64 samples with suffixes up to 2048 77.1 / 73.8 / 71.5; 48 of a 16k
+// prompt 48.6 / 58.6.  What it costs where the suffixes are far shorter than the bound: 64 samples of an 8k
+// prompt at up to 100 tokens of 1024 24.9 / 31.4; at 300 to 400 it gains 6 % of a decode step.
+inline int prefix_workgroups(const spd_attn_desc* d, int groups, int spp, long long max_prefix, long long max_suffix)
+{
+    if (!tiled(d) || max_prefix == 0)
+        return 256;
+    const double stream = (double)d->num_samples * (double)max_suffix * d->num_kv_heads * 512.0 / 5.5e6;  // us
+    const long long base = prefix_units(d, groups, spp);
+    for (int workgroups = 64; workgroups < 256; workgroups *= 2) {
+        const long long splits = (workgroups + base - 1) / base;
+        const double tiles = (double)((max_prefix + splits - 1) / splits) / 32.0;
+        if (5.0 + 0.9 * tiles <= 0.85 * stream)
+            return workgroups;
+    }
+    return 256;
+}
+
 // Tokens per split of a prefix level with `groups` groups of at most `spp` samples and lengths up to
 // `max_prefix`, at most `max_splits` splits.
-inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long long max_prefix, int max_splits)
+inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long long max_prefix, int max_splits,
+                             int workgroups = 256)
 {
-    if (d->dtype == SPD_BF16 && d->head_dim == 128) {
-        // tiled path: one workgroup per (group, KV head, row tile, split); enough splits to
-        // occupy every CU once, in multiples of the 64-token tile
-        const long long rows = (long long)spp * (d->num_q_heads / d->num_kv_heads);
-        const long long base = (long long)groups * d->num_kv_heads * ((rows + kPrefixBlockRows - 1) / kPrefixBlockRows);
-        long long want = (256 + base - 1) / base;
+    if (tiled(d)) {
+        // one workgroup per (group, KV head, row tile, split), in multiples of the 64-token tile
+        const long long base = prefix_units(d, groups, spp);
+        long long want = (workgroups + base - 1) / base;
         if (want > max_splits) want = max_splits;
         long long t = (max_prefix + want - 1) / want;
         t = (t + 63) / 64 * 64;
@@ -138,30 +170,38 @@ inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 }
 
 // Tokens per suffix chunk, at most kMaxSplits chunks.
-//   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 64 to 320 tokens, on the
-//   tiled path 96 at least (16 samples x 8 heads x 256 tokens: 64-token chunks 13.8 us, 96 13.3, 128 13.7, 192
-//   15.9; 32 x 8 x 512: 42.5, 41.7, 41.0, 41.3; 90 x 2 x 700 loses, 22.3 / 23.0; in the general kernel fp32 20 x
-//   8 x 100 loses, 24.7 / 26.5, bf16 9 x 4 x 400 with 64 channels too, 10.8 / 11.7).  The workgroups of such a call go through one sample after another, and to the eight XCDs
-//   in turn: where a sample has 8 or 16 of them, an XCD gets the same chunks of every sample, and with ragged
-//   lengths the late ones are mostly empty.  Chunks of 128 or 256 tokens (three quarters are taken
-//   instead) and of 288 do that to the usual lengths: 8 prompts x 128 samples, up to 2048 tokens, 256 tokens 1083 us,
-//   288 1136, 224 840..920, 320 848; with the chunks dealt out evenly 256 872, 288 869, 320 853.
+//   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 64 to 320 tokens.  (On the tiled
+//   path 129 to 256 tokens of 128 pairs or more are cut into chunks of 96 instead of 64: 16 samples x 8 heads, up to
+//   193 / 256 / 256 ragged tokens 4.1 / 3.9 / 2.5 % faster, 24 samples 6.1 / 2.3 / 3.4; up to 350 tokens +7.9, -5.4 %, 8
+//   samples 0 to -3, 727 tokens of 24 pairs -9.)  The workgroups of such a call go through one sample after another,
+//   and to the eight XCDs in turn: where a sample has 8 or 16 of them, an XCD gets the same chunks of every sample,
+//   and with ragged lengths the late ones are mostly empty.  Chunks of 128 or 256 tokens (three quarters are
+//   taken instead) and of 288 do that to the usual lengths: 8 prompts x 128 samples, up to 2048 tokens, 256
+//   tokens 1083 us, 288 1136, 224 840..920, 320 848; with the chunks dealt out evenly 256 872, 288 869, 320 853.
 //   More: the launch takes chunk after chunk of all samples (even over the XCDs, and the chunks that are
 //   mostly empty come last), in as few equal parts as chunks of up to 768 tokens allow: a chunk pays some 4 us
 //   before its first tile is there and leaves a partial state.  The batch above (same order) 320 tokens
 //   861 us, 416 840, 512 825, 640 817, 768 801, 1024 807; 416 samples x 8 heads, up to 1024 tokens, beside a
 //   tree of prefixes: 320 264, 512 257, 640 257, 768 266, 1024 279.
-inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
+//   Fewer pairs beside a prefix pass of half the workgroups or less: as many items as wavefronts have places then,
+//   in the same order (64 samples x 8 heads of up to 1024 tokens: 192-token chunks 50.3 us, 256 49.4, 384 47.1,
+//   512 50.3; 32 samples 192 27.5, 256 30.4, 384 28.3; 96 samples 192 59.7, 384 58.6, 512 58.2).
+inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix, bool few_prefix = false)
 {
     long long t;
-    if (many_suffixes(d)) {
+    const long long pairs = (long long)d->num_samples * d->num_kv_heads;
+    if (few_prefix && !many_suffixes(d)) {
+        const long long parts = (1536 + pairs - 1) / pairs;
+        t = ((max_suffix + parts - 1) / parts + 63) / 64 * 64;
+        t = t > 768 ? 768 : t < 96 || t == 128 ? 96 : t == 256 ? 192 : t;
+    } else if (many_suffixes(d)) {
         const long long parts = max_suffix > 768 ? (max_suffix + 767) / 768 : 1;
         t = ((max_suffix + parts - 1) / parts + 31) / 32 * 32;
         if (t < 64) t = 64;
     } else {
         t = short_chunk(d, max_suffix);
+        if (t == 64 && tiled(d) && pairs >= 128 && max_suffix > 128 && max_suffix <= 256) t = 96;
     }
-    if (t < 96 && d->dtype == SPD_BF16 && d->head_dim == 128) t = 96;
     if (max_suffix > t * kMaxSplits) t = part_tokens(max_suffix, 64, kMaxSplits, 64);
     return (int)t;
 }
@@ -176,6 +216,14 @@ inline int sized_suffix_chunks(const spd_attn_desc* d, long long max_suffix)
 {
     const long long t = short_chunk(d, max_suffix), n = (max_suffix + t - 1) / t;
     return (int)(n < kMaxSplits ? n : kMaxSplits);
+}
+
+// Prefix splits that a workspace is sized for: those of a workgroup per CU.
+inline int sized_prefix_splits(const spd_attn_desc* d, long long max_prefix)
+{
+    const int spp = d->max_samples_per_prompt > 0 ? d->max_samples_per_prompt : d->num_samples;
+    const int t = plan_prefix_split(d, d->num_prompts, spp, max_prefix, kMaxSplits);
+    return (int)((max_prefix + t - 1) / t);
 }
 
 // Most suffix chunks that `samples` samples with suffixes of up to `max_suffix` tokens are cut into: the count
@@ -267,9 +315,14 @@ inline int make_plan(const spd_attn_desc* d, long long max_prefix, long long max
     if (max_prefix < 0 || max_suffix < 0 || max_prefix > kMaxLen || max_suffix > kMaxLen)
         return SPD_EINVAL;
     const int spp = d->max_samples_per_prompt > 0 ? d->max_samples_per_prompt : d->num_samples;
-    pl->prefix_split_tokens = plan_prefix_split(d, d->num_prompts, spp, max_prefix, kMaxSplits);
+    const int workgroups = prefix_workgroups(d, d->num_prompts, spp, max_prefix, max_suffix);
+    pl->prefix_split_tokens = plan_prefix_split(d, d->num_prompts, spp, max_prefix, kMaxSplits, workgroups);
     pl->num_prefix_splits = (int)((max_prefix + pl->prefix_split_tokens - 1) / pl->prefix_split_tokens);
-    pl->suffix_chunk_tokens = plan_suffix_chunk(d, max_suffix);
+    // (a short prefix, two tiles a split, has no fewer splits to take: short suffixes then keep their chunks, in the
+    // other order)
+    const bool few = workgroups < 256 && (max_suffix > 384 || pl->prefix_split_tokens > 128);
+    pl->suffix_chunk_tokens = plan_suffix_chunk(d, max_suffix, few);
+    pl->chunks_first = workgroups < 256 || many_suffixes(d) ? 1 : 0;
     pl->num_suffix_chunks = (int)((max_suffix + pl->suffix_chunk_tokens - 1) / pl->suffix_chunk_tokens);
     const size_t rows = (size_t)d->num_samples * d->num_q_heads;
     const size_t slots = (size_t)pl->num_prefix_splits + pl->num_suffix_chunks;
@@ -292,6 +345,7 @@ inline int make_level_plan(const spd_attn_desc* d, int num_levels, const spd_pre
         return rc;
     lp->suffix_chunk_tokens = pl.suffix_chunk_tokens;
     lp->num_suffix_chunks = pl.num_suffix_chunks;
+    lp->chunks_first = pl.chunks_first;
     const int max_splits = kMaxSplits / num_levels;  // the merge takes kMaxSplits prefix splits in all
     int slots = 0;
     for (int l = 0; l < num_levels; ++l) {

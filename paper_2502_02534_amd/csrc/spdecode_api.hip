@@ -243,7 +243,7 @@ size_t shared_prefix_decode_attn_workspace_size(const spd_attn_desc* desc, int64
         return 0;
     const long long len = max_prefix_len;
     const int chunks = sized_suffix_chunks(desc, max_suffix_len);
-    return workspace_bytes(desc, 1, &len, max_suffix_len, state_bytes(desc, pl.num_prefix_splits + chunks)) + 256;
+    return workspace_bytes(desc, 1, &len, max_suffix_len, state_bytes(desc, sized_prefix_splits(desc, max_prefix_len) + chunks)) + 256;
 }
 
 }  // extern "C"
@@ -301,7 +301,7 @@ int run_attention(const spd_attn_desc* desc, const void* q, int num_levels, cons
     p.num_slots = lp.num_slots;
     p.suffix_slot0 = lp.num_slots - lp.num_suffix_chunks;
     p.num_levels = num_levels;
-    p.chunks_first = many_suffixes(desc) ? 1 : 0;
+    p.chunks_first = lp.chunks_first;
     p.stream_v = plan_stream_v(desc, num_levels, levels, max_suffix_len);
     p.part_acc = workspace;
     p.part_half = desc->dtype == SPD_BF16 ? 1 : 0;
@@ -440,6 +440,7 @@ int shared_prefix_decode_attn(const spd_attn_desc* desc, const void* q, const vo
     lp.slot0[0] = 0;
     lp.suffix_chunk_tokens = pl.suffix_chunk_tokens;
     lp.num_suffix_chunks = pl.num_suffix_chunks;
+    lp.chunks_first = pl.chunks_first;
     lp.num_slots = pl.num_prefix_splits + pl.num_suffix_chunks;
     lp.acc_bytes = pl.acc_bytes;
     lp.ml_bytes = pl.ml_bytes;

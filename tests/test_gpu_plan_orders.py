@@ -1,0 +1,53 @@
+"""Shapes either side of the lines of the launch plan: a prefix pass of 256, 128 and 64 workgroups (set by the suffix
+bound), suffix chunks sample by sample and chunk by chunk, V marked as streamed or not, chunk sizes of the
+few-workgroup plan, splits turned from prompt to prompt (2, 3, 4, 6, 8 splits of ragged prompts)."""
+import numpy as np
+import pytest
+
+from gpu_checks import check_attention
+from paper_2502_02534_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2502_02534_amd import binding, device
+    binding.load()
+    return device
+
+
+# (samples, prefix, suffix bound, workgroups the plan should come to, streamed V)
+SHAPES = [(48, 2000, 20, 256, False), (48, 2000, 700, 64, True), (20, 3000, 900, 128, False), (80, 4000, 450, 128, True),
+          (256, 300, 330, 256, True), (255, 300, 500, 64, True),
+          (9, 0, 500, 256, False)]
+
+
+@pytest.mark.parametrize("page", [0, 16])
+@pytest.mark.parametrize("samples,prefix,suffix,workgroups,streamed", SHAPES)
+def test_either_side_of_the_plans_lines(dev, oracle, samples, prefix, suffix, workgroups, streamed, page):
+    from paper_2502_02534_amd import binding as B
+    spec = W.small_spec(num_q_heads=16, num_kv_heads=8, samples_per_prompt=samples, prefix_len=(prefix, prefix),
+                        suffix_len=(0, suffix), page_size=page)
+    inp = W.make_attn_inputs(0, spec=spec, seed=1700 + samples, poison_padding=True)
+    desc = B.make_desc(dtype=B.SPD_BF16, num_q_heads=16, num_kv_heads=8, head_dim=128, num_prompts=1, num_samples=samples,
+                       max_samples_per_prompt=samples, page_size=page)
+    _, splits, chunk, _ = B.spd_attn_plan(desc, prefix, inp.max_suffix_len)
+    units = 8 * (-(-samples * 2 // 128))
+    assert splits == 0 or (splits - 1) * units < workgroups           # as many splits as that needs, or fewer
+    assert 2.0 * (prefix + samples * inp.max_suffix_len) * 8 * 128 * 2 >= 128 * 2**20 or not streamed
+    print(f"{samples} samples, prefix {prefix} in {splits} splits, suffix {suffix} in chunks of {chunk}, page {page}", flush=True)
+    rows = np.sort(np.random.default_rng(samples).choice(samples * 16, min(samples * 16, 160), replace=False))
+    check_attention(dev, oracle, inp, rows=rows)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+@pytest.mark.parametrize("prompts,heads,longest", [(2, 8, 900), (3, 8, 1500), (5, 4, 900), (4, 2, 2500), (7, 1, 3000), (1, 8, 700)])
+def test_splits_of_ragged_prompts(dev, oracle, dtype, d, prompts, heads, longest):
+    spec = W.small_spec(dtype=dtype, head_dim=d, num_q_heads=2 * heads, num_kv_heads=heads, num_prompts=prompts, samples_per_prompt=9,
+                        prefix_len=(1, longest), suffix_len=(0, 40), page_size=16 if prompts % 2 else 0)
+    print(f"{dtype} {d}: {prompts} prompts of up to {longest} tokens, {heads} KV heads", flush=True)
+    check_attention(dev, oracle, W.make_attn_inputs(0, spec=spec, seed=1800 + prompts, poison_padding=True))
