@@ -29,12 +29,12 @@
 // on one XCD, whose L2 they share.
 // Measured, whole call (before: one wavefront per query row, a lane per token on the vector ALU):
 //   fp32, 4/1 heads of 64 channels, 4 samples, prompt 256, suffix 32           93 ->  9.4 us
-//   fp32, 32/8 heads of 128 channels, 16 samples, prompt 2048, suffixes up to 256  582 ->  24 us
+//   fp32, 32/8 heads of 128 channels, 16 samples, prompt 2048, suffixes up to 256  582 ->  21 us
 //   bf16, 32/8 heads of 64 channels, 3 prompts of up to 4001 tokens x 21 samples,
-//   suffixes up to 501, paged                                                 840..1060 -> 25 us
-// Where the last two go: launch and first loads 5 us, the tiles (1 to 2 us each with one or two
-// wavefronts per SIMD: dependent products, softmax, a load round trip) 15, the merge 3 (the first is bound
-// by the host).
+//   suffixes up to 501, paged                                                 840..1060 -> 22 us
+// Where the last two go: launch and first loads 4 us, the tiles (fp32, from registers, 2.5 us each; bf16, from
+// LDS, 1.2, with one or two wavefronts per SIMD: dependent products, softmax, load round trips) 10 to 12, the merge
+// 3 (the first call is bound by the host).
 #include "spd_internal.h"
 #include "plan.h"
 #include "attn_prefix_body.h"

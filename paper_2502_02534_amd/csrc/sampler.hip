@@ -1805,9 +1805,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // their statistics.  Phases of a row of 64 x 128256 (clock stamps, us; before: four pairs of every slice per
 // thread, kept mass to its segment, a list reservation per step, every select of two levels): statistics and
 // histograms 3.4, pick 1.8, pairs 7.6 -> 4.7, sums 1.9 -> 2.2, select 3.7 -> 3.0, the slice and segment of the
-// token 1.0 -> 2.0, walk 1.4.  Whole calls: 64 rows 37.8 -> 36.0 us, 1 row 27.7 -> 25.0, 39 x 167649 39.0 -> 37.3,
-// 300 x 32000 32.9 -> 31.8, 1024 x 128256 204.6 -> 202.3.  Three workgroups share a CU (79 registers, 50 KB
-// of LDS each).
+// token 1.0 -> 2.0, walk 1.4.  Whole calls: 64 rows 37.8 -> 36.0 us (33.8 with the narrower margin around the cut, whose
+// lists are shorter), 1 row 27.7 -> 25.0, 39 x 167649 39.0 -> 37.3, 300 x 32000 32.9 -> 31.8, 1024 x 128256 204.6 -> 202.3
+// (197.5; 194.6 with the logits read past the cache).  Three workgroups share a CU (79 registers, 50 KB of LDS each).
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
 // needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory: the
 // filtered routine reads its pairs twice instead of holding them across the selection, and the whole-row
