@@ -25,7 +25,7 @@ namespace {
 constexpr int kFusedWaves = 4;
 constexpr int kFusedLds = prefix_impl::kPrefixLds;
 
-template <bool PAGED, bool STREAM_V>
+template <bool PAGED, int STREAM>
 __global__ __launch_bounds__(kFusedWaves * 64) __attribute__((amdgpu_waves_per_eu(2))) void attn_fused_kernel(
     AttnParams p, FusedLevels fl, int spread)
 {
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) __attribute__((amdgpu_waves_per_e
     } else {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const long long item = sidx * kFusedWaves + wave;
-        suffix_impl::suffix_body<PAGED, STREAM_V>(p, p.suffix_slot0, item);
+        suffix_impl::suffix_body<PAGED, STREAM>(p, p.suffix_slot0, item);
     }
 }
 
@@ -73,8 +73,9 @@ hipError_t launch_fused(const AttnParams& p, const FusedLevels& fl, hipStream_t 
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)(prefix_blocks + suffix_blocks));
     const int spread = prefix_blocks > 256 ? 1 : 0;  // more prefix workgroups than CUs
-    const auto kernel = p.page_size ? (p.stream_v ? attn_fused_kernel<true, true> : attn_fused_kernel<true, false>)
-                                    : (p.stream_v ? attn_fused_kernel<false, true> : attn_fused_kernel<false, false>);
+    const auto kernel = p.page_size ? (p.stream >= 1 ? attn_fused_kernel<true, 1> : attn_fused_kernel<true, 0>)
+                                    : p.stream >= 2 ? attn_fused_kernel<false, 2>
+                                    : p.stream == 1 ? attn_fused_kernel<false, 1> : attn_fused_kernel<false, 0>;
     hipLaunchKernelGGL(kernel, grid, dim3(kFusedWaves * 64), 0, s, p, fl, spread);
     return hipGetLastError();
 }

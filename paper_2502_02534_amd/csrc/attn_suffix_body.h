@@ -23,12 +23,12 @@
 // page numbers of the tile after that are fetched at the same time, so that no KV load waits
 // for a page-table load.  The body uses no LDS.
 // Bound: HBM.  Whole lines per K load instead of 64-byte halves, two instructions apart, and V marked as
-// streamed where the call's KV does not stay in the last-level cache anyway (stream_v: kStreamBytes),
+// streamed where the call's KV does not stay in the last-level cache anyway (stream: kStreamBytes, kStreamKBytes),
 // whole calls on alternating inputs: 64 samples of an 8k prompt (186 MB) 56.5 -> 54.7 with whole lines ->
 // 52.1 us with both, 32 samples x 64 heads of a 16k prompt (134 MB) 46.0 -> 45.6 -> 43.4, 8 prompts x 128
 // samples paged (4.6 GB) 902 -> 891 -> 845, the tree of 416 samples (1.1 GB) 273 -> 256 -> 250.  Streamed K
-// gains another 2 % on the first two and loses 4 % where steps repeat on the same 175 MB; halves of lines
-// must not be streamed (64 samples: 58.0 us, inputs in the cache, against 48.5).
+// takes the tree from 257.6 to 251.7 us (246.9 from 260.1 where steps repeat on the same KV) and loses 4 % where they
+// repeat on 175 MB, so only far larger calls have it; halves of lines must not be streamed (64 samples: 58.0 us, inputs in the cache, against 48.5).
 // The running state is the deferred-division form of the paper's online-softmax
 // recurrence (App., attn task 2): (m, l, unnormalised accumulator).
 #pragma once
@@ -111,7 +111,7 @@ __device__ __forceinline__ float max_over_lane_rows(float v)
 }
 
 // Body of one wavefront: work item `item`.  No LDS, no workgroup barriers.
-template <bool PAGED, bool STREAM_V>
+template <bool PAGED, int STREAM>
 __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long long item)
 {
 
@@ -193,11 +193,11 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
             const char* vb = (const char*)vg + second * 256;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                kk[s] = load16<false>(ka + (size_t)(s & 1) * row_bytes + koff + 128 * (s >> 1));
-                kk[4 + s] = load16<false>(kb + (size_t)(s & 1) * row_bytes + koff + 128 * (s >> 1));
+                kk[s] = load16<(STREAM >= 2)>(ka + (size_t)(s & 1) * row_bytes + koff + 128 * (s >> 1));
+                kk[4 + s] = load16<(STREAM >= 2)>(kb + (size_t)(s & 1) * row_bytes + koff + 128 * (s >> 1));
                 // V register s holds token 4 r + s, register 4 + s token 16 + 4 r + s
-                vv[s] = load16<STREAM_V>(va + (size_t)s * row_bytes + voff);
-                vv[4 + s] = load16<STREAM_V>(vb + (size_t)s * row_bytes + voff);
+                vv[s] = load16<(STREAM >= 1)>(va + (size_t)s * row_bytes + voff);
+                vv[4 + s] = load16<(STREAM >= 1)>(vb + (size_t)s * row_bytes + voff);
             }
             return;
         }
@@ -213,10 +213,10 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const int t = (c & ~1) + (s & 1);
-            kk[s] = load16<false>(ka + (unsigned)min(t, last0) * row_bytes + kpiece + 128 * (s >> 1));
-            kk[4 + s] = load16<false>(kb + (unsigned)(two ? min(t, last1) : last1) * row_bytes + kpiece + 128 * (s >> 1));
-            vv[s] = load16<STREAM_V>(va + (unsigned)min(4 * r + s, last0) * row_bytes + 16u * (unsigned)c);
-            vv[4 + s] = load16<STREAM_V>(vb + (unsigned)(two ? min(4 * r + s, last1) : last1) * row_bytes + 16u * (unsigned)c);
+            kk[s] = load16<(STREAM >= 2)>(ka + (unsigned)min(t, last0) * row_bytes + kpiece + 128 * (s >> 1));
+            kk[4 + s] = load16<(STREAM >= 2)>(kb + (unsigned)(two ? min(t, last1) : last1) * row_bytes + kpiece + 128 * (s >> 1));
+            vv[s] = load16<(STREAM >= 1)>(va + (unsigned)min(4 * r + s, last0) * row_bytes + 16u * (unsigned)c);
+            vv[4 + s] = load16<(STREAM >= 1)>(vb + (unsigned)(two ? min(4 * r + s, last1) : last1) * row_bytes + 16u * (unsigned)c);
         }
     };
 

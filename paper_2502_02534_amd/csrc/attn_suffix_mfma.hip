@@ -6,11 +6,11 @@ namespace {
 
 using namespace suffix_impl;
 
-template <bool PAGED, bool STREAM_V>
+template <bool PAGED, int STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_suffix_mfma_kernel(AttnParams p, int slot0)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    suffix_body<PAGED, STREAM_V>(p, slot0, (long long)blockIdx.x * kWavesPerBlock + wave);
+    suffix_body<PAGED, STREAM>(p, slot0, (long long)blockIdx.x * kWavesPerBlock + wave);
 }
 
 }  // namespace
@@ -26,8 +26,9 @@ hipError_t launch_attn_suffix_mfma(const AttnParams& p, hipStream_t s)
         return hipSuccess;
     const long long total = (long long)p.N * p.Hkv * p.num_suffix_chunks;
     const dim3 grid((unsigned)((total + kWavesPerBlock - 1) / kWavesPerBlock));
-    const auto kernel = p.page_size ? (p.stream_v ? attn_suffix_mfma_kernel<true, true> : attn_suffix_mfma_kernel<true, false>)
-                                    : (p.stream_v ? attn_suffix_mfma_kernel<false, true> : attn_suffix_mfma_kernel<false, false>);
+    const auto kernel = p.page_size ? (p.stream >= 1 ? attn_suffix_mfma_kernel<true, 1> : attn_suffix_mfma_kernel<true, 0>)
+                                    : p.stream >= 2 ? attn_suffix_mfma_kernel<false, 2>
+                                    : p.stream == 1 ? attn_suffix_mfma_kernel<false, 1> : attn_suffix_mfma_kernel<false, 0>;
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, p, p.suffix_slot0);
     return hipGetLastError();
 }

@@ -143,13 +143,21 @@ inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long l
 // use) 54.7 / 52.1, 4.6 GB 891 / 845.  A single buffer that every step reads again: 302 MB (175 in use) 95.8 /
 // 94.8 us a step, but 97 MB 61.8 / 63.9, 124 MB (71 in use) 72.0 / 73.7, 170 MB (84 in use) 62.7 / 65.3.
 constexpr double kStreamBytes = 128.0 * 1024 * 1024;
+// K too from eight times as many on, and only of contiguous KV: nothing of it is left from the step before.  Among other
+// steps / repeated on the same KV, us: the tree of 416 samples (1.7 GiB) 257.6 -> 251.7 / 260.1 -> 246.9, 6 prompts x 128
+// samples (2.9 GiB) 279.5 -> 270.5 / 275.2 -> 268.8; but 0.9 GiB 133.2 -> 126.6 / 122.6 -> 124.7 and 104.7 -> 101.9 /
+// 94.5 -> 98.2, 512 MiB (half of it in use) 67.3 -> 62.4 / 60.4 -> 62.4.  Paged KV, 512 MiB: 86.8 -> 86.9.
+constexpr double kStreamKBytes = 8 * kStreamBytes;
 
-inline int plan_stream_v(const spd_attn_desc* d, int num_levels, const spd_prefix_level* levels, long long max_suffix)
+inline int plan_stream(const spd_attn_desc* d, int num_levels, const spd_prefix_level* levels, long long max_suffix)
 {
     double tokens = (double)d->num_samples * (double)max_suffix;
     for (int l = 0; l < num_levels; ++l)
         tokens += (double)levels[l].num_groups * (double)levels[l].max_len;
-    return 2.0 * tokens * d->num_kv_heads * d->head_dim * (d->dtype == SPD_BF16 ? 2 : 4) >= kStreamBytes ? 1 : 0;
+    const double bytes = 2.0 * tokens * d->num_kv_heads * d->head_dim * (d->dtype == SPD_BF16 ? 2 : 4);
+    if (bytes < kStreamBytes)
+        return 0;
+    return bytes >= kStreamKBytes && d->page_size == 0 ? 2 : 1;
 }
 
 // From how many (sample, KV head) pairs the chunks alone fill the chip's 2048 wavefront places.

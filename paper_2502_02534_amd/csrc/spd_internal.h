@@ -64,7 +64,7 @@ struct AttnParams {
     int prefix_slot0; // first slot of the prefix level the prefix fields describe
     int suffix_slot0; // first slot of the suffix chunks
     int chunks_first; // order of the suffix items: chunk after chunk of all samples, else sample after sample
-    int stream_v;     // suffix V is marked as streamed (see kStreamBytes)
+    int stream;       // suffix KV marked as streamed: 0 none, 1 V, 2 K too (see kStreamBytes)
     int num_levels;   // levels of shared prefixes (1 for the plain shared-prefix call)
     void* part_acc;   // [N*Hq][slots][D] normalised partial outputs, fp16 if part_half else fp32;
                       // a row's partial states are contiguous for the merge

@@ -302,7 +302,7 @@ int run_attention(const spd_attn_desc* desc, const void* q, int num_levels, cons
     p.suffix_slot0 = lp.num_slots - lp.num_suffix_chunks;
     p.num_levels = num_levels;
     p.chunks_first = lp.chunks_first;
-    p.stream_v = plan_stream_v(desc, num_levels, levels, max_suffix_len);
+    p.stream = plan_stream(desc, num_levels, levels, max_suffix_len);
     p.part_acc = workspace;
     p.part_half = desc->dtype == SPD_BF16 ? 1 : 0;
     p.part_ml = (float2*)((char*)workspace + lp.acc_bytes);

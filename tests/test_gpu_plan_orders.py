@@ -51,3 +51,15 @@ def test_splits_of_ragged_prompts(dev, oracle, dtype, d, prompts, heads, longest
                         prefix_len=(1, longest), suffix_len=(0, 40), page_size=16 if prompts % 2 else 0)
     print(f"{dtype} {d}: {prompts} prompts of up to {longest} tokens, {heads} KV heads", flush=True)
     check_attention(dev, oracle, W.make_attn_inputs(0, spec=spec, seed=1800 + prompts, poison_padding=True))
+
+
+@pytest.mark.parametrize("prefix", [0, 40])
+def test_streamed_keys(dev, oracle, prefix):
+    """From 1 GiB of contiguous KV on, by its bounds, K is marked as streamed too: the suffix kernel by itself, and beside a prefix."""
+    samples = 345
+    spec = W.small_spec(num_q_heads=16, num_kv_heads=8, samples_per_prompt=samples, prefix_len=(prefix, prefix), suffix_len=(0, 800))
+    inp = W.make_attn_inputs(0, spec=spec, seed=1900 + prefix, poison_padding=True)
+    assert 2.0 * samples * inp.max_suffix_len * 8 * 128 * 2 >= 2**30
+    print(f"{samples} samples, prefix {prefix}, suffix up to {inp.max_suffix_len}", flush=True)
+    rows = np.sort(np.random.default_rng(prefix).choice(samples * 16, 160, replace=False))
+    check_attention(dev, oracle, inp, rows=rows)
