@@ -667,8 +667,8 @@ struct RowsLaunch {
 };
 
 // Prefix and suffix items in one launch: workgroups below prefix_blocks take prefix items (the row
-// blocks of one split, prompt and KV head on one XCD), the others suffix items (row block fastest, then
-// KV head, chunk, sample, so that neighbours read one contiguous stretch).
+// blocks of one split, prompt and KV head on one XCD), the others suffix items (row block fastest, then KV
+// head, so that neighbours read the heads of the same tokens, one contiguous stretch; then suffix_place's order).
 template <typename T, int DT, int QB, bool PAGED, bool RING>
 __global__ __launch_bounds__(kWaves * 64) void attn_rows_kernel(AttnParams p, RowsLaunch a)
 {
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(kWaves * 64) void attn_rows_kernel(AttnParams p, Ro
         }
         it.j = (int)(rest % (unsigned)p.Hkv);
         rest /= (unsigned)p.Hkv;
-        const SuffixPlace at = suffix_place(p, rest);
+        const plan::SuffixPlace at = plan::suffix_place(rest, (unsigned)p.N);
         const int chunk = at.chunk, n = at.n;
         it.s0 = n;
         it.rows = p.G;

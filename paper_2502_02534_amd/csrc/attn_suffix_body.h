@@ -33,6 +33,7 @@
 // recurrence (App., attn task 2): (m, l, unnormalised accumulator).
 #pragma once
 
+#include "plan.h"
 #include "spd_internal.h"
 
 #include <hip/hip_fp16.h>
@@ -123,7 +124,7 @@ __device__ __forceinline__ void suffix_body(const AttnParams& p, int slot0, long
     // KV head fastest: the waves of a workgroup (and neighbouring workgroups) read the heads of
     // the same tokens at the same time, i.e. one contiguous stretch of the [token][head][D] cache
     const int j = (int)(item % p.Hkv);
-    const SuffixPlace at = suffix_place(p, (unsigned)(item / p.Hkv));
+    const plan::SuffixPlace at = plan::suffix_place((unsigned)(item / p.Hkv), (unsigned)p.N);
     const int chunk = at.chunk, n = at.n;
     const int Ls = p.suffix_lens[n];
     const int t0 = chunk * p.suffix_chunk_tokens;

@@ -17,14 +17,13 @@ namespace plan {
 struct Plan {
     int prefix_split_tokens, num_prefix_splits;
     int suffix_chunk_tokens, num_suffix_chunks;
-    int chunks_first;  // order of the suffix items: chunk after chunk of all samples, else sample after sample
     size_t acc_bytes, ml_bytes;
 };
 
 // Plan of a multi-level call: split size and count per level, slot offsets, suffix chunks.
 struct LevelPlan {
     int split_tokens[SPD_MAX_PREFIX_LEVELS], num_splits[SPD_MAX_PREFIX_LEVELS], slot0[SPD_MAX_PREFIX_LEVELS];
-    int suffix_chunk_tokens, num_suffix_chunks, chunks_first, num_slots;
+    int suffix_chunk_tokens, num_suffix_chunks, num_slots;
     size_t acc_bytes, ml_bytes;
 };
 
@@ -160,6 +159,23 @@ inline int plan_stream(const spd_attn_desc* d, int num_levels, const spd_prefix_
     return bytes >= kStreamKBytes && d->page_size == 0 ? 2 : 1;
 }
 
+// Sample and chunk of suffix unit `unit` (a suffix item without its KV head, which runs fastest).  Units go chunk
+// after chunk through all samples, so that with ragged lengths the chunks that are mostly empty come last, and
+// an even number of samples starts every chunk one sample further on.  Workgroups go to the eight XCDs in turn: where
+// the samples' workgroups of a chunk are a multiple of eight, all chunks of a sample would else be on the same ones
+// (24 samples x 8 KV heads, 512 to 1024 tokens, prompt of 1k: 25.5 us, turned 22.4); turned, a sample's next chunk is
+// an odd number of samples on.  In sample-major order, where a sample has 8 or 16 workgroups, all last chunks
+// are on the same ones (128 samples x 8 heads, up to 1024 tokens beside a prompt of 4k: 96 us, 70).
+struct SuffixPlace {
+    int n, chunk;
+};
+constexpr SuffixPlace suffix_place(unsigned unit, unsigned samples)
+{
+    const unsigned chunk = unit / samples;
+    const unsigned place = unit - chunk * samples;
+    return {(int)(samples % 2 ? place : (place + chunk) % samples), (int)chunk};
+}
+
 // From how many (sample, KV head) pairs the chunks alone fill the chip's 2048 wavefront places.
 constexpr long long kManyPairs = 2048;
 
@@ -181,18 +197,13 @@ inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 //   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 64 to 320 tokens.  (On the tiled
 //   path 129 to 256 tokens of 128 pairs or more are cut into chunks of 96 instead of 64: 16 samples x 8 heads, up to
 //   193 / 256 / 256 ragged tokens 4.1 / 3.9 / 2.5 % faster, 24 samples 6.1 / 2.3 / 3.4; up to 350 tokens +7.9, -5.4 %, 8
-//   samples 0 to -3, 727 tokens of 24 pairs -9.)  The workgroups of such a call go through one sample after another,
-//   and to the eight XCDs in turn: where a sample has 8 or 16 of them, an XCD gets the same chunks of every sample,
-//   and with ragged lengths the late ones are mostly empty.  Chunks of 128 or 256 tokens (three quarters are
-//   taken instead) and of 288 do that to the usual lengths: 8 prompts x 128 samples, up to 2048 tokens, 256
-//   tokens 1083 us, 288 1136, 224 840..920, 320 848; with the chunks dealt out evenly 256 872, 288 869, 320 853.
-//   More: the launch takes chunk after chunk of all samples (even over the XCDs, and the chunks that are
-//   mostly empty come last), in as few equal parts as chunks of up to 768 tokens allow: a chunk pays some 4 us
-//   before its first tile is there and leaves a partial state.  The batch above (same order) 320 tokens
+//   samples 0 to -3, 727 tokens of 24 pairs -9.)
+//   More: as few equal parts as chunks of up to 768 tokens allow: a chunk pays some 4 us
+//   before its first tile is there and leaves a partial state.  8 prompts x 128 samples, up to 2048 tokens, 320 tokens
 //   861 us, 416 840, 512 825, 640 817, 768 801, 1024 807; 416 samples x 8 heads, up to 1024 tokens, beside a
 //   tree of prefixes: 320 264, 512 257, 640 257, 768 266, 1024 279.
-//   Fewer pairs beside a prefix pass of half the workgroups or less: as many items as wavefronts have places then,
-//   in the same order (64 samples x 8 heads of up to 1024 tokens: 192-token chunks 50.3 us, 256 49.4, 384 47.1,
+//   Fewer pairs beside a prefix pass of half the workgroups or less: as many items as wavefronts have places then
+//   (64 samples x 8 heads of up to 1024 tokens: 192-token chunks 50.3 us, 256 49.4, 384 47.1,
 //   512 50.3; 32 samples 192 27.5, 256 30.4, 384 28.3; 96 samples 192 59.7, 384 58.6, 512 58.2).
 inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix, bool few_prefix = false)
 {
@@ -326,11 +337,9 @@ inline int make_plan(const spd_attn_desc* d, long long max_prefix, long long max
     const int workgroups = prefix_workgroups(d, d->num_prompts, spp, max_prefix, max_suffix);
     pl->prefix_split_tokens = plan_prefix_split(d, d->num_prompts, spp, max_prefix, kMaxSplits, workgroups);
     pl->num_prefix_splits = (int)((max_prefix + pl->prefix_split_tokens - 1) / pl->prefix_split_tokens);
-    // (a short prefix, two tiles a split, has no fewer splits to take: short suffixes then keep their chunks, in the
-    // other order)
+    // (a short prefix, two tiles a split, has no fewer splits to take: short suffixes then keep their chunks)
     const bool few = workgroups < 256 && (max_suffix > 384 || pl->prefix_split_tokens > 128);
     pl->suffix_chunk_tokens = plan_suffix_chunk(d, max_suffix, few);
-    pl->chunks_first = workgroups < 256 || many_suffixes(d) ? 1 : 0;
     pl->num_suffix_chunks = (int)((max_suffix + pl->suffix_chunk_tokens - 1) / pl->suffix_chunk_tokens);
     const size_t rows = (size_t)d->num_samples * d->num_q_heads;
     const size_t slots = (size_t)pl->num_prefix_splits + pl->num_suffix_chunks;
@@ -353,7 +362,6 @@ inline int make_level_plan(const spd_attn_desc* d, int num_levels, const spd_pre
         return rc;
     lp->suffix_chunk_tokens = pl.suffix_chunk_tokens;
     lp->num_suffix_chunks = pl.num_suffix_chunks;
-    lp->chunks_first = pl.chunks_first;
     const int max_splits = kMaxSplits / num_levels;  // the merge takes kMaxSplits prefix splits in all
     int slots = 0;
     for (int l = 0; l < num_levels; ++l) {

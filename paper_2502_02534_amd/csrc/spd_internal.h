@@ -63,7 +63,6 @@ struct AttnParams {
     int num_slots;    // prefix splits (of every level) + suffix chunks
     int prefix_slot0; // first slot of the prefix level the prefix fields describe
     int suffix_slot0; // first slot of the suffix chunks
-    int chunks_first; // order of the suffix items: chunk after chunk of all samples, else sample after sample
     int stream;       // suffix KV marked as streamed: 0 none, 1 V, 2 K too (see kStreamBytes)
     int num_levels;   // levels of shared prefixes (1 for the plain shared-prefix call)
     void* part_acc;   // [N*Hq][slots][D] normalised partial outputs, fp16 if part_half else fp32;
@@ -135,20 +134,6 @@ struct SamplerParams {
 __device__ __forceinline__ long long part_index(const AttnParams& p, long long row, int slot)
 {
     return row * p.num_slots + slot;
-}
-
-// Sample and chunk of suffix unit `unit` (an item without its KV head).
-struct SuffixPlace {
-    int n, chunk;
-};
-__device__ __forceinline__ SuffixPlace suffix_place(const AttnParams& p, unsigned unit)
-{
-    SuffixPlace at;
-    const unsigned per = (unsigned)(p.chunks_first ? p.N : p.num_suffix_chunks);
-    const int hi = (int)(unit / per), lo = (int)(unit % per);
-    at.n = p.chunks_first ? lo : hi;
-    at.chunk = p.chunks_first ? hi : lo;
-    return at;
 }
 
 hipError_t launch_attn_rows(const AttnParams& p, bool prefix, bool suffix, hipStream_t s);

@@ -5,6 +5,7 @@
 
 #include <cstdio>
 #include <initializer_list>
+#include <vector>
 
 using namespace spd::plan;
 
@@ -14,8 +15,33 @@ static int fail(const char* what, long long a, long long b)
     return 1;
 }
 
+// Order of the suffix items: every (sample, chunk) once, and a sample's chunks on at least half of the eight XCDs (four
+// wavefront items a workgroup, workgroups to the XCDs in turn).
+static int check_suffix_order()
+{
+    for (unsigned heads : {4u, 8u, 16u, 32u})
+        for (unsigned samples = 1; samples <= 132; ++samples) {
+            const unsigned chunks = 8;
+            std::vector<char> seen(samples * chunks, 0);
+            std::vector<unsigned> xcds(samples, 0u);
+            for (unsigned unit = 0; unit < samples * chunks; ++unit) {
+                const SuffixPlace at = suffix_place(unit, samples);
+                if (at.n < 0 || at.n >= (int)samples || at.chunk < 0 || at.chunk >= (int)chunks || seen[at.n * chunks + at.chunk]++)
+                    return fail("suffix order is no permutation", samples, unit);
+                for (unsigned head = 0; head < heads; ++head)
+                    xcds[at.n] |= 1u << ((unit * heads + head) / 4 % 8);
+            }
+            for (unsigned n = 0; n < samples; ++n)
+                if (__builtin_popcount(xcds[n]) < 4)
+                    return fail("a sample's chunks are on too few XCDs", samples, heads);
+        }
+    return 0;
+}
+
 int main()
 {
+    if (check_suffix_order())
+        return 1;
     const long long lens[] = {0, 1, 63, 64, 65, 127, 129, 2048, 8192, 16384, 100000, 300001, 1ll << 30};
     const int samples[] = {1, 3, 16, 64, 192, 1024, 100000};
     const int prompts[] = {1, 2, 8, 26};
