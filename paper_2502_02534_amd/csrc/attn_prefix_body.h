@@ -181,11 +181,11 @@ constexpr int kRing = kCopyAhead + 1;
 constexpr int kPrefixLds = 2 * kRing * kTileBytes;
 
 // Body of one workgroup of WAVES wavefronts for prefix level `lv`: (split, rowtile,
-// z = group * Hkv + KV head).  `lds` is
+// z = group * Hkv + KV head); `folded`: the even ones of two splits take both, the odd ones are empty.  `lds` is
 // kPrefixLds bytes of LDS; every wavefront of the workgroup must call it (it uses workgroup barriers).
 template <int WAVES, bool PAGED>
 __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLevelParams& lv, uint4* lds, int split,
-                                            int rowtile, int z)
+                                            int rowtile, int z, bool folded = false)
 {
     constexpr int kIPW = 16 / WAVES;  // copy instructions per wave per step
 
@@ -200,7 +200,7 @@ __device__ __forceinline__ void prefix_body(const AttnParams& p, const PrefixLev
     const int row0 = rowtile * 32 * WAVES;
     const int Lp = lv.lens[b];
     const int t0 = split * lv.split_tokens;
-    const int t1 = min(Lp, t0 + lv.split_tokens);
+    const int t1 = min(Lp, t0 + (folded ? (split & 1 ? 0 : 2) : 1) * lv.split_tokens);
     if (row0 >= rows_b)
         return;
     if (t0 >= t1) {

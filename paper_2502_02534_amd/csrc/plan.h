@@ -17,6 +17,7 @@ namespace plan {
 struct Plan {
     int prefix_split_tokens, num_prefix_splits;
     int suffix_chunk_tokens, num_suffix_chunks;
+    double fold_tokens;  // suffix tokens from which a prefix workgroup takes two splits (0: never)
     size_t acc_bytes, ml_bytes;
 };
 
@@ -24,6 +25,7 @@ struct Plan {
 struct LevelPlan {
     int split_tokens[SPD_MAX_PREFIX_LEVELS], num_splits[SPD_MAX_PREFIX_LEVELS], slot0[SPD_MAX_PREFIX_LEVELS];
     int suffix_chunk_tokens, num_suffix_chunks, num_slots;
+    double fold_tokens;
     size_t acc_bytes, ml_bytes;
 };
 
@@ -90,27 +92,44 @@ inline long long prefix_units(const spd_attn_desc* d, int groups, int spp)
     return (long long)groups * d->num_kv_heads * ((rows + kPrefixBlockRows - 1) / kPrefixBlockRows);
 }
 
-// Workgroups that the prefix pass of a plain call should have on the tiled path: one per CU, or half or a quarter as
-// many where the suffix stream (by the call's bounds, 5.5 TB/s) lasts longer than those take (0.9 us a
-// 32-token tile beside the stream, 5 us before the first): every workgroup less is a place for four wavefronts that
-// stream, and a partial state less per row.  256 / 128 / 64 workgroups (with the chunks that go with them): 32
-// samples of an 8k prompt, suffixes up to 1024 tokens 33.6 / 27.3 / 34.0 us, 64 samples 51.6 / 47.1 / 60.4, of a 3k
-// prompt 41.5 / 39.5 / 35.8, 96 samples 68.3 / 58.6; 64 samples with suffixes up to 2048 77.1 / 73.8 / 71.5; 48 of a 16k
-// prompt 48.6 / 58.6.  What it costs where the suffixes are far shorter than the bound: 64 samples of an 8k
-// prompt at up to 100 tokens of 1024 24.9 / 31.4; at 300 to 400 it gains 6 % of a decode step.
+// us that a prefix workgroup beside the suffix stream takes for `tokens` tokens: 0.9 a 32-token tile, 5 before the first.
+inline double prefix_time(long long tokens) { return 5.0 + 0.9 * (double)tokens / 32.0; }
+
+// Suffix tokens that the stream takes `us` for (5.5 TB/s, bf16, 128 channels).
+inline double stream_tokens(const spd_attn_desc* d, double us) { return us * 5.5e6 / (512.0 * d->num_kv_heads); }
+
+// Workgroups that the prefix pass of a plain call should have on the tiled path: one per CU, or half as many where their
+// splits hold no more than 512 tokens and the suffix stream, by the call's bounds, lasts longer: every workgroup
+// less is a place for four wavefronts that stream, and a partial state less per row.  The bound says little about the
+// lengths (a slot's capacity, of which a step may use a tenth), so the line lies where the pass alone takes as long
+// either way.  256 / 128 / 64 workgroups, at 20 to 60, 100 to 300 and 500 to 1000 tokens of a bound of 1024: 32 samples of
+// an 8k prompt (512 tokens in 128) 22.6 / 22.9 / 30.3, 24.3 / 25.6 / 32.5, 38.4 / 35.1 / 38.8 us, 64 samples of a 3k
+// prompt (384) 20.0 / 20.4 / 25.7, 28.3 / 24.4 / 29.3, 49.9 / 44.6 / 47.7, 256 samples of a 1k prompt (512)
+// 27.1 / 25.3 / 33.8, 60.7 / 56.2 / 50.5, 155 / 145 / 138; but 64 samples of an 8k prompt (1024) 26.5 / 32.6 / 48.8,
+// 29.9 / 35.6 / 51.8, 51.3 / 51.6 / 61.1: see fold_tokens.
+constexpr int kHalfSplitTokens = 512;
+
 inline int prefix_workgroups(const spd_attn_desc* d, int groups, int spp, long long max_prefix, long long max_suffix)
 {
     if (!tiled(d) || max_prefix == 0)
         return 256;
-    const double stream = (double)d->num_samples * (double)max_suffix * d->num_kv_heads * 512.0 / 5.5e6;  // us
-    const long long base = prefix_units(d, groups, spp);
-    for (int workgroups = 64; workgroups < 256; workgroups *= 2) {
-        const long long splits = (workgroups + base - 1) / base;
-        const double tiles = (double)((max_prefix + splits - 1) / splits) / 32.0;
-        if (5.0 + 0.9 * tiles <= 0.85 * stream)
-            return workgroups;
-    }
-    return 256;
+    const long long base = prefix_units(d, groups, spp), splits = (128 + base - 1) / base;
+    const long long tokens = (max_prefix + splits - 1) / splits;
+    const bool longer = (double)d->num_samples * (double)max_suffix * 0.85 >= stream_tokens(d, prefix_time(tokens));
+    return tokens <= kHalfSplitTokens && longer ? 128 : 256;
+}
+
+// Longer splits are put together on the device, where the lengths are: a workgroup of the fused launch takes two splits,
+// and the other one of the two ends at once, where the suffixes hold this many tokens (two splits take no
+// more than 1.45 of the stream's time).  0: never.  One split / two / as the tokens say, 64 samples of an 8k prompt,
+// suffixes up to 50, 300, 600, 1000 tokens, bound 2048: 27.1 / 32.0 / 27.3, 35.3 / 33.1 / 35.2, 38.6 / 39.9 / 38.9,
+// 55.0 / 45.5 / 47.0 us; 96 samples, 128 to 1024 tokens 72.2 / 63.4 / 61.7.
+inline double fold_tokens(const spd_attn_desc* d, int split_tokens, int splits, int workgroups, long long max_suffix)
+{
+    if (!tiled(d) || splits < 2 || workgroups < 256)
+        return 0.0;
+    const double tokens = stream_tokens(d, prefix_time(2ll * split_tokens) / 1.45);
+    return (double)d->num_samples * (double)max_suffix >= tokens ? tokens : 0.0;
 }
 
 // Tokens per split of a prefix level with `groups` groups of at most `spp` samples and lengths up to
@@ -202,18 +221,11 @@ inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 //   before its first tile is there and leaves a partial state.  8 prompts x 128 samples, up to 2048 tokens, 320 tokens
 //   861 us, 416 840, 512 825, 640 817, 768 801, 1024 807; 416 samples x 8 heads, up to 1024 tokens, beside a
 //   tree of prefixes: 320 264, 512 257, 640 257, 768 266, 1024 279.
-//   Fewer pairs beside a prefix pass of half the workgroups or less: as many items as wavefronts have places then
-//   (64 samples x 8 heads of up to 1024 tokens: 192-token chunks 50.3 us, 256 49.4, 384 47.1,
-//   512 50.3; 32 samples 192 27.5, 256 30.4, 384 28.3; 96 samples 192 59.7, 384 58.6, 512 58.2).
-inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix, bool few_prefix = false)
+inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
 {
     long long t;
     const long long pairs = (long long)d->num_samples * d->num_kv_heads;
-    if (few_prefix && !many_suffixes(d)) {
-        const long long parts = (1536 + pairs - 1) / pairs;
-        t = ((max_suffix + parts - 1) / parts + 63) / 64 * 64;
-        t = t > 768 ? 768 : t < 96 || t == 128 ? 96 : t == 256 ? 192 : t;
-    } else if (many_suffixes(d)) {
+    if (many_suffixes(d)) {
         const long long parts = max_suffix > 768 ? (max_suffix + 767) / 768 : 1;
         t = ((max_suffix + parts - 1) / parts + 31) / 32 * 32;
         if (t < 64) t = 64;
@@ -337,9 +349,8 @@ inline int make_plan(const spd_attn_desc* d, long long max_prefix, long long max
     const int workgroups = prefix_workgroups(d, d->num_prompts, spp, max_prefix, max_suffix);
     pl->prefix_split_tokens = plan_prefix_split(d, d->num_prompts, spp, max_prefix, kMaxSplits, workgroups);
     pl->num_prefix_splits = (int)((max_prefix + pl->prefix_split_tokens - 1) / pl->prefix_split_tokens);
-    // (a short prefix, two tiles a split, has no fewer splits to take: short suffixes then keep their chunks)
-    const bool few = workgroups < 256 && (max_suffix > 384 || pl->prefix_split_tokens > 128);
-    pl->suffix_chunk_tokens = plan_suffix_chunk(d, max_suffix, few);
+    pl->fold_tokens = fold_tokens(d, pl->prefix_split_tokens, pl->num_prefix_splits, workgroups, max_suffix);
+    pl->suffix_chunk_tokens = plan_suffix_chunk(d, max_suffix);
     pl->num_suffix_chunks = (int)((max_suffix + pl->suffix_chunk_tokens - 1) / pl->suffix_chunk_tokens);
     const size_t rows = (size_t)d->num_samples * d->num_q_heads;
     const size_t slots = (size_t)pl->num_prefix_splits + pl->num_suffix_chunks;
@@ -362,6 +373,7 @@ inline int make_level_plan(const spd_attn_desc* d, int num_levels, const spd_pre
         return rc;
     lp->suffix_chunk_tokens = pl.suffix_chunk_tokens;
     lp->num_suffix_chunks = pl.num_suffix_chunks;
+    lp->fold_tokens = 0.0;
     const int max_splits = kMaxSplits / num_levels;  // the merge takes kMaxSplits prefix splits in all
     int slots = 0;
     for (int l = 0; l < num_levels; ++l) {

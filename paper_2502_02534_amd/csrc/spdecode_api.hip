@@ -301,6 +301,7 @@ int run_attention(const spd_attn_desc* desc, const void* q, int num_levels, cons
     p.num_slots = lp.num_slots;
     p.suffix_slot0 = lp.num_slots - lp.num_suffix_chunks;
     p.num_levels = num_levels;
+    p.fold_tokens = (float)lp.fold_tokens;
     p.stream = plan_stream(desc, num_levels, levels, max_suffix_len);
     p.part_acc = workspace;
     p.part_half = desc->dtype == SPD_BF16 ? 1 : 0;
@@ -439,6 +440,7 @@ int shared_prefix_decode_attn(const spd_attn_desc* desc, const void* q, const vo
     lp.slot0[0] = 0;
     lp.suffix_chunk_tokens = pl.suffix_chunk_tokens;
     lp.num_suffix_chunks = pl.num_suffix_chunks;
+    lp.fold_tokens = pl.fold_tokens;
     lp.num_slots = pl.num_prefix_splits + pl.num_suffix_chunks;
     lp.acc_bytes = pl.acc_bytes;
     lp.ml_bytes = pl.ml_bytes;

@@ -73,6 +73,13 @@ int main()
                                     if (pl.num_prefix_splits > 0 &&
                                         (long long)(pl.num_prefix_splits - 1) * pl.prefix_split_tokens >= lp)
                                         return fail("an empty last split", lp, pl.prefix_split_tokens);
+                                    // whatever the suffix bound: splits no longer than a workgroup per CU gives, or 512 tokens
+                                    const int finest = plan_prefix_split(&d, B, (N + B - 1) / B, lp, kMaxSplits);
+                                    if (pl.prefix_split_tokens > (finest > 512 ? finest : 512))
+                                        return fail("splits grow with the suffix bound", finest, pl.prefix_split_tokens);
+                                    if (pl.fold_tokens < 0.0 || (pl.fold_tokens > 0.0 && (pl.num_prefix_splits < 2 || !tiled(&d) ||
+                                        pl.fold_tokens > (double)N * (double)ls)))
+                                        return fail("splits folded in vain", lp, ls);
                                     const size_t slots = (size_t)pl.num_prefix_splits + pl.num_suffix_chunks;
                                     if (pl.acc_bytes < slots * N * d.num_q_heads * D * 4 || pl.acc_bytes % 256 ||
                                         pl.ml_bytes < slots * N * d.num_q_heads * 8 || pl.ml_bytes % 256)

@@ -1,6 +1,6 @@
-"""Shapes either side of the lines of the launch plan: a prefix pass of 256, 128 and 64 workgroups (set by the suffix
-bound), suffix chunks sample by sample and chunk by chunk, V marked as streamed or not, chunk sizes of the
-few-workgroup plan, splits turned from prompt to prompt (2, 3, 4, 6, 8 splits of ragged prompts)."""
+"""Shapes either side of the lines of the launch plan: a prefix pass of 256 and 128 workgroups (by the length of a split
+and by the suffix bound), chunk sizes below and from 2048 (sample, KV head) pairs on, V marked as streamed or not,
+splits turned from prompt to prompt (2, 3, 4, 6, 8 splits of ragged prompts)."""
 import numpy as np
 import pytest
 
@@ -20,25 +20,25 @@ def dev():
     return device
 
 
-# (samples, prefix, suffix bound, workgroups the plan should come to, streamed V)
-SHAPES = [(48, 2000, 20, 256, False), (48, 2000, 700, 64, True), (20, 3000, 900, 128, False), (80, 4000, 450, 128, True),
-          (256, 300, 330, 256, True), (255, 300, 500, 64, True),
-          (9, 0, 500, 256, False)]
+# (samples, prefix, suffix bound, tokens per split, splits, tokens per chunk, chunks)
+SHAPES = [(48, 2000, 20, 128, 16, 64, 1), (48, 2000, 700, 128, 16, 96, 8),
+          (33, 3000, 480, 128, 24, 64, 8), (33, 3000, 500, 192, 16, 64, 8),      # the stream outlasts 128 workgroups
+          (33, 8192, 940, 512, 16, 96, 10), (33, 8193, 940, 320, 26, 96, 10),    # 512 tokens a split in 128 workgroups
+          (80, 4000, 450, 512, 8, 96, 5),
+          (255, 300, 500, 128, 3, 192, 3), (256, 300, 330, 128, 3, 352, 1),      # 2040 and 2048 pairs
+          (9, 0, 500, 128, 0, 64, 8)]
 
 
 @pytest.mark.parametrize("page", [0, 16])
-@pytest.mark.parametrize("samples,prefix,suffix,workgroups,streamed", SHAPES)
-def test_either_side_of_the_plans_lines(dev, oracle, samples, prefix, suffix, workgroups, streamed, page):
+@pytest.mark.parametrize("samples,prefix,suffix,split,splits,chunk,chunks", SHAPES)
+def test_either_side_of_the_plans_lines(dev, oracle, samples, prefix, suffix, split, splits, chunk, chunks, page):
     from paper_2502_02534_amd import binding as B
     spec = W.small_spec(num_q_heads=16, num_kv_heads=8, samples_per_prompt=samples, prefix_len=(prefix, prefix),
                         suffix_len=(0, suffix), page_size=page)
     inp = W.make_attn_inputs(0, spec=spec, seed=1700 + samples, poison_padding=True)
     desc = B.make_desc(dtype=B.SPD_BF16, num_q_heads=16, num_kv_heads=8, head_dim=128, num_prompts=1, num_samples=samples,
                        max_samples_per_prompt=samples, page_size=page)
-    _, splits, chunk, _ = B.spd_attn_plan(desc, prefix, inp.max_suffix_len)
-    units = 8 * (-(-samples * 2 // 128))
-    assert splits == 0 or (splits - 1) * units < workgroups           # as many splits as that needs, or fewer
-    assert 2.0 * (prefix + samples * inp.max_suffix_len) * 8 * 128 * 2 >= 128 * 2**20 or not streamed
+    assert B.spd_attn_plan(desc, prefix, inp.max_suffix_len) == (split, splits, chunk, chunks)
     print(f"{samples} samples, prefix {prefix} in {splits} splits, suffix {suffix} in chunks of {chunk}, page {page}", flush=True)
     rows = np.sort(np.random.default_rng(samples).choice(samples * 16, min(samples * 16, 160), replace=False))
     check_attention(dev, oracle, inp, rows=rows)
