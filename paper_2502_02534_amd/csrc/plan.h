@@ -92,6 +92,13 @@ inline long long prefix_units(const spd_attn_desc* d, int groups, int spp)
     return (long long)groups * d->num_kv_heads * ((rows + kPrefixBlockRows - 1) / kPrefixBlockRows);
 }
 
+// The prefix and suffix passes of a tiled call share a launch up to 16 query heads per KV head (the columns of the suffix
+// pass's product) and 65535 (group, KV head) pairs.
+inline bool one_launch(const spd_attn_desc* d, int groups)
+{
+    return tiled(d) && d->num_q_heads <= 16 * d->num_kv_heads && (long long)groups * d->num_kv_heads <= 65535;
+}
+
 // us that a prefix workgroup beside the suffix stream takes for `tokens` tokens: 0.9 a 32-token tile, 5 before the first.
 inline double prefix_time(long long tokens) { return 5.0 + 0.9 * (double)tokens / 32.0; }
 
@@ -111,7 +118,7 @@ constexpr int kHalfSplitTokens = 512;
 
 inline int prefix_workgroups(const spd_attn_desc* d, int groups, int spp, long long max_prefix, long long max_suffix)
 {
-    if (!tiled(d) || max_prefix == 0)
+    if (!one_launch(d, groups) || max_prefix == 0)
         return 256;
     const long long base = prefix_units(d, groups, spp), splits = (128 + base - 1) / base;
     const long long tokens = (max_prefix + splits - 1) / splits;
@@ -124,9 +131,9 @@ inline int prefix_workgroups(const spd_attn_desc* d, int groups, int spp, long l
 // more than 1.45 of the stream's time).  0: never.  One split / two / as the tokens say, 64 samples of an 8k prompt,
 // suffixes up to 50, 300, 600, 1000 tokens, bound 2048: 27.1 / 32.0 / 27.3, 35.3 / 33.1 / 35.2, 38.6 / 39.9 / 38.9,
 // 55.0 / 45.5 / 47.0 us; 96 samples, 128 to 1024 tokens 72.2 / 63.4 / 61.7.
-inline double fold_tokens(const spd_attn_desc* d, int split_tokens, int splits, int workgroups, long long max_suffix)
+inline double fold_tokens(const spd_attn_desc* d, int groups, int split_tokens, int splits, int workgroups, long long max_suffix)
 {
-    if (!tiled(d) || splits < 2 || workgroups < 256)
+    if (!one_launch(d, groups) || splits < 2 || workgroups < 256)
         return 0.0;
     const double tokens = stream_tokens(d, prefix_time(2ll * split_tokens) / 1.45);
     return (double)d->num_samples * (double)max_suffix >= tokens ? tokens : 0.0;
@@ -349,7 +356,7 @@ inline int make_plan(const spd_attn_desc* d, long long max_prefix, long long max
     const int workgroups = prefix_workgroups(d, d->num_prompts, spp, max_prefix, max_suffix);
     pl->prefix_split_tokens = plan_prefix_split(d, d->num_prompts, spp, max_prefix, kMaxSplits, workgroups);
     pl->num_prefix_splits = (int)((max_prefix + pl->prefix_split_tokens - 1) / pl->prefix_split_tokens);
-    pl->fold_tokens = fold_tokens(d, pl->prefix_split_tokens, pl->num_prefix_splits, workgroups, max_suffix);
+    pl->fold_tokens = fold_tokens(d, d->num_prompts, pl->prefix_split_tokens, pl->num_prefix_splits, workgroups, max_suffix);
     pl->suffix_chunk_tokens = plan_suffix_chunk(d, max_suffix);
     pl->num_suffix_chunks = (int)((max_suffix + pl->suffix_chunk_tokens - 1) / pl->suffix_chunk_tokens);
     const size_t rows = (size_t)d->num_samples * d->num_q_heads;

@@ -38,8 +38,29 @@ static int check_suffix_order()
     return 0;
 }
 
+// Where the suffix pass does not share the prefix pass's launch (32 query heads per KV head, too many groups), the prefix
+// pass gets a workgroup per CU whatever the suffixes are.
+static int check_two_launches()
+{
+    for (int hq : {16, 32})
+        for (int groups : {1, 70000}) {
+            const int n = groups > 1 ? groups : 256;
+            spd_attn_desc d = {SPD_BF16, hq, 1, 128, groups, n, groups > 1 ? 1 : 256, 0, 0.f, 0};
+            Plan with, without;
+            if (make_plan(&d, 1024, 2048, &with) != SPD_OK || make_plan(&d, 1024, 0, &without) != SPD_OK)
+                return fail("make_plan refused a valid description", hq, groups);
+            const bool one = hq == 16 && groups == 1;
+            if (one_launch(&d, groups) != one || (!one && with.prefix_split_tokens != without.prefix_split_tokens) ||
+                (!one && with.fold_tokens != 0.0) || (one && with.prefix_split_tokens <= without.prefix_split_tokens))
+                return fail("prefix plan of two launches", hq, with.prefix_split_tokens);
+        }
+    return 0;
+}
+
 int main()
 {
+    if (check_two_launches())
+        return 1;
     if (check_suffix_order())
         return 1;
     const long long lens[] = {0, 1, 63, 64, 65, 127, 129, 2048, 8192, 16384, 100000, 300001, 1ll << 30};
