@@ -23,12 +23,11 @@
 // page numbers of the tile after that are fetched at the same time, so that no KV load waits
 // for a page-table load.  The body uses no LDS.
 // Bound: HBM.  Whole lines per K load instead of 64-byte halves, two instructions apart, and V marked as
-// streamed where the call's KV does not stay in the last-level cache anyway (stream: kStreamBytes, kStreamKBytes),
-// whole calls on alternating inputs: 64 samples of an 8k prompt (186 MB) 56.5 -> 54.7 with whole lines ->
-// 52.1 us with both, 32 samples x 64 heads of a 16k prompt (134 MB) 46.0 -> 45.6 -> 43.4, 8 prompts x 128
-// samples paged (4.6 GB) 902 -> 891 -> 845, the tree of 416 samples (1.1 GB) 273 -> 256 -> 250.  Streamed K
-// takes the tree from 257.6 to 251.7 us (246.9 from 260.1 where steps repeat on the same KV) and loses 4 % where they
-// repeat on 175 MB, so only far larger calls have it; halves of lines must not be streamed (64 samples: 58.0 us, inputs in the cache, against 48.5).
+// streamed where the call's KV does not stay in the last-level cache anyway (stream: kStreamBytes, kStreamKBytes).
+// Whole calls when that came in, on alternating inputs, halves -> whole lines -> V streamed: 64 samples of an 8k prompt
+// (186 MB) 56.5 -> 54.7 -> 52.1 us, 8 prompts x 128 samples paged (4.6 GB) 902 -> 891 -> 845, the tree of 416
+// samples (1.1 GB) 273 -> 256 -> 250; with whole lines 32 samples x 64 heads of a 16k prompt (134 MB) 46.0 -> 45.6.  Halves of
+// lines must not be streamed (64 samples: 58.0 us, inputs in the cache, against 48.5).
 // The running state is the deferred-division form of the paper's online-softmax
 // recurrence (App., attn task 2): (m, l, unnormalised accumulator).
 #pragma once

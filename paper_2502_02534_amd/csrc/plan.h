@@ -162,17 +162,22 @@ inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long l
     return part_tokens(max_prefix, min_split_tokens(d), (int)(want > max_splits ? max_splits : want), 64);
 }
 
-// From how many bytes of KV (by the call's bounds) the suffix pass marks V as streamed.  The last-level cache
-// holds 256 MB: where two such buffers (layers, or batches taken in turn) fill it, leaving V out saves the
-// cache's own traffic.  Alternating inputs, not marked / marked: 134 MB 45.6 / 43.4 us, 302 MB (186 MB in
-// use) 54.7 / 52.1, 4.6 GB 891 / 845.  A single buffer that every step reads again: 302 MB (175 in use) 95.8 /
-// 94.8 us a step, but 97 MB 61.8 / 63.9, 124 MB (71 in use) 72.0 / 73.7, 170 MB (84 in use) 62.7 / 65.3.
-constexpr double kStreamBytes = 128.0 * 1024 * 1024;
-// K too from eight times as many on, and only of contiguous KV: nothing of it is left from the step before.  Among other
-// steps / repeated on the same KV, us: the tree of 416 samples (1.7 GiB) 257.6 -> 251.7 / 260.1 -> 246.9, 6 prompts x 128
-// samples (2.9 GiB) 279.5 -> 270.5 / 275.2 -> 268.8; but 0.9 GiB 133.2 -> 126.6 / 122.6 -> 124.7 and 104.7 -> 101.9 /
-// 94.5 -> 98.2, 512 MiB (half of it in use) 67.3 -> 62.4 / 60.4 -> 62.4.  Paged KV, 512 MiB: 86.8 -> 86.9.
-constexpr double kStreamKBytes = 8 * kStreamBytes;
+// From how many bytes of KV (by the call's bounds) the suffix pass marks V as streamed: three quarters of the last-level
+// cache's 256 MB.  Where such buffers (layers, or batches) are taken in turn, leaving V out of the cache saves the cache's own
+// traffic; a single buffer that every step reads again loses what it kept there.  Not marked / marked, us, three
+// buffers in turn | the same one, bounds in MB, tokens present in parentheses: 138 MB (half) 25.9 / 26.0 | 24.7 / 25.9, paged
+// 25.8 / 26.7 | 25.2 / 26.9; 172 MB (half) 30.1 / 29.0 | 26.4 / 28.5; 205 MB (half) 34.5 / 30.8 | 29.7 / 30.5, (three
+// quarters) 44.1 / 39.4 | 36.3 / 37.1; 272 MB (half) 46.9 / 42.2 | 38.0 / 40.1; 340 MB (nine tenths) 73.4 / 68.6 | 60.5 / 57.2; 1 GB
+// (a tenth) 36.6 / 33.6 | 31.5 / 32.4.  Below the line what a repeated buffer loses made such calls slower than they were
+// with neither whole-line K loads nor streaming (25.1 and 27.8 us at 138 and 172 MB).
+constexpr double kStreamBytes = 192.0 * 1024 * 1024;
+// K too from 1 GiB on, and only of contiguous KV.  V only / both, in turn | the same one: 416 samples, a tree (1.7 GiB by its
+// bounds, 1 GB present) 241.7 / 235.0 | 240.7 / 226.7, 2000 samples (2.5 GB, two thirds) 318.8 / 302.2 | 323.8 / 305.5, 256 samples
+// (1.1 GB, half) 125.9 / 119.3 | 118.4 / 118.7, 128 samples at 100 to 200, 200 to 400, 400 to 800 of 4096 tokens
+// 34.4 / 32.3 | 32.4 / 32.3, 44.4 / 42.1 | 40.1 / 42.1, 72.1 / 68.5 | 62.7 / 67.0 (the last two before
+// any streaming, in other chunks: 64.6, 92.1 | 54.6, 77.9).  At 0.9 GiB in turn -3 to -5 %, the same one +2 to +4 %.  To let the lengths decide costs
+// every wavefront a round trip (2000 samples at up to 30 tokens 76 -> 87).
+constexpr double kStreamKBytes = 1024.0 * 1024 * 1024;
 
 inline int plan_stream(const spd_attn_desc* d, int num_levels, const spd_prefix_level* levels, long long max_suffix)
 {

@@ -57,8 +57,41 @@ static int check_two_launches()
     return 0;
 }
 
+// What of the suffix KV is marked as streamed, on both sides of the lines (bytes by the bounds of 8 KV heads of 128
+// bf16 channels: 4096 a token), in whole calls and in trees.
+static int check_stream()
+{
+    const long long v_line = 192ll * 1024 * 1024 / 4096, k_line = 1024ll * 1024 * 1024 / 4096;
+    for (int page : {0, 16})
+        for (int prefix : {0, 1000})
+            for (int side = 0; side < 2; ++side)
+                for (int levels : {1, 3}) {
+                    spd_prefix_level lv[3] = {};
+                    for (int l = 0; l < levels; ++l) {
+                        lv[l].num_groups = l + 1;
+                        lv[l].max_len = prefix;
+                    }
+                    const long long before = levels == 1 ? prefix : 6ll * prefix;
+                    spd_attn_desc d = {SPD_BF16, 32, 8, 128, 1, 1, 0, page, 0.f, 0};
+                    if (plan_stream(&d, levels, lv, v_line - before - 1 + side) != side)
+                        return fail("line of the streamed V", before, side);
+                    if (plan_stream(&d, levels, lv, k_line - before - 1 + side) != (side && !page ? 2 : 1))
+                        return fail("line of the streamed K", before, side);
+                }
+    // 32 samples x 8 KV heads of up to 512 tokens after a 16k prompt, 128 MiB: kept
+    spd_attn_desc d = {SPD_BF16, 64, 8, 128, 1, 32, 32, 0, 0.f, 0};
+    spd_prefix_level lv = {};
+    lv.num_groups = 1;
+    lv.max_len = 16384;
+    if (plan_stream(&d, 1, &lv, 512) != 0)
+        return fail("a call of half the cache is streamed", 0, 0);
+    return 0;
+}
+
 int main()
 {
+    if (check_stream())
+        return 1;
     if (check_two_launches())
         return 1;
     if (check_suffix_order())
