@@ -212,7 +212,9 @@ constexpr long long kManyPairs = 2048;
 
 inline bool many_suffixes(const spd_attn_desc* d) { return (long long)d->num_samples * d->num_kv_heads >= kManyPairs; }
 
-// Tokens per chunk for about a place per (pair, chunk) item: 64 to 320, neither 128 nor 256 (see below).
+// Tokens per chunk for about a place per (pair, chunk) item: 64 to 320.  (96 and 192 in place of 128 and 256: in the items'
+// order neither is the better one throughout.  192 / 256, us, up to 1024 tokens of 8 KV heads: 64 samples of an 8k
+// prompt at 150 to 300 30.3 / 32.5, 300 to 600 47.9 / 37.5, 500 to 1000 50.7 / 51.5, 32 samples 24.7 / 31.7, 37.3 / 32.7.)
 inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 {
     const long long pairs = (long long)d->num_samples * d->num_kv_heads;
@@ -225,10 +227,7 @@ inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 }
 
 // Tokens per suffix chunk, at most kMaxSplits chunks.
-//   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 64 to 320 tokens.  (On the tiled
-//   path 129 to 256 tokens of 128 pairs or more are cut into chunks of 96 instead of 64: 16 samples x 8 heads, up to
-//   193 / 256 / 256 ragged tokens 4.1 / 3.9 / 2.5 % faster, 24 samples 6.1 / 2.3 / 3.4; up to 350 tokens +7.9, -5.4 %, 8
-//   samples 0 to -3, 727 tokens of 24 pairs -9.)
+//   Fewer pairs than places: enough (pair, chunk) items to fill them, chunks of 64 to 320 tokens.
 //   More: as few equal parts as chunks of up to 768 tokens allow: a chunk pays some 4 us
 //   before its first tile is there and leaves a partial state.  8 prompts x 128 samples, up to 2048 tokens, 320 tokens
 //   861 us, 416 840, 512 825, 640 817, 768 801, 1024 807; 416 samples x 8 heads, up to 1024 tokens, beside a
@@ -236,14 +235,12 @@ inline long long short_chunk(const spd_attn_desc* d, long long max_suffix)
 inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
 {
     long long t;
-    const long long pairs = (long long)d->num_samples * d->num_kv_heads;
     if (many_suffixes(d)) {
         const long long parts = max_suffix > 768 ? (max_suffix + 767) / 768 : 1;
         t = ((max_suffix + parts - 1) / parts + 31) / 32 * 32;
         if (t < 64) t = 64;
     } else {
         t = short_chunk(d, max_suffix);
-        if (t == 64 && tiled(d) && pairs >= 128 && max_suffix > 128 && max_suffix <= 256) t = 96;
     }
     if (max_suffix > t * kMaxSplits) t = part_tokens(max_suffix, 64, kMaxSplits, 64);
     return (int)t;

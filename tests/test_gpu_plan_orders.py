@@ -25,6 +25,7 @@ SHAPES = [(48, 2000, 20, 128, 16, 64, 1), (48, 2000, 700, 128, 16, 96, 8),
           (33, 3000, 480, 128, 24, 64, 8), (33, 3000, 500, 192, 16, 64, 8),      # the stream outlasts 128 workgroups
           (33, 8192, 940, 512, 16, 96, 10), (33, 8193, 940, 320, 26, 96, 10),    # 512 tokens a split in 128 workgroups
           (80, 4000, 450, 512, 8, 96, 5),
+          (16, 2000, 250, 128, 16, 64, 4),
           (255, 300, 500, 128, 3, 192, 3), (256, 300, 330, 128, 3, 352, 1),      # 2040 and 2048 pairs
           (9, 0, 500, 128, 0, 64, 8)]
 
