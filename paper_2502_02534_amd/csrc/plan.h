@@ -73,16 +73,6 @@ inline int rows_per_block(int head_dim, long long rows) { return rows > 16 && he
 // Fewest tokens per split in the general kernel: a tile or more for each of four wavefronts.
 inline int min_split_tokens(const spd_attn_desc* d) { return d->dtype == SPD_BF16 ? 128 : 64; }
 
-// Workgroups that the splits of a prefix level should give in the general kernel: one per CU, or, from LDS (bf16, 64
-// channels) with several prompts, whose lengths differ, half as many again: the splits past the end of the
-// shorter ones are empty.  One per CU / 1.5 / 2: 3 prompts x 21 samples 24.7 / 23.5 / 27.2 us, 2 x 128 87.9 / 78.4 /
-// 78.4, 4 x 20 on one KV head 19.2 / 16.9 / 16.0; one prompt of 8k tokens 35.5 / 37.8 / 39.7, fp32 3 x 100
-// 74.8 / 78.0 / 76.4.
-inline int split_workgroups(const spd_attn_desc* d, int groups)
-{
-    return d->dtype == SPD_BF16 && d->head_dim == 64 && groups > 1 ? 384 : 256;
-}
-
 inline bool tiled(const spd_attn_desc* d) { return d->dtype == SPD_BF16 && d->head_dim == 128; }
 
 // Workgroups of 128 rows, independent of the splits, that a prefix level of the tiled path has.
@@ -154,11 +144,14 @@ inline int plan_prefix_split(const spd_attn_desc* d, int groups, int spp, long l
         if (t < 128) t = 128;  // at least two tiles per split: a one-tile workgroup is all start-up
         return (int)t;
     }
-    // general kernel: enough splits for a workgroup per CU, a tile or more per wavefront
+    // general kernel: enough splits for a workgroup per CU, a tile or more per wavefront.  (bf16, 64 channels, 1.5 per CU
+    // for several prompts: where their lengths differ 2 prompts of 500 to 4000 tokens x 128 samples 42.0 -> 36 us, 3 x 21
+    // 25.0 -> 22.3, but of equal lengths 16 prompts of 512 x 4 10.6 -> 14.0, 8 of 1024 x 8 13.3 -> 15.3, 2 of 2048
+    // x 128 50.0 -> 58.4: the lengths are on the device.)
     const long long rows = (long long)spp * (d->num_q_heads / d->num_kv_heads);
     const int block = rows_per_block(d->head_dim, rows);
     const long long base = (long long)groups * d->num_kv_heads * ((rows + block - 1) / block);
-    const long long want = (split_workgroups(d, groups) + base - 1) / base;
+    const long long want = (256 + base - 1) / base;
     return part_tokens(max_prefix, min_split_tokens(d), (int)(want > max_splits ? max_splits : want), 64);
 }
 
@@ -289,19 +282,13 @@ inline int most_suffix_chunks(const spd_attn_desc* d, long long samples, long lo
 }
 
 // Most splits of a prefix level of up to `max_len` tokens that `samples` samples share.  One group takes the
-// fewest row blocks, so it is cut into the most splits (two of half the samples into more where they are planned
-// for more workgroups).
+// fewest row blocks, so it is cut into the most splits.
 inline int most_prefix_splits(const spd_attn_desc* d, long long samples, long long max_len, int max_splits)
 {
     const long long rows = samples * (d->num_q_heads / d->num_kv_heads);
     const int block = rows_per_block(d->head_dim, kPrefixBlockRows);  // the larger of the two blocks
     const long long base = (long long)d->num_kv_heads * ((rows + block - 1) / block);
-    const long long base2 = base > 2 * d->num_kv_heads ? base : 2 * d->num_kv_heads;  // of two groups
-    long long want = (split_workgroups(d, 1) + base - 1) / base;
-    if (samples > 1) {
-        const long long two = (split_workgroups(d, 2) + base2 - 1) / base2;
-        want = two > want ? two : want;
-    }
+    long long want = (256 + base - 1) / base;
     want = want > max_splits ? max_splits : want;
     const int least = min_split_tokens(d);
     const long long splits = (max_len + least - 1) / least;

@@ -88,8 +88,30 @@ static int check_stream()
     return 0;
 }
 
+// General kernel: one workgroup per CU and no more, however many prompts there are and whatever the type (their lengths
+// may be equal).
+static int check_general_splits()
+{
+    for (int dtype : {SPD_F32, SPD_BF16})
+        for (int D : {64, 96})
+            for (int groups : {1, 2, 3, 8, 16})
+                for (long long len : {512ll, 2048ll, 8192ll}) {
+                    spd_attn_desc d = {dtype, 32, 8, D, groups, 64, (64 + groups - 1) / groups, 0, 0.f, 0};
+                    Plan pl;
+                    if (make_plan(&d, len, 100, &pl) != SPD_OK)
+                        return fail("make_plan refused a valid description", groups, len);
+                    const int block = rows_per_block(D, 4ll * d.max_samples_per_prompt);
+                    const long long units = 8ll * groups * ((4 * d.max_samples_per_prompt + block - 1) / block);
+                    if ((pl.num_prefix_splits - 1) * units >= 256)
+                        return fail("more workgroups than CUs", units, pl.num_prefix_splits);
+                }
+    return 0;
+}
+
 int main()
 {
+    if (check_general_splits())
+        return 1;
     if (check_stream())
         return 1;
     if (check_two_launches())
