@@ -31,10 +31,10 @@
 //   fp32, 4/1 heads of 64 channels, 4 samples, prompt 256, suffix 32           93 ->  9.4 us
 //   fp32, 32/8 heads of 128 channels, 16 samples, prompt 2048, suffixes up to 256  582 ->  21 us
 //   bf16, 32/8 heads of 64 channels, 3 prompts of up to 4001 tokens x 21 samples,
-//   suffixes up to 501, paged                                                 840..1060 -> 22 us
-// Where the last two go: launch and first loads 4 us, the tiles (fp32, from registers, 2.5 us each; bf16, from
-// LDS, 1.2, with one or two wavefronts per SIMD: dependent products, softmax, load round trips) 10 to 12, the merge
-// 3 (the first call is bound by the host).
+//   suffixes up to 501, paged                                                 840..1060 -> 25 us
+// Where the last two go: launch and first loads 4 us, the tiles (from registers, 2.5 us each in fp32, 2 in bf16, with
+// two to three wavefronts per SIMD: dependent products, softmax, load round trips) 10 to 15, the merge 3 (the first
+// call is bound by the host).
 #include "spd_internal.h"
 #include "plan.h"
 #include "attn_prefix_body.h"
@@ -76,11 +76,10 @@ struct RowsItem {
 };
 
 // How K and V reach the products.
-//   RING (bf16, 64 channels): tiles go from global memory straight into LDS (global_load_lds_dwordx4), into two K
-//     and two V slots of the wavefront's own, two tiles ahead of their use, so that a wavefront nearly alone on
-//     its SIMD does not wait for a round trip in every tile; no barrier is needed.  3 prompts of up to 4001
-//     tokens x 21 samples 28.5 -> 24.9 us, 64 samples of an 8k prompt 38.3 -> 35.7, 4 x 100 samples, suffixes up to
-//     1000 tokens, 131.6 -> 111.0.
+//   RING (bf16, 64 channels, long chunks: plan::rows_through_lds has the figures): tiles go from global memory straight
+//     into LDS (global_load_lds_dwordx4), into two K and two V slots of the wavefront's own, two tiles ahead of their
+//     use, so that a wavefront nearly alone on its SIMD does not wait for a round trip in every tile; no
+//     barrier is needed.
 //   otherwise: registers, reloaded in place.  (With a ring fp32 loses: 128 channels 22.3 -> 28.7 us, 128 KB of LDS
 //     leave one wavefront per SIMD; 64 channels 23.7 -> 25.6, its products already hide the loads.)
 constexpr int kDepth = 2;
@@ -734,10 +733,10 @@ void launch_rows(const AttnParams& p, unsigned grid, const RowsLaunch& a, hipStr
 }
 
 template <typename T>
-void launch_rows_dim(const AttnParams& p, int qb, unsigned grid, const RowsLaunch& a, hipStream_t s)
+void launch_rows_dim(const AttnParams& p, int qb, bool ring, unsigned grid, const RowsLaunch& a, hipStream_t s)
 {
     constexpr bool kRing = std::is_same<T, uint16_t>::value;
-    if (kRing && p.D == 64)
+    if (kRing && ring)
         qb == 1 ? launch_rows<T, 64, 1, kRing>(p, grid, a, s) : launch_rows<T, 64, 2, kRing>(p, grid, a, s);
     else if (p.D <= 64)
         qb == 1 ? launch_rows<T, 64, 1, false>(p, grid, a, s) : launch_rows<T, 64, 2, false>(p, grid, a, s);
@@ -790,10 +789,11 @@ hipError_t launch_attn_rows(const AttnParams& p, bool prefix, bool suffix, hipSt
     a.g_inv = p.G > 1 ? (unsigned)((1ll << 32) / p.G) : 0xffffffffu;
     a.prefix_rowblocks = (int)rowblocks;
     a.prefix_blocks = (int)prefix_blocks;
+    const bool ring = suffix && plan::rows_through_lds(p.dtype, p.D, p.suffix_chunk_tokens, a.suffix_share);
     if (p.dtype == 0)
-        launch_rows_dim<float>(p, block / 16, (unsigned)blocks, a, s);
+        launch_rows_dim<float>(p, block / 16, false, (unsigned)blocks, a, s);
     else
-        launch_rows_dim<uint16_t>(p, block / 16, (unsigned)blocks, a, s);
+        launch_rows_dim<uint16_t>(p, block / 16, ring, (unsigned)blocks, a, s);
     return hipGetLastError();
 }
 

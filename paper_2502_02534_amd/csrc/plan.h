@@ -239,6 +239,17 @@ inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
     return (int)t;
 }
 
+// Whether the general kernel takes bf16 with 64 channels through LDS, two tiles ahead: where a wavefront has a suffix
+// chunk of eight tiles or more to itself.  Its 64 KB leave two workgroups on a CU, registers three, which shorter chunks, a second
+// round of workgroups and short splits need more.  Registers / LDS, us: 4 prompts x 100 samples at up to 256, 501, 1000
+// tokens 48.8 / 47.4, 67.5 / 62.3, 117.6 / 112.3, 2 x 128 at 256 to 512 64.2 / 59.2, 1 x 300 at up to 1000 83.9 / 80.4; 16 prompts x 4
+// samples at up to 256 (64-token chunks) 15.2 / 18.0, 4 x 16 at 256 to 512 (96) 27.0 / 29.1, 8 x 8 22.6 / 24.4, 3 x 21
+// at up to 501 25.3 / 26.2, 64 x 1 at up to 1000 (192) 29.9 / 31.0, 32 x 8 at up to 64 18.9 / 20.1.
+inline bool rows_through_lds(int dtype, int head_dim, int chunk_tokens, int share)
+{
+    return dtype == SPD_BF16 && head_dim == 64 && share == 1 && chunk_tokens >= 256;
+}
+
 // ---- workspace sizes -----------------------------------------------------------------------------------
 // A program allocates once, for its largest batch and its longest lengths.  Split counts fall in steps as
 // rows are added, so a call's own need is not monotone; what the size functions report is the most

@@ -108,8 +108,22 @@ static int check_general_splits()
     return 0;
 }
 
+// Chunks shorter than eight tiles, or shared by wavefronts, do not go through LDS; nor do other types and widths.
+static int check_rows_through_lds()
+{
+    for (int chunk : {64, 96, 192, 224, 256, 320, 768})
+        for (int share : {1, 2, 4})
+            for (int D : {56, 64, 96})
+                for (int dtype : {SPD_F32, SPD_BF16})
+                    if (rows_through_lds(dtype, D, chunk, share) != (dtype == SPD_BF16 && D == 64 && share == 1 && chunk >= 256))
+                        return fail("rows through LDS", chunk, share);
+    return 0;
+}
+
 int main()
 {
+    if (check_rows_through_lds())
+        return 1;
     if (check_general_splits())
         return 1;
     if (check_stream())
