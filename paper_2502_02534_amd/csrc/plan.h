@@ -254,12 +254,14 @@ inline bool rows_through_lds(int dtype, int head_dim, int chunk_tokens, int shar
 // A program allocates once, for its largest batch and its longest lengths.  Split counts fall in steps as
 // rows are added, so a call's own need is not monotone; what the size functions report is the most
 // that any call of no more samples, however grouped, and no longer lengths can need.  (On the bf16 /
-// head_dim 128 path they report the call's own need.)  Suffixes are counted in the chunks of short_chunk, of
+// head_dim 128 path they report what this one call needs in the finest plan: splits of a workgroup per CU and short
+// chunks.)  Suffixes are counted in the chunks of short_chunk, of
 // which plan_suffix_chunk never makes more: the longer chunks of many pairs are no help to smaller batches.
 inline int sized_suffix_chunks(const spd_attn_desc* d, long long max_suffix)
 {
-    const long long t = short_chunk(d, max_suffix), n = (max_suffix + t - 1) / t;
-    return (int)(n < kMaxSplits ? n : kMaxSplits);
+    long long t = short_chunk(d, max_suffix);
+    if (max_suffix > t * kMaxSplits) t = part_tokens(max_suffix, 64, kMaxSplits, 64);
+    return (int)((max_suffix + t - 1) / t);
 }
 
 // Prefix splits that a workspace is sized for: those of a workgroup per CU.

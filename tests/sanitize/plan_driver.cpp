@@ -132,8 +132,8 @@ int main()
         return 1;
     if (check_suffix_order())
         return 1;
-    const long long lens[] = {0, 1, 63, 64, 65, 127, 129, 2048, 8192, 16384, 100000, 300001, 1ll << 30};
-    const int samples[] = {1, 3, 16, 64, 192, 1024, 100000};
+    const long long lens[] = {0, 1, 63, 64, 65, 97, 127, 129, 193, 257, 385, 769, 1025, 2048, 4097, 8192, 47104, 100000, 1ll << 30};
+    const int samples[] = {1, 3, 16, 64, 191, 192, 255, 256, 1024, 1536, 2047, 100000};
     const int prompts[] = {1, 2, 8, 26};
     int checked = 0;
     for (int dtype : {SPD_F32, SPD_BF16})
@@ -175,7 +175,11 @@ int main()
                                         pl.ml_bytes < slots * N * d.num_q_heads * 8 || pl.ml_bytes % 256)
                                         return fail("workspace too small or misaligned", (long long)pl.acc_bytes,
                                                     (long long)pl.ml_bytes);
-                                    if (workspace_bytes(&d, 1, &lp, ls, pl.acc_bytes + pl.ml_bytes) < pl.acc_bytes + pl.ml_bytes)
+                                    // what the size functions count covers the plan, part by part and in bytes
+                                    const int splits = sized_prefix_splits(&d, lp), chunks = sized_suffix_chunks(&d, ls);
+                                    if (splits < pl.num_prefix_splits || chunks < pl.num_suffix_chunks || chunks > kMaxSplits)
+                                        return fail("more parts than the workspace is sized for", lp, ls);
+                                    if (workspace_bytes(&d, 1, &lp, ls, state_bytes(&d, splits + chunks)) < pl.acc_bytes + pl.ml_bytes)
                                         return fail("reported size below the call's own need", lp, ls);
                                     // the same problem as a tree of one to four levels
                                     for (int levels = 1; levels <= SPD_MAX_PREFIX_LEVELS; ++levels) {
@@ -194,6 +198,9 @@ int main()
                                                 return fail("slot ranges not consecutive", l, lpn.slot0[l]);
                                             slots_seen += lpn.num_splits[l];
                                         }
+                                        if (chunks < lpn.num_suffix_chunks ||
+                                            state_bytes(&d, slots_seen + chunks) < lpn.acc_bytes + lpn.ml_bytes)
+                                            return fail("a tree's need above its reported size", levels, ls);
                                         if (slots_seen > kMaxSplits || slots_seen + lpn.num_suffix_chunks != lpn.num_slots)
                                             return fail("slot count", slots_seen, lpn.num_slots);
                                     }

@@ -1,6 +1,7 @@
 """The size functions report enough for every smaller call too: a program that allocates once, for its
 largest batch and longest lengths, is never refused a smaller one (general kernel: fp32, or head
-dimensions other than 128).  Host arithmetic, no GPU."""
+dimensions other than 128); on the tiled path (bf16, 128 channels) they report the finest plan of the call itself.  Host
+arithmetic, no GPU."""
 import os
 import random
 
@@ -8,6 +9,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
+TILED = [(1, 32, 8, 128), (1, 64, 8, 128), (1, 8, 8, 128), (1, 32, 1, 128)]
 SHAPES = [(0, 32, 8, 128), (0, 4, 1, 64), (0, 8, 8, 256), (1, 8, 8, 256), (1, 32, 8, 64), (1, 24, 1, 96), (0, 1, 1, 8)]
 
 
@@ -86,3 +88,38 @@ def test_trees_of_prefixes_too(B, shape):
             m = rng.randint(1, n)
             small = size(m, [(rng.randint(1, m), rng.randint(1, x)) for x in lens], rng.randint(1, ls))
             assert 0 < small <= big, (n, lens, ls, m)
+
+
+def finest(shape, n, prompts, max_prefix, max_suffix):
+    """Slots of a tiled call in the finest plan: prefix splits for a workgroup per CU, chunks for a wavefront place each."""
+    _, hq, hkv, _ = shape
+    spp = (n + prompts - 1) // prompts
+    base = prompts * hkv * -(-spp * (hq // hkv) // 128)
+    split = max(128, up64(-(-max_prefix // min(64, -(-256 // base)))))
+    pairs = n * hkv
+    chunk = min(320, max(64, up64(-(-max_suffix // -(-2048 // pairs)))))
+    chunk = {128: 96, 256: 192}.get(chunk, chunk)
+    if max_suffix > 64 * chunk:
+        chunk = up64(-(-max_suffix // 64))
+    return -(-max_prefix // split) + -(-max_suffix // chunk)
+
+
+def up64(n):
+    return (n + 63) // 64 * 64
+
+
+@pytest.mark.parametrize("shape", TILED)
+def test_tiled_calls_report_their_finest_plan_and_need_no_more(B, shape):
+    rng = random.Random(shape[1] * 7 + shape[2])
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    pairs = [1535, 1536, 1537, 2047, 2048, 2049, 1023, 1024, 767]
+    lengths = [0, 63, 95, 96, 97, 128, 129, 192, 193, 255, 256, 257, 383, 385, 767, 768, 769, 1024, 4096, 4097, 6000, 20480, 20481, 46080, 47104]
+    for i in range(4000):
+        n = max(1, rng.choice(pairs) // shape[2]) if i % 3 == 0 else log(1, 3000)
+        prompts = rng.randint(1, min(n, 9))
+        lp, ls = log(1, 200000), rng.choice(lengths) if i % 2 == 0 else log(1, 50000)
+        desc = make(B, shape, n, prompts)
+        rows = finest(shape, n, prompts, lp, ls) * n * shape[1]
+        size = B.shared_prefix_decode_attn_workspace_size(desc, lp, ls)
+        assert size == up(rows * 512) + up(rows * 8) + 256, (n, prompts, lp, ls)
+        assert need(B, desc, lp, ls) <= size, (n, prompts, lp, ls)
