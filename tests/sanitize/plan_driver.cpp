@@ -120,8 +120,49 @@ static int check_rows_through_lds()
     return 0;
 }
 
+// Just below and just above each line of a plain tiled call (8 KV heads, one prompt).
+static int check_lines()
+{
+    struct Line {
+        int samples, q_heads;
+        long long prefix, suffix;
+        int split_tokens, splits, chunk_tokens, chunks;
+        bool folds;
+    };
+    const Line lines[] = {
+        // the stream, by its bound, outlasts a pass of 128 workgroups (33 x suffix x 0.85 tokens, 1343 of them a us)
+        {33, 16, 3000, 492, 128, 24, 64, 8, true}, {33, 16, 3000, 493, 192, 16, 64, 8, false},
+        // whose splits hold 512 tokens
+        {33, 16, 8192, 940, 512, 16, 96, 10, false}, {33, 16, 8193, 940, 320, 26, 96, 10, true},
+        // the bound allows for a stream beside which two splits are taken together
+        {64, 32, 8192, 489, 512, 16, 96, 6, false}, {64, 32, 8192, 490, 512, 16, 96, 6, true},
+        // one split only
+        {1024, 32, 4096, 700, 4096, 1, 704, 1, false},
+        // 2048 and 2040 (sample, KV head) pairs
+        {256, 16, 300, 700, 128, 3, 704, 1, false}, {255, 16, 300, 700, 128, 3, 320, 3, false},
+    };
+    for (const Line& x : lines) {
+        spd_attn_desc d = {SPD_BF16, x.q_heads, 8, 128, 1, x.samples, x.samples, 0, 0.f, 0};
+        Plan pl;
+        if (make_plan(&d, x.prefix, x.suffix, &pl) != SPD_OK)
+            return fail("make_plan refused a valid description", x.prefix, x.suffix);
+        if (pl.prefix_split_tokens != x.split_tokens || pl.num_prefix_splits != x.splits)
+            return fail("prefix splits at a line", pl.prefix_split_tokens, pl.num_prefix_splits);
+        if (pl.suffix_chunk_tokens != x.chunk_tokens || pl.num_suffix_chunks != x.chunks)
+            return fail("suffix chunks at a line", pl.suffix_chunk_tokens, pl.num_suffix_chunks);
+        if ((pl.fold_tokens > 0.0) != x.folds)
+            return fail("folded splits at a line", x.prefix, x.suffix);
+    }
+    spd_attn_desc d = {SPD_BF16, 1, 1, 128, 1, 2047, 2047, 0, 0.f, 0};
+    if (plan_suffix_chunk(&d, 700) != 320 || (d.num_samples = 2048, plan_suffix_chunk(&d, 700)) != 704)
+        return fail("chunks at 2048 pairs", 0, 0);
+    return 0;
+}
+
 int main()
 {
+    if (check_lines())
+        return 1;
     if (check_rows_through_lds())
         return 1;
     if (check_general_splits())

@@ -23,6 +23,11 @@ CASES = [
          prefix_len=(100, 500), suffix_len=(0, 70), page_size=16),
     dict(dtype="f32", num_q_heads=4, num_kv_heads=2, head_dim=64, num_prompts=1, samples_per_prompt=5,
          prefix_len=(33, 33), suffix_len=(0, 20)),
+    # 196 MiB of KV by the bounds: the tokens that a step appends are read by the next one's streamed loads
+    dict(dtype="bf16", num_q_heads=8, num_kv_heads=8, head_dim=128, num_prompts=1, samples_per_prompt=49,
+         prefix_len=(300, 300), suffix_len=(0, 1024)),
+    dict(dtype="bf16", num_q_heads=8, num_kv_heads=8, head_dim=128, num_prompts=1, samples_per_prompt=49,
+         prefix_len=(300, 300), suffix_len=(0, 1024), page_size=16),
 ]
 
 
