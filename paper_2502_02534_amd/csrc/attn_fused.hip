@@ -8,7 +8,9 @@
 // more of them than CUs, evenly spread through the grid), so that a CU holds one prefix workgroup
 // and, beside it, suffix workgroups: each SIMD has one wavefront that multiplies and one that
 // streams, HBM is busy during the prefix pass, and there is no launch (with its ramp and tail)
-// between the two passes.  Both bodies are the ones the separate kernels use.
+// between the two passes.  Both bodies are the ones the separate kernels use.  Where the suffixes hold tokens enough
+// (plan::fold_tokens) a prefix workgroup takes two splits and the other of the two ends at once, which leaves its
+// place to the stream.
 //
 // The kernel takes a table of prefix levels (a tree of shared prefixes has several; the plain call
 // has one), each with its own range of prefix workgroups.

@@ -120,7 +120,8 @@ inline int prefix_workgroups(const spd_attn_desc* d, int groups, int spp, long l
 // and the other one of the two ends at once, where the suffixes hold this many tokens (two splits take no
 // more than 1.45 of the stream's time).  0: never.  One split / two / as the tokens say, 64 samples of an 8k prompt,
 // suffixes up to 50, 300, 600, 1000 tokens, bound 2048: 27.1 / 32.0 / 27.3, 35.3 / 33.1 / 35.2, 38.6 / 39.9 / 38.9,
-// 55.0 / 45.5 / 47.0 us; 96 samples, 128 to 1024 tokens 72.2 / 63.4 / 61.7.
+// 55.0 / 45.5 / 47.0 us; 96 samples, 128 to 1024 tokens 72.2 / 63.4 / 61.7; 128 samples of a 4k prompt at 300 to 600 of 1024
+// lose 54.1 / 55.9 / 58.4, at 500 to 1000 of 2048 stay 86.3 / 83.2 / 86.3.  To read the lengths costs a call 0.3 us.
 inline double fold_tokens(const spd_attn_desc* d, int groups, int split_tokens, int splits, int workgroups, long long max_suffix)
 {
     if (!one_launch(d, groups) || splits < 2 || workgroups < 256)
@@ -168,8 +169,8 @@ constexpr double kStreamBytes = 192.0 * 1024 * 1024;
 // bounds, 1 GB present) 241.7 / 235.0 | 240.7 / 226.7, 2000 samples (2.5 GB, two thirds) 318.8 / 302.2 | 323.8 / 305.5, 256 samples
 // (1.1 GB, half) 125.9 / 119.3 | 118.4 / 118.7, 128 samples at 100 to 200, 200 to 400, 400 to 800 of 4096 tokens
 // 34.4 / 32.3 | 32.4 / 32.3, 44.4 / 42.1 | 40.1 / 42.1, 72.1 / 68.5 | 62.7 / 67.0 (the last two before
-// any streaming, in other chunks: 64.6, 92.1 | 54.6, 77.9).  At 0.9 GiB in turn -3 to -5 %, the same one +2 to +4 %.  To let the lengths decide costs
-// every wavefront a round trip (2000 samples at up to 30 tokens 76 -> 87).
+// any streaming, in other chunks: 64.6, 92.1 | 54.6, 77.9).  At 0.9 GiB in turn -3 to -5 %, the same one +2 to +4 %.  To let the
+// lengths decide costs every wavefront a round trip (2000 samples at up to 30 tokens 76 -> 87).
 constexpr double kStreamKBytes = 1024.0 * 1024 * 1024;
 
 inline int plan_stream(const spd_attn_desc* d, int num_levels, const spd_prefix_level* levels, long long max_suffix)
@@ -240,8 +241,8 @@ inline int plan_suffix_chunk(const spd_attn_desc* d, long long max_suffix)
 }
 
 // Whether the general kernel takes bf16 with 64 channels through LDS, two tiles ahead: where a wavefront has a suffix
-// chunk of eight tiles or more to itself.  Its 64 KB leave two workgroups on a CU, registers three, which shorter chunks, a second
-// round of workgroups and short splits need more.  Registers / LDS, us: 4 prompts x 100 samples at up to 256, 501, 1000
+// chunk of eight tiles or more to itself.  Fewer tiles do not pay back the way through LDS, and its 64 KB leave two
+// workgroups on a CU (registers: four where a wavefront has 16 query rows, two where it has 32).  Registers / LDS, us: 4 prompts x 100 samples at up to 256, 501, 1000
 // tokens 48.8 / 47.4, 67.5 / 62.3, 117.6 / 112.3, 2 x 128 at 256 to 512 64.2 / 59.2, 1 x 300 at up to 1000 83.9 / 80.4; 16 prompts x 4
 // samples at up to 256 (64-token chunks) 15.2 / 18.0, 4 x 16 at 256 to 512 (96) 27.0 / 29.1, 8 x 8 22.6 / 24.4, 3 x 21
 // at up to 501 25.3 / 26.2, 64 x 1 at up to 1000 (192) 29.9 / 31.0, 32 x 8 at up to 64 18.9 / 20.1.
