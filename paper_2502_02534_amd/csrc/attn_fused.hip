@@ -58,8 +58,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) __attribute__((amdgpu_waves_per_e
         const PrefixLevelParams& lv = fl.level[l];
         const prefix_impl::PrefixItem it =
             prefix_impl::prefix_item(pidx - fl.first_block[l], lv.num_splits, lv.rowtiles, lv.groups * p.Hkv);
-        const bool folded = p.fold_tokens > 0.f && suffix_tokens(p) >= p.fold_tokens;
-        prefix_impl::prefix_body<kFusedWaves, PAGED>(p, lv, lds, it.split, it.rowtile, it.z, folded);
+        prefix_impl::prefix_body<kFusedWaves, PAGED>(p, lv, lds, it.split, it.rowtile, it.z, splits_folded(p));
     } else {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const long long item = sidx * kFusedWaves + wave;

@@ -12,7 +12,8 @@ attn_prefix_mfma_kernel(AttnParams p, int rowtiles)
 {
     __shared__ uint4 lds[kPrefixLds / 16];
     const PrefixItem it = prefix_item((int)blockIdx.x, p.num_prefix_splits, rowtiles, p.B * p.Hkv);
-    prefix_body<WAVES, PAGED>(p, level_of(p, rowtiles), lds, it.split, it.rowtile, it.z);
+    // (folded as in the fused launch, where that would be: stages run one at a time give the bits of a whole call)
+    prefix_body<WAVES, PAGED>(p, level_of(p, rowtiles), lds, it.split, it.rowtile, it.z, splits_folded(p));
 }
 
 template <int WAVES>

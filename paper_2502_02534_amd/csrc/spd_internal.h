@@ -63,7 +63,7 @@ struct AttnParams {
     int num_slots;    // prefix splits (of every level) + suffix chunks
     int prefix_slot0; // first slot of the prefix level the prefix fields describe
     int suffix_slot0; // first slot of the suffix chunks
-    float fold_tokens;  // suffix tokens from which a prefix workgroup of the fused launch takes two splits (0: never)
+    float fold_tokens;  // suffix tokens from which a prefix workgroup takes two splits (0: never)
     int stream;       // suffix KV marked as streamed: 0 none, 1 V, 2 K too (see kStreamBytes)
     int num_levels;   // levels of shared prefixes (1 for the plain shared-prefix call)
     void* part_acc;   // [N*Hq][slots][D] normalised partial outputs, fp16 if part_half else fp32;
@@ -137,10 +137,12 @@ __device__ __forceinline__ long long part_index(const AttnParams& p, long long r
     return row * p.num_slots + slot;
 }
 
-// Tokens that the suffixes of the call hold, by every lane of a wavefront: the sum of up to 512 lengths, of every
-// second, third, ... sample where there are more.
-__device__ __forceinline__ float suffix_tokens(const AttnParams& p)
+// Whether a prefix workgroup takes two splits, by every lane of a wavefront (and the same in all of them): the tokens
+// that the suffixes hold, summed over up to 512 lengths, of every second, third, ... sample where there are more.
+__device__ __forceinline__ bool splits_folded(const AttnParams& p)
 {
+    if (!(p.fold_tokens > 0.f))
+        return false;
     const int step = (p.N + 511) / 512;
     float sum = 0.f;
     for (int n = (int)(threadIdx.x & 63) * step; n < p.N; n += 64 * step)
@@ -148,7 +150,7 @@ __device__ __forceinline__ float suffix_tokens(const AttnParams& p)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
         sum += __shfl_xor(sum, o);
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(sum))) * (float)step;
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(sum))) * (float)step >= p.fold_tokens;
 }
 
 hipError_t launch_attn_rows(const AttnParams& p, bool prefix, bool suffix, hipStream_t s);

@@ -52,3 +52,11 @@ def test_splits_folded_by_the_lengths(dev, oracle, hq, hkv, prompts, spp, prefix
     ml = d.workspace[at:at + n * hq * slots * 8].view(torch.float32).reshape(n * hq, slots, 2)
     assert splits >= 2 and bool((ml[:, 0, 1] > 0).all())
     assert bool((ml[:, 1, 1] > 0).all()) != folded and bool((ml[:, 1, 1] == 0).all()) == folded
+    # the stages one call at a time: the same bits
+    full, lse = d.out.clone(), d.lse.clone()
+    d.out.zero_()
+    d.workspace.fill_(255)
+    for stage in (B.STAGE_PREFIX, B.STAGE_SUFFIX, B.STAGE_MERGE):
+        d.run(stage)
+    torch.cuda.synchronize()
+    assert torch.equal(full.view(torch.int16), d.out.view(torch.int16)) and torch.equal(lse, d.lse)
