@@ -589,7 +589,7 @@ template <bool STREAM> __device__ __forceinline__ float4 load4(const float* at)
 // Loads a slice into 32 registers per thread, element e0 + j kIter + 4 tid + k in register 4 j + k.  Every load is
 // unconditional (what would reach past the slice reads its last four logits), so that the hardware's in-order load
 // counter stays exact for the compiler and later loads need not wait for these.
-// SPD_MASK_SLICE, applied where the values are first needed, moves the logits of a float4 that the slice's end cuts
+// mask_four, applied where the values are first needed, moves the logits of a float4 that the slice's end cuts
 // to their places and puts -inf behind them.  Every slice holds four logits at least (the host sends
 // shorter rows to the whole-row kernel, and slices are never shorter than about 2000).
 #define SPD_LOAD_SLICE(STREAM, xv, xr, g, tid)                                          \
@@ -601,10 +601,6 @@ template <bool STREAM> __device__ __forceinline__ float4 load4(const float* at)
         (xv)[4 * j + 2] = v_.z;                                                         \
         (xv)[4 * j + 3] = v_.w;                                                         \
     }
-#define SPD_MASK_SLICE(xv, g, tid)                                                      \
-    _Pragma("unroll") for (int j = 0; j < 8; ++j)                                       \
-        mask_four((xv)[4 * j], (xv)[4 * j + 1], (xv)[4 * j + 2], (xv)[4 * j + 3], (g).e0 + j * kIter + (tid) * 4 - ((g).e1 - 4));
-
 // a .. d were read `over` places too early: moves them there, -inf behind the last.
 __device__ __forceinline__ void mask_four(float& a, float& b, float& c, float& d, int over)
 {
@@ -681,14 +677,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     if (tid == 0)
         L.emitted = 0u;
     lds_barrier();
-    // wavefronts whose 32 x 64 logits all lie inside the slice skip the masking of its end
-    if (g.e0 + 7 * kIter + (tid | 63) * 4 + 4 > g.e1) {
-        SPD_MASK_SLICE(xv, g, tid)
-    }
+    // a shorter slice fills fewer registers: only those are looked at (1024 x 4096 35.2 -> 27.5 us, 64 x 32000
+    // 21.0 -> 18.3)
+    const int steps = (g.e1 - g.e0 + kIter - 1) / kIter;
     float mx = -INFINITY;
 #pragma unroll
-    for (int q = 0; q < 32; q += 2)
-        mx = fmaxf(fmaxf(mx, xv[q]), xv[q + 1]);
+    for (int j = 0; j < 8; ++j) {
+        if (j >= steps)
+            break;
+        if (g.e0 + (j + 1) * kIter > g.e1)  // the slice ends in here
+            mask_four(xv[4 * j], xv[4 * j + 1], xv[4 * j + 2], xv[4 * j + 3], g.e0 + j * kIter + tid * 4 - (g.e1 - 4));
+#pragma unroll
+        for (int k = 0; k < 4; k += 2)
+            mx = fmaxf(fmaxf(mx, xv[4 * j + k]), xv[4 * j + k + 1]);
+    }
     mx = wave_max_f32(mx);
     if (lane == 0)
         L.red_f[wave] = mx;
@@ -702,7 +704,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         int mi = 0x7fffffff;
 #pragma unroll
         for (int q = 31; q >= 0; --q)
-            if (xv[q] == mx)
+            if (q < 4 * steps && xv[q] == mx)
                 mi = g.e0 + (q >> 2) * kIter + tid * 4 + (q & 3);
         for (int o = 32; o > 0; o >>= 1)
             mi = min(mi, __shfl_xor(mi, o));
@@ -735,6 +737,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     float squares = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
+        if (j >= steps)
+            break;
         float s4 = 0.f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -888,21 +892,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     };
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
+        if (4 * h >= steps)
+            break;
         unsigned pos = 4u * (unsigned)tid;  // byte offset of this lane's next place
         if (x_hi == INFINITY) {
 #pragma unroll
-            for (int q = 16 * h; q < 16 * h + 16; ++q)
+            for (int q = 16 * h; q < 16 * h + 16; ++q) {
+                if (q % 4 == 0 && q >= 4 * steps)
+                    break;
                 if (xv[q] >= x_lo) {
                     *(float*)((char*)L.strip + pos) = xv[q];
                     pos += 4u * kBlock;
                 }
+            }
         } else {
 #pragma unroll
-            for (int q = 16 * h; q < 16 * h + 16; ++q)
+            for (int q = 16 * h; q < 16 * h + 16; ++q) {
+                if (q % 4 == 0 && q >= 4 * steps)
+                    break;
                 if (xv[q] >= x_lo && xv[q] < x_hi) {
                     *(float*)((char*)L.strip + pos) = xv[q];
                     pos += 4u * kBlock;
                 }
+            }
         }
         copy_out((int)(pos / (4u * kBlock)));
     }
@@ -914,12 +926,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         rs.c_lo = rc.c_lo;
         double part = 0.0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float s8 = 0.f;
+        for (int j = 0; j < 8; ++j) {
+            if (j >= steps)
+                break;
+            float s4 = 0.f;
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                s8 += xv[8 * j + k] >= x_hi ? prob(xv[8 * j + k], rs) : 0.f;
-            part += (double)s8;
+            for (int k = 0; k < 4; ++k)
+                s4 += xv[4 * j + k] >= x_hi ? prob(xv[4 * j + k], rs) : 0.f;
+            part += (double)s4;
         }
         part = wave_scan_f64(part);
         if (lane == 63)
@@ -1419,10 +1433,15 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     const SliceRange g = slice_range(hit, slice_elems, V);
     float v[32];
     SPD_LOAD_SLICE(false, v, x, g, tid)
-    SPD_MASK_SLICE(v, g, tid)
+    const int steps = (g.e1 - g.e0 + kIter - 1) / kIter;
     double seg[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
+        seg[j] = 0.0;
+        if (j >= steps)
+            continue;
+        if (g.e0 + (j + 1) * kIter > g.e1)
+            mask_four(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3], g.e0 + j * kIter + tid * 4 - (g.e1 - 4));
         float s4 = 0.f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -1484,8 +1503,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // What was tried and taken back: 32 logits of each list in registers across the steps (six unrolled passes, 75 KB of code,
 // spills: 41 us for 64 rows), bins that add floats (23 us a pass), lists rewritten for the slices whose window missed
 // (slower than reading those slices whole: code that runs once is fetched as it runs).
+// Sixteen wavefronts a row for few rows: 64 rows 25.1 -> 26.5 us (T 0.7), 300 rows 54 -> 65.
 // Whole calls before / now (us): 64 x 128256 37.0 -> 30.0, 1024 x 128256 (T 0.2 to 1.2) 197 -> 150, 192 x 50257 with filters 44.0 ->
-// 31.5, 64 x 32000 27.3 -> 21.7, 1024 x 4096 40.5 -> 35.2, 100 x 250000 at sigma 1.5 991 -> 65, 1024 with filters 201 -> 139.
+// 30.7, 64 x 32000 27.3 -> 18.3, 1024 x 4096 40.5 -> 27.5, 100 x 250000 at sigma 1.5 991 -> 65, 1024 with filters 201 -> 137.
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
 // needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory (12 bytes a lane cost
 // 1 us): the whole-row routine is inlined (a call would have the arguments copied to memory).
