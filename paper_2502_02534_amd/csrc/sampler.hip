@@ -1063,7 +1063,7 @@ struct FinishLds {
 
 // One row without (FILTERED = false) or with (true) a min-p / top-k filter, by one workgroup.  False: the
 // row has to go to the whole-row routine.
-template <bool FILTERED>
+template <bool FILTERED, bool MANY>
 __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, int slices, int slice_elems, FinishLds& L)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1112,11 +1112,11 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         unsigned full = (unsigned)__ballot(some && st.count < 0);  // slices that are read again, all of them (bit s)
         const int wps = slices > 4 ? 1 : slices > 2 ? 2 : slices == 2 ? 4 : 8;  // wavefronts per slice
         const int part = wave & (wps - 1), groups = (slices + kWaves - 1) / kWaves;
-        // The listed logits, four per lane and step, two steps requested ahead: a slice belongs to one wavefront (to 2,
+        // The listed logits, four per lane and step, two steps requested ahead (one where four workgroups share a CU): a slice belongs to one wavefront (to 2,
         // 4, 8 where there are no more than 4, 2, 1 slices).  Then the slices that are read again, by all wavefronts.
         // f(four logits, slice) for every step, end(slice) behind a slice; no barriers inside.
         auto for_all = [&](auto f, auto end) __attribute__((always_inline)) {
-            constexpr int kAhead = 2;
+            constexpr int kAhead = MANY ? 1 : 2;
             unsigned left = full;
             for (int n = 0; n < groups + __popc(full); ++n) {
                 int s, first, step, count;
@@ -1509,16 +1509,18 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
 // needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory (12 bytes a lane cost
 // 1 us): the whole-row routine is inlined (a call would have the arguments copied to memory).
-template <bool ANY>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
+// MANY: 64 registers instead of 80 and four workgroups a CU, for numbers of rows that take fewer rounds so; only one step of the
+// lists requested ahead and a few spilled registers are what that costs, half a microsecond to two where the rounds are as many.
+template <bool ANY, bool MANY>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MANY ? 8 : 6))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
 {
     __shared__ FinishLds L;
     const long long r = blockIdx.x;
     bool done;
     if (ANY && sp.temperature[r] != 0.f && ((sp.top_k && sp.top_k[r] > 0) || (sp.min_p && sp.min_p[r] > 0.f)))
-        done = finish_row<true>(sp, ws, slices, slice_elems, L);
+        done = finish_row<true, MANY>(sp, ws, slices, slice_elems, L);
     else
-        done = finish_row<false>(sp, ws, slices, slice_elems, L);
+        done = finish_row<false, MANY>(sp, ws, slices, slice_elems, L);
     if (!done) {
         __syncthreads();
         sample_row_from_memory(sp, r, L.row);
@@ -1578,8 +1580,13 @@ hipError_t launch_sampler(const SamplerParams& p, void* ws, hipStream_t s)
     const bool stream = 4.0 * (double)p.rows * (double)p.vocab >= 256e6;
     hipLaunchKernelGGL(stream ? sampler_scan_kernel<true> : sampler_scan_kernel<false>, dim3((unsigned)(p.rows * slices)), dim3(kBlock), 0, s, p, (char*)ws, slices,
                        slice_elems);
-    hipLaunchKernelGGL(filters ? sampler_finish_kernel<true> : sampler_finish_kernel<false>, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p, (char*)ws,
-                       slices, slice_elems);
+    // Four row-level workgroups a CU (1024 at once) instead of three (768) where that takes fewer rounds; three / four, us a call:
+    // 800 x 50256 63.5 / 60.6, 1024 x 128256 153.8 / 145.0, 1024 x 32000 56.4 / 53.8, 4096 x 8192 94.6 / 90.1; as many rounds:
+    // 1536 x 50256 106.0 / 108.2, 512 x 128256 81.2 / 82.1.  With filters three (1024 x 128256, top-k 50: 133.1 / 134.4).
+    const auto finish = filters                                          ? sampler_finish_kernel<true, false>
+                        : (p.rows + 1023) / 1024 < (p.rows + 767) / 768 ? sampler_finish_kernel<false, true>
+                                                                         : sampler_finish_kernel<false, false>;
+    hipLaunchKernelGGL(finish, dim3((unsigned)p.rows), dim3(kBlock), 0, s, p, (char*)ws, slices, slice_elems);
     return hipGetLastError();
 }
 

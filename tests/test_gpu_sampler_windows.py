@@ -52,3 +52,26 @@ def test_windows_that_miss_and_cuts_far_down(dev, oracle, vocab, filters):
     torch.cuda.synchronize()
     o = oracle.sample_tokens_filtered(x, t, top_p, u, top_k, min_p) if filters else oracle.sample_tokens(x, t, top_p, u)
     compare_tokens(tokens.cpu().numpy(), o, u, vocab)
+
+
+@pytest.mark.parametrize("filters", [False, True])
+@pytest.mark.parametrize("rows, vocab", [(768, 5249), (769, 5249), (1025, 6144), (771, 40003)])
+def test_more_rows_than_three_workgroups_a_cu(dev, oracle, rows, vocab, filters):
+    from paper_2502_02534_amd import binding as B
+    print(f"{rows} x {vocab}, filters {filters}", flush=True)
+    rng = np.random.default_rng(rows + vocab)
+    x = (rng.standard_normal((rows, vocab)) * rng.choice([0.3, 3.0], (rows, 1))).astype(np.float32)
+    x[::97] += np.linspace(4.0, -4.0, vocab, dtype=np.float32)     # windows that miss
+    t = rng.choice(np.array([0.0, 0.7, 1.0], np.float32), rows)
+    top_p = rng.choice(np.array([0.5, 0.95, 1.0], np.float32), rows)
+    u = rng.random(rows, dtype=np.float32)
+    top_k = rng.choice(np.array([0, 1, 600], np.int32), rows) if filters else None
+    min_p = rng.choice(np.array([0.0, 0.01], np.float32), rows) if filters else None
+    to = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ws = torch.full((B.sample_tokens_workspace_size(rows, vocab),), 255, dtype=torch.uint8, device="cuda")
+    tokens = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+    xd, td, pd, ud, kd, md = to(x), to(t), to(top_p), to(u), to(top_k), to(min_p)
+    B.sample_tokens_filtered(xd, B.SPD_F32, rows, vocab, vocab, td, pd, kd, md, ud, tokens, ws)
+    torch.cuda.synchronize()
+    o = oracle.sample_tokens_filtered(x, t, top_p, u, top_k, min_p) if filters else oracle.sample_tokens(x, t, top_p, u)
+    compare_tokens(tokens.cpu().numpy(), o, u, vocab)
