@@ -637,6 +637,7 @@ struct ScanLds {
     float strip[kStrip][kBlock];   // each lane's listed logits
     double mass[kWaves];
     float red_f[kWaves];
+    float squares[kWaves];         // (not red_f again: a wavefront may still be reading the maxima there)
     int red_i[kWaves];
     float x_lo, x_hi;
     unsigned emitted;              // places reserved in the slice's list so far
@@ -760,7 +761,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
     squares = wave_scan_f32(squares);
     if (lane == 63) {
         L.mass[wave] = m;
-        L.red_f[wave] = squares;
+        L.squares[wave] = squares;
     }
     lds_barrier();
     if (wave == 0) {
@@ -768,7 +769,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         float sq = 0.f;
         for (int w = 0; w < kWaves; ++w) {
             S += L.mass[w];
-            sq += L.red_f[w];
+            sq += L.squares[w];
         }
         float x_lo = INFINITY, x_hi = INFINITY, x_cut = 0.f;
         if (cut) {
