@@ -1012,16 +1012,16 @@ __device__ __forceinline__ BinPick block_pick(const unsigned* H, double unit, do
 // Folds eight per-lane partial sums (one per 256-element segment j of the wavefront's pass) across the
 // wavefront: after the exchange across 32 lanes each half keeps four segments, then two, then one,
 // so that lanes 8 s .. 8 s + 7 end up with the sum of segment s (10 exchanges instead of 48).
-__device__ __forceinline__ double fold_segments(const double (&s_seg)[8])
+__device__ __forceinline__ double fold_segments(const float (&s_seg)[8])
 {
     const int lane = threadIdx.x & 63;
     const bool up32 = (lane & 32) != 0, up16 = (lane & 16) != 0, up8 = (lane & 8) != 0;
     double a4[4], a2[2], a1;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const double keep = up32 ? s_seg[4 + j] : s_seg[j];
-        const double give = up32 ? s_seg[j] : s_seg[4 + j];
-        a4[j] = keep + __shfl_xor(give, 32);
+        const float keep = up32 ? s_seg[4 + j] : s_seg[j];
+        const float give = up32 ? s_seg[j] : s_seg[4 + j];
+        a4[j] = (double)keep + (double)__shfl_xor(give, 32);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -1056,6 +1056,7 @@ struct FinishLds {
     double upper[kDirect];           // sums of what is not below, cut among wavefronts
     PickLds pick;
     double slice_mass[kMaxSlices];   // kept mass of every slice
+    double above[kMaxSlices];        // what lies above each slice's window
     unsigned cands;
     uint32_t best;
     int differ;
@@ -1187,7 +1188,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         // looked for first
         const float reach = wave_max_f32(some && st.count >= 0 ? st.x_lo : -INFINITY);
         const float start = wave_max_f32(some ? st.x_cut : -INFINITY) + 0.03125f * octave64;
-        const double above_s = some && !FILTERED ? st.above * scale : 0.0;  // lane s: what lies above slice s's window
+        if (!FILTERED && tid < kMaxSlices)
+            L.above[tid] = some ? st.above * scale : 0.0;  // (read behind the next barrier)
         for (int stage = FILTERED && top_k > 0 ? 0 : 1; stage < 2; ++stage) {
             // stage 0 (rows with top-k): the k-th largest logit of what min-p leaves; stage 1: the nucleus cut
             by_count = FILTERED && stage == 0;
@@ -1232,7 +1234,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     break;
                 __syncthreads();
             }
-            const double need = of_lane(by_count ? (double)top_k : (double)top_p * S, 0);  // (in scalar registers)
+            float share = uniform(top_p);
+            asm volatile("" : "+s"(share));  // (formed here, not ahead of the loop, where it would take a vector register pair)
+            const double need = of_lane(by_count ? (double)top_k : (double)share * S, 0);  // (in scalar registers)
             // Steps that narrow [x_cand, x_above) down: bin what lies there, find the bins that take the running mass across
             // `need`, sum up what lies above them and list what lies in them.  One is enough, but for many equal or
             // nearly equal logits, and where a window does not reach around the bins.
@@ -1279,9 +1283,10 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     },
                     [](int) {});
                 // (what lies above a window counts from its edge on)
-                if (tries == 0 && wave == 0 && above_s > 0.0 && !((full >> lane) & 1u)) {
+                if (!FILTERED && tries == 0 && tid < kMaxSlices && !((full >> lane) & 1u)) {
+                    const double above_s = L.above[tid];
                     const float bin = fmaxf((st.x_hi - top) * per, 0.f);
-                    if (bin < (float)kBins)
+                    if (above_s > 0.0 && bin < (float)kBins)
                         atomicAdd(&L.bins[(unsigned)bin], (unsigned)(above_s / unit));
                 }
                 upper = wave_reduce_u32(upper, 0u, [](unsigned a, unsigned b) { return a + b; });
@@ -1289,7 +1294,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     atomicAdd(&L.bins[0], upper);
                 lds_barrier();
                 // (the bins' masses are good to 1e-6 of what is binned; a miss is noticed below)
-                const double tol = by_count ? 0.5 : 2e-6 * binned;
+                const double tol = of_lane(by_count ? 0.5 : 2e-6 * binned, 0);
                 const BinPick e = block_pick(L.bins, unit, above, need - tol, by_count ? need - tol : need + tol, L.pick);
                 const int lo = __builtin_amdgcn_readfirstlane(e.lo), hi = __builtin_amdgcn_readfirstlane(e.hi);
                 // (wider by the rounding of all this)
@@ -1329,7 +1334,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 if (by_count && e.total < need - tol)
                     break;  // there are no k: all of them
                 if (tid < kMaxSlices)
-                    L.slice_mass[tid] = (full >> lane) & 1u ? 0.0 : above_s;
+                    L.slice_mass[tid] = FILTERED || ((full >> lane) & 1u) ? 0.0 : L.above[tid];
                 lds_barrier();
                 double sure = 0.0;
                 for_all(
@@ -1435,10 +1440,10 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     float v[32];
     SPD_LOAD_SLICE(false, v, x, g, tid)
     const int steps = (g.e1 - g.e0 + kIter - 1) / kIter;
-    double seg[8];
+    float seg[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        seg[j] = 0.0;
+        seg[j] = 0.f;
         if (j >= steps)
             continue;
         if (g.e0 + (j + 1) * kIter > g.e1)
@@ -1449,7 +1454,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             v[4 * j + k] = v[4 * j + k] >= x_tau ? prob(v[4 * j + k], rs) : 0.f;
             s4 += v[4 * j + k];
         }
-        seg[j] = (double)s4;
+        seg[j] = s4;
     }
     const double own = fold_segments(seg);
     if ((lane & 7) == 0)
@@ -1508,10 +1513,11 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // Whole calls before / now (us): 64 x 128256 37.0 -> 30.0, 1024 x 128256 (T 0.2 to 1.2) 197 -> 150, 192 x 50257 with filters 44.0 ->
 // 30.7, 64 x 32000 27.3 -> 18.3, 1024 x 4096 40.5 -> 27.5, 100 x 250000 at sigma 1.5 991 -> 65, 1024 with filters 201 -> 137.
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
-// needs in one launch, so that the two kinds run side by side.  Neither instantiation uses scratch memory (12 bytes a lane cost
-// 1 us): the whole-row routine is inlined (a call would have the arguments copied to memory).
+// needs in one launch, so that the two kinds run side by side.  No instantiation uses scratch memory (12 bytes a lane cost
+// 1 us): the whole-row routine is inlined (a call would have the arguments copied to memory), what a slice has above its window
+// waits in LDS, and the thresholds of a stage are formed in it, in scalar registers.
 // MANY: 64 registers instead of 80 and four workgroups a CU, for numbers of rows that take fewer rounds so; only one step of the
-// lists requested ahead and a few spilled registers are what that costs, half a microsecond to two where the rounds are as many.
+// lists requested ahead is what that costs, half a microsecond to two where the rounds are as many.
 template <bool ANY, bool MANY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MANY ? 8 : 6))) void sampler_finish_kernel(SamplerParams sp, char* ws, int slices, int slice_elems)
 {
