@@ -1262,7 +1262,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     L.differ = 0;
                 }
                 lds_barrier();  // (the bins are cleared)
-                unsigned upper = 0u;  // what lies above the bins
+                unsigned upper = 0u, beyond = 0u;  // what lies above the bins, and (counts) past the last
                 for_all(
                     [&](const float (&v)[4], int) __attribute__((always_inline)) {
 #pragma unroll
@@ -1277,6 +1277,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                             if (tries > 0)  // (what lies above is in `above` by then)
                                 w = v[k] < x_above ? w : 0u;
                             upper += d > 0.f ? w : 0u;
+                            if (FILTERED)
+                                beyond += by_count && bin >= (float)kBins ? w : 0u;
                             if (d <= 0.f && bin < (float)kBins)
                                 atomicAdd(&L.bins[(unsigned)bin], w);
                         }
@@ -1292,11 +1294,17 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 upper = wave_reduce_u32(upper, 0u, [](unsigned a, unsigned b) { return a + b; });
                 if (lane == 0 && upper)
                     atomicAdd(&L.bins[0], upper);
+                if (FILTERED && by_count) {  // the last bin has no end: the k-th may lie further down than bins reach
+                    beyond = wave_reduce_u32(beyond, 0u, [](unsigned a, unsigned b) { return a + b; });
+                    if (lane == 0 && beyond)
+                        atomicAdd(&L.bins[kBins - 1], beyond);
+                }
                 lds_barrier();
                 // (the bins' masses are good to 1e-6 of what is binned; a miss is noticed below)
                 const double tol = of_lane(by_count ? 0.5 : 2e-6 * binned, 0);
                 const BinPick e = block_pick(L.bins, unit, above, need - tol, by_count ? need - tol : need + tol, L.pick);
-                const int lo = __builtin_amdgcn_readfirstlane(e.lo), hi = __builtin_amdgcn_readfirstlane(e.hi);
+                const int lo = __builtin_amdgcn_readfirstlane(e.lo);
+                const int hi = by_count && e.hi == kBins - 1 ? kBins : __builtin_amdgcn_readfirstlane(e.hi);
                 // (wider by the rounding of all this)
                 const float slack = 4e-3f * width + ulps, below_bins = tries > 0 ? x_cand : -3.402823466e38f;
                 const float next_above = lo <= 0 ? x_above : fminf(x_above, top - (float)lo * width + slack);
@@ -1331,8 +1339,11 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     lds_barrier();
                 }
                 *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
-                if (by_count && e.total < need - tol)
-                    break;  // there are no k: all of them
+                if (by_count && e.total < need - tol) {
+                    if (tries > 0)
+                        return false;  // (there were k when all of them were counted)
+                    break;             // there are no k: all of them
+                }
                 if (tid < kMaxSlices)
                     L.slice_mass[tid] = FILTERED || ((full >> lane) & 1u) ? 0.0 : L.above[tid];
                 lds_barrier();
