@@ -1182,8 +1182,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         float x_floor = -INFINITY;  // rows with a filter: the lowest logit that survives it
         bool by_count = false;
         auto weight = [&](float xq) __attribute__((always_inline)) { return FILTERED && by_count ? (prob(xq, rs) >= min_p ? 1.f : 0.f) : prob(xq, rs); };
-        // 64 octaves of p; rounding of the logits' places
-        const float octave64 = uniform(64.f * __builtin_amdgcn_rcpf(rc.c_hi)), ulps = uniform(4e-7f * fabsf(M));
+        const float octave64 = uniform(64.f * __builtin_amdgcn_rcpf(rc.c_hi));  // 64 octaves of p
         // where all lists reach down to, and two octaves above the highest of the slices' own cuts: where the row's is
         // looked for first
         const float reach = wave_max_f32(some && st.count >= 0 ? st.x_lo : -INFINITY);
@@ -1242,7 +1241,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             // nearly equal logits, and where a window does not reach around the bins.
             double above = 0.0, binned = S, next_binned = S;
             int n = 0;
-            bool equal = false;
+            bool equal = false, all = false;
             int rounds = 0;
             x_above = INFINITY;
             x_cand = reach;
@@ -1305,8 +1304,10 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 const BinPick e = block_pick(L.bins, unit, above, need - tol, by_count ? need - tol : need + tol, L.pick);
                 const int lo = __builtin_amdgcn_readfirstlane(e.lo);
                 const int hi = by_count && e.hi == kBins - 1 ? kBins : __builtin_amdgcn_readfirstlane(e.hi);
-                // (wider by the rounding of all this)
-                const float slack = 4e-3f * width + ulps, below_bins = tries > 0 ? x_cand : -3.402823466e38f;
+                // (wider by the rounding of all this: of a bin's number, which grows with its distance from the top, and of the edges,
+                // by what the logits there are rounded to, whatever the maximum is; an edge that fell on the value of a
+                // tie would count all of it as above)
+                const float slack = 4e-3f * width + 4e-7f * fmaxf(fabsf(top), fabsf(top - range)), below_bins = tries > 0 ? x_cand : -3.402823466e38f;
                 const float next_above = lo <= 0 ? x_above : fminf(x_above, top - (float)lo * width + slack);
                 x_cand = uniform(hi >= kBins ? below_bins : fmaxf(below_bins, top - (float)(hi + 1) * width - slack));
                 x_above = uniform(next_above);
@@ -1342,7 +1343,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 if (by_count && e.total < need - tol) {
                     if (tries > 0)
                         return false;  // (there were k when all of them were counted)
-                    break;             // there are no k: all of them
+                    all = true;        // there are no k: all of them
+                    break;
                 }
                 if (tid < kMaxSlices)
                     L.slice_mass[tid] = FILTERED || ((full >> lane) & 1u) ? 0.0 : L.above[tid];
@@ -1419,8 +1421,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             lds_barrier();
             const uint32_t best = L.best;
             // (0: all of them together fall short)
-            if (!by_count && !(above < need && best))
-                return false;  // the bins missed the cut
+            if (!all && !(above < need && best))
+                return false;  // the bins missed the threshold
             const float x_cut = uniform(best ? key_value(best) : -INFINITY);
             if (by_count) {
                 x_floor = x_cut;
