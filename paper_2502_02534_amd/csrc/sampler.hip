@@ -744,7 +744,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const float d = xv[4 * j + k] - ref;
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(d, c_hi, d * c_lo));
+            // (a logit that is not a number: zero, as in prob(); 0 .. 1 is a modifier of the instruction and costs nothing)
+            const float p = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(d, c_hi, d * c_lo)), 0.f, 1.f);
             s4 += p;
             squares = __builtin_fmaf(p, p, squares);
             if (k == (j & 3) && cut) {
