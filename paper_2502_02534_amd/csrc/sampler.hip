@@ -167,6 +167,7 @@ __device__ void pick_bin(const double* hist, double above, double need, int* bin
         scratch[wave] = incl;
     __syncthreads();
     double before = above + (incl - own);
+#pragma unroll 1  // (unrolled it takes registers that the row-level kernels do not have)
     for (int w = 0; w < wave; ++w)
         before += scratch[w];
     int best = -1, low = kBins;
@@ -195,6 +196,7 @@ __device__ void pick_bin(const double* hist, double above, double need, int* bin
     } else if (chosen <= top && chosen > top - kBinsPerThread) {
         // everything above the lowest non-empty bin
         double b2 = above + (incl - own);
+#pragma unroll 1
         for (int w = 0; w < wave; ++w)
             b2 += scratch[w];
         for (int k = 0; k < top - chosen; ++k)
@@ -1094,6 +1096,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         return true;
     }
     RowConst rc = row_const(T);
+    if ((cut || FILTERED) && rc.cd == 0.0)
+        return false;  // an infinite temperature: all tokens tie, whatever their logits are
     rc.c_hi = uniform(rc.c_hi);
     rc.c_lo = uniform(rc.c_lo);
     RowScale rs;
@@ -1443,7 +1447,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     const unsigned long long past = __ballot(kept > 0.0 && inc > target), any = __ballot(kept > 0.0);
     bool take_last = past == 0ull;
     const int hit = past ? __ffsll((long long)past) - 1 : any ? 63 - __clzll((long long)any) : -1;
-    if (hit < 0) {
+    if (hit < 0) {  // (nothing has any mass)
+        if (FILTERED)
+            return false;
         if (tid == 0)
             sp.tokens[r] = 0;
         return true;
