@@ -1062,8 +1062,7 @@ struct FinishLds {
     double above[kMaxSlices];        // what lies above each slice's window
     unsigned cands;
     uint32_t best;
-    int differ;
-    float lowest[kWaves];
+    float lowest[kWaves], highest[kWaves];
 };
 
 // One row without (FILTERED = false) or with (true) a min-p / top-k filter, by one workgroup.  False: the
@@ -1246,115 +1245,119 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             // nearly equal logits, and where a window does not reach around the bins.
             double above = 0.0, binned = S, next_binned = S;
             int n = 0;
-            bool equal = false, all = false;
+            bool equal = false, all = false;  // (of the candidates; there are no k logits)
+            uint32_t tie = 0u;                // equal candidates: their key, if the threshold lies there
             int rounds = 0;
             x_above = INFINITY;
             x_cand = reach;
             for (int tries = 0;; ++tries) {
-                const float top = tries == 0 && rounds == 0 ? fminf(start, M) : fminf(x_above, M);
-                const float range = uniform(fminf(fmaxf(top - x_cand, 1e-30f), (tries > 1 ? 256.f : 1.f) * octave64));
-                const float per = uniform(-(float)kBins * __builtin_amdgcn_rcpf(range)), width = range * (1.f / (float)kBins);  // bins (counted down)
-                // a unit is 2^-31 of what is binned, rounded up to a power of two (no bin overflows), but for the rounding of
-                // its logarithm
-                const int power = ((__double2hiint(binned) >> 20) & 0x7ff) - 1022;
-                const double log_exact = (double)(31 - power) + ((double)top - (double)M) * rc.cd;
-                const float log_unit = uniform((float)log_exact);
-                const double unit = by_count ? 1.0 : of_lane(ldexp(1.0 + 0.6931471805599453 * (log_exact - (double)log_unit), power - 31), 0);
-                if (tid == 0) {
-                    L.cands = 0u;
-                    L.best = 0u;
-                    L.differ = 0;
-                }
-                lds_barrier();  // (the bins are cleared)
-                unsigned upper = 0u, beyond = 0u;  // what lies above the bins, and (counts) past the last
-                for_all(
-                    [&](const float (&v)[4], int) __attribute__((always_inline)) {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const float d = v[k] - top, bin = d * per;
-                            unsigned w = (unsigned)(__builtin_amdgcn_exp2f(__builtin_fmaf(d, rc.c_hi, log_unit)) + 0.5f);
-                            if (FILTERED) {
-                                if (by_count)
-                                    w = v[k] > -INFINITY && weight(v[k]) > 0.f ? 1u : 0u;
-                                w = v[k] >= x_floor ? w : 0u;
-                            }
-                            if (tries > 0)  // (what lies above is in `above` by then)
-                                w = v[k] < x_above ? w : 0u;
-                            upper += d > 0.f ? w : 0u;
-                            if (FILTERED)
-                                beyond += by_count && bin >= (float)kBins ? w : 0u;
-                            if (d <= 0.f && bin < (float)kBins)
-                                atomicAdd(&L.bins[(unsigned)bin], w);
-                        }
-                    },
-                    [](int) {});
-                // (what lies above a window counts from its edge on)
-                if (!FILTERED && tries == 0 && tid < kMaxSlices && !((full >> lane) & 1u)) {
-                    const double above_s = L.above[tid];
-                    const float bin = fmaxf((st.x_hi - top) * per, 0.f);
-                    if (above_s > 0.0 && bin < (float)kBins)
-                        atomicAdd(&L.bins[(unsigned)bin], (unsigned)(above_s / unit));
-                }
-                upper = wave_reduce_u32(upper, 0u, [](unsigned a, unsigned b) { return a + b; });
-                if (lane == 0 && upper)
-                    atomicAdd(&L.bins[0], upper);
-                if (FILTERED && by_count) {  // the last bin has no end: the k-th may lie further down than bins reach
-                    beyond = wave_reduce_u32(beyond, 0u, [](unsigned a, unsigned b) { return a + b; });
-                    if (lane == 0 && beyond)
-                        atomicAdd(&L.bins[kBins - 1], beyond);
-                }
-                lds_barrier();
-                // (the bins' masses are good to 1e-6 of what is binned; a miss is noticed below)
-                const double tol = of_lane(by_count ? 0.5 : 2e-6 * binned, 0);
-                const BinPick e = block_pick(L.bins, unit, above, need - tol, by_count ? need - tol : need + tol, L.pick);
-                const int lo = __builtin_amdgcn_readfirstlane(e.lo);
-                const int hi = by_count && e.hi == kBins - 1 ? kBins : __builtin_amdgcn_readfirstlane(e.hi);
-                // (wider by the rounding of all this: of a bin's number, which grows with its distance from the top, and of the edges,
-                // by what the logits there are rounded to, whatever the maximum is; an edge that fell on the value of a
-                // tie would count all of it as above)
-                const float slack = 4e-3f * width + 4e-7f * fmaxf(fabsf(top), fabsf(top - range)), below_bins = tries > 0 ? x_cand : -3.402823466e38f;
-                const float next_above = lo <= 0 ? x_above : fminf(x_above, top - (float)lo * width + slack);
-                x_cand = uniform(hi >= kBins ? below_bins : fmaxf(below_bins, top - (float)(hi + 1) * width - slack));
-                x_above = uniform(next_above);
-                // does every slice's window reach around them?  (rows with a filter: all survivors are listed)
-                if (!(FILTERED && !by_count)) {
-                    // (what is listed reaches `need` nowhere: the cut lies below some windows, an octave and more is tried)
-                    if (hi >= kBins && !by_count && rounds < 6)
-                        x_cand = uniform(wave_max_f32(some && !((full >> lane) & 1u) ? st.x_lo : -INFINITY) - octave64 * 0.015625f * (float)(1 << rounds));
-                    const bool below = st.x_lo <= x_cand || (by_count && prob(st.x_lo, rs) < min_p);
-                    const unsigned lacking = (unsigned)__ballot(some && !(below && st.x_hi >= x_above)) & ~full;
-                    if (lacking != 0u) {
-                        // once more from the start, with all logits of those slices
-                        full |= lacking;
-                        ++rounds;
-                        above = 0.0;
-                        binned = S;
-                        x_above = INFINITY;
-                        x_cand = -3.402823466e38f;
-                        tries = -1;
-                        *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
-                        continue;
+                if (!equal) {
+                    const float top = tries == 0 && rounds == 0 ? fminf(start, M) : fminf(x_above, M);
+                    const float range = uniform(fminf(fmaxf(top - x_cand, 1e-30f), (tries > 1 ? 256.f : 1.f) * octave64));
+                    const float per = uniform(-(float)kBins * __builtin_amdgcn_rcpf(range)), width = range * (1.f / (float)kBins);  // bins (counted down)
+                    // a unit is 2^-31 of what is binned, rounded up to a power of two (no bin overflows), but for the rounding of
+                    // its logarithm
+                    const int power = ((__double2hiint(binned) >> 20) & 0x7ff) - 1022;
+                    const double log_exact = (double)(31 - power) + ((double)top - (double)M) * rc.cd;
+                    const float log_unit = uniform((float)log_exact);
+                    const double unit = by_count ? 1.0 : of_lane(ldexp(1.0 + 0.6931471805599453 * (log_exact - (double)log_unit), power - 31), 0);
+                    if (tid == 0) {
+                        L.cands = 0u;
+                        L.best = 0u;
                     }
-                }
-                if (!by_count) {  // what the bins from lo to hi hold: all that another step bins
-                    unsigned inside = 0u;
-                    for (int b = max(lo, 0) + lane; b <= min(hi, kBins - 1); b += 64)
-                        inside += L.bins[b];
-                    inside = wave_reduce_u32(inside, 0u, [](unsigned a, unsigned b) { return a + b; });
-                    next_binned = of_lane(hi >= kBins ? binned : (double)inside * unit * 1.001 + 1e-30, 0);
+                    lds_barrier();  // (the bins are cleared)
+                    unsigned upper = 0u, beyond = 0u;  // what lies above the bins, and (counts) past the last
+                    for_all(
+                        [&](const float (&v)[4], int) __attribute__((always_inline)) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const float d = v[k] - top, bin = d * per;
+                                unsigned w = (unsigned)(__builtin_amdgcn_exp2f(__builtin_fmaf(d, rc.c_hi, log_unit)) + 0.5f);
+                                if (FILTERED) {
+                                    if (by_count)
+                                        w = v[k] > -INFINITY && weight(v[k]) > 0.f ? 1u : 0u;
+                                    w = v[k] >= x_floor ? w : 0u;
+                                }
+                                if (tries > 0)  // (what lies above is in `above` by then)
+                                    w = v[k] < x_above ? w : 0u;
+                                upper += d > 0.f ? w : 0u;
+                                if (FILTERED)
+                                    beyond += by_count && bin >= (float)kBins ? w : 0u;
+                                if (d <= 0.f && bin < (float)kBins)
+                                    atomicAdd(&L.bins[(unsigned)bin], w);
+                            }
+                        },
+                        [](int) {});
+                    // (what lies above a window counts from its edge on)
+                    if (!FILTERED && tries == 0 && tid < kMaxSlices && !((full >> lane) & 1u)) {
+                        const double above_s = L.above[tid];
+                        const float bin = fmaxf((st.x_hi - top) * per, 0.f);
+                        if (above_s > 0.0 && bin < (float)kBins)
+                            atomicAdd(&L.bins[(unsigned)bin], (unsigned)(above_s / unit));
+                    }
+                    upper = wave_reduce_u32(upper, 0u, [](unsigned a, unsigned b) { return a + b; });
+                    if (lane == 0 && upper)
+                        atomicAdd(&L.bins[0], upper);
+                    if (FILTERED && by_count) {  // the last bin has no end: the k-th may lie further down than bins reach
+                        beyond = wave_reduce_u32(beyond, 0u, [](unsigned a, unsigned b) { return a + b; });
+                        if (lane == 0 && beyond)
+                            atomicAdd(&L.bins[kBins - 1], beyond);
+                    }
                     lds_barrier();
-                }
-                *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
-                if (by_count && e.total < need - tol) {
-                    if (tries > 0)
-                        return false;  // (there were k when all of them were counted)
-                    all = true;        // there are no k: all of them
-                    break;
+                    // (the bins' masses are good to 1e-6 of what is binned; a miss is noticed below)
+                    const double tol = of_lane(by_count ? 0.5 : 2e-6 * binned, 0);
+                    const BinPick e = block_pick(L.bins, unit, above, need - tol, by_count ? need - tol : need + tol, L.pick);
+                    const int lo = __builtin_amdgcn_readfirstlane(e.lo);
+                    const int hi = by_count && e.hi == kBins - 1 ? kBins : __builtin_amdgcn_readfirstlane(e.hi);
+                    // (wider by the rounding of all this: of a bin's number, which grows with its distance from the top, and of the edges,
+                    // by what the logits there are rounded to, whatever the maximum is; an edge that fell on the value of a
+                    // tie would count all of it as above)
+                    const float slack = 4e-3f * width + 4e-7f * fmaxf(fabsf(top), fabsf(top - range)), below_bins = tries > 0 ? x_cand : -3.402823466e38f;
+                    const float next_above = lo <= 0 ? x_above : fminf(x_above, top - (float)lo * width + slack);
+                    x_cand = uniform(hi >= kBins ? below_bins : fmaxf(below_bins, top - (float)(hi + 1) * width - slack));
+                    x_above = uniform(next_above);
+                    // does every slice's window reach around them?  (rows with a filter: all survivors are listed)
+                    if (!(FILTERED && !by_count)) {
+                        // (what is listed reaches `need` nowhere: the cut lies below some windows, an octave and more is tried)
+                        if (hi >= kBins && !by_count && rounds < 6)
+                            x_cand = uniform(wave_max_f32(some && !((full >> lane) & 1u) ? st.x_lo : -INFINITY) - octave64 * 0.015625f * (float)(1 << rounds));
+                        const bool below = st.x_lo <= x_cand || (by_count && prob(st.x_lo, rs) < min_p);
+                        const unsigned lacking = (unsigned)__ballot(some && !(below && st.x_hi >= x_above)) & ~full;
+                        if (lacking != 0u) {
+                            // once more from the start, with all logits of those slices
+                            full |= lacking;
+                            ++rounds;
+                            above = 0.0;
+                            binned = S;
+                            x_above = INFINITY;
+                            x_cand = -3.402823466e38f;
+                            tries = -1;
+                            *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
+                            continue;
+                        }
+                    }
+                    if (!by_count) {  // what the bins from lo to hi hold: all that another step bins
+                        unsigned inside = 0u;
+                        for (int b = max(lo, 0) + lane; b <= min(hi, kBins - 1); b += 64)
+                            inside += L.bins[b];
+                        inside = wave_reduce_u32(inside, 0u, [](unsigned a, unsigned b) { return a + b; });
+                        next_binned = of_lane(hi >= kBins ? binned : (double)inside * unit * 1.001 + 1e-30, 0);
+                        lds_barrier();
+                    }
+                    *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
+                    if (by_count && e.total < need - tol) {
+                        if (tries > 0)
+                            return false;  // (there were k when all of them were counted)
+                        all = true;        // there are no k: all of them
+                        n = 0;
+                        break;
+                    }
                 }
                 if (tid < kMaxSlices)
                     L.slice_mass[tid] = FILTERED || ((full >> lane) & 1u) ? 0.0 : L.above[tid];
                 lds_barrier();
                 double sure = 0.0;
+                float least = INFINITY, most = -INFINITY;  // of the candidates
                 for_all(
                     [&](const float (&v)[4], int s) __attribute__((always_inline)) {
                         float s4 = 0.f;
@@ -1363,6 +1366,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                             const float xq = FILTERED && !(v[k] >= x_floor) ? -INFINITY : v[k], w = weight(xq);
                             s4 += xq >= x_above ? w : 0.f;
                             if (xq >= x_cand && xq < x_above) {
+                                least = fminf(least, xq);
+                                most = fmaxf(most, xq);
                                 const unsigned at = atomicAdd(&L.cands, 1u);
                                 if (at < (unsigned)kDirect) {
                                     L.cand[at] = make_float2(xq, w);
@@ -1380,27 +1385,45 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     });
                 lds_barrier();
                 kept = mine ? L.slice_mass[lane] : 0.0;
+                if (equal)
+                    break;
                 above = wave_total(kept);
                 n = __builtin_amdgcn_readfirstlane((int)L.cands);
+                if (n > 64) {
+                    least = -wave_max_f32(-least);
+                    most = wave_max_f32(most);
+                    if (lane == 0) {
+                        L.lowest[wave] = least;
+                        L.highest[wave] = most;
+                    }
+                    lds_barrier();
+                    for (int w = 0; w < kWaves; ++w) {
+                        least = fminf(least, L.lowest[w]);
+                        most = fmaxf(most, L.highest[w]);
+                    }
+                    equal = least == most;
+                    if (equal) {
+                        // any number of equal ones needs no list: they are the threshold or it was missed.  What each slice
+                        // keeps comes from one more pass over the lists where there are more than the list of candidates holds.
+                        if (above < need && above + (double)n * (double)weight(least) >= need)
+                            tie = order_key(least);
+                        if (!tie || by_count || n <= kDirect)
+                            break;
+                        x_above = least;
+                        x_cand = INFINITY;
+                        continue;
+                    }
+                }
                 if (n <= kDirect)
                     break;
                 if (tries == 3)
-                    return false;  // hundreds of equal logits at the cut
+                    return false;  // hundreds of nearly equal logits at the cut
                 binned = next_binned;
                 __syncthreads();
             }
             // ---- the threshold among them: every thread sums what is not below its own (where there are fewer than eight
-            // wavefronts' worth, the wavefronts share the sums); equal ones need no sums ----
-            if (n > 64) {
-                if (tid < n && L.cand[tid].x != L.cand[0].x)
-                    L.differ = 1;
-                lds_barrier();
-                equal = L.differ == 0;
-            }
-            if (equal) {
-                if (tid == 0 && above + (double)n * (double)L.cand[0].y >= need)
-                    L.best = order_key(L.cand[0].x);
-            } else {
+            // wavefronts' worth, the wavefronts share the sums) ----
+            if (!equal) {
                 const int share = n <= 64 ? 3 : n <= 128 ? 2 : n <= 256 ? 1 : 0, first = (wave >> share) * 64, part = wave & ((1 << share) - 1);
                 if (first < n) {
                     const float own = L.cand[min(first + lane, n - 1)].x;
@@ -1424,9 +1447,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 }
             }
             lds_barrier();
-            const uint32_t best = L.best;
+            const uint32_t best = equal ? tie : L.best;
             // (0: all of them together fall short)
-            if (!all && !(above < need && best))
+            if (!all && !(best && (equal || above < need)))
                 return false;  // the bins missed the threshold
             const float x_cut = uniform(best ? key_value(best) : -INFINITY);
             if (by_count) {
@@ -1434,7 +1457,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 __syncthreads();
             } else {
                 x_tau = x_cut;
-                if (tid < n && L.cand[tid].x >= x_tau)
+                if (n <= kDirect && tid < n && L.cand[tid].x >= x_tau)
                     atomicAdd(&L.slice_mass[L.cand_slice[tid]], (double)L.cand[tid].y);
                 lds_barrier();
                 kept = mine ? L.slice_mass[lane] : 0.0;
