@@ -1208,15 +1208,13 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 double mass = 0.0;
                 for_all(
                     [&](const float (&v)[4], int) __attribute__((always_inline)) {
-                        float s4 = 0.f;
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             const float p = prob(v[k], rs);
                             const bool keep = v[k] >= x_floor && p >= min_p && p > 0.f;
-                            s4 += keep ? p : 0.f;
+                            mass += (double)(keep ? p : 0.f);
                             lowest = keep ? fminf(lowest, v[k]) : lowest;
                         }
-                        mass += (double)s4;
                     },
                     [&](int s) __attribute__((always_inline)) {
                         mass = wave_scan_f64(mass);
@@ -1360,11 +1358,10 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 float least = INFINITY, most = -INFINITY;  // of the candidates
                 for_all(
                     [&](const float (&v)[4], int s) __attribute__((always_inline)) {
-                        float s4 = 0.f;
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             const float xq = FILTERED && !(v[k] >= x_floor) ? -INFINITY : v[k], w = weight(xq);
-                            s4 += xq >= x_above ? w : 0.f;
+                            sure += (double)(xq >= x_above ? w : 0.f);
                             if (xq >= x_cand && xq < x_above) {
                                 least = fminf(least, xq);
                                 most = fmaxf(most, xq);
@@ -1375,7 +1372,6 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                                 }
                             }
                         }
-                        sure += (double)s4;
                     },
                     [&](int s) __attribute__((always_inline)) {
                         sure = wave_scan_f64(sure);
