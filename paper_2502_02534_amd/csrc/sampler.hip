@@ -61,6 +61,21 @@ constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118, kBcast
 // A value that is the same in every lane, moved to a scalar register.
 __device__ __forceinline__ float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 
+// The same value in a scalar register, for the compiler another one: what is formed from it is formed here, not ahead of the loop
+// around, where it would take vector registers (of uniform values too: scalar arithmetic has no floats).
+__device__ __forceinline__ float here(float v)
+{
+    int s = __builtin_amdgcn_readfirstlane(__float_as_int(v));
+    asm volatile("" : "+s"(s));
+    return __int_as_float(s);
+}
+__device__ __forceinline__ double here(double v)
+{
+    int lo = __builtin_amdgcn_readfirstlane(__double2loint(v)), hi = __builtin_amdgcn_readfirstlane(__double2hiint(v));
+    asm volatile("" : "+s"(lo), "+s"(hi));
+    return __hiloint2double(hi, lo);
+}
+
 // Inclusive scan over the lanes.
 __device__ __forceinline__ double wave_scan_f64(double v)
 {
@@ -830,22 +845,30 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
                     z_lo = fminf(z_lo, -4.f * __builtin_amdgcn_logf(min_p) + 0.01f);
                 z_lo = fminf(z_lo, place(5));
             } else {
-                const float z_cut = place(0), z_far = place(1) + 1.f;
+                auto upto = [&](float zz) __attribute__((always_inline)) {
+                    zz = fminf(fmaxf(zz, 0.f), (float)kGuessBins - 0.001f);
+                    const int i = (int)zz;
+                    return L.cum[i] + (L.cum[i + 1] - L.cum[i]) * (zz - (float)i);
+                };
+                // (few logits below the cut, as with a top-p next to 1: their mass says little about where the row's cut lies, and
+                // all of them fit)
+                const float z_cut = place(0), most = 0.25f * kListMost, at_cut = upto(z_cut);
+                const float z_far = L.cum[kGuessBins] - at_cut <= 0.25f * most ? (float)kGuessBins : place(1) + 1.f;
                 z_lo = fminf(fmaxf(z_far, place(4)), place(5));
                 if (z_far > place(5)) {
-                    // Not from the top: around the place, moving both ends towards it until what lies between fits (lane l
-                    // tries (l + 1) / 64 of the way).
+                    // Not from the top: around the place, moving each end towards it until what lies between fits half of the
+                    // list, or what the other end leaves of it (lane l tries (l + 1) / 64 of the way).
                     z_hi = fmaxf(place(2) - 1.f, 0.f);
-                    auto upto = [&](float zz) __attribute__((always_inline)) {
-                        zz = fminf(fmaxf(zz, 0.f), (float)kGuessBins - 0.001f);
-                        const int i = (int)zz;
-                        return L.cum[i] + (L.cum[i + 1] - L.cum[i]) * (zz - (float)i);
-                    };
                     const float f = (float)(lane + 1) * (1.f / 64.f);
-                    const unsigned long long fit = __ballot(upto(z_cut + (z_far - z_cut) * f) - upto(z_cut - (z_cut - z_hi) * f) <= 0.25f * kListMost);
-                    const int widest = ~fit ? __ffsll((long long)~fit) - 1 : 64;  // (and whatever is narrower)
-                    z_lo = z_cut + (z_far - z_cut) * ((float)widest * (1.f / 64.f));
-                    z_hi = z_cut - (z_cut - z_hi) * ((float)widest * (1.f / 64.f));
+                    const float under = upto(z_cut + (z_far - z_cut) * f) - at_cut, over = at_cut - upto(z_cut - (z_cut - z_hi) * f);
+                    auto last = [&](float v) __attribute__((always_inline)) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); };
+                    auto widest = [&](bool fits) __attribute__((always_inline)) {
+                        const unsigned long long fit = __ballot(fits);
+                        return (float)(~fit ? __ffsll((long long)~fit) - 1 : 64) * (1.f / 64.f);  // (and whatever is narrower)
+                    };
+                    const float room = fmaxf(0.5f * most, most - last(over));
+                    z_lo = z_cut + (z_far - z_cut) * widest(under <= room);
+                    z_hi = z_cut - (z_cut - z_hi) * widest(over <= most - fminf(last(under), room));
                 }
                 x_cut = z_cut;
             }
@@ -1106,9 +1129,10 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
     auto of_lane = [&](double d, int l) __attribute__((always_inline)) -> double {
         return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(d), l), __builtin_amdgcn_readlane(__double2loint(d), l));
     };
+    const double cd = of_lane(rc.cd, 0);
     auto wave_total = [&](double d) __attribute__((always_inline)) -> double { return of_lane(wave_scan_f64(d), 63); };
     // lane s: what slice s's masses are worth relative to the row's maximum
-    const double scale = mine && st.max_x != -INFINITY ? exp2(((double)st.max_x - (double)M) * rc.cd) : 0.0;
+    const double scale = mine && st.max_x != -INFINITY ? exp2(((double)st.max_x - (double)M) * cd) : 0.0;
     double kept = scale != 0.0 ? st.mass * scale : 0.0;  // lane s: kept mass of slice s
     double S = wave_total(kept);                         // the row's mass
     float x_tau = -INFINITY;                             // kept: x >= x_tau
@@ -1189,7 +1213,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         const float octave64 = uniform(64.f * __builtin_amdgcn_rcpf(rc.c_hi));  // 64 octaves of p
         // where all lists reach down to, and two octaves above the highest of the slices' own cuts: where the row's is
         // looked for first
-        const float reach = wave_max_f32(some && st.count >= 0 ? st.x_lo : -INFINITY);
+        const float reach = fmaxf(wave_max_f32(some && st.count >= 0 ? st.x_lo : -INFINITY), -3.402823466e38f);
         const float start = wave_max_f32(some ? st.x_cut : -INFINITY) + 0.03125f * octave64;
         if (!FILTERED && tid < kMaxSlices)
             L.above[tid] = some ? st.above * scale : 0.0;  // (read behind the next barrier)
@@ -1235,19 +1259,27 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     break;
                 __syncthreads();
             }
-            float share = uniform(top_p);
-            asm volatile("" : "+s"(share));  // (formed here, not ahead of the loop, where it would take a vector register pair)
-            const double need = of_lane(by_count ? (double)top_k : (double)share * S, 0);  // (in scalar registers)
+            const double need = of_lane(by_count ? (double)top_k : (double)here(top_p) * S, 0);  // (in scalar registers)
             // Steps that narrow [x_cand, x_above) down: bin what lies there, find the bins that take the running mass across
             // `need`, sum up what lies above them and list what lies in them.  One is enough, but for many equal or
             // nearly equal logits, and where a window does not reach around the bins.
-            double above = 0.0, binned = S, next_binned = S;
+            double above = 0.0;
+            float binned = uniform((float)S), next_binned = binned;  // what a step bins, about
             int n = 0;
-            bool equal = false, all = false;  // (of the candidates; there are no k logits)
+            bool equal = false, all = false, open = false;  // (of the candidates; there are no k logits; see below)
             uint32_t tie = 0u;                // equal candidates: their key, if the threshold lies there
             int rounds = 0;
             x_above = INFINITY;
             x_cand = reach;
+            auto again = [&](unsigned lacking) __attribute__((always_inline)) {
+                // once more from the start, with all logits of those slices
+                full |= lacking;
+                ++rounds;
+                above = 0.0;
+                binned = uniform((float)S);
+                x_above = INFINITY;
+                x_cand = -3.402823466e38f;
+            };
             for (int tries = 0;; ++tries) {
                 if (!equal) {
                     const float top = tries == 0 && rounds == 0 ? fminf(start, M) : fminf(x_above, M);
@@ -1255,8 +1287,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     const float per = uniform(-(float)kBins * __builtin_amdgcn_rcpf(range)), width = range * (1.f / (float)kBins);  // bins (counted down)
                     // a unit is 2^-31 of what is binned, rounded up to a power of two (no bin overflows), but for the rounding of
                     // its logarithm
-                    const int power = ((__double2hiint(binned) >> 20) & 0x7ff) - 1022;
-                    const double log_exact = (double)(31 - power) + ((double)top - (double)M) * rc.cd;
+                    const int power = ((__float_as_int(binned) >> 23) & 0xff) - 126;
+                    const double log_exact = (double)(31 - power) + ((double)top - (double)here(M)) * here(cd);
                     const float log_unit = uniform((float)log_exact);
                     const double unit = by_count ? 1.0 : of_lane(ldexp(1.0 + 0.6931471805599453 * (log_exact - (double)log_unit), power - 31), 0);
                     if (tid == 0) {
@@ -1303,8 +1335,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     }
                     lds_barrier();
                     // (the bins' masses are good to 1e-6 of what is binned; a miss is noticed below)
-                    const double tol = of_lane(by_count ? 0.5 : 2e-6 * binned, 0);
+                    const double tol = of_lane(by_count ? 0.5 : ldexp((double)binned, -19), 0);
                     const BinPick e = block_pick(L.bins, unit, above, need - tol, by_count ? need - tol : need + tol, L.pick);
+                    const double total = of_lane(e.total, 0);
                     const int lo = __builtin_amdgcn_readfirstlane(e.lo);
                     const int hi = by_count && e.hi == kBins - 1 ? kBins : __builtin_amdgcn_readfirstlane(e.hi);
                     // (wider by the rounding of all this: of a bin's number, which grows with its distance from the top, and of the edges,
@@ -1312,23 +1345,24 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     // tie would count all of it as above)
                     const float slack = 4e-3f * width + 4e-7f * fmaxf(fabsf(top), fabsf(top - range)), below_bins = tries > 0 ? x_cand : -3.402823466e38f;
                     const float next_above = lo <= 0 ? x_above : fminf(x_above, top - (float)lo * width + slack);
-                    x_cand = uniform(hi >= kBins ? below_bins : fmaxf(below_bins, top - (float)(hi + 1) * width - slack));
+                    // `need` may lie among the bins' last or below all of them, for all that they can tell (top-p within 2e-6 of 1): the
+                    // next step bins what is left from lo down, with as much finer a unit
+                    open = !by_count && lo < kBins && hi >= kBins;
+                    x_cand = uniform(open ? x_cand : hi >= kBins ? below_bins : fmaxf(below_bins, top - (float)(hi + 1) * width - slack));
                     x_above = uniform(next_above);
+                    if (open) {  // (from where all windows begin, if they do below: what lies above is known as a sum)
+                        const float begin = -wave_max_f32(some && !((full >> lane) & 1u) ? -st.x_hi : -INFINITY);
+                        x_above = uniform(begin > x_cand ? fminf(x_above, begin) : x_above);
+                    }
                     // does every slice's window reach around them?  (rows with a filter: all survivors are listed)
                     if (!(FILTERED && !by_count)) {
                         // (what is listed reaches `need` nowhere: the cut lies below some windows, an octave and more is tried)
-                        if (hi >= kBins && !by_count && rounds < 6)
-                            x_cand = uniform(wave_max_f32(some && !((full >> lane) & 1u) ? st.x_lo : -INFINITY) - octave64 * 0.015625f * (float)(1 << rounds));
+                        if (hi >= kBins && !open && !by_count && rounds < 6)
+                            x_cand = uniform(fmaxf(wave_max_f32(some && !((full >> lane) & 1u) ? st.x_lo : -INFINITY) - octave64 * 0.015625f * (float)(1 << rounds), -3.402823466e38f));
                         const bool below = st.x_lo <= x_cand || (by_count && prob(st.x_lo, rs) < min_p);
                         const unsigned lacking = (unsigned)__ballot(some && !(below && st.x_hi >= x_above)) & ~full;
                         if (lacking != 0u) {
-                            // once more from the start, with all logits of those slices
-                            full |= lacking;
-                            ++rounds;
-                            above = 0.0;
-                            binned = S;
-                            x_above = INFINITY;
-                            x_cand = -3.402823466e38f;
+                            again(lacking);
                             tries = -1;
                             *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
                             continue;
@@ -1339,11 +1373,13 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                         for (int b = max(lo, 0) + lane; b <= min(hi, kBins - 1); b += 64)
                             inside += L.bins[b];
                         inside = wave_reduce_u32(inside, 0u, [](unsigned a, unsigned b) { return a + b; });
-                        next_binned = of_lane(hi >= kBins ? binned : (double)inside * unit * 1.001 + 1e-30, 0);
+                        // (without an end: and what lies beyond the bins, with the rounding of them all)
+                        const float past = hi >= kBins ? fabsf(binned - (float)(total - above)) + 4e-6f * binned : 0.f;
+                        next_binned = uniform(1.001f * ((float)((double)inside * unit) + past) + 1e-30f);
                         lds_barrier();
                     }
                     *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
-                    if (by_count && e.total < need - tol) {
+                    if (by_count && total < need - tol) {
                         if (tries > 0)
                             return false;  // (there were k when all of them were counted)
                         all = true;        // there are no k: all of them
@@ -1384,6 +1420,15 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                 if (equal)
                     break;
                 above = wave_total(kept);
+                if (open && above >= need) {  // (the cut lies above some window after all)
+                    const unsigned lacking = (unsigned)__ballot(some && st.x_hi < INFINITY) & ~full;
+                    if (lacking == 0u)
+                        return false;
+                    again(lacking);
+                    tries = -1;
+                    __syncthreads();
+                    continue;
+                }
                 n = __builtin_amdgcn_readfirstlane((int)L.cands);
                 if (n > 64) {
                     least = -wave_max_f32(-least);
@@ -1397,7 +1442,9 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                         least = fminf(least, L.lowest[w]);
                         most = fmaxf(most, L.highest[w]);
                     }
-                    equal = least == most;
+                    least = uniform(least);  // (a branch on what the compiler takes to differ from lane to lane costs registers)
+                    most = uniform(most);
+                    equal = least == most && !(open && above + (double)n * (double)weight(least) < need);
                     if (equal) {
                         // any number of equal ones needs no list: they are the threshold or it was missed.  What each slice
                         // keeps comes from one more pass over the lists where there are more than the list of candidates holds.
@@ -1410,7 +1457,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                         continue;
                     }
                 }
-                if (n <= kDirect)
+                if (n <= kDirect && !open)
                     break;
                 if (tries == 3)
                     return false;  // hundreds of nearly equal logits at the cut

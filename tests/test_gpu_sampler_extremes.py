@@ -50,3 +50,24 @@ def test_rows_without_any_token_left(vocab):
     for top_p in (1.0, 0.9):
         got = _run(x, one, one * np.float32(top_p), top_k, one * np.float32(0.0), one * np.float32(0.5))
         assert np.all(got == vocab - 1), (top_p, got)
+
+
+@pytest.mark.parametrize("filters", [False, True])
+@pytest.mark.parametrize("vocab", [5248, 9001, 50257, 128256])
+def test_a_top_p_next_to_one(oracle, vocab, filters):
+    print(f"top-p next to 1: vocab {vocab}, filters {filters}", flush=True)
+    rng = np.random.default_rng(vocab + 5)
+    shares = [1 - 1e-5, 1 - 4e-6, 1 - 2e-6, 1 - 1e-6, 1 - 2.0 ** -22, 1 - 2.0 ** -24]
+    rows = 4 * len(shares)
+    top_p = np.repeat(np.array(shares, np.float32), 4)
+    x = (rng.standard_normal((rows, vocab)) * 3.0).astype(np.float32)
+    x[1::4] += np.linspace(4.0, -4.0, vocab, dtype=np.float32)
+    x[2::4] = np.round(x[2::4])                             # thousands of equal logits in the tail
+    x[3::4, rng.permutation(vocab)[300:]] = -np.inf         # a few hundred tokens left
+    t = rng.choice(np.array([0.7, 1.0, 2.0], np.float32), rows)
+    u = rng.random(rows, dtype=np.float32)
+    u[::3] = rng.random(rows, dtype=np.float32)[::3] * np.float32(1e-6)
+    top_k = rng.choice(np.array([0, 40, 4000], np.int32), rows) if filters else None
+    min_p = rng.choice(np.array([0.0, 1e-7], np.float32), rows) if filters else None
+    o = oracle.sample_tokens_filtered(x, t, top_p, u, top_k, min_p) if filters else oracle.sample_tokens(x, t, top_p, u)
+    compare_tokens(_run(x, t, top_p, top_k, min_p, u), o, u, vocab)
