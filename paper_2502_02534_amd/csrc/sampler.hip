@@ -827,7 +827,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
             n = lane == 2 ? m_all - q * (per_slice * 2.f + 4.f + 8.f * spread) : n;
             n = lane == 4 ? 0.25f * kListLeast : n;
             n = lane == 5 ? 0.25f * kListMost : n;
-            n = lane == 6 ? fminf(0.5f * (float)top_k + 64.f, 1.0e6f) : n;
+            // (all k may lie in one slice: a quarter of them are in the sample, 0.43 sqrt(k) more or less, and four times that)
+            n = lane == 6 ? fminf(0.25f * (float)top_k + 1.75f * __builtin_amdgcn_sqrtf((float)max(top_k, 0)) + 4.f, 1.0e6f) : n;
             const float* const table = lane < 3 ? L.below : L.cum;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             int b = 0;  // the last place with no more than n above it (tables begin with 0 and never fall)
