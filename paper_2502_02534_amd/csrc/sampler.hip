@@ -1083,7 +1083,8 @@ struct FinishLds {
     double upper[kDirect];           // sums of what is not below, cut among wavefronts
     PickLds pick;
     double slice_mass[kMaxSlices];   // kept mass of every slice
-    double above[kMaxSlices];        // what lies above each slice's window
+    double above[kMaxSlices];        // what lies above each slice's window, where it begins, the slice's maximum
+    float x_hi[kMaxSlices], max_x[kMaxSlices];
     unsigned cands;
     uint32_t best;
     float lowest[kWaves], highest[kWaves];
@@ -1216,8 +1217,16 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
         // looked for first
         const float reach = fmaxf(wave_max_f32(some && st.count >= 0 ? st.x_lo : -INFINITY), -3.402823466e38f);
         const float start = wave_max_f32(some ? st.x_cut : -INFINITY) + 0.03125f * octave64;
-        if (!FILTERED && tid < kMaxSlices)
-            L.above[tid] = some ? st.above * scale : 0.0;  // (read behind the next barrier)
+        if (tid < kMaxSlices) {  // (read behind the next barrier)
+            L.above[tid] = some && !FILTERED ? st.above * scale : 0.0;
+            L.x_hi[tid] = st.x_hi;
+            L.max_x[tid] = st.max_x;
+        }
+        auto per_lane = [&](const float (&a)[kMaxSlices]) __attribute__((always_inline)) {
+            int l = lane;
+            asm("" : "+v"(l));  // (its address is not kept in a register)
+            return a[l & (kMaxSlices - 1)];
+        };
         for (int stage = FILTERED && top_k > 0 ? 0 : 1; stage < 2; ++stage) {
             // stage 0 (rows with top-k): the k-th largest logit of what min-p leaves; stage 1: the nucleus cut
             by_count = FILTERED && stage == 0;
@@ -1322,7 +1331,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     // (what lies above a window counts from its edge on)
                     if (!FILTERED && tries == 0 && tid < kMaxSlices && !((full >> lane) & 1u)) {
                         const double above_s = L.above[tid];
-                        const float bin = fmaxf((st.x_hi - top) * per, 0.f);
+                        const float bin = fmaxf((L.x_hi[tid] - top) * per, 0.f);
                         if (above_s > 0.0 && bin < (float)kBins)
                             atomicAdd(&L.bins[(unsigned)bin], (unsigned)(above_s / unit));
                     }
@@ -1352,7 +1361,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     x_cand = uniform(open ? x_cand : hi >= kBins ? below_bins : fmaxf(below_bins, top - (float)(hi + 1) * width - slack));
                     x_above = uniform(next_above);
                     if (open) {  // (from where all windows begin, if they do below: what lies above is known as a sum)
-                        const float begin = -wave_max_f32(some && !((full >> lane) & 1u) ? -st.x_hi : -INFINITY);
+                        const float begin = -wave_max_f32(some && !((full >> lane) & 1u) && per_lane(L.max_x) >= x_cand ? -per_lane(L.x_hi) : -INFINITY);
                         x_above = uniform(begin > x_cand ? fminf(x_above, begin) : x_above);
                     }
                     // does every slice's window reach around them?  (rows with a filter: all survivors are listed)
@@ -1361,7 +1370,8 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                         if (hi >= kBins && !open && !by_count && rounds < 6)
                             x_cand = uniform(fmaxf(wave_max_f32(some && !((full >> lane) & 1u) ? st.x_lo : -INFINITY) - octave64 * 0.015625f * (float)(1 << rounds), -3.402823466e38f));
                         const bool below = st.x_lo <= x_cand || (by_count && prob(st.x_lo, rs) < min_p);
-                        const unsigned lacking = (unsigned)__ballot(some && !(below && st.x_hi >= x_above)) & ~full;
+                        // (a slice that lies below all of it has nothing to tell, whatever it listed)
+                        const unsigned lacking = (unsigned)__ballot(some && per_lane(L.max_x) >= x_cand && !(below && per_lane(L.x_hi) >= x_above)) & ~full;
                         if (lacking != 0u) {
                             again(lacking);
                             tries = -1;
@@ -1389,7 +1399,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     }
                 }
                 if (tid < kMaxSlices)
-                    L.slice_mass[tid] = FILTERED || ((full >> lane) & 1u) ? 0.0 : L.above[tid];
+                    L.slice_mass[tid] = ((full >> lane) & 1u) || L.max_x[tid] < x_above ? 0.0 : L.above[tid];
                 lds_barrier();
                 double sure = 0.0;
                 float least = INFINITY, most = -INFINITY;  // of the candidates
@@ -1422,7 +1432,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     break;
                 above = wave_total(kept);
                 if (open && above >= need) {  // (the cut lies above some window after all)
-                    const unsigned lacking = (unsigned)__ballot(some && st.x_hi < INFINITY) & ~full;
+                    const unsigned lacking = (unsigned)__ballot(some && per_lane(L.x_hi) < INFINITY) & ~full;
                     if (lacking == 0u)
                         return false;
                     again(lacking);
