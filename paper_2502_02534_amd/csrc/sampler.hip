@@ -1281,18 +1281,20 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
             int rounds = 0;
             x_above = INFINITY;
             x_cand = reach;
-            auto again = [&](unsigned lacking) __attribute__((always_inline)) {
-                // once more from the start, with all logits of those slices
+            float from = start;               // where the first step's bins begin
+            auto again = [&](unsigned lacking, float high, float low) __attribute__((always_inline)) {
+                // once more, with all logits of those slices, between these two first
                 full |= lacking;
                 ++rounds;
                 above = 0.0;
                 binned = uniform((float)S);
                 x_above = INFINITY;
-                x_cand = -3.402823466e38f;
+                from = FILTERED ? INFINITY : uniform(high);
+                x_cand = FILTERED ? -3.402823466e38f : uniform(low);
             };
             for (int tries = 0;; ++tries) {
                 if (!equal) {
-                    const float top = tries == 0 && rounds == 0 ? fminf(start, M) : fminf(x_above, M);
+                    const float top = fminf(tries == 0 ? from : x_above, M);
                     const float range = uniform(fminf(fmaxf(top - x_cand, 1e-30f), (tries > 1 ? 256.f : 1.f) * octave64));
                     const float per = uniform(-(float)kBins * __builtin_amdgcn_rcpf(range)), width = range * (1.f / (float)kBins);  // bins (counted down)
                     // a unit is 2^-31 of what is binned, rounded up to a power of two (no bin overflows), but for the rounding of
@@ -1366,14 +1368,23 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     }
                     // does every slice's window reach around them?  (rows with a filter: all survivors are listed)
                     if (!(FILTERED && !by_count)) {
-                        // (what is listed reaches `need` nowhere: the cut lies below some windows, an octave and more is tried)
-                        if (hi >= kBins && !open && !by_count && rounds < 6)
-                            x_cand = uniform(fmaxf(wave_max_f32(some && !((full >> lane) & 1u) ? st.x_lo : -INFINITY) - octave64 * 0.015625f * (float)(1 << rounds), -3.402823466e38f));
+                        // (what is listed reaches `need` nowhere: the cut lies below some windows.  How far follows from the mass that is
+                        // left there, over what the cut leaves: it falls by half an octave in one at least, but in the flattest rows)
+                        const bool deeper = !FILTERED && hi >= kBins && !open && rounds < 4;
+                        if (deeper) {
+                            const float left = 1.f + (float)(need - total) / fmaxf((float)(S - need), 1e-30f);
+                            x_cand = uniform(fmaxf(x_above - octave64 * (0.03125f * (float)(1 << rounds)) * (0.25f + __builtin_amdgcn_logf(left)), -3.402823466e38f));
+                        }
                         const bool below = st.x_lo <= x_cand || (by_count && prob(st.x_lo, rs) < min_p);
                         // (a slice that lies below all of it has nothing to tell, whatever it listed)
                         const unsigned lacking = (unsigned)__ballot(some && per_lane(L.max_x) >= x_cand && !(below && per_lane(L.x_hi) >= x_above)) & ~full;
-                        if (lacking != 0u) {
-                            again(lacking);
+                        if (lacking != 0u || deeper) {
+                            // (it lies above a window: what lies above that one counted from its edge on, so that the cut lies here
+                            // or higher, and windows that end just above it are no help either)
+                            const float near = x_above + octave64 * (0.015625f * (float)(1 << min(rounds, 4)));
+                            const bool over = !FILTERED && ((unsigned)__ballot(some && per_lane(L.x_hi) < x_above) & lacking) != 0u;
+                            const unsigned more = over ? (unsigned)__ballot(some && per_lane(L.max_x) >= x_cand && per_lane(L.x_hi) < near) & ~full : 0u;
+                            again(lacking | more, open ? INFINITY : over ? fmaxf(start, x_above + 0.0625f * octave64) : x_above + 0.004f * octave64, open ? -3.402823466e38f : x_cand);
                             tries = -1;
                             *reinterpret_cast<uint4*>(L.bins + 4 * tid) = make_uint4(0u, 0u, 0u, 0u);
                             continue;
@@ -1435,7 +1446,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                     const unsigned lacking = (unsigned)__ballot(some && per_lane(L.x_hi) < INFINITY) & ~full;
                     if (lacking == 0u)
                         return false;
-                    again(lacking);
+                    again(lacking, INFINITY, -3.402823466e38f);
                     tries = -1;
                     __syncthreads();
                     continue;

@@ -75,3 +75,35 @@ def test_more_rows_than_three_workgroups_a_cu(dev, oracle, rows, vocab, filters)
     torch.cuda.synchronize()
     o = oracle.sample_tokens_filtered(x, t, top_p, u, top_k, min_p) if filters else oracle.sample_tokens(x, t, top_p, u)
     compare_tokens(tokens.cpu().numpy(), o, u, vocab)
+
+
+@pytest.mark.parametrize("vocab", [9001, 32000, 128256, 262144])
+def test_rows_read_again(dev, oracle, vocab):
+    """Rows whose cut lies below some slices' lists or above their windows, by little or by much: the lists' own places are guesses
+    from one slice each, and other slices hold more or less of the row."""
+    from paper_2502_02534_amd import binding as B
+    rows = 40
+    print(f"rows read again: vocab {vocab}", flush=True)
+    rng = np.random.default_rng(vocab + 3)
+    x = rng.standard_normal((rows, vocab)).astype(np.float32)
+    x *= np.repeat(np.array([3.0, 1.0, 2.5, 0.2], np.float32), 10)[:, None]
+    fall = np.array([0, 2, 4, 6, 20, -2, -6, 0, 0, 0], np.float32)
+    x += np.tile(fall, 4)[:, None] * np.linspace(1.0, 0.0, vocab, dtype=np.float32)
+    for r in range(rows):
+        if r % 10 == 7:       # fifty boosted tokens, in any slice
+            x[r, rng.integers(0, vocab, 50)] += rng.uniform(2.0, 12.0, 50).astype(np.float32)
+        elif r % 10 == 8:     # ... in the last one alone
+            x[r, rng.integers(vocab - vocab // 9, vocab, 50)] += rng.uniform(2.0, 12.0, 50).astype(np.float32)
+        elif r % 10 == 9:
+            x[r] = np.sort(x[r])[::-1]
+    one = np.ones(rows, np.float32)
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ws = torch.full((B.sample_tokens_workspace_size(rows, vocab),), 255, dtype=torch.uint8, device="cuda")
+    for share in (0.5, 0.9, 0.98, 0.9999):
+        u = rng.random(rows, dtype=np.float32)
+        tokens = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+        xd, td, pd, ud = to(x), to(one), to(one * np.float32(share)), to(u)
+        B.sample_tokens(xd, B.SPD_F32, rows, vocab, vocab, td, pd, ud, tokens, ws)
+        torch.cuda.synchronize()
+        # 160 rows in all, near a boundary by chance where tens of thousands of tokens are kept
+        compare_tokens(tokens.cpu().numpy(), oracle.sample_tokens(x, one, one * np.float32(share), u), u, vocab)
