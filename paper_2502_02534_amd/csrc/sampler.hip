@@ -662,6 +662,11 @@ struct ScanLds {
 
 constexpr float kListLeast = 500.f;               // a slice lists at least about that many of its largest logits
 constexpr float kListMost = 0.92f * kListCap;     // ... and at most about that many (by a sample of a quarter)
+// Up to that many rows lists reach further down: a longer list costs 1 to 2 us there, a row that looks again 13.  Without / with,
+// us, 128256 logits at top-p 0.9: falling by 4 over the vocabulary, 8 rows 34.3 / 21.7, 64 38.6 / 26.7, 256 55.7 / 44.2; rows
+// without a trend 20.8 / 21.7, 25.1 / 26.8, 42.8 / 44.5.  With more rows a CU has others to work on meanwhile: 1024 rows that
+// fall 161 / 142 (184 before the lists), without a trend 135 / 140.
+constexpr unsigned kFewRows = 256;
 
 // What bounds it: the loads (1024 x 128256 logits, 525 MB: greedy rows 80 us, 6.5 TB/s, rows without a cut 86, with one 95 to 100),
 // as long as enough wavefronts are there to compute while others wait: 64 registers and 36 KB of LDS let four workgroups share
@@ -815,21 +820,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
             // The row's cut lies where the mass below is 1 - top_p of the row's, and this slice's share of the row is not
             // known: one logit that holds much of its mass has none like it in the other slices, and they may have ones
             // that it has not.  So the window reaches from where the cut would lie if the shares were twice this slice's
-            // mass and more to where it would if they were less by twice the spread of its mass, down to 0.15 of it.  Missed by
-            // none of 6000 rows of 128256 normal logits with sigma / T from 2.5 to 15 (1200 logits at least and an octave past the
-            // place, as fixed margins: as few, but 18 us more for 1024 rows at 0.7), by one in 22 with fifty boosted tokens and top-p
-            // 0.98, by one in four where the logits fall by 6 over the vocabulary: those rows read one or two slices
-            // again, 10 to 15 us.
+            // mass and more to where it would if they were less by twice the spread of its mass, down to 0.15 of it (fixed margins of
+            // 1200 logits at least and an octave past the place: as few misses, but 18 us more for 1024 rows at 0.7).  Rows of 128256
+            // logits that have to look again (kFewRows rows or less / more), sigma 3: none of 4096 at top-p 0.9 to 0.98, one in 350 at 0.999;
+            // with fifty boosted tokens none at 0.95, one in 300 at 0.98, one in three at 0.99; falling by 4 over the vocabulary none /
+            // half at 0.9, one in 18 / four in five at 0.95; sigma 1 with boosted tokens nearly all.
             const float per_slice = (float)S - 1.f + 1.f / (float)slices, spread = __builtin_amdgcn_sqrtf(fmaxf(sq - 1.f, 0.f));
             const float q = 0.25f * (1.f - top_p);
             float n = m_all - q * per_slice;
             n = lane == 1 ? m_all - q * fmaxf(per_slice - 2.f * spread, 0.15f * per_slice) : n;
             n = lane == 2 ? m_all - q * (per_slice * 2.f + 4.f + 8.f * spread) : n;
+            n = lane == 3 ? m_all - 0.5f * q * per_slice : n;
             n = lane == 4 ? 0.25f * kListLeast : n;
             n = lane == 5 ? 0.25f * kListMost : n;
             // (all k may lie in one slice: a quarter of them are in the sample, 0.43 sqrt(k) more or less, and four times that)
             n = lane == 6 ? fminf(0.25f * (float)top_k + 1.75f * __builtin_amdgcn_sqrtf((float)max(top_k, 0)) + 4.f, 1.0e6f) : n;
-            const float* const table = lane < 3 ? L.below : L.cum;
+            const float* const table = lane < 4 ? L.below : L.cum;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             int b = 0;  // the last place with no more than n above it (tables begin with 0 and never fall)
 #pragma unroll 1
@@ -855,7 +861,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
                 // all of them fit)
                 const float z_cut = place(0), most = 0.25f * kListMost, at_cut = upto(z_cut);
                 const float z_far = L.cum[kGuessBins] - at_cut <= 0.25f * most ? (float)kGuessBins : place(1) + 1.f;
-                z_lo = fminf(fmaxf(z_far, place(4)), place(5));
+                // (at one row a CU the slowest row is the call, and one that looks again takes 13 us more: lists from the top reach to half
+                // of the slice's own mass below the cut, which rows that fall or rise over the vocabulary need)
+                const float z_deep = gridDim.x <= kFewRows * (unsigned)slices ? fmaxf(z_far, place(3)) : z_far;
+                z_lo = fminf(fmaxf(z_deep, place(4)), place(5));
                 if (z_far > place(5)) {
                     // Not from the top: around the place, moving each end towards it until what lies between fits half of the
                     // list, or what the other end leaves of it (lane l tries (l + 1) / 64 of the way).
