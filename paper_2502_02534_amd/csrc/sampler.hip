@@ -3,13 +3,18 @@
 // Two paths.  The sliced path (below: two stream-ordered kernels) reads a row from HBM once, leaves
 // what the row-level step needs in the workspace, and finds the exact nucleus threshold without
 // sorting.  The whole-row routine (one workgroup per row, every pass from memory) covers what the
-// sliced path does not take: vocabularies of fewer than 4 logits, rows with more than 512 equal or nearly equal
-// logits at the cut, and, among rows that do not start on a 16-byte boundary, short ones.
+// sliced path does not take: vocabularies of fewer than 4 logits, rows with more than 512 logits at a threshold that are
+// nearly but not quite equal, rows with a cut at an infinite temperature, and, among rows that do not start on a
+// 16-byte boundary, short ones.
 //
-// Probabilities are evaluated by one shared routine, p_i = 2^((x_i - max) c) with
-// c = log2(e)/T carried as hi + lo floats, so every pass sees the same bits; every sum that
-// decides something is carried in fp64; comparisons that define the kept set are on bit
-// patterns, so all ties with the threshold are kept by construction.
+// Probabilities are p_i = 2^((x_i - max) c) with c = log2(e)/T carried as hi + lo floats, by one routine (prob)
+// but for two things: the scan's mass of a slice splits c in another place (so that its second part is positive) and is
+// relative to the slice's maximum, and the bins of the row-level step use c_hi alone.  Bins only point at a place:
+// what lies above it and in it is then summed logit by logit in fp64, and a threshold that those sums do not bear out
+// sends the row to the whole-row routine.  Masses of slices and of the segments that the walk goes through are fp64 sums of
+// groups of four in fp32.  The whole-row routine keeps what is not below the threshold by the bit pattern of p, the sliced
+// path by the logit, so that all ties with the threshold are kept.  A list's order depends on which wavefront reserved its
+// places first; with it the last bits of fp64 sums can differ from call to call, and nothing else.
 #include "spd_internal.h"
 
 #include <type_traits>
@@ -1388,7 +1393,7 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
                         // (a slice that lies below all of it has nothing to tell, whatever it listed)
                         const unsigned lacking = (unsigned)__ballot(some && per_lane(L.max_x) >= x_cand && !(below && per_lane(L.x_hi) >= x_above)) & ~full;
                         if (lacking != 0u || deeper) {
-                            // (it lies above a window: what lies above that one counted from its edge on, so that the cut lies here
+                            // (where it lies above a window: what lies above that one counted from its edge on, so that the cut lies here
                             // or higher, and windows that end just above it are no help either)
                             const float near = x_above + octave64 * (0.015625f * (float)(1 << min(rounds, 4)));
                             const bool over = !FILTERED && ((unsigned)__ballot(some && per_lane(L.x_hi) < x_above) & lacking) != 0u;
@@ -1627,8 +1632,12 @@ __device__ __forceinline__ bool finish_row(const SamplerParams& sp, char* ws, in
 // spills: 41 us for 64 rows), bins that add floats (23 us a pass), lists rewritten for the slices whose window missed
 // (slower than reading those slices whole: code that runs once is fetched as it runs).
 // Sixteen wavefronts a row for few rows: 64 rows 25.1 -> 26.5 us (T 0.7), 300 rows 54 -> 65.
-// Whole calls before / now (us): 64 x 128256 37.0 -> 30.0, 1024 x 128256 (T 0.2 to 1.2) 197 -> 150, 192 x 50257 with filters 44.0 ->
-// 30.7, 64 x 32000 27.3 -> 18.3, 1024 x 4096 40.5 -> 27.5, 100 x 250000 at sigma 1.5 991 -> 65, 1024 with filters 201 -> 137.
+// Whole calls before / now (us, sigma 3 at top-p 0.95 where nothing else is said): 64 x 128256 33.6 -> 30.0, at T 0.7 31.8 -> 22.7,
+// 1024 x 128256 (T 0.2 to 1.2) 194 -> 143, 192 x 50257 with filters 43.6 -> 31.2, 64 x 32000 28.8 -> 18.1, 1024 x 4096 40.9 -> 25.8,
+// 1024 x 128256 with filters 201 -> 144, 64 x 128256 with a top-k of 50 39.8 -> 28.4, of 20000 609 -> 73, min-p 1e-5 217 -> 46.
+// Rows that look again, 64 x 128256: a trend of 10 over the vocabulary 29.6 -> 34.9, fifty boosted tokens over sigma 1 87 -> 109
+// (256 rows 401 -> 140), over sigma 2.5 at top-p 0.98 72 -> 95, top-p 0.999 90 -> 79, 0.999999 50 -> 139.  Such a look is two passes over
+// all the logits of a slice by one workgroup, vector instructions again (4 us a slice; more loads in flight change nothing).
 // ANY = false: no row has a filter.  ANY = true (filter arrays are given): every row takes the routine it
 // needs in one launch, so that the two kinds run side by side.  No instantiation uses scratch memory (12 bytes a lane cost
 // 1 us): the whole-row routine is inlined (a call would have the arguments copied to memory), what a slice has above its window

@@ -1,7 +1,7 @@
 """The row-level sampler step at the edges of how it shares its work out: every number of slices that a row is cut
-into (one, two, four or eight wavefronts per slice, two slices per wavefront), sorted rows (all candidates
-with one wavefront, its share of the list flushed more than once), and the cut among 3, 64, 65 or 700 equal
-logits (told apart directly, or by another level of the select)."""
+into (one, two, four or eight wavefronts per slice, two slices per wavefront), sorted rows (all that is kept
+in the first slices), and the cut among 3, 64, 65 or 700 equal logits (told apart directly, settled by their value and
+count, or by those and a second look at the lists for what every slice keeps)."""
 import numpy as np
 import pytest
 
