@@ -55,3 +55,30 @@ def test_slices_sorted_rows_and_ties_at_the_cut(dev, oracle, vocab, filters):
     torch.cuda.synchronize()
     o = oracle.sample_tokens_filtered(x, t, top_p, u, top_k, min_p) if filters else oracle.sample_tokens(x, t, top_p, u)
     compare_tokens(tokens.cpu().numpy(), o, u, vocab)
+
+
+@pytest.mark.parametrize("filters", [False, True])
+@pytest.mark.parametrize("vocab", [50257, 128256])
+def test_the_same_call_returns_the_same_tokens(dev, oracle, vocab, filters):
+    """Uniforms next to the boundaries of the running mass, on rows of long lists whose order differs from call to call: what is
+    summed in 64 bits moves by 1e-16 with it, the nearest uniform is 3e-8 away."""
+    from paper_2502_02534_amd import binding as B
+    rows = 64
+    print(f"the same call again: vocab {vocab}, filters {filters}", flush=True)
+    rng = np.random.default_rng(vocab + 17)
+    x = (rng.standard_normal((rows, vocab)) * 2.0).astype(np.float32)
+    x[::4] += np.linspace(5.0, 0.0, vocab, dtype=np.float32)        # some slices are read again
+    one = np.ones(rows, np.float32)
+    top_p, top_k = one * np.float32(0.9), np.full(rows, 3000, np.int32) if filters else None
+    u = rng.random(rows, dtype=np.float32)
+    o = oracle.sample_tokens_filtered(x, one, top_p, u, top_k, None) if filters else oracle.sample_tokens(x, one, top_p, u)
+    u = np.minimum(o["cdf_hi"].astype(np.float32), np.float32(1.0 - 2.0 ** -24))
+    to = lambda a: None if a is None else torch.from_numpy(a).cuda()
+    xd, td, pd, ud, kd = to(x), to(one), to(top_p), to(u), to(top_k)
+    ws = torch.empty(B.sample_tokens_workspace_size(rows, vocab), dtype=torch.uint8, device="cuda")
+    tokens = torch.full((12, rows), -7, dtype=torch.int32, device="cuda")
+    for i in range(12):
+        ws.fill_(255 if i % 2 else 127)
+        B.sample_tokens_filtered(xd, B.SPD_F32, rows, vocab, vocab, td, pd, kd, None, ud, tokens[i], ws)
+    torch.cuda.synchronize()
+    assert bool((tokens == tokens[0]).all()) and bool((tokens >= 0).all())
